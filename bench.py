@@ -38,7 +38,7 @@ MFMA_BF16_PEAK_TFLOPS = 2500.0
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "traffic_tile256_n256_t1024_fp32.md")
 
 
-COUNT_KERNEL_SOURCES = ("bnlat_dev.h", "device_common.h", "count.hip")
+COUNT_KERNEL_SOURCES = ("lattice_lines.h", "bnlat_dev.h", "device_common.h", "count.hip")
 
 
 def kernel_digest() -> str:

@@ -288,7 +288,7 @@ struct bn_problem_s {
 
 // A group of batch members served by one launch of one kernel variant.
 struct BatchGroup {
-  int kind = 0;               // counting-kernel variant (count_kind: N up to 64, else 64 + lanes per item)
+  int kind = 0;               // counting-kernel variant (count_kind)
   uint32_t radius = 0, k = 0; // staged energy-change variant
   std::vector<uint32_t> idx;  // member indices
   // member view tables on the device: counting groups, one per proposal set
@@ -910,7 +910,7 @@ bn_status batch_upload(bn_batch b) {
   };
   bn_status s;
   for (BatchGroup& g : b->count_groups)
-    if ((s = upload(g, 0, [](const DevView& v) { return count_blocks(v, true); }, false)) != BN_OK) return s;
+    if ((s = upload(g, 0, [](const DevView& v) { return count_blocks(v); }, false)) != BN_OK) return s;
   for (BatchGroup& g : b->stage_groups)
     if ((s = upload(g, 1, [](const DevView&) { return 0u; }, true)) != BN_OK) return s;
   if ((s = upload(b->finish_all, 1, [](const DevView& v) { return (v.pc + 255) / 256; }, false)) != BN_OK) return s;
@@ -922,7 +922,7 @@ bn_status batch_upload(bn_batch b) {
 // counter, into proposal set `set`, on stream st.
 bn_status batch_recount(bn_batch b, int set, uint32_t ahead, hipStream_t st) {
   for (BatchGroup& g : b->count_groups)
-    HIPCHK(launch_count_batch(g.kind, g.views[set], g.d_pre, (uint32_t)g.idx.size(), g.blocks, ahead, true, st));
+    HIPCHK(launch_count_batch(g.kind, g.views[set], g.d_pre, (uint32_t)g.idx.size(), g.blocks, ahead, st));
   return BN_OK;
 }
 
@@ -1294,11 +1294,32 @@ bn_status bn_create_problem_ext(const bn_config* cfg, const bn_heaviside* heavis
     areaf[t] = (float)area[t];
   }
 
+  // the lattice as lines (count.hip): tables of the shift classes and of the
+  // integrands; up to N = 8 counting sample by sample costs less
+  v.gx = cfg->g[0] & (v.n - 1);
+  v.gy = cfg->g[1] & (v.n - 1);
+  v.lines = 0;
+  std::vector<uint32_t> lrow;
+  std::vector<LineRec> lrec;
+  if (v.n >= 16) {
+    const LatticeLines g = lattice_lines(v.n, v.gx, v.gy);
+    v.lines = line_template(g.lines);
+    if (!g.lines || !v.lines || !lattice_rows(v.n, v.gx, v.gy, g, v.lines, line_row_words(v.lines), lrow)) {
+      delete p;
+      return fail(BN_EINVAL, "the lattice (%u, %u) / %u has no line decomposition", cfg->g[0], cfg->g[1], v.n);
+    }
+    lrec.resize(v.tp, line_padding());
+    for (uint32_t t = 0; t < v.t; ++t) lrec[t] = line_record(g, step, heav[t].nx, heav[t].ny, heav[t].cx, heav[t].cy);
+  }
+
   uint32_t* lat_d;
+  uint32_t* lrow_d;
+  LineRec* lrec_d;
   int2* ihp_d;
   float* area_d;
   double* wd_d;
   if ((s = p->alloc(&lat_d, v.n)) != BN_OK || (s = p->alloc(&ihp_d, v.tp)) != BN_OK ||
+      (s = p->alloc(&lrow_d, lrow.size())) != BN_OK || (s = p->alloc(&lrec_d, lrec.size())) != BN_OK ||
       (s = p->alloc(&area_d, v.tp)) != BN_OK || (s = p->alloc(&wd_d, v.ncls)) != BN_OK ||
       (s = p->adopt(&v.U, bufs ? bufs->offsets : nullptr, P)) != BN_OK ||
       (s = p->adopt(&v.cnt, bufs ? bufs->counts : nullptr, P * v.tp)) != BN_OK ||
@@ -1311,6 +1332,8 @@ bn_status bn_create_problem_ext(const bn_config* cfg, const bn_heaviside* heavis
     return s;
   }
   v.lat = lat_d;
+  v.lrow = lrow_d;
+  v.lrec = lrec_d;
   v.ihp = ihp_d;
   v.area = area_d;
   v.wd = wd_d;
@@ -1352,6 +1375,9 @@ bn_status bn_create_problem_ext(const bn_config* cfg, const bn_heaviside* heavis
   }
   hipError_t e = v.mfma ? prepare_bf_kernels(v.radius, v.k) : hipSuccess;
   if (e == hipSuccess) e = hipMemcpyAsync(lat_d, lat.data(), v.n * 4, hipMemcpyHostToDevice, p->stream);
+  if (e == hipSuccess && v.lines) e = hipMemcpyAsync(lrow_d, lrow.data(), lrow.size() * 4, hipMemcpyHostToDevice, p->stream);
+  if (e == hipSuccess && v.lines)
+    e = hipMemcpyAsync(lrec_d, lrec.data(), lrec.size() * sizeof(LineRec), hipMemcpyHostToDevice, p->stream);
   if (e == hipSuccess) e = hipMemcpyAsync(ihp_d, ihp.data(), v.tp * 8, hipMemcpyHostToDevice, p->stream);
   if (e == hipSuccess) e = hipMemcpyAsync(area_d, areaf.data(), v.tp * 4, hipMemcpyHostToDevice, p->stream);
   if (e == hipSuccess) e = hipMemcpyAsync(wd_d, p->cls_w.data(), v.ncls * 8, hipMemcpyHostToDevice, p->stream);

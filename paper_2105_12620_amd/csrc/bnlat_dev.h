@@ -3,6 +3,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "lattice_lines.h"
+
 namespace bnlat {
 
 // Philox stream tags (fourth counter word).
@@ -32,6 +34,10 @@ struct DevView {
   uint32_t radius, ncls;
   const uint32_t* lat;       // [n] lattice points, x | y << 16, index order i
   const int2* ihp;           // [tp] (nx | ny << 16, D' = n . (C - 2^15))
+  uint32_t lines;            // lattice lines of the line counter (a template size; 0: sample counter)
+  uint32_t gx, gy;           // lattice generator
+  const uint32_t* lrow;      // [n][line_row_words(lines)] lattice lines of each shift class
+  const LineRec* lrec;       // [tp]
   const float* area;         // [tp] FP32 exact integrals (0 for padding)
   const double* wd;          // [ncls] class weights exp(-d / sigma^2)
   uint32_t* U;               // [P] offsets, x | y << 16
@@ -90,12 +96,12 @@ hipError_t launch_gauss_energy(const DevView& v, double* gsum, hipStream_t s);
 
 // batched launches: member i of a group owns blocks pre[i] .. pre[i+1]-1
 int count_kind(const DevView& v);
-uint32_t count_blocks(const DevView& v, bool sweep);
+uint32_t count_blocks(const DevView& v);
 // staged-kernel block shape 0 (default) or 1 (the tuner's alternative)
 uint32_t stage_rows(uint32_t k, uint32_t shape);
 void stage_geometry(const DevView& v, uint32_t shape, uint32_t* gx, uint32_t* gy, uint32_t* gz, uint32_t* trlen);
 hipError_t launch_count_batch(int kind, const DevView* views, const uint32_t* pre, uint32_t nmem,
-                              uint32_t blocks, uint32_t kappa, bool sweep, hipStream_t s);
+                              uint32_t blocks, uint32_t kappa, hipStream_t s);
 hipError_t launch_stage_batch(uint32_t radius, uint32_t k, uint32_t shape, const DevView* views, const uint32_t* pre,
                               const uint32_t* geo, uint32_t nmem, uint32_t blocks, uint32_t kappa,
                               hipStream_t s);

@@ -9,7 +9,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
-#include <algorithm>
+#include <type_traits>
 
 #include "bnlat_dev.h"
 #include "device_common.h"
@@ -54,23 +54,55 @@ __device__ inline void count_target(const DevView& v, uint32_t kappa, uint32_t j
 // ----------------------------------------------------------- hit counting
 //
 // Estimator of the test-integrand map (Sec. 2): c[p][t] = number of the N
-// scrambled samples on the hit side of Heaviside t.
+// scrambled samples on the hit side of Heaviside t.  Every lane owns one work
+// item (a pixel, or a proposal); a wave walks a chunk of integrands with
+// wave-uniform parameters from scalar loads.  Two counters give the same
+// integers:
 //
-// k_count: every lane holds NS samples of one work item (a pixel, or a
-// proposal), and L = N / NS consecutive lanes share the item (NS = N up to 64,
-// else 64).  A wave walks a chunk of integrands with wave-uniform parameters
-// from scalar loads, two integrands at a time.  Per (sample, integrand) the
-// only vector work is one v_dot2 with the threshold folded in (n.s > D'
-// exactly when r = n.s - D' - 1 >= 0; |n.s|, |D'| <= 2^30, so r never
-// overflows); per sample one v_perm_b32 turns the sign bits of the two
+// LineCounter (N >= 16).  The samples are the points of a shifted plane
+// lattice in the unit square, so they lie on parallel lines: with b1 the
+// lattice vector of smallest |x| + |y| (in units of 1/N), at most
+// |x| + |y| <= sqrt(2 N) lines meet the square, and a line's samples are
+// A + l b2 + j b1 for consecutive j in [lo_l, hi_l).  A Heaviside's edge
+// crosses line l at one place, which moves by the same amount from each line
+// to the next, so per (line, integrand) the work is one 64-bit add (the
+// crossing in units of b1, 32 fraction bits), one clamp of its integer part
+// to [lo_l, hi_l] and half a three-operand add: 2.5 lane-operations per line
+// in place of 1.75 per sample (at N = 256: 16 lines, 45 against 466 with the
+// set-up of an integrand).  lo and hi depend only on which of N classes the
+// pixel's shift falls in (shifts that differ by a lattice vector give the
+// same lines) and come from a table; A is a sample of the pixel.  Bound by
+// the vector ALU; measured at 256^2, N = 256, T = 1000 with the error vectors
+// written: 102 us per bn_compute_errors against 877 us sample by sample
+// (393 MB written, 3.8 TB/s).
+//   Exactness: with D' + 1/2 in place of D', the crossings are odd multiples
+// of 1 / (2 |m|), m = n . b1, hence at least that far from an integer.  The
+// fixed-point value is off by at most 2^-33 per rounding: the first crossing
+// (one FP64 fma onto 1.5 2^20, whose last bit is 2^-32), the uniform offset
+// and the slope of each further line, (R + 1) 2^-33 in all for R lines;
+// |m| <= 2^30 R / N and R^2 <= 2 N keep that below 1 / (2 |m|).  Integrands
+// with |m| < LINE_MIN_M (edges nearly along the lines, about one in 10^4) are
+// counted sample by sample, so that the crossings stay inside the fma's range.
+//
+// SampleCounter (N <= 8, where it costs less: 14 lane-operations at N = 8
+// against 17): per (sample, integrand) one v_dot2 with the threshold folded in
+// (n.s > D' exactly when r = n.s - D' - 1 >= 0; |n.s|, |D'| <= 2^30, so r
+// never overflows); per sample one v_perm_b32 turns the sign bits of two
 // integrands' residues into 0x00/0xFF bytes in the two 16-bit halves of a
-// word, and per two such words one v_add3_u32 sums them.  A lane's halves then
-// hold 255 x its misses of integrands i and i + 1 (at most 255 * 64, so no
-// carry crosses the halves); they become miss counts, the L lanes of an item
-// add them with DPP / lane shuffles, and N - misses is the item's pair of
-// counts, already packed as the tile layout stores them.
+// word, and per two such words one v_add3_u32 sums them: 255 x the misses of
+// integrands i and i + 1, which become N - misses, already packed as the tile
+// layout stores them.
 
 typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
+
+// The integrand tables never change while a kernel runs: read through the
+// constant address space, wave-uniform elements come by scalar loads although
+// the kernel stores counts (which the compiler must take to alias).
+#define BN_UNIFORM __attribute__((address_space(4)))
+template <class T>
+__device__ inline const BN_UNIFORM T* uniform(const T* p) {
+  return (const BN_UNIFORM T*)p;
+}
 
 // Sign bytes of a sample's residues for two integrands: byte 0 is 0xFF when
 // lo < 0 and byte 2 is 0xFF when hi < 0 (v_perm_b32 selectors 9 and 11 repeat
@@ -86,49 +118,19 @@ __device__ inline uint32_t halves_div255(uint32_t x) {
   return __builtin_bit_cast(uint32_t, (u16x2)((h + (u16x2){255, 255}) >> (u16x2){8, 8}));
 }
 
-// Sum of x over each aligned group of L consecutive lanes, in every lane of
-// the group.
-template <int L>
-__device__ inline uint32_t lane_group_sum(uint32_t x) {
-  if (L >= 2) x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0xB1, 0xF, 0xF, true);  // quad_perm 1,0,3,2
-  if (L >= 4) x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x4E, 0xF, 0xF, true);  // quad_perm 2,3,0,1
-#pragma unroll
-  for (int o = 4; o < L; o <<= 1) x += (uint32_t)__shfl_xor((int)x, o);
-  return x;
-}
-
-template <int NS, int L, int MODE>
-__device__ __forceinline__ void count_lanes_body(const DevView& v, const int2* __restrict__ ihp, uint32_t kappa,
-                                                 uint32_t m, uint32_t tch, uint32_t blk) {
-  constexpr uint32_t IPW = 64 / L;  // work items per wave
-  constexpr uint32_t N = NS * L;
-  const uint32_t lane = threadIdx.x & 63;
-  const uint32_t wave = __builtin_amdgcn_readfirstlane(blk * 4 + (threadIdx.x >> 6));
-  const uint32_t nch = (v.tp + tch - 1) / tch;
-  const uint32_t jg = wave / nch, ch = wave - jg * nch;
-  if (jg * IPW >= m) return;
-  const uint32_t slot = lane % L, j0 = jg * IPW + lane / L;
-  // lanes past the last item repeat it (the group sums need whole lane
-  // groups) and store nothing
-  const bool live = j0 < m;
-  const uint32_t j = live ? j0 : m - 1;
-  uint32_t p, u, row, rows;
-  uint16_t* buf;
-  count_target<MODE>(v, kappa, j, m, p, u, buf, row, rows);
-  if ((MODE == MODE_CLASS || MODE == MODE_SWEEP) && ch == 0 && slot == 0 && live) v.u_new[j] = u;
+// Packed hit counts of integrands t .. t + 7 at offset u (t wave-uniform).
+template <int NS>
+struct SampleCounter {
   uint32_t sp[NS];
+  __device__ __forceinline__ SampleCounter(const DevView& v, uint32_t u) {
 #pragma unroll
-  for (int k = 0; k < NS; ++k) sp[k] = centre(wrap_add(v.lat[slot * NS + k], u));
-  const float inv_n = 1.0f / (float)N;
-  const uint32_t t0 = ch * tch, t1 = min(t0 + tch, v.tp);
-  const int4* ip = (const int4*)(ihp + t0);
-#pragma unroll 1
-  for (uint32_t t = t0; t < t1; t += 8, ip += 4) {
-    // eight integrands' parameters in one scalar load
-    const int4 q0 = ip[0], q1 = ip[1], q2 = ip[2], q3 = ip[3];
-    const int nn[8] = {q0.x, q0.z, q1.x, q1.z, q2.x, q2.z, q3.x, q3.z};
-    const int dd[8] = {q0.y, q0.w, q1.y, q1.w, q2.y, q2.w, q3.y, q3.w};
-    uint32_t c[4];
+    for (int k = 0; k < NS; ++k) sp[k] = centre(wrap_add(uniform(v.lat)[k], u));
+  }
+  __device__ __forceinline__ void count8(const DevView& v, uint32_t t, uint32_t c[4]) const {
+    const BN_UNIFORM int* ip = uniform((const int*)(v.ihp + t));
+    int nn[8], dd[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) nn[i] = ip[2 * i], dd[i] = ip[2 * i + 1];
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const uint32_t n0 = (uint32_t)nn[2 * i], n1 = (uint32_t)nn[2 * i + 1];
@@ -149,18 +151,171 @@ __device__ __forceinline__ void count_lanes_body(const DevView& v, const int2* _
         else if (G == 2) a = a + w[0] + w[1];
         else a += w[0];
       }
-      // misses per half: at most 64 per lane, N per item (no carry)
-      c[i] = (N | (N << 16)) - lane_group_sum<L>(halves_div255(a));
+      c[i] = (NS | (NS << 16)) - halves_div255(a);
     }
-    // computed in every lane (an empty asm consumes them): otherwise, with
-    // one lane per item, the counting would move under the store's branch
-    asm volatile("" : : "v"(c[0]), "v"(c[1]), "v"(c[2]), "v"(c[3]));
-    if (slot == 0 && live) {
-      *(uint4*)(buf + tix(row, t, rows)) = make_uint4(c[0], c[1], c[2], c[3]);
-      if (MODE == MODE_ALL) {
-        float* e = v.err + (size_t)p * v.tp + t;
+  }
+};
+
+// v_med3_i32 (x clamped to [lo, hi] for lo <= hi).
+__device__ inline int med3(int x, int lo, int hi) { return max(min(x, lo), min(max(x, lo), hi)); }
+
+// One LineRec out of the 16 words of a pair.
+typedef int i32x16 __attribute__((ext_vector_type(16)));
+struct LineTerms {
+  uint32_t n;
+  int d, inv_hi;
+  double inv;
+  unsigned long long off, slope;
+  __device__ __forceinline__ LineTerms(const i32x16 q, int k) : n((uint32_t)q[k]), d(q[k + 1]), inv_hi(q[k + 3]) {
+    auto two = [&](int i) { return (unsigned long long)(uint32_t)q[i] | ((unsigned long long)(uint32_t)q[i + 1] << 32); };
+    inv = __builtin_bit_cast(double, two(k + 2));
+    off = two(k + 4);
+    slope = two(k + 6);
+  }
+};
+static_assert(sizeof(LineRec) == 32, "LineTerms reads 8 words per integrand");
+
+template <int R>
+struct LineCounter {
+  static constexpr double MAGIC = 0x1.8p20;      // a sum with it has 32 fraction bits in the low word
+  static constexpr int BIAS = 0x41380000;        // its high word
+  uint32_t u, a;                                 // offset; centred sample A
+  int start;                                     // -(sum of lo, all lines, with their bias)
+  int lo[R], hi[R];
+  __device__ __forceinline__ LineCounter(const DevView& v, uint32_t u_) : u(u_) {
+    const uint32_t sh = 16 - v.log2n;
+    const uint32_t ux = u & 0xFFFFu, uy = u >> 16;
+    const uint32_t cls = ((uy >> sh) * v.gx - (ux >> sh) * v.gy) & (v.n - 1);
+    constexpr uint32_t W = line_row_words(R);
+    uint32_t w[W];
+    const u32x4* row = (const u32x4*)(v.lrow + (size_t)cls * W);
 #pragma unroll
-        for (int i = 0; i < 8; ++i) e[i] = (float)((c[i >> 1] >> (16 * (i & 1))) & 0xFFFFu) * inv_n - v.area[t + i];
+    for (uint32_t i = 0; i < W / 4; ++i) {
+      const u32x4 q = row[i];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) w[4 * i + e] = q[e];
+    }
+    const uint32_t fm = (1u << sh) - 1;
+    const uint32_t ax = ((w[0] & 0xFFFFu) << sh) + (ux & fm), ay = ((w[0] >> 16) << sh) + (uy & fm);
+    a = centre(ax | (ay << 16));
+    start = -(int)w[1] - (int)((uint32_t)R * (uint32_t)BIAS);
+#pragma unroll
+    for (int l = 0; l < R; ++l) {
+      lo[l] = (int)(int16_t)(w[2 + l] & 0xFFFFu) + BIAS;
+      hi[l] = ((int)w[2 + l] >> 16) + BIAS;
+    }
+  }
+  __device__ __forceinline__ uint32_t by_sample(const DevView& v, uint32_t n, int d) const {
+    uint32_t c = 0;
+#pragma unroll 1
+    for (uint32_t k = 0; k < v.n; ++k) c += dot2(n, centre(wrap_add(uniform(v.lat)[k], u)), -d - 1) >= 0 ? 1u : 0u;
+    return c;
+  }
+  __device__ __forceinline__ void count8(const DevView& v, uint32_t t, uint32_t c[4]) const {
+    const BN_UNIFORM i32x16* rec = uniform((const i32x16*)(v.lrec + t));
+    i32x16 next = rec[0];
+    uint32_t plain = 1;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      // the next pair's terms load while this pair is counted
+      const LineTerms q0(next, 0), q1(next, 8);
+      if (i < 3) next = rec[i + 1];
+      unsigned long long x0 = __builtin_bit_cast(unsigned long long,
+                                                 __fma_rn((double)dot2(q0.n, a, 0), q0.inv, MAGIC));
+      unsigned long long x1 = __builtin_bit_cast(unsigned long long,
+                                                 __fma_rn((double)dot2(q1.n, a, 0), q1.inv, MAGIC));
+      uint32_t s0 = (uint32_t)start, s1 = (uint32_t)start;
+      x0 += q0.off;
+      x1 += q1.off;
+#pragma unroll
+      for (int l = 0; l < R; l += 2) {
+        const int k00 = med3((int)(x0 >> 32), lo[l], hi[l]), k10 = med3((int)(x1 >> 32), lo[l], hi[l]);
+        x0 += q0.slope;
+        x1 += q1.slope;
+        const int k01 = med3((int)(x0 >> 32), lo[l + 1], hi[l + 1]), k11 = med3((int)(x1 >> 32), lo[l + 1], hi[l + 1]);
+        s0 = s0 + (uint32_t)k00 + (uint32_t)k01;
+        s1 = s1 + (uint32_t)k10 + (uint32_t)k11;
+        if (l + 2 < R) {
+          x0 += q0.slope;
+          x1 += q1.slope;
+        }
+      }
+      // s counts the samples before the crossing: the misses where m > 0
+      // (inv < 0), the hits where m < 0; per half N - s = (s ^ 0xFFFF) + N + 1
+      // less the carry out of the half
+      const bool g0 = q0.inv_hi < 0, g1 = q1.inv_hi < 0;
+      const uint32_t flip = (g0 ? 0xFFFFu : 0u) | (g1 ? 0xFFFF0000u : 0u);
+      const uint32_t add = (g0 ? v.n + 1u - 0x10000u : 0u) + (g1 ? (v.n + 1u) << 16 : 0u);
+      c[i] = ((s0 | (s1 << 16)) ^ flip) + add;
+      plain = min(plain, min((uint32_t)q0.inv_hi, (uint32_t)q1.inv_hi));
+    }
+    if (plain == 0) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const LineTerms q0(rec[i], 0), q1(rec[i], 8);
+        if (q0.inv_hi == 0) c[i] = (c[i] & 0xFFFF0000u) | by_sample(v, q0.n, q0.d);
+        if (q1.inv_hi == 0) c[i] = (c[i] & 0xFFFFu) | (by_sample(v, q1.n, q1.d) << 16);
+      }
+    }
+  }
+};
+
+// Counts of one chunk of tch integrands (a multiple of 32) for 64 work items.
+// MODE_ALL also writes the FP32 error vectors [P][Tp]: 32 integrands' counts
+// of the wave's pixels change hands through LDS, so that eight lanes write one
+// pixel's whole 128-byte line.
+constexpr uint32_t ERR_PITCH = 17;   // words of a pixel's 32 counts in LDS
+
+template <class Counter, int MODE>
+__device__ __forceinline__ void count_body(const DevView& v, uint32_t kappa, uint32_t m, uint32_t tch, uint32_t blk,
+                                           uint32_t* lds) {
+  const uint32_t lane = threadIdx.x & 63;
+  const uint32_t wave = __builtin_amdgcn_readfirstlane(blk * 4 + (threadIdx.x >> 6));
+  const uint32_t nch = (v.tp + tch - 1) / tch;
+  const uint32_t jg = wave / nch, ch = wave - jg * nch;
+  if (jg * 64 >= m) return;
+  // lanes past the last item repeat it and store nothing
+  const uint32_t j0 = jg * 64 + lane;
+  const bool live = j0 < m;
+  const uint32_t j = live ? j0 : m - 1;
+  uint32_t p, u, row, rows;
+  uint16_t* buf;
+  count_target<MODE>(v, kappa, j, m, p, u, buf, row, rows);
+  if ((MODE == MODE_CLASS || MODE == MODE_SWEEP) && ch == 0 && live) v.u_new[j] = u;
+  const Counter counter(v, u);
+  const float inv_n = 1.0f / (float)v.n;
+  const uint32_t t0 = ch * tch, t1 = min(t0 + tch, v.tp), tz = min(t1, (v.t + 7) & ~7u);
+  uint32_t* el = lds + (MODE == MODE_ALL ? (threadIdx.x >> 6) * 64 * ERR_PITCH : 0);
+#pragma unroll 1
+  for (uint32_t t = t0; t < t1; t += 8) {
+    uint32_t c[4] = {0, 0, 0, 0};   // padded integrands count 0
+    if (t < tz) counter.count8(v, t, c);
+    // computed in every lane (an empty asm consumes them): otherwise the
+    // counting would move under the store's branch
+    asm volatile("" : : "v"(c[0]), "v"(c[1]), "v"(c[2]), "v"(c[3]));
+    if (live) *(uint4*)(buf + tix(row, t, rows)) = make_uint4(c[0], c[1], c[2], c[3]);
+    if (MODE == MODE_ALL) {
+      const uint32_t e = (t - t0) & 31;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) el[lane * ERR_PITCH + e / 2 + i] = c[i];
+      if (e == 24) {
+        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        const uint32_t tb = t - 24 + 4 * (lane & 7);
+        const float4 ar = *(const float4*)(v.area + tb);
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+          const uint32_t q = 8 * i + (lane >> 3), jq = jg * 64 + q;
+          const uint32_t w0 = el[q * ERR_PITCH + 2 * (lane & 7)], w1 = el[q * ERR_PITCH + 2 * (lane & 7) + 1];
+          float4 o;
+          o.x = (float)(w0 & 0xFFFFu) * inv_n - ar.x;
+          o.y = (float)(w0 >> 16) * inv_n - ar.y;
+          o.z = (float)(w1 & 0xFFFFu) * inv_n - ar.z;
+          o.w = (float)(w1 >> 16) * inv_n - ar.w;
+          if (jq < m) *(float4*)(v.err + (size_t)jq * v.tp + tb) = o;
+        }
+        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+        __builtin_amdgcn_wave_barrier();
       }
     }
   }
@@ -170,52 +325,58 @@ __device__ __forceinline__ void count_lanes_body(const DevView& v, const int2* _
 // sweep-wide recount of the overlapped schedule is capped so that it leaves
 // room on every CU for the colour phases running beside it): workgroups then
 // stride over the virtual blocks.
-//
-// Occupancy target four waves per SIMD: aiming higher, the compiler fed each
-// v_perm from the v_dot2 just before it and padded the pair with s_nop (about
-// 250 per eight integrands at N = 64).
-template <int NS, int L, int MODE>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) void k_count(
-    DevView v, const int2* __restrict__ ihp, uint32_t kappa, uint32_t m, uint32_t tch, uint32_t vblocks) {
-  for (uint32_t b = blockIdx.x; b < vblocks; b += gridDim.x) count_lanes_body<NS, L, MODE>(v, ihp, kappa, m, tch, b);
+template <class Counter, int MODE>
+__global__ __launch_bounds__(256) void k_count(DevView v, uint32_t kappa, uint32_t m, uint32_t tch,
+                                               uint32_t vblocks) {
+  __shared__ uint32_t lds[MODE == MODE_ALL ? 4 * 64 * ERR_PITCH : 1];
+  for (uint32_t b = blockIdx.x; b < vblocks; b += gridDim.x) count_body<Counter, MODE>(v, kappa, m, tch, b, lds);
 }
 
-// Batched form: member i owns blocks pre[i] .. pre[i+1]-1.  MODE_CLASS counts
-// the proposals of colour class kappa; MODE_SWEEP those of every pixel of the
-// sweep kappa steps ahead of the member's sweep counter (the overlapped
-// schedule's sweep-wide recount).
-template <int NS, int L, int MODE>
+// Batched form: member i owns blocks pre[i] .. pre[i+1]-1; the proposals of
+// every pixel of the sweep kappa steps ahead of the member's sweep counter
+// (the overlapped schedule's sweep-wide recount).
+template <class Counter>
 __global__ __launch_bounds__(256) void k_count_batch(const DevView* __restrict__ views,
                                                      const uint32_t* __restrict__ pre, uint32_t nmem,
                                                      uint32_t kappa) {
   const uint32_t i = batch_member(pre, nmem, blockIdx.x);
   const DevView v = views[i];
-  const uint32_t m = MODE == MODE_SWEEP ? v.w * v.h : v.pc;
-  count_lanes_body<NS, L, MODE>(v, v.ihp, kappa, m, L == 1 ? 64u : v.tch, blockIdx.x - pre[i]);
+  count_body<Counter, MODE_SWEEP>(v, kappa, v.w * v.h, v.tch, blockIdx.x - pre[i], nullptr);
 }
 
-// Lanes per work item (N / 64 above N = 64) and the integrand chunk of a wave:
-// 64 integrands up to N = 64, else v.tch (whole rows at T <= 1024 by
-// default), halved while a launch over m items would hold under 8192 waves.
-inline uint32_t count_lanes(uint32_t n) { return n <= 64 ? 1u : n / 64; }
-
+// The integrand chunk of a wave: v.tch, halved while a launch over m items
+// would hold under 8192 waves.
 inline uint32_t count_chunk(const DevView& v, uint32_t m, uint32_t tch) {
-  if (v.n <= 64) return 64;
-  const uint64_t groups = (m + 64 / count_lanes(v.n) - 1) / (64 / count_lanes(v.n));
-  while (tch > 64 && groups * ((v.tp + tch - 1) / tch) < 8192) tch >>= 1;
+  const uint64_t groups = (m + 63) / 64;
+  while (tch > 32 && groups * ((v.tp + tch - 1) / tch) < 8192) tch = ((tch >> 1) + 31) & ~31u;
   return tch;
 }
 
-inline uint64_t count_waves(const DevView& v, uint32_t m, uint32_t tch) {
-  const uint32_t ipw = 64 / count_lanes(v.n);
-  return (uint64_t)((m + ipw - 1) / ipw) * ((v.tp + tch - 1) / tch);
+inline uint32_t count_vblocks(const DevView& v, uint32_t m, uint32_t tch) {
+  return (uint32_t)(((uint64_t)((m + 63) / 64) * ((v.tp + tch - 1) / tch) + 3) / 4);
+}
+
+// Calls f with the counter of launch kind `kind` (N up to 8, else 16 + the
+// line counter's template size).
+template <class F>
+hipError_t with_counter(int kind, F f) {
+#define BN_LINES(R) case 16 + R: return f((LineCounter<R>*)nullptr);
+  switch (kind) {
+    case 1: return f((SampleCounter<1>*)nullptr);
+    case 2: return f((SampleCounter<2>*)nullptr);
+    case 4: return f((SampleCounter<4>*)nullptr);
+    case 8: return f((SampleCounter<8>*)nullptr);
+    BN_LINE_TEMPLATES(BN_LINES)
+    default: return hipErrorInvalidValue;
+  }
+#undef BN_LINES
 }
 
 template <int MODE>
 hipError_t count_dispatch(const DevView& v, uint32_t kappa, uint32_t m, hipStream_t s) {
   if (m == 0) return hipSuccess;
   const uint32_t tch = count_chunk(v, m, v.tch);
-  const uint32_t vb = (uint32_t)((count_waves(v, m, tch) + 3) / 4);
+  const uint32_t vb = count_vblocks(v, m, tch);
   // a capped launch gets the fewest rounds the cap allows and as few
   // workgroups as those rounds need, so that every workgroup strides over the
   // same number of blocks
@@ -224,26 +385,11 @@ hipError_t count_dispatch(const DevView& v, uint32_t kappa, uint32_t m, hipStrea
     const uint32_t rounds = (vb + v.count_cap - 1) / v.count_cap;
     nb = (vb + rounds - 1) / rounds;
   }
-  const dim3 g(nb), b(256);
-#define BN_COUNT(NS, L) hipLaunchKernelGGL((k_count<NS, L, MODE>), g, b, 0, s, v, v.ihp, kappa, m, tch, vb); break
-  switch (v.n) {
-    case 1: BN_COUNT(1, 1);
-    case 2: BN_COUNT(2, 1);
-    case 4: BN_COUNT(4, 1);
-    case 8: BN_COUNT(8, 1);
-    case 16: BN_COUNT(16, 1);
-    case 32: BN_COUNT(32, 1);
-    case 64: BN_COUNT(64, 1);
-    case 128: BN_COUNT(64, 2);
-    case 256: BN_COUNT(64, 4);
-    case 512: BN_COUNT(64, 8);
-    case 1024: BN_COUNT(64, 16);
-    case 2048: BN_COUNT(64, 32);
-    case 4096: BN_COUNT(64, 64);
-    default: return hipErrorInvalidValue;
-  }
-#undef BN_COUNT
-  return hipGetLastError();
+  return with_counter(count_kind(v), [&](auto* c) {
+    using Counter = std::remove_pointer_t<decltype(c)>;
+    hipLaunchKernelGGL((k_count<Counter, MODE>), dim3(nb), dim3(256), 0, s, v, kappa, m, tch, vb);
+    return hipGetLastError();
+  });
 }
 
 }  // namespace
@@ -257,44 +403,19 @@ hipError_t launch_count(const DevView& v, int mode, uint32_t kappa, uint32_t m, 
   }
 }
 
-// Launch kind of a batch member's recount: N itself up to 64, else 64 + the
-// lanes per work item (one kernel per N either way).
-int count_kind(const DevView& v) { return v.n <= 64 ? (int)v.n : 64 + (int)count_lanes(v.n); }
+// Launch kind of a problem's counting kernel: N up to 8, else 16 + the line
+// counter's template size.
+int count_kind(const DevView& v) { return v.lines ? 16 + (int)v.lines : (int)v.n; }
 
-uint32_t count_blocks(const DevView& v, bool sweep) {
-  return (uint32_t)((count_waves(v, sweep ? v.w * v.h : v.pc, v.n <= 64 ? 64u : v.tch) + 3) / 4);
-}
-
-template <int MODE>
-hipError_t count_batch_dispatch(int kind, const DevView* views, const uint32_t* pre, uint32_t nmem,
-                                uint32_t blocks, uint32_t kappa, hipStream_t s) {
-  const dim3 g(blocks), b(256);
-#define BN_COUNT(NS, L) \
-  hipLaunchKernelGGL((k_count_batch<NS, L, MODE>), g, b, 0, s, views, pre, nmem, kappa); break
-  switch (kind) {
-    case 1: BN_COUNT(1, 1);
-    case 2: BN_COUNT(2, 1);
-    case 4: BN_COUNT(4, 1);
-    case 8: BN_COUNT(8, 1);
-    case 16: BN_COUNT(16, 1);
-    case 32: BN_COUNT(32, 1);
-    case 64: BN_COUNT(64, 1);
-    case 66: BN_COUNT(64, 2);
-    case 68: BN_COUNT(64, 4);
-    case 72: BN_COUNT(64, 8);
-    case 80: BN_COUNT(64, 16);
-    case 96: BN_COUNT(64, 32);
-    case 128: BN_COUNT(64, 64);
-    default: return hipErrorInvalidValue;
-  }
-#undef BN_COUNT
-  return hipGetLastError();
-}
+uint32_t count_blocks(const DevView& v) { return count_vblocks(v, v.w * v.h, v.tch); }
 
 hipError_t launch_count_batch(int kind, const DevView* views, const uint32_t* pre, uint32_t nmem,
-                              uint32_t blocks, uint32_t kappa, bool sweep, hipStream_t s) {
-  return sweep ? count_batch_dispatch<MODE_SWEEP>(kind, views, pre, nmem, blocks, kappa, s)
-               : count_batch_dispatch<MODE_CLASS>(kind, views, pre, nmem, blocks, kappa, s);
+                              uint32_t blocks, uint32_t kappa, hipStream_t s) {
+  return with_counter(kind, [&](auto* c) {
+    using Counter = std::remove_pointer_t<decltype(c)>;
+    hipLaunchKernelGGL(k_count_batch<Counter>, dim3(blocks), dim3(256), 0, s, views, pre, nmem, kappa);
+    return hipGetLastError();
+  });
 }
 
 }  // namespace bnlat

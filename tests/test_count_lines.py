@@ -1,0 +1,72 @@
+"""The line counter (hit counts from one clamped crossing per lattice line)
+against the direct count of the samples, on the library's own tables: every N
+it serves, generators of every kind, offsets and edges chosen so that samples
+lie on or next to the edge."""
+import ctypes as C
+import os
+import subprocess
+
+import numpy as np
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+
+
+@pytest.fixture(scope="module")
+def model(tmp_path_factory):
+    out = str(tmp_path_factory.mktemp("lines") / "libmodel.so")
+    subprocess.run(["g++", "-O2", "-std=c++17", "-shared", "-fPIC", "-ffp-contract=off",
+                    os.path.join(HERE, "count_lines_model.cpp"), "-o", out], check=True)
+    return C.CDLL(out)
+
+
+def rows(n, k, g, rng):
+    theta = rng.uniform(0, 2 * np.pi, k)
+    nx = np.rint(16384 * np.cos(theta)).astype(np.int16)
+    ny = np.rint(16384 * np.sin(theta)).astype(np.int16)
+    q = k // 4
+    # axis-parallel and diagonal edges, tiny and extreme normals
+    nx[:q], ny[:q] = rng.choice([-16384, -1, 0, 1, 16384], q), rng.choice([-16384, -2, 1, 3, 16384], q)
+    # edges nearly along short lattice vectors
+    step = 65536 // n
+    s = rng.integers(1, n + 1, q)
+    vx, vy = (s * g[0] + n // 2) % n - n // 2, (s * g[1] + n // 2) % n - n // 2
+    f = 16000 // np.maximum(1, np.maximum(abs(vx), abs(vy)))
+    nx[q:2 * q], ny[q:2 * q] = -vy * f + rng.integers(-1, 2, q), vx * f
+    zero = (nx == 0) & (ny == 0)
+    nx[zero] = 1
+    c = rng.integers(0, 65536, (2, k), dtype=np.uint16)
+    u = rng.integers(0, 65536, (2, k), dtype=np.uint16)
+    # offsets on the grid's corners, and edge points on a sample of the pixel
+    u[:, ::5] = rng.choice([0, 1, step - 1, 65535], (2, len(u[0, ::5])))
+    i = rng.integers(0, n, k)
+    on = rng.random(k) < 0.5
+    c[0][on] = (u[0] + i * g[0] % n * step)[on].astype(np.uint16)
+    c[1][on] = (u[1] + i * g[1] % n * step)[on].astype(np.uint16)
+    return nx, ny, c[0].copy(), c[1].copy(), u[0].copy(), u[1].copy()
+
+
+@pytest.mark.parametrize("n", [16, 32, 64, 128, 256, 512, 1024, 2048, 4096])
+def test_line_counts_equal_direct_counts(model, n):
+    rng = np.random.default_rng(n)
+    gens = [(1, 1), (1, n - 1), (1, 3), (3, 1), (1, n // 2 + 1), (1, n // 2 - 1), (1, int(n * 0.618) | 1)]
+    gens += [(int(2 * rng.integers(0, n // 2) + 1), int(2 * rng.integers(0, n // 2) + 1)) for _ in range(24)]
+    k, by_sample = 4000 if n <= 1024 else 1000, 0
+    for g in gens:
+        a = rows(n, k, g, rng)
+        got, want, few = np.zeros(k, np.uint32), np.zeros(k, np.uint32), C.c_uint32()
+        lines = model.count_lines_model(n, g[0], g[1], k, *[x.ctypes.data_as(C.c_void_p) for x in a],
+                                        got.ctypes.data_as(C.c_void_p), want.ctypes.data_as(C.c_void_p), C.byref(few))
+        assert 0 < lines <= (2 * n) ** 0.5
+        np.testing.assert_array_equal(got, want, err_msg=f"g={g}")
+        by_sample += few.value
+    assert 0 < by_sample < 0.5 * k * len(gens)
+
+
+@pytest.mark.parametrize("n", [16, 64, 256, 1024, 4096])
+def test_every_generator_has_lines(model, n):
+    """Each lattice of N points is that of (1, y) for an odd y: its line table
+    exists for all of them (every 16th at the largest N), and padded integrands
+    count nothing."""
+    for y in range(1, n, 2 if n <= 1024 else 32):
+        assert model.count_lines_padding(n, 1, y) == 0, y
