@@ -217,14 +217,12 @@ struct bn_problem_s {
   bool have_offsets = false;
   bool have_counts = false;
   bool errors_valid = false;   // FP32 error vectors match the counts
-  hipGraph_t graph = nullptr;
-  hipGraphExec_t graph_exec = nullptr;
-  bool graph_failed = false;
   // Overlapped sweeps: proposals of a whole sweep, rows grouped by colour
   // class, in two buffer sets; set 0 always holds the proposals of the
   // current sweep index `prefetched` when that equals `sweep`.
   struct SweepSet {
-    uint16_t* cn = nullptr;
+    uint16_t* cn = nullptr;   // counts, or (narrow forms) their int8 deviations:
+    int8_t* n8 = nullptr;     // one of the two
     uint32_t* un = nullptr;
     float* gn = nullptr;
   } sets[2];
@@ -268,8 +266,6 @@ struct bn_problem_s {
     return BN_OK;
   }
   ~bn_problem_s() {
-    if (graph_exec) (void)hipGraphExecDestroy(graph_exec);
-    if (graph) (void)hipGraphDestroy(graph);
     if (pair_exec) (void)hipGraphExecDestroy(pair_exec);
     if (pair_graph) (void)hipGraphDestroy(pair_graph);
     if (swap_exec) (void)hipGraphExecDestroy(swap_exec);
@@ -289,7 +285,7 @@ struct bn_problem_s {
 // A group of batch members served by one launch of one kernel variant.
 struct BatchGroup {
   int kind = 0;               // counting-kernel variant (count_kind)
-  uint32_t radius = 0, k = 0; // staged energy-change variant
+  uint32_t radius = 0, k = 0, form = 0; // staged energy-change variant
   std::vector<uint32_t> idx;  // member indices
   // member view tables on the device: counting groups, one per proposal set
   // (whole sweep); phase groups, one per (set, colour class): set * K^2 + kappa
@@ -403,6 +399,23 @@ bn_status untile_counts(bn_problem p, const uint16_t* dev, uint32_t rows, uint16
   return BN_OK;
 }
 
+// The same from a tiled buffer of int8 deviations ([tp/16][rows][16]).
+bn_status untile_narrow(bn_problem p, const int8_t* dev, uint32_t rows, uint16_t* host) {
+  const uint32_t t = p->v.t, tp = p->v.tp;
+  std::vector<int8_t> tmp((size_t)rows * tp);
+  std::vector<uint32_t> bias(tp / 2);
+  HIPCHK(hipMemcpyAsync(tmp.data(), dev, tmp.size(), hipMemcpyDeviceToHost, p->stream));
+  HIPCHK(hipMemcpyAsync(bias.data(), p->v.bias8, bias.size() * 4, hipMemcpyDeviceToHost, p->stream));
+  bn_status s = sync(p);
+  if (s != BN_OK) return s;
+  for (uint32_t i = 0; i < t; ++i) {
+    const int base = (int)(((0x00800080u - bias[i / 2]) >> (16 * (i & 1))) & 0xFFFFu);
+    for (uint32_t r = 0; r < rows; ++r)
+      host[(size_t)r * t + i] = (uint16_t)(tmp[((size_t)(i >> 4) * rows + r) * 16 + (i & 15)] + base);
+  }
+  return BN_OK;
+}
+
 bn_status ensure_list(bn_problem p, uint32_t m) {
   if (m <= p->list_cap) return BN_OK;
   bn_status s;
@@ -455,23 +468,12 @@ bn_status refresh_errors(bn_problem p) {
   return BN_OK;
 }
 
-bn_status record_sweep(bn_problem p) {
-  for (uint32_t kappa = 0; kappa < p->cfg.colour_k * p->cfg.colour_k; ++kappa) {
-    HIPCHK(launch_count(p->v, MODE_CLASS, kappa, p->v.pc, p->stream));
-    HIPCHK(launch_gauss_est(p->v, MODE_CLASS, p->v.pc, p->stream));
-    HIPCHK(launch_gauss_delta(p->v, MODE_CLASS, kappa, p->v.pc, p->stream));
-    HIPCHK(launch_delta(p->v, MODE_CLASS, kappa, p->v.pc, p->stream));
-    HIPCHK(launch_commit(p->v, kappa, p->stream));
-    HIPCHK(launch_gauss_commit(p->v, kappa, p->stream));
-  }
-  HIPCHK(launch_advance(p->v, p->stream));
-  return BN_OK;
-}
-
 // The view of colour phase kappa reading proposals from sweep buffer set b.
 DevView phase_view(bn_problem p, int b, uint32_t kappa) {
   DevView v = p->v;
-  v.c_new = p->sets[b].cn + (size_t)kappa * v.pc * v.tp;
+  const size_t first = (size_t)kappa * v.pc * v.tp;
+  v.c_new = p->sets[b].cn ? p->sets[b].cn + first : nullptr;
+  v.n8 = p->sets[b].n8 ? p->sets[b].n8 + first : nullptr;
   v.u_new = p->sets[b].un + (size_t)kappa * v.pc;
   if (v.tgp) v.g_new = p->sets[b].gn + (size_t)kappa * v.pc * v.tgp;
   return v;
@@ -480,6 +482,7 @@ DevView phase_view(bn_problem p, int b, uint32_t kappa) {
 DevView sweep_view(bn_problem p, int b) {
   DevView v = p->v;
   v.c_new = p->sets[b].cn;
+  v.n8 = p->sets[b].n8;
   v.u_new = p->sets[b].un;
   if (v.tgp) v.g_new = p->sets[b].gn;
   return v;
@@ -500,7 +503,9 @@ bn_status ensure_sweep_sets(bn_problem p) {
   const size_t P = (size_t)p->v.w * p->v.h;
   bn_status s;
   for (int b = 0; b < 2; ++b) {
-    if ((s = p->alloc(&p->sets[b].cn, P * p->v.tp)) != BN_OK) return s;
+    if ((s = p->v.form == FIELD_WIDE ? p->alloc(&p->sets[b].cn, P * p->v.tp) : p->alloc(&p->sets[b].n8, P * p->v.tp)) !=
+        BN_OK)
+      return s;
     if ((s = p->alloc(&p->sets[b].un, P)) != BN_OK) return s;
     if (p->v.tgp && (s = p->alloc(&p->sets[b].gn, P * p->v.tgp)) != BN_OK) return s;
   }
@@ -550,19 +555,25 @@ bn_status record_proposals(bn_problem p, int b, uint32_t ahead, hipStream_t st, 
   return BN_OK;
 }
 
-bn_status record_phases(bn_problem p, int b) {
-  for (uint32_t kappa = 0; kappa < p->cfg.colour_k * p->cfg.colour_k; ++kappa) {
+// The colour phases of one sweep from proposal set b; advance: also the sweep
+// counter (by the last phase's commit where it can).
+bn_status record_phases(bn_problem p, int b, bool advance) {
+  const uint32_t phases = p->cfg.colour_k * p->cfg.colour_k;
+  const bool staged = staged_phases(p->v);
+  for (uint32_t kappa = 0; kappa < phases; ++kappa) {
     const DevView v = phase_view(p, b, kappa);
     ProfMark me(p, &p->prof_eval, p->stream);
     HIPCHK(launch_gauss_delta(v, MODE_CLASS, kappa, v.pc, p->stream));
-    HIPCHK(launch_delta(v, MODE_CLASS, kappa, v.pc, p->stream));
+    HIPCHK(staged ? launch_stage(v, kappa, p->stream) : launch_delta(v, MODE_CLASS, kappa, v.pc, p->stream));
     bn_status s = me.end();
     if (s != BN_OK) return s;
     ProfMark mc(p, &p->prof_commit, p->stream);
-    HIPCHK(launch_commit(v, kappa, p->stream));
+    if (staged) HIPCHK(launch_decide_commit(v, kappa, advance && kappa + 1 == phases, p->stream));
+    else HIPCHK(launch_commit(v, kappa, p->stream));
     HIPCHK(launch_gauss_commit(v, kappa, p->stream));
     if ((s = mc.end()) != BN_OK) return s;
   }
+  if (advance && !staged) HIPCHK(launch_advance(p->v, p->stream));
   return BN_OK;
 }
 
@@ -580,7 +591,7 @@ bn_status record_pair(bn_problem p) {
     HIPCHK(hipStreamWaitEvent(p->aux, p->ev[2 * half], 0));
     if ((s = record_proposals(p, nxt, 1, p->aux)) != BN_OK) return s;
     HIPCHK(hipEventRecord(p->ev[2 * half + 1], p->aux));
-    if ((s = record_phases(p, cur)) != BN_OK) return s;
+    if ((s = record_phases(p, cur, false)) != BN_OK) return s;
     HIPCHK(hipStreamWaitEvent(p->stream, p->ev[2 * half + 1], 0));
     HIPCHK(launch_advance(p->v, p->stream));
   }
@@ -595,8 +606,8 @@ bn_status record_pair(bn_problem p) {
 // pair's second half, or, at the start of a captured pair or of a call
 // (`fork`), everything before on the main stream.  The phases of a sweep are
 // done long before the recount beside them, so a recount does not wait for
-// the join and advance after the previous one; the main stream still joins
-// each recount before its advance.
+// the join after the previous one; the main stream still joins each recount
+// after its phases, the last of which advance the sweep counter.
 bn_status record_pair_chained(bn_problem p, bool fork) {
   bn_status s;
   for (int half = 0; half < 2; ++half) {
@@ -612,10 +623,9 @@ bn_status record_pair_chained(bn_problem p, bool fork) {
     if ((s = record_proposals(p, nxt, (uint32_t)half, p->aux, true)) != BN_OK) return s;
     if (half == 1) HIPCHK(launch_recount_advance_pair(p->v, p->aux));
     HIPCHK(hipEventRecord(p->ev[2 * half + 1], p->aux));
-    if ((s = record_phases(p, cur)) != BN_OK) return s;
+    if ((s = record_phases(p, cur, true)) != BN_OK) return s;
     HIPCHK(hipEventRecord(p->ev[half == 0 ? 2 : 4], p->stream));
     HIPCHK(hipStreamWaitEvent(p->stream, p->ev[2 * half + 1], 0));
-    HIPCHK(launch_advance(p->v, p->stream));
   }
   return BN_OK;
 }
@@ -670,8 +680,7 @@ bn_status overlapped_sweeps(bn_problem p, uint32_t k) {
   }
   if (done < k) {
     // one more sweep, then the next sweep's proposals into set 0
-    if ((s = record_phases(p, 0)) != BN_OK) return s;
-    HIPCHK(launch_advance(p->v, p->stream));
+    if ((s = record_phases(p, 0, true)) != BN_OK) return s;
     if ((s = record_proposals(p, 0, 0, p->stream)) != BN_OK) return s;
     done += 1;
   }
@@ -795,38 +804,6 @@ bn_status swap_sweeps(bn_problem p, uint32_t k) {
   return BN_OK;
 }
 
-bn_status build_graph(bn_problem p) {
-  if (p->graph_exec || p->graph_failed) return BN_OK;
-  if (p->stream == nullptr) {
-    p->graph_failed = true;
-    return BN_OK;
-  }
-  HIPCHK(hipStreamBeginCapture(p->stream, hipStreamCaptureModeThreadLocal));
-  bn_status s = record_sweep(p);
-  hipGraph_t g = nullptr;
-  hipError_t e = hipStreamEndCapture(p->stream, &g);
-  if (s != BN_OK) {
-    if (g) (void)hipGraphDestroy(g);
-    return s;
-  }
-  if (e != hipSuccess) {
-    (void)hipGetLastError();
-    p->graph_failed = true;
-    return BN_OK;
-  }
-  e = hipGraphInstantiate(&p->graph_exec, g, nullptr, nullptr, 0);
-  if (e != hipSuccess) {
-    (void)hipGetLastError();
-    (void)hipGraphDestroy(g);
-    p->graph_exec = nullptr;
-    p->graph_failed = true;
-    return BN_OK;
-  }
-  p->graph = g;
-  return BN_OK;
-}
-
-
 // Candidates of the launch-shape tuner: integrands per counting wave and the
 // workgroup target of the staged energy-change launch.
 const uint32_t kTuneTch[] = {64, 128, 256, 512};
@@ -914,7 +891,7 @@ bn_status batch_upload(bn_batch b) {
   for (BatchGroup& g : b->stage_groups)
     if ((s = upload(g, 1, [](const DevView&) { return 0u; }, true)) != BN_OK) return s;
   if ((s = upload(b->finish_all, 1, [](const DevView& v) { return (v.pc + 255) / 256; }, false)) != BN_OK) return s;
-  if ((s = upload(b->commit_all, 1, [](const DevView& v) { return commit_blocks(v); }, false)) != BN_OK) return s;
+  if ((s = upload(b->commit_all, 1, [](const DevView& v) { return decide_commit_blocks(v); }, false)) != BN_OK) return s;
   return BN_OK;
 }
 
@@ -926,14 +903,22 @@ bn_status batch_recount(bn_batch b, int set, uint32_t ahead, hipStream_t st) {
   return BN_OK;
 }
 
-// Energy change and decision of colour class kappa for every grouped member,
-// proposals from set `set` (no state change).
+// Class sums of colour class kappa for every grouped member, proposals from
+// set `set`.
+bn_status batch_stage(bn_batch b, int set, uint32_t kappa) {
+  const uint32_t t = set * b->colour_k * b->colour_k + kappa;
+  for (BatchGroup& g : b->stage_groups)
+    HIPCHK(launch_stage_batch(g.form, g.radius, g.k, b->shape, g.views[t], g.d_pre, g.d_geo, (uint32_t)g.idx.size(),
+                              g.blocks, kappa, b->stream));
+  return BN_OK;
+}
+
+// Class sums and decision alone (no state change).
 bn_status batch_evaluate(bn_batch b, int set, uint32_t kappa) {
   if (b->finish_all.idx.empty()) return BN_OK;   // no grouped members
   const uint32_t t = set * b->colour_k * b->colour_k + kappa;
-  for (BatchGroup& g : b->stage_groups)
-    HIPCHK(launch_stage_batch(g.radius, g.k, b->shape, g.views[t], g.d_pre, g.d_geo, (uint32_t)g.idx.size(), g.blocks,
-                              kappa, b->stream));
+  bn_status s = batch_stage(b, set, kappa);
+  if (s != BN_OK) return s;
   HIPCHK(launch_finish_batch(b->finish_all.views[t], b->finish_all.d_pre, (uint32_t)b->finish_all.idx.size(),
                              b->finish_all.blocks, b->stream));
   return BN_OK;
@@ -942,10 +927,10 @@ bn_status batch_evaluate(bn_batch b, int set, uint32_t kappa) {
 bn_status batch_phases(bn_batch b, int set) {
   bn_status s;
   for (uint32_t kappa = 0; kappa < b->colour_k * b->colour_k; ++kappa) {
-    if ((s = batch_evaluate(b, set, kappa)) != BN_OK) return s;
+    if ((s = batch_stage(b, set, kappa)) != BN_OK) return s;
     const uint32_t t = set * b->colour_k * b->colour_k + kappa;
-    HIPCHK(launch_commit_batch(b->commit_all.views[t], b->commit_all.d_pre, (uint32_t)b->commit_all.idx.size(),
-                               b->commit_all.blocks, kappa, b->stream));
+    HIPCHK(launch_decide_commit_batch(b->commit_all.views[t], b->commit_all.d_pre, (uint32_t)b->commit_all.idx.size(),
+                                      b->commit_all.blocks, kappa, b->stream));
   }
   return BN_OK;
 }
@@ -1013,8 +998,7 @@ bn_status batch_single_sweep(bn_batch b) {
     if (p->cfg.move == BN_SWAP) {
       if ((s = record_swap_sweep(p)) != BN_OK) return s;
     } else {
-      if ((s = record_phases(p, 0)) != BN_OK) return s;
-      HIPCHK(launch_advance(p->v, p->stream));
+      if ((s = record_phases(p, 0, true)) != BN_OK) return s;
       if ((s = record_proposals(p, 0, 0, p->stream)) != BN_OK) return s;
     }
   }
@@ -1301,8 +1285,8 @@ bn_status bn_create_problem_ext(const bn_config* cfg, const bn_heaviside* heavis
   v.lines = 0;
   std::vector<uint32_t> lrow;
   std::vector<LineRec> lrec;
+  const LatticeLines g = lattice_lines(v.n, v.gx, v.gy);
   if (v.n >= 16) {
-    const LatticeLines g = lattice_lines(v.n, v.gx, v.gy);
     v.lines = line_template(g.lines);
     if (!g.lines || !v.lines || !lattice_rows(v.n, v.gx, v.gy, g, v.lines, line_row_words(v.lines), lrow)) {
       delete p;
@@ -1312,8 +1296,23 @@ bn_status bn_create_problem_ext(const bn_config* cfg, const bn_heaviside* heavis
     for (uint32_t t = 0; t < v.t; ++t) lrec[t] = line_record(g, step, heav[t].nx, heav[t].ny, heav[t].cx, heav[t].cy);
   }
 
+  // Operands of the FP32 form's colour phases (stage_dev.h): int8 deviations of
+  // the counts from a base of their integrand where they are known to fit.
+  // The base is N / 2 (|c - base| <= N / 2) or N x area (the lines' bound).
+  uint32_t dev = std::max(1u, v.n / 2);
+  const uint32_t by_lines = count_deviation(v.n, g);
+  const bool centred = v.n > 64 && by_lines && by_lines < dev;
+  if (centred) dev = by_lines;
+  v.form = FIELD_WIDE;
+  if (v.mfma == 0 && cfg->move == BN_REDRAW && (v.k == 1 || v.k == 2 || v.k == 4))
+    v.form = dev <= 63 ? FIELD_NARROW : dev <= 126 ? FIELD_SPLIT : FIELD_WIDE;
+  std::vector<uint32_t> bias8(v.tp / 2, 0x00800080u);
+  for (uint32_t t = 0; t < v.t; ++t)
+    bias8[t / 2] -= (centred ? (uint32_t)std::lround(v.n * area[t]) : v.n / 2) << (16 * (t & 1));
+
   uint32_t* lat_d;
   uint32_t* lrow_d;
+  uint32_t* bias_d;
   LineRec* lrec_d;
   int2* ihp_d;
   float* area_d;
@@ -1324,7 +1323,9 @@ bn_status bn_create_problem_ext(const bn_config* cfg, const bn_heaviside* heavis
       (s = p->adopt(&v.U, bufs ? bufs->offsets : nullptr, P)) != BN_OK ||
       (s = p->adopt(&v.cnt, bufs ? bufs->counts : nullptr, P * v.tp)) != BN_OK ||
       (s = p->adopt(&v.err, bufs ? bufs->errors : nullptr, P * v.tp)) != BN_OK || (s = p->alloc(&v.u_new, v.pc)) != BN_OK ||
-      (s = p->alloc(&v.c_new, (size_t)v.pc * v.tp)) != BN_OK || (s = p->alloc(&v.delta, v.pc)) != BN_OK ||
+      (s = p->alloc(&bias_d, bias8.size())) != BN_OK ||
+      (v.form == FIELD_WIDE && (s = p->alloc(&v.c_new, (size_t)v.pc * v.tp)) != BN_OK) ||
+      (v.form != FIELD_WIDE && ((s = p->alloc(&v.d8, P * v.tp)) != BN_OK || (s = p->alloc(&v.n8, (size_t)v.pc * v.tp)) != BN_OK)) || (s = p->alloc(&v.delta, v.pc)) != BN_OK ||
       (s = p->alloc(&v.accept, v.pc)) != BN_OK || (s = p->alloc(&v.ctr, 4)) != BN_OK ||
       (s = p->alloc(&v.unsure, v.pc)) != BN_OK ||
       (s = p->alloc(&p->ysum, v.ncls)) != BN_OK || (s = p->alloc(&v.xpart, xpart_words(v))) != BN_OK) {
@@ -1332,6 +1333,7 @@ bn_status bn_create_problem_ext(const bn_config* cfg, const bn_heaviside* heavis
     return s;
   }
   v.lat = lat_d;
+  v.bias8 = bias_d;
   v.lrow = lrow_d;
   v.lrec = lrec_d;
   v.ihp = ihp_d;
@@ -1378,6 +1380,7 @@ bn_status bn_create_problem_ext(const bn_config* cfg, const bn_heaviside* heavis
   if (e == hipSuccess && v.lines) e = hipMemcpyAsync(lrow_d, lrow.data(), lrow.size() * 4, hipMemcpyHostToDevice, p->stream);
   if (e == hipSuccess && v.lines)
     e = hipMemcpyAsync(lrec_d, lrec.data(), lrec.size() * sizeof(LineRec), hipMemcpyHostToDevice, p->stream);
+  if (e == hipSuccess) e = hipMemcpyAsync(bias_d, bias8.data(), bias8.size() * 4, hipMemcpyHostToDevice, p->stream);
   if (e == hipSuccess) e = hipMemcpyAsync(ihp_d, ihp.data(), v.tp * 8, hipMemcpyHostToDevice, p->stream);
   if (e == hipSuccess) e = hipMemcpyAsync(area_d, areaf.data(), v.tp * 4, hipMemcpyHostToDevice, p->stream);
   if (e == hipSuccess) e = hipMemcpyAsync(wd_d, p->cls_w.data(), v.ncls * 8, hipMemcpyHostToDevice, p->stream);
@@ -2031,7 +2034,7 @@ bn_status bn_get_phase(bn_problem p, uint16_t* u_new, uint16_t* c_new, double* d
   const uint32_t M = p->v.pc;
   if (u_new) HIPCHK(hipMemcpyAsync(u_new, p->v.u_new, (size_t)M * 4, hipMemcpyDeviceToHost, p->stream));
   if (c_new) {
-    bn_status s = untile_counts(p, p->v.c_new, M, c_new);
+    bn_status s = p->v.form == FIELD_WIDE ? untile_counts(p, p->v.c_new, M, c_new) : untile_narrow(p, p->v.n8, M, c_new);
     if (s != BN_OK) return s;
   }
   if (delta) HIPCHK(hipMemcpyAsync(delta, p->v.delta, (size_t)M * 8, hipMemcpyDeviceToHost, p->stream));
@@ -2073,11 +2076,12 @@ bn_status bn_create_batch(const bn_problem* members, uint32_t m, const char* tun
       cg = b->count_groups.end() - 1;
     }
     cg->idx.push_back(i);
-    auto sg = std::find_if(b->stage_groups.begin(), b->stage_groups.end(), [&](const BatchGroup& g) { return g.radius == v.radius; });
+    auto sg = std::find_if(b->stage_groups.begin(), b->stage_groups.end(), [&](const BatchGroup& g) { return g.radius == v.radius && g.form == v.form; });
     if (sg == b->stage_groups.end()) {
       b->stage_groups.push_back(BatchGroup());
       b->stage_groups.back().radius = v.radius;
       b->stage_groups.back().k = K;
+      b->stage_groups.back().form = v.form;
       sg = b->stage_groups.end() - 1;
     }
     sg->idx.push_back(i);

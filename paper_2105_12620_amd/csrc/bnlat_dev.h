@@ -26,6 +26,9 @@ constexpr size_t NOALLOC_SCRATCH_BYTES = (size_t)32 << 20;
 // look-ahead added to the device sweep counter.
 enum CountMode : int { MODE_ALL = 0, MODE_CLASS = 1, MODE_LIST = 2, MODE_SWEEP = 3 };
 
+// Operands of the staged energy change (stage_dev.h).
+enum FieldForm : int { FIELD_WIDE = 0, FIELD_NARROW = 1, FIELD_SPLIT = 2 };
+
 // Everything a kernel needs to know about one problem, passed by value.
 struct DevView {
   uint32_t n, log2n, w, h, t, tp, k, cw, ch, pc;
@@ -45,6 +48,10 @@ struct DevView {
   float* err;                // [P][tp] error vectors
   uint32_t* u_new;           // [M] proposals of the current phase / list
   uint16_t* c_new;           // [tp/8][M][8] recounted hits of the proposals
+  uint32_t form;             // FieldForm of the colour phases
+  int8_t* d8;                // narrow forms: [tp/16][P][16] counts less their integrand's base, else null
+  int8_t* n8;                // narrow forms: [tp/16][M][16] the same of the proposals (c_new is null)
+  const uint32_t* bias8;     // [tp/2] 0x00800080 - (base of 2 i | base of 2 i + 1 << 16)
   double* delta;             // [M] energy change
   uint8_t* accept;           // [M] decision
   const uint32_t* pix_list;  // [M] pixels (list mode)
@@ -77,7 +84,12 @@ hipError_t launch_count(const DevView& v, int mode, uint32_t kappa, uint32_t m, 
 hipError_t launch_delta(const DevView& v, int mode, uint32_t kappa, uint32_t m, hipStream_t s);
 uint32_t xpart_words(const DevView& v);
 hipError_t launch_commit(const DevView& v, uint32_t kappa, hipStream_t s);
-uint32_t commit_blocks(const DevView& v);
+// a colour phase of the FP32 form whose class sums are staged (K = 1, 2, 4)
+bool staged_phases(const DevView& v);
+hipError_t launch_stage(const DevView& v, uint32_t kappa, hipStream_t s);
+// decision and commit in one launch; advance: also the sweep counter
+hipError_t launch_decide_commit(const DevView& v, uint32_t kappa, bool advance, hipStream_t s);
+uint32_t decide_commit_blocks(const DevView& v);
 hipError_t launch_errors(const DevView& v, hipStream_t s);
 hipError_t launch_advance(const DevView& v, hipStream_t s);
 hipError_t launch_recount_index(const DevView& v, hipStream_t s);
@@ -94,21 +106,34 @@ hipError_t launch_gauss_commit(const DevView& v, uint32_t kappa, hipStream_t s);
 hipError_t launch_gauss_errors(const DevView& v, hipStream_t s);
 hipError_t launch_gauss_energy(const DevView& v, double* gsum, hipStream_t s);
 
+// staged energy change, one source per form
+hipError_t launch_stage_wide(const DevView& v, uint32_t kappa, hipStream_t s);
+hipError_t launch_stage_batch_wide(uint32_t radius, uint32_t k, uint32_t shape, const DevView* views, const uint32_t* pre,
+                               const uint32_t* geo, uint32_t nmem, uint32_t blocks, uint32_t kappa, hipStream_t s);
+void stage_geometry_wide(const DevView& v, uint32_t shape, uint32_t* gx, uint32_t* gy, uint32_t* gz, uint32_t* trlen);
+hipError_t launch_stage_narrow(const DevView& v, uint32_t kappa, hipStream_t s);
+hipError_t launch_stage_batch_narrow(uint32_t radius, uint32_t k, uint32_t shape, const DevView* views, const uint32_t* pre,
+                               const uint32_t* geo, uint32_t nmem, uint32_t blocks, uint32_t kappa, hipStream_t s);
+void stage_geometry_narrow(const DevView& v, uint32_t shape, uint32_t* gx, uint32_t* gy, uint32_t* gz, uint32_t* trlen);
+hipError_t launch_stage_split(const DevView& v, uint32_t kappa, hipStream_t s);
+hipError_t launch_stage_batch_split(uint32_t radius, uint32_t k, uint32_t shape, const DevView* views, const uint32_t* pre,
+                               const uint32_t* geo, uint32_t nmem, uint32_t blocks, uint32_t kappa, hipStream_t s);
+void stage_geometry_split(const DevView& v, uint32_t shape, uint32_t* gx, uint32_t* gy, uint32_t* gz, uint32_t* trlen);
+
 // batched launches: member i of a group owns blocks pre[i] .. pre[i+1]-1
 int count_kind(const DevView& v);
 uint32_t count_blocks(const DevView& v);
 // staged-kernel block shape 0 (default) or 1 (the tuner's alternative)
-uint32_t stage_rows(uint32_t k, uint32_t shape);
 void stage_geometry(const DevView& v, uint32_t shape, uint32_t* gx, uint32_t* gy, uint32_t* gz, uint32_t* trlen);
 hipError_t launch_count_batch(int kind, const DevView* views, const uint32_t* pre, uint32_t nmem,
                               uint32_t blocks, uint32_t kappa, hipStream_t s);
-hipError_t launch_stage_batch(uint32_t radius, uint32_t k, uint32_t shape, const DevView* views, const uint32_t* pre,
+hipError_t launch_stage_batch(uint32_t form, uint32_t radius, uint32_t k, uint32_t shape, const DevView* views, const uint32_t* pre,
                               const uint32_t* geo, uint32_t nmem, uint32_t blocks, uint32_t kappa,
                               hipStream_t s);
 hipError_t launch_finish_batch(const DevView* views, const uint32_t* pre, uint32_t nmem, uint32_t blocks,
                                hipStream_t s);
-hipError_t launch_commit_batch(const DevView* views, const uint32_t* pre, uint32_t nmem, uint32_t blocks,
-                               uint32_t kappa, hipStream_t s);
+hipError_t launch_decide_commit_batch(const DevView* views, const uint32_t* pre, uint32_t nmem, uint32_t blocks,
+                                      uint32_t kappa, hipStream_t s);
 hipError_t launch_advance_batch(const DevView* views, uint32_t nmem, hipStream_t s);
 
 // BF16 precision form (mfma.hip): the field from counts / estimates, the

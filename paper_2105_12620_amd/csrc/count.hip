@@ -17,35 +17,41 @@
 namespace bnlat {
 namespace {
 
-// Resolve the pixel, offset and output buffer (row index, row count) of work
-// item j of a count launch.
+// Resolve the pixel, offset and output buffers (row index, row count) of work
+// item j of a count launch: counts as uint16 [Tp/8][rows][8] in wide, as int8
+// [Tp/16][rows][16] less their integrand's base in narrow (either null).
 template <int MODE>
 __device__ inline void count_target(const DevView& v, uint32_t kappa, uint32_t j, uint32_t m,
-                                    uint32_t& p, uint32_t& u, uint16_t*& buf, uint32_t& row,
+                                    uint32_t& p, uint32_t& u, uint16_t*& wide, int8_t*& narrow, uint32_t& row,
                                     uint32_t& rows) {
   if (MODE == MODE_ALL) {
     p = j;
     u = v.U[p];
-    buf = v.cnt;
+    wide = v.cnt;
+    narrow = v.d8;
     row = p;
     rows = v.w * v.h;
   } else if (MODE == MODE_CLASS) {
     p = class_pixel(v, kappa, j);
     u = proposal(v, p, (uint32_t)v.ctr[0]);
-    buf = v.c_new;
+    wide = v.c_new;
+    narrow = v.n8;
     row = j;
     rows = v.pc;
   } else if (MODE == MODE_SWEEP) {
     const uint32_t cls = j / v.pc, jj = j - cls * v.pc;
     p = class_pixel(v, cls, jj);
     u = proposal(v, p, (uint32_t)v.ctr[0] + kappa);
-    buf = v.c_new + (size_t)cls * v.pc * v.tp;
+    const size_t first = (size_t)cls * v.pc * v.tp;
+    wide = v.c_new ? v.c_new + first : nullptr;
+    narrow = v.n8 ? v.n8 + first : nullptr;
     row = jj;
     rows = v.pc;
   } else {
     p = v.pix_list[j];
     u = v.u_new[j];
-    buf = v.c_new;
+    wide = v.c_new;
+    narrow = nullptr;
     row = j;
     rows = m;
   }
@@ -279,13 +285,17 @@ __device__ __forceinline__ void count_body(const DevView& v, uint32_t kappa, uin
   const bool live = j0 < m;
   const uint32_t j = live ? j0 : m - 1;
   uint32_t p, u, row, rows;
-  uint16_t* buf;
-  count_target<MODE>(v, kappa, j, m, p, u, buf, row, rows);
+  uint16_t* wide;
+  int8_t* narrow;
+  count_target<MODE>(v, kappa, j, m, p, u, wide, narrow, row, rows);
+  const bool to_wide = MODE == MODE_ALL || MODE == MODE_LIST || v.form == FIELD_WIDE;
+  const bool to_narrow = MODE != MODE_LIST && v.form != FIELD_WIDE;
   if ((MODE == MODE_CLASS || MODE == MODE_SWEEP) && ch == 0 && live) v.u_new[j] = u;
   const Counter counter(v, u);
   const float inv_n = 1.0f / (float)v.n;
   const uint32_t t0 = ch * tch, t1 = min(t0 + tch, v.tp), tz = min(t1, (v.t + 7) & ~7u);
   uint32_t* el = lds + (MODE == MODE_ALL ? (threadIdx.x >> 6) * 64 * ERR_PITCH : 0);
+  uint32_t b0 = 0, b1 = 0;   // narrow counts of the first half of a 16-integrand word
 #pragma unroll 1
   for (uint32_t t = t0; t < t1; t += 8) {
     uint32_t c[4] = {0, 0, 0, 0};   // padded integrands count 0
@@ -293,7 +303,20 @@ __device__ __forceinline__ void count_body(const DevView& v, uint32_t kappa, uin
     // computed in every lane (an empty asm consumes them): otherwise the
     // counting would move under the store's branch
     asm volatile("" : : "v"(c[0]), "v"(c[1]), "v"(c[2]), "v"(c[3]));
-    if (live) *(uint4*)(buf + tix(row, t, rows)) = make_uint4(c[0], c[1], c[2], c[3]);
+    if (to_wide && live) *(uint4*)(wide + tix(row, t, rows)) = make_uint4(c[0], c[1], c[2], c[3]);
+    if (to_narrow) {
+      // per half count - base + 128 (no borrow between the halves), then
+      // the low bytes, less 128
+      const BN_UNIFORM uint32_t* bias = uniform(v.bias8) + t / 2;
+      const uint32_t w0 = __builtin_amdgcn_perm(c[1] + bias[1], c[0] + bias[0], 0x06040200u) ^ 0x80808080u;
+      const uint32_t w1 = __builtin_amdgcn_perm(c[3] + bias[3], c[2] + bias[2], 0x06040200u) ^ 0x80808080u;
+      if (!(t & 8)) {
+        b0 = w0;
+        b1 = w1;
+      } else if (live) {
+        *(uint4*)(narrow + ((size_t)(t >> 4) * rows + row) * 16) = make_uint4(b0, b1, w0, w1);
+      }
+    }
     if (MODE == MODE_ALL) {
       const uint32_t e = (t - t0) & 31;
 #pragma unroll

@@ -63,6 +63,16 @@ __device__ inline int dot2(uint32_t a, uint32_t b, int c) {
   return __builtin_amdgcn_sdot2(__builtin_bit_cast(v2i16, a), __builtin_bit_cast(v2i16, b), c, true);
 }
 
+// Signed int8x4 dot product plus accumulator (v_dot4_i32_i8; the clamp as above).
+__device__ inline int dot4(uint32_t a, uint32_t b, int c) {
+  return __builtin_amdgcn_sdot4((int)a, (int)b, c, true);
+}
+
+// Bytewise a - b mod 2^8.
+__device__ inline uint32_t sub_bytes(uint32_t a, uint32_t b) {
+  return ((a | 0x80808080u) - (b & 0x7F7F7F7Fu)) ^ ((a ^ ~b) & 0x80808080u);
+}
+
 __device__ inline uint32_t wave_id() {
   return __builtin_amdgcn_readfirstlane(blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6));
 }

@@ -97,221 +97,6 @@ __global__ __launch_bounds__(256) void k_delta(DevView v, uint32_t kappa, uint32
   }
 }
 
-// LDS-staged energy change for one colour phase.  A workgroup owns a block of
-// 32 x (BY V) class pixels; thread (tx, ty) owns the V class pixels of column
-// tx in class rows ty V .. ty V + V - 1.  Their windows overlap, so each count
-// word the thread reads from LDS serves all of them.  The workgroup also owns
-// a slice of the integrands: for 8 integrands at a time it stages the counts of
-// its block plus the window halo (region of RH x RW pixels, 16 bytes each) and
-// the class pixels' recounted rows in LDS.  Region columns are grouped by
-// residue mod K, so the 32 lanes of a class row read 32 consecutive 16-byte
-// words for every window offset, each with one ds_read_b128 at a compile-time
-// offset from the thread's base.  Where the staging words fit in registers,
-// the next stage's global loads are issued before the current stage is
-// evaluated.  Class sums stay in int32 over a
-// slice: its length is bounded so that |sum_t dc_t c_q,t| < 2^31 for every
-// class; they are added into xsum[class][pixel] with 64-bit integer atomics
-// (exact, so the order of the slices does not matter); k_delta_finish takes
-// the decision and clears xsum.
-template <int R, int K, int BY, int V>
-struct StageGeom {
-  static constexpr int BX = 32;
-  static constexpr int CR = BY * V;                                // class rows per block
-  static constexpr int RH = K * (CR - 1) + 2 * R + 1;
-  static constexpr int RW = ((K * (BX - 1) + 2 * R + 1 + K - 1) / K) * K;
-  static constexpr int RWK = RW / K;
-  static constexpr int RA = RH * RW;                               // region pixels
-  static constexpr int NB = BX * CR;                               // class pixels per block
-  static constexpr int NT = BX * BY;                               // threads per block
-  static constexpr int DR = K * (V - 1) + 2 * R + 1;               // region rows one thread reads
-  static constexpr int LDS_BYTES = 16 * (RA + NB);
-  // word of region column K tx + R + ox relative to that of column K tx
-  static constexpr int dcol(int ox) { return ((R + ox) % K) * RWK + (R + ox) / K; }
-};
-
-// Block shape of the staged kernel for K colour classes per axis and radius R:
-// class rows per thread (V) and thread rows (BY), within 64 KiB of LDS.
-// Shape 0 is the single-problem default; the batched form's tuner also tries
-// shape 1 (twice the waves per workgroup for K = 4, half for K = 1, 2).
-template <int R, int K, int SH = 0>
-struct StageShape {
-  static constexpr int V = (K == 4) ? 1 : 2;
-  static constexpr int BY = (K == 4) ? (SH ? 4 : 2) : (SH ? 4 : 8);
-};
-
-// Largest slice (a multiple of 8 integrands) whose class sums fit int32: every
-// product dc_t c_q,t is at most N^2 in size and a class has at most 12 offsets
-// for radii up to 6.
-inline uint32_t stage_max_slice(uint32_t n) {
-  const uint64_t per = (uint64_t)12 * n * n;
-  uint64_t t = 0x7FFFFFFFull / per;
-  t &= ~(uint64_t)7;
-  return t < 8 ? 8 : (t > 0x40000000u ? 0x40000000u : (uint32_t)t);
-}
-
-// Count changes of a 16-byte count word (8 integrands) as four int16 pairs, and
-// sum_t dc_t (c'_t + c_t) over the word.
-__device__ __forceinline__ int stage_dc(const u32x4 cn, const u32x4 co, uint32_t d[4]) {
-  int z = 0;
-#pragma unroll
-  for (int k = 0; k < 4; ++k) {
-    const int n0 = (int)(cn[k] & 0xFFFFu), n1 = (int)(cn[k] >> 16);
-    const int o0 = (int)(co[k] & 0xFFFFu), o1 = (int)(co[k] >> 16);
-    d[k] = ((uint32_t)(n0 - o0) & 0xFFFFu) | ((uint32_t)(n1 - o1) << 16);
-    z += (n0 - o0) * (n0 + o0) + (n1 - o1) * (n1 + o1);
-  }
-  return z;
-}
-
-template <int R, int K, int BY, int V>
-__device__ __forceinline__ void delta_stage_body(const DevView& v, uint32_t kappa, uint32_t trlen,
-                                                 long long* __restrict__ xpart, uint32_t bkx,
-                                                 uint32_t bky, uint32_t bkz) {
-  using G = StageGeom<R, K, BY, V>;
-  constexpr Window<R> W = WinConst<R>::w;
-  constexpr int NCLS = WinConst<R>::NCLS;
-  constexpr int ITER = (G::RA + G::NT - 1) / G::NT;
-  constexpr bool PREFETCH = ITER <= 16;
-  constexpr int WS = 2 * R + 1;
-  extern __shared__ u32x4 lds4[];
-  u32x4* reg = lds4;                 // [RA] region counts
-  u32x4* cnb = lds4 + G::RA;         // [NB] recounted rows of the class pixels
-  const uint32_t tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
-  const uint32_t a0 = bky * G::CR, b0 = bkx * G::BX;
-  const uint32_t b = b0 + tx;
-  const uint32_t ky = kappa / K, kx = kappa - ky * K;
-  // top-left region pixel, made non-negative modulo the tile
-  const uint32_t ys = (ky + K * a0 + v.h * (R / v.h + 1) - R) % v.h;
-  const uint32_t xs = (kx + K * b0 + v.w * (R / v.w + 1) - R) % v.w;
-  const uint32_t P = v.w * v.h;
-
-  // staging byte offsets: the region is the same for every stage.  Lanes past
-  // the region load pixel 0 and do not store it.
-  uint32_t poff[ITER], wi[ITER];
-#pragma unroll
-  for (int it = 0; it < ITER; ++it) {
-    const uint32_t i = threadIdx.x + it * G::NT;
-    poff[it] = 0;
-    wi[it] = 0xFFFFFFFFu;
-    if (i < (uint32_t)G::RA) {
-      const uint32_t rr = i / G::RW, cc = i - rr * G::RW;
-      uint32_t gy = ys + rr, gx = xs + cc;
-      while (gy >= v.h) gy -= v.h;
-      while (gx >= v.w) gx -= v.w;
-      poff[it] = (gy * v.w + gx) * 16;
-      wi[it] = rr * G::RW + (cc % K) * G::RWK + cc / K;
-    }
-  }
-  uint32_t coff[V];
-  bool act[V];
-#pragma unroll
-  for (int vv = 0; vv < V; ++vv) {
-    const uint32_t a = a0 + ty * V + vv;
-    act[vv] = (a < v.ch) && (b < v.cw);
-    coff[vv] = act[vv] ? (a * v.cw + b) * 16 : 0;
-  }
-  const uint32_t top = K * ty * V * G::RW + tx;
-
-  int z0[V];
-  int part[V][NCLS];
-#pragma unroll
-  for (int vv = 0; vv < V; ++vv) {
-    z0[vv] = 0;
-#pragma unroll
-    for (int c = 0; c < NCLS; ++c) part[vv][c] = 0;
-  }
-
-  const uint32_t t_begin = bkz * trlen, t_end = min(t_begin + trlen, v.tp);
-  u32x4 q[ITER], qc[V];
-  auto issue = [&](uint32_t t0) {
-    const char* cs = (const char*)(v.cnt + (size_t)(t0 >> 3) * P * 8);
-    const char* ns = (const char*)(v.c_new + (size_t)(t0 >> 3) * v.pc * 8);
-#pragma unroll
-    for (int it = 0; it < ITER; ++it) q[it] = *(const u32x4*)(cs + poff[it]);
-#pragma unroll
-    for (int vv = 0; vv < V; ++vv) qc[vv] = *(const u32x4*)(ns + coff[vv]);
-  };
-  if (PREFETCH && t_begin < t_end) issue(t_begin);
-  for (uint32_t t0 = t_begin; t0 < t_end; t0 += 8) {
-    __syncthreads();
-    if (!PREFETCH) issue(t0);
-#pragma unroll
-    for (int it = 0; it < ITER; ++it)
-      if (wi[it] != 0xFFFFFFFFu) reg[wi[it]] = q[it];
-#pragma unroll
-    for (int vv = 0; vv < V; ++vv) cnb[(ty * V + vv) * G::BX + tx] = qc[vv];
-    __syncthreads();
-    if (PREFETCH && t0 + 8 < t_end) issue(t0 + 8);
-    uint32_t d[V][4];
-#pragma unroll
-    for (int vv = 0; vv < V; ++vv)
-      z0[vv] += stage_dc(cnb[(ty * V + vv) * G::BX + tx], reg[top + (R + K * vv) * G::RW + G::dcol(0)], d[vv]);
-#pragma unroll
-    for (int dr = 0; dr < G::DR; ++dr) {
-      // a row's words are loaded together, so their LDS latencies overlap
-      u32x4 row[WS];
-#pragma unroll
-      for (int ox = -R; ox <= R; ++ox) row[ox + R] = reg[top + dr * G::RW + G::dcol(ox)];
-#pragma unroll
-      for (int ox = -R; ox <= R; ++ox) {
-        const u32x4 cq = row[ox + R];
-#pragma unroll
-        for (int vv = 0; vv < V; ++vv) {
-          const int oy = dr - R - K * vv;
-          if (oy < -R || oy > R || (ox == 0 && oy == 0)) continue;
-          const int c = W.cmap[(oy + R) * WS + ox + R];
-          int x = part[vv][c];
-          x = dot2(d[vv][0], cq[0], x);
-          x = dot2(d[vv][1], cq[1], x);
-          x = dot2(d[vv][2], cq[2], x);
-          part[vv][c] = dot2(d[vv][3], cq[3], x);
-        }
-      }
-    }
-  }
-#pragma unroll
-  for (int vv = 0; vv < V; ++vv) {
-    if (act[vv]) {
-      const uint32_t j = (a0 + ty * V + vv) * v.cw + b;
-#pragma unroll
-      for (int c = 0; c < NCLS; ++c)
-        atomicAdd((unsigned long long*)&xpart[(size_t)c * v.pc + j],
-                  (unsigned long long)((long long)W.csize[c] * z0[vv] - 2 * (long long)part[vv][c]));
-    }
-  }
-}
-
-// One-dimensional grid of gx x gy blocks x slices, renumbered per XCD: the
-// blocks one L2 serves at a time are whole rows of blocks of one slice, whose
-// window halos are then read from HBM once.
-template <int R, int K, int BY, int V>
-__global__ __launch_bounds__(32 * BY) void k_delta_stage(DevView v, uint32_t kappa, uint32_t trlen,
-                                                         long long* __restrict__ xpart, uint32_t gx,
-                                                         uint32_t gy) {
-  // the colour phases' waves issue ahead of the sweep-wide recount running
-  // beside them (k_delta_finish, k_commit and the BF16 form's k_delta_bf
-  // and k_delta_refine likewise), which fills the remaining issue slots
-  __builtin_amdgcn_s_setprio(2);
-  const uint32_t wk = xcd_block(blockIdx.x, gridDim.x), bxy = wk % (gx * gy);
-  delta_stage_body<R, K, BY, V>(v, kappa, trlen, xpart, bxy % gx, bxy / gx, wk / (gx * gy));
-}
-
-// Batched form: member i owns blocks pre[i] .. pre[i+1]-1, laid out as its own
-// (x, y, slice) grid; its slice length is in trl[i].
-template <int R, int K, int BY, int V>
-__global__ __launch_bounds__(32 * BY) void k_delta_stage_batch(const DevView* __restrict__ views,
-                                                               const uint32_t* __restrict__ pre,
-                                                               const uint32_t* __restrict__ geo,
-                                                               uint32_t nmem, uint32_t kappa) {
-  // like the single problem's phase kernels: issue ahead of the recount
-  __builtin_amdgcn_s_setprio(2);
-  const uint32_t i = batch_member(pre, nmem, blockIdx.x);
-  const DevView v = views[i];
-  const uint32_t lb = blockIdx.x - pre[i];
-  const uint32_t gx = geo[3 * i], gy = geo[3 * i + 1], trlen = geo[3 * i + 2];
-  delta_stage_body<R, K, BY, V>(v, kappa, trlen, v.xpart, lb % gx, (lb / gx) % gy, lb / (gx * gy));
-}
-
 // Decide from the summed class sums (one thread per pixel) and clear them.
 __device__ __forceinline__ void delta_finish_body(const DevView& v, long long* __restrict__ xsum,
                                                   uint32_t blk) {
@@ -350,9 +135,103 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 // ------------------------------------------------------------------ commit
 // Accepted moves of the phase become the state (Sec. 3.4): offset and hit
 // counts of the pixel (error vectors are refreshed from the counts on
-// demand).  A thread copies CT consecutive 8-integrand tiles of one class
-// pixel; pixels are fastest across the threads, so every tile's proposal rows
-// are read coalesced.
+// demand).
+//
+// FP32 form: decision and commit in one launch.  A workgroup owns 64 class
+// pixels: its first wave sums up and decides them (a lane each, the class sums
+// of 64 pixels are one 512-byte run) and clears the sums, then its four waves
+// copy the accepted pixels' rows, a 16-byte word per lane, pixels fastest, so
+// that the proposal rows are read coalesced.  Bound by latency and the launch
+// itself: measured at 256^2, N = 256, T = 1024 17 us per phase beside the recount against
+// 7 + 10 us as two launches with 16-bit proposal rows.
+constexpr uint32_t DC_WAVES = 4;
+
+// 16 proposal counts (narrow forms) back as 16-bit counts.
+__device__ __forceinline__ void widen8(const u32x4 d, const uint32_t* __restrict__ bias, uint4& lo, uint4& hi) {
+  uint32_t o[8];
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    const uint32_t x = d[k] ^ 0x80808080u;   // byte = count - base + 128
+    o[2 * k] = __builtin_amdgcn_perm(0u, x, 0x0C010C00u) - bias[2 * k];
+    o[2 * k + 1] = __builtin_amdgcn_perm(0u, x, 0x0C030C02u) - bias[2 * k + 1];
+  }
+  lo = make_uint4(o[0], o[1], o[2], o[3]);
+  hi = make_uint4(o[4], o[5], o[6], o[7]);
+}
+
+__device__ __forceinline__ void decide_commit_body(const DevView& v, uint32_t kappa, uint32_t blk, bool advance) {
+  __shared__ unsigned long long taken;
+  const uint32_t lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const uint32_t j = blk * 64 + lane;
+  if (w == 0) {
+    bool acc = false;
+    if (j < v.pc) {
+      double sum = 0.0;
+      for (uint32_t c0 = 0; c0 < v.ncls; c0 += 7) {
+        long long x[7];
+#pragma unroll
+        for (uint32_t e = 0; e < 7; ++e) x[e] = c0 + e < v.ncls ? v.xpart[(size_t)(c0 + e) * v.pc + j] : 0;
+#pragma unroll
+        for (uint32_t e = 0; e < 7; ++e)
+          if (c0 + e < v.ncls) {
+            v.xpart[(size_t)(c0 + e) * v.pc + j] = 0;
+            sum = __dadd_rn(sum, __dmul_rn(v.wd[c0 + e], (double)x[e]));
+          }
+      }
+      double total = __dmul_rn(sum, v.xscale);
+      if (v.tgp) total = __dadd_rn(total, v.gdelta[j]);
+      acc = (v.objective > 0) ? (total < 0.0) : (total > 0.0);
+      v.delta[j] = total;
+      v.accept[j] = acc;
+    }
+    const unsigned long long m = __ballot(acc);
+    if (lane == 0) {
+      taken = m;
+      if (m) atomicAdd(&v.ctr[1], (unsigned long long)__popcll(m));
+      if (advance && blk == 0) atomicAdd(&v.ctr[0], 1ull);
+    }
+    if (acc) v.U[class_pixel(v, kappa, j)] = v.u_new[j];
+  }
+  __syncthreads();
+  if (!(taken >> lane & 1)) return;
+  const uint32_t p = class_pixel(v, kappa, j);
+  const size_t P = (size_t)v.w * v.h;
+  if (v.form != FIELD_WIDE) {
+    const uint32_t words = (v.t + 15) >> 4;
+#pragma unroll 4
+    for (uint32_t tt = w; tt < words; tt += DC_WAVES) {
+      const u32x4 d = *(const u32x4*)(v.n8 + ((size_t)tt * v.pc + j) * 16);
+      *(u32x4*)(v.d8 + (tt * P + p) * 16) = d;
+      uint4 lo, hi;
+      widen8(d, v.bias8 + 8 * tt, lo, hi);
+      *(uint4*)(v.cnt + (2 * tt * P + p) * 8) = lo;
+      *(uint4*)(v.cnt + ((2 * tt + 1) * P + p) * 8) = hi;
+    }
+  } else {
+    const uint32_t words = (v.t + 7) >> 3;
+#pragma unroll 4
+    for (uint32_t tt = w; tt < words; tt += DC_WAVES)
+      *(uint4*)(v.cnt + (tt * P + p) * 8) = *(const uint4*)(v.c_new + ((size_t)tt * v.pc + j) * 8);
+  }
+}
+
+__global__ __launch_bounds__(64 * DC_WAVES) void k_decide_commit(DevView v, uint32_t kappa, bool advance) {
+  __builtin_amdgcn_s_setprio(2);
+  decide_commit_body(v, kappa, blockIdx.x, advance);
+}
+
+__global__ __launch_bounds__(64 * DC_WAVES) void k_decide_commit_batch(const DevView* __restrict__ views,
+                                                                       const uint32_t* __restrict__ pre,
+                                                                       uint32_t nmem, uint32_t kappa) {
+  __builtin_amdgcn_s_setprio(2);
+  const uint32_t i = batch_member(pre, nmem, blockIdx.x);
+  const DevView v = views[i];
+  decide_commit_body(v, kappa, blockIdx.x - pre[i], false);
+}
+
+// The commit of decided moves alone (the BF16 forms, colour moduli without a
+// staged kernel, the phase-stepping calls): a thread copies CT consecutive
+// 8-integrand tiles of one class pixel.
 constexpr uint32_t CT = 8;
 __device__ __forceinline__ void commit_body(const DevView& v, uint32_t kappa, uint32_t blk) {
   const uint32_t ngrp = ((v.tp >> 3) + CT - 1) / CT;
@@ -368,6 +247,17 @@ __device__ __forceinline__ void commit_body(const DevView& v, uint32_t kappa, ui
   if (g == 0) v.U[p] = v.u_new[j];
   const uint32_t t0 = g * CT, t1 = min(t0 + CT, v.tp >> 3);
   const size_t P = (size_t)v.w * v.h;
+  if (v.form != FIELD_WIDE) {
+    for (uint32_t tt = t0 / 2; tt < t1 / 2; ++tt) {
+      const u32x4 d = *(const u32x4*)(v.n8 + ((size_t)tt * v.pc + j) * 16);
+      *(u32x4*)(v.d8 + (tt * P + p) * 16) = d;
+      uint4 lo, hi;
+      widen8(d, v.bias8 + 8 * tt, lo, hi);
+      *(uint4*)(v.cnt + (2 * tt * P + p) * 8) = lo;
+      *(uint4*)(v.cnt + ((2 * tt + 1) * P + p) * 8) = hi;
+    }
+    return;
+  }
   for (uint32_t tt = t0; tt < t1; ++tt) {
     const uint4 c8 = *(const uint4*)(v.c_new + ((size_t)tt * v.pc + j) * 8);
     *(uint4*)(v.cnt + (tt * P + p) * 8) = c8;
@@ -403,15 +293,6 @@ __global__ __launch_bounds__(256) void k_errors(DevView v) {
 __global__ __launch_bounds__(256) void k_commit(DevView v, uint32_t kappa) {
   __builtin_amdgcn_s_setprio(2);
   commit_body(v, kappa, blockIdx.x);
-}
-
-__global__ __launch_bounds__(256) void k_commit_batch(const DevView* __restrict__ views,
-                                                      const uint32_t* __restrict__ pre, uint32_t nmem,
-                                                      uint32_t kappa) {
-  __builtin_amdgcn_s_setprio(2);
-  const uint32_t i = batch_member(pre, nmem, blockIdx.x);
-  const DevView v = views[i];
-  commit_body(v, kappa, blockIdx.x - pre[i]);
 }
 
 __global__ void k_advance(unsigned long long* ctr) {
@@ -850,53 +731,6 @@ hipError_t delta_dispatch(const DevView& v, uint32_t kappa, uint32_t m, hipStrea
   return hipGetLastError();
 }
 
-// Integrand slices of a staged launch: about slice_target workgroups in total
-// (512 by default), each slice a whole number of stages of `gran` integrands
-// (8 for the integer stencil, 16 for the matrix-core form), at least `min_len`
-// integrands long where the rows have that many and at most `cap` long.
-inline uint32_t stage_slices(const DevView& v, uint32_t blocks, uint32_t* trlen, uint32_t gran = 8,
-                             uint32_t cap = 0xFFFFFFFFu, uint32_t min_len = 0) {
-  const uint32_t chunks = v.tp / gran;
-  const uint32_t target = v.slice_target ? v.slice_target : 512;
-  uint32_t want = (target + blocks - 1) / blocks;
-  if (want > chunks) want = chunks;
-  uint32_t per = (chunks + want - 1) / want;
-  const uint32_t min_per = min(chunks, min_len / gran);
-  if (per < min_per) per = min_per;
-  const uint32_t cap_stages = cap / gran ? cap / gran : 1;
-  if (per > cap_stages) per = cap_stages;
-  *trlen = per * gran;
-  return (chunks + per - 1) / per;
-}
-
-template <int R, int K>
-hipError_t stage_launch(const DevView& v, uint32_t kappa, long long* xpart, hipStream_t s, bool finish = true) {
-  using S = StageShape<R, K>;
-  using G = StageGeom<R, K, S::BY, S::V>;
-  static_assert(G::LDS_BYTES <= 65536, "staged block exceeds 64 KiB of LDS");
-  uint32_t trlen = 0;
-  const uint32_t blocks = ((v.cw + G::BX - 1) / G::BX) * ((v.ch + G::CR - 1) / G::CR);
-  // slices of at least 64 integrands: each adds its class sums with atomics
-  // and restages the window halo
-  const uint32_t ns = stage_slices(v, blocks, &trlen, 8, stage_max_slice(v.n), 64);
-  const uint32_t gx = (v.cw + G::BX - 1) / G::BX, gy = (v.ch + G::CR - 1) / G::CR;
-  hipLaunchKernelGGL((k_delta_stage<R, K, S::BY, S::V>), dim3(gx * gy * ns), dim3(G::NT), (size_t)G::LDS_BYTES, s,
-                     v, kappa, trlen, xpart, gx, gy);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess || !finish) return e;
-  return launch_finish(v, s);
-}
-
-template <int R>
-hipError_t stage_by_k(const DevView& v, uint32_t kappa, long long* xpart, hipStream_t s, bool finish = true) {
-  switch (v.k) {
-    case 1: return stage_launch<R, 1>(v, kappa, xpart, s, finish);
-    case 2: return stage_launch<R, 2>(v, kappa, xpart, s, finish);
-    case 4: return stage_launch<R, 4>(v, kappa, xpart, s, finish);
-    default: return delta_dispatch<MODE_CLASS>(v, kappa, v.pc, s);
-  }
-}
-
 }  // namespace
 
 hipError_t launch_init_offsets(const DevView& v, hipStream_t s) {
@@ -906,22 +740,23 @@ hipError_t launch_init_offsets(const DevView& v, hipStream_t s) {
 }
 
 
-hipError_t launch_delta(const DevView& v, int mode, uint32_t kappa, uint32_t m, hipStream_t s) {
-  // BF16 precision form: matrix-core Gram pass, decision, exact re-evaluation
-  if (mode == MODE_CLASS && v.mfma) return launch_delta_bf16(v, kappa, s);
-  if (mode == MODE_CLASS && v.xpart) {
-    switch (v.radius) {
-      case 1: return stage_by_k<1>(v, kappa, v.xpart, s);
-      case 2: return stage_by_k<2>(v, kappa, v.xpart, s);
-      case 3: return stage_by_k<3>(v, kappa, v.xpart, s);
-      case 4: return stage_by_k<4>(v, kappa, v.xpart, s);
-      case 5: return stage_by_k<5>(v, kappa, v.xpart, s);
-      case 6: return stage_by_k<6>(v, kappa, v.xpart, s);
-      default: return hipErrorInvalidValue;
-    }
+bool staged_phases(const DevView& v) { return !v.mfma && (v.k == 1 || v.k == 2 || v.k == 4); }
+
+hipError_t launch_stage(const DevView& v, uint32_t kappa, hipStream_t s) {
+  switch (v.form) {
+    case FIELD_NARROW: return launch_stage_narrow(v, kappa, s);
+    case FIELD_SPLIT: return launch_stage_split(v, kappa, s);
+    default: return launch_stage_wide(v, kappa, s);
   }
-  return mode == MODE_CLASS ? delta_dispatch<MODE_CLASS>(v, kappa, m, s)
-                            : delta_dispatch<MODE_LIST>(v, kappa, m, s);
+}
+
+hipError_t launch_delta(const DevView& v, int mode, uint32_t kappa, uint32_t m, hipStream_t s) {
+  if (mode != MODE_CLASS) return delta_dispatch<MODE_LIST>(v, kappa, m, s);
+  // BF16 precision form: matrix-core Gram pass, decision, exact re-evaluation
+  if (v.mfma) return launch_delta_bf16(v, kappa, s);
+  if (!staged_phases(v)) return delta_dispatch<MODE_CLASS>(v, kappa, m, s);
+  const hipError_t e = launch_stage(v, kappa, s);
+  return e != hipSuccess ? e : launch_finish(v, s);
 }
 
 uint32_t xpart_words(const DevView& v) { return v.ncls * v.pc; }
@@ -931,12 +766,16 @@ hipError_t launch_finish(const DevView& v, hipStream_t s) {
   return hipGetLastError();
 }
 
-uint32_t commit_blocks(const DevView& v) {
-  return (uint32_t)(((uint64_t)v.pc * (((v.tp >> 3) + CT - 1) / CT) + 255) / 256);
+hipError_t launch_commit(const DevView& v, uint32_t kappa, hipStream_t s) {
+  const uint32_t blocks = (uint32_t)(((uint64_t)v.pc * (((v.tp >> 3) + CT - 1) / CT) + 255) / 256);
+  hipLaunchKernelGGL(k_commit, dim3(blocks), dim3(256), 0, s, v, kappa);
+  return hipGetLastError();
 }
 
-hipError_t launch_commit(const DevView& v, uint32_t kappa, hipStream_t s) {
-  hipLaunchKernelGGL(k_commit, dim3(commit_blocks(v)), dim3(256), 0, s, v, kappa);
+uint32_t decide_commit_blocks(const DevView& v) { return (v.pc + 63) / 64; }
+
+hipError_t launch_decide_commit(const DevView& v, uint32_t kappa, bool advance, hipStream_t s) {
+  hipLaunchKernelGGL(k_decide_commit, dim3(decide_commit_blocks(v)), dim3(64 * DC_WAVES), 0, s, v, kappa, advance);
   return hipGetLastError();
 }
 
@@ -1067,17 +906,8 @@ hipError_t launch_gauss_delta(const DevView& v, int mode, uint32_t kappa, uint32
                             : gauss_delta_dispatch<MODE_LIST>(v, kappa, m, s);
 }
 
-hipError_t launch_stage_exact(const DevView& v, uint32_t kappa, hipStream_t s) {
-  switch (v.radius) {
-    case 1: return stage_by_k<1>(v, kappa, v.xpart, s, false);
-    case 2: return stage_by_k<2>(v, kappa, v.xpart, s, false);
-    case 3: return stage_by_k<3>(v, kappa, v.xpart, s, false);
-    case 4: return stage_by_k<4>(v, kappa, v.xpart, s, false);
-    case 5: return stage_by_k<5>(v, kappa, v.xpart, s, false);
-    case 6: return stage_by_k<6>(v, kappa, v.xpart, s, false);
-    default: return hipErrorInvalidValue;
-  }
-}
+// The BF16 form's exact re-evaluation: the counts' form, K = 1, 2, 4.
+hipError_t launch_stage_exact(const DevView& v, uint32_t kappa, hipStream_t s) { return launch_stage_wide(v, kappa, s); }
 
 hipError_t launch_gauss_delta_exact(const DevView& v, uint32_t kappa, hipStream_t s) {
   if (!v.tgp) return hipSuccess;
@@ -1124,59 +954,21 @@ hipError_t launch_gauss_energy(const DevView& v, double* gsum, hipStream_t s) {
 
 // ------------------------------------------------------------------ batches
 
-uint32_t stage_rows(uint32_t k, uint32_t shape) {
-  if (k == 4) return shape ? StageShape<1, 4, 1>::BY * StageShape<1, 4, 1>::V : StageShape<1, 4>::BY * StageShape<1, 4>::V;
-  return shape ? StageShape<1, 2, 1>::BY * StageShape<1, 2, 1>::V : StageShape<1, 2>::BY * StageShape<1, 2>::V;
-}
-
 void stage_geometry(const DevView& v, uint32_t shape, uint32_t* gx, uint32_t* gy, uint32_t* gz, uint32_t* trlen) {
-  const uint32_t cr = stage_rows(v.k, shape);
-  *gx = (v.cw + 31) / 32;
-  *gy = (v.ch + cr - 1) / cr;
-  *gz = stage_slices(v, *gx * *gy, trlen, 8, stage_max_slice(v.n), 64);
-}
-
-
-namespace {
-template <int R, int K, int SH>
-hipError_t stage_batch_rk(const DevView* views, const uint32_t* pre, const uint32_t* geo, uint32_t nmem,
-                          uint32_t blocks, uint32_t kappa, hipStream_t s) {
-  using S = StageShape<R, K, SH>;
-  using G = StageGeom<R, K, S::BY, S::V>;
-  static_assert(G::LDS_BYTES <= 65536, "staged block exceeds 64 KiB of LDS");
-  static_assert(G::CR == StageShape<1, K == 4 ? 4 : 2, SH>::BY * StageShape<1, K == 4 ? 4 : 2, SH>::V,
-                "batched geometry assumes one block shape per (K, shape)");
-  hipLaunchKernelGGL((k_delta_stage_batch<R, K, S::BY, S::V>), dim3(blocks), dim3(G::NT), (size_t)G::LDS_BYTES, s,
-                     views, pre, geo, nmem, kappa);
-  return hipGetLastError();
-}
-
-template <int R>
-hipError_t stage_batch_r(uint32_t k, uint32_t shape, const DevView* views, const uint32_t* pre, const uint32_t* geo,
-                         uint32_t nmem, uint32_t blocks, uint32_t kappa, hipStream_t s) {
-  switch (k * 2 + (shape ? 1 : 0)) {
-    case 2: return stage_batch_rk<R, 1, 0>(views, pre, geo, nmem, blocks, kappa, s);
-    case 3: return stage_batch_rk<R, 1, 1>(views, pre, geo, nmem, blocks, kappa, s);
-    case 4: return stage_batch_rk<R, 2, 0>(views, pre, geo, nmem, blocks, kappa, s);
-    case 5: return stage_batch_rk<R, 2, 1>(views, pre, geo, nmem, blocks, kappa, s);
-    case 8: return stage_batch_rk<R, 4, 0>(views, pre, geo, nmem, blocks, kappa, s);
-    case 9: return stage_batch_rk<R, 4, 1>(views, pre, geo, nmem, blocks, kappa, s);
-    default: return hipErrorInvalidValue;
+  switch (v.form) {
+    case FIELD_NARROW: return stage_geometry_narrow(v, shape, gx, gy, gz, trlen);
+    case FIELD_SPLIT: return stage_geometry_split(v, shape, gx, gy, gz, trlen);
+    default: return stage_geometry_wide(v, shape, gx, gy, gz, trlen);
   }
 }
-}  // namespace
 
-hipError_t launch_stage_batch(uint32_t radius, uint32_t k, uint32_t shape, const DevView* views, const uint32_t* pre,
-                              const uint32_t* geo, uint32_t nmem, uint32_t blocks, uint32_t kappa,
-                              hipStream_t s) {
-  switch (radius) {
-    case 1: return stage_batch_r<1>(k, shape, views, pre, geo, nmem, blocks, kappa, s);
-    case 2: return stage_batch_r<2>(k, shape, views, pre, geo, nmem, blocks, kappa, s);
-    case 3: return stage_batch_r<3>(k, shape, views, pre, geo, nmem, blocks, kappa, s);
-    case 4: return stage_batch_r<4>(k, shape, views, pre, geo, nmem, blocks, kappa, s);
-    case 5: return stage_batch_r<5>(k, shape, views, pre, geo, nmem, blocks, kappa, s);
-    case 6: return stage_batch_r<6>(k, shape, views, pre, geo, nmem, blocks, kappa, s);
-    default: return hipErrorInvalidValue;
+hipError_t launch_stage_batch(uint32_t form, uint32_t radius, uint32_t k, uint32_t shape, const DevView* views,
+                              const uint32_t* pre, const uint32_t* geo, uint32_t nmem, uint32_t blocks,
+                              uint32_t kappa, hipStream_t s) {
+  switch (form) {
+    case FIELD_NARROW: return launch_stage_batch_narrow(radius, k, shape, views, pre, geo, nmem, blocks, kappa, s);
+    case FIELD_SPLIT: return launch_stage_batch_split(radius, k, shape, views, pre, geo, nmem, blocks, kappa, s);
+    default: return launch_stage_batch_wide(radius, k, shape, views, pre, geo, nmem, blocks, kappa, s);
   }
 }
 
@@ -1186,9 +978,9 @@ hipError_t launch_finish_batch(const DevView* views, const uint32_t* pre, uint32
   return hipGetLastError();
 }
 
-hipError_t launch_commit_batch(const DevView* views, const uint32_t* pre, uint32_t nmem, uint32_t blocks,
-                               uint32_t kappa, hipStream_t s) {
-  hipLaunchKernelGGL(k_commit_batch, dim3(blocks), dim3(256), 0, s, views, pre, nmem, kappa);
+hipError_t launch_decide_commit_batch(const DevView* views, const uint32_t* pre, uint32_t nmem, uint32_t blocks,
+                                      uint32_t kappa, hipStream_t s) {
+  hipLaunchKernelGGL(k_decide_commit_batch, dim3(blocks), dim3(64 * DC_WAVES), 0, s, views, pre, nmem, kappa);
   return hipGetLastError();
 }
 

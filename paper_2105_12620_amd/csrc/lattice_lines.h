@@ -152,6 +152,18 @@ inline LineRec line_record(const LatticeLines& g, int64_t step, int64_t nx, int6
   return r;
 }
 
+// How far a hit count can be from N times the integrand's area, for every
+// shift (0: no useful bound).  A line's samples on one side of the edge are
+// the integers in an interval, off its length by at most one; the lengths are
+// a concave function of the line's place (chords of a convex polygon), so
+// their sum over the lines is off its integral, N times the area, by at most
+// the longest chord, N / max(|x|, |y|) for b1 = (x, y) / N; at most lines + 1
+// lines meet the square.
+inline uint32_t count_deviation(int64_t n, const LatticeLines& g) {
+  const int64_t m = std::max(std::llabs(g.b1[0]), std::llabs(g.b1[1]));
+  return g.lines && m ? (uint32_t)(g.lines + 1 + (n + m - 1) / m) : 0;
+}
+
 // A padded integrand: a crossing far before every line, counted on the m < 0
 // side, so that it never counts a sample.
 inline LineRec line_padding() { return LineRec{0u, 0, 1e-300, -(1ll << 52), 0}; }

@@ -85,3 +85,8 @@ extern "C" int count_lines_padding(uint32_t n, uint32_t gx, uint32_t gy) {
   }
   return bad;
 }
+
+// The bound on |count - N area| that decides the operands of the colour phases.
+extern "C" uint32_t count_lines_deviation(uint32_t n, uint32_t gx, uint32_t gy) {
+  return count_deviation(n, lattice_lines(n, gx, gy));
+}

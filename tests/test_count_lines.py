@@ -9,6 +9,8 @@ import subprocess
 import numpy as np
 import pytest
 
+from oracle import integrands
+
 HERE = os.path.dirname(os.path.abspath(__file__))
 
 
@@ -70,3 +72,22 @@ def test_every_generator_has_lines(model, n):
     count nothing."""
     for y in range(1, n, 2 if n <= 1024 else 32):
         assert model.count_lines_padding(n, 1, y) == 0, y
+
+
+@pytest.mark.parametrize("n", [128, 256, 512, 1024, 2048])
+def test_counts_stay_within_the_lines_bound(model, n):
+    """|count - round(N area)| of random and nearly lattice-aligned edges stays
+    within the bound, and the bound is of use for good generators."""
+    rng = np.random.default_rng(n + 1)
+    gens = [(1, 1), (1, int(n * 0.618) | 1)] + [(1, int(2 * rng.integers(0, n // 2) + 1)) for _ in range(6)]
+    k = 2000
+    for g in gens:
+        bound = model.count_lines_deviation(n, g[0], g[1])
+        a = rows(n, k, g, rng)
+        got, want, few = np.zeros(k, np.uint32), np.zeros(k, np.uint32), C.c_uint32()
+        model.count_lines_model(n, g[0], g[1], k, *[x.ctypes.data_as(C.c_void_p) for x in a],
+                                got.ctypes.data_as(C.c_void_p), want.ctypes.data_as(C.c_void_p), C.byref(few))
+        areas = np.array([integrands.heaviside_area(*(int(x[i]) for x in a[:4])) for i in range(k)])
+        assert np.abs(want.astype(int) - np.rint(n * areas).astype(int)).max() <= bound, g
+    assert model.count_lines_deviation(256, 1, 79) <= 63
+    assert model.count_lines_deviation(1024, 1, 381) <= 126
