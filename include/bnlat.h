@@ -58,8 +58,10 @@ typedef enum {
 } bn_status;
 
 /* Arithmetic of the colour phases' energy change (Eq. (1) over the window).
- * BN_FP32: exact integer class sums of the hit counts on the vector ALUs
- *          (Gaussian rows: FP64 arithmetic on FP32 estimates).
+ * BN_FP32: exact integer class sums of the hit counts, from int8 deviations of
+ *          the counts on the matrix cores where those are known to fit, else
+ *          on the vector ALUs (Gaussian rows: FP64 arithmetic on FP32
+ *          estimates).
  * BN_BF16: the neighbour (Gram) products sum_t d_t e_{p+o,t}, d = e' - e, on
  *          the matrix cores (v_mfma_f32_16x16x16_bf16, FP32 accumulation)
  *          from a BF16 copy of the error field kept in device memory; the

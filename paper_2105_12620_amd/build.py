@@ -11,7 +11,7 @@ import tempfile
 from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
-SOURCES = ["csrc/count.hip", "csrc/stage_wide.hip", "csrc/stage_narrow.hip", "csrc/stage_split.hip",
+SOURCES = ["csrc/count.hip", "csrc/phase_wide.hip", "csrc/phase_narrow.hip", "csrc/phase_split.hip",
            "csrc/kernels.hip", "csrc/swap.hip", "csrc/sampler.hip", "csrc/mfma.hip",
            "csrc/noalloc.hip", "csrc/peaks.hip",
            "csrc/spectrum.hip", "csrc/api.cpp"]

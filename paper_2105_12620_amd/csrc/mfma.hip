@@ -428,32 +428,6 @@ __global__ __launch_bounds__(256) void k_delta_refine(DevView v, uint32_t kappa,
   }
 }
 
-// Approximate mode: every move the BF16 value accepted is re-evaluated with
-// the FP32 form's arithmetic (its staged stencils have just summed the exact
-// integer class sums into xsum and the Gaussian rows' part into gdelta, for
-// every class pixel of the phase: staging the window costs the same for one
-// pixel of a block as for all of them).  The exact value is combined in the
-// FP32 form's order; a move it rejects is a veto.  Clears xsum.
-__global__ __launch_bounds__(256) void k_refine_combine(DevView v, long long* __restrict__ xsum) {
-  __builtin_amdgcn_s_setprio(2);
-  const uint32_t j = blockIdx.x * blockDim.x + threadIdx.x;
-  if (j >= v.pc) return;
-  double acc = 0.0;
-  for (uint32_t c = 0; c < v.ncls; ++c) {
-    const long long x = xsum[(size_t)c * v.pc + j];
-    xsum[(size_t)c * v.pc + j] = 0;
-    acc = __dadd_rn(acc, __dmul_rn(v.wd[c], (double)x));
-  }
-  if (!v.accept[j]) return;
-  double total = __dmul_rn(acc, 2.0 / ((double)v.n * (double)v.n));
-  if (v.tgp) total = __dadd_rn(total, v.gdelta[j]);
-  v.delta[j] = total;
-  if (!((v.objective > 0) ? (total < 0.0) : (total > 0.0))) {
-    v.accept[j] = 0;
-    atomicAdd(&v.ctr[2], 1ull);
-  }
-}
-
 // BF16 energy of Eq. (1): the half window's sums of |f_p - f_q|^2 over the
 // field, per distance class (FP32 per 8-integrand tile, FP64 across tiles,
 // FP64 atomics); the host doubles them and scales them by 1/N^2 in the exact
@@ -596,10 +570,12 @@ hipError_t bf_launch(const DevView& v, uint32_t kappa, hipStream_t s) {
     hipLaunchKernelGGL((k_delta_refine<R>), dim3((v.pc + 255) / 256), dim3(256), 0, s, v, kappa, v.unsure);
     return hipGetLastError();
   }
-  if ((e = launch_stage_exact(v, kappa, s)) != hipSuccess) return e;
+  // approximate mode: every move the BF16 value accepted is re-evaluated with
+  // the FP32 form's arithmetic, over the whole phase (staging a block's window
+  // costs the same for one of its class pixels as for all of them); a move
+  // the exact value rejects is a veto
   if ((e = launch_gauss_delta_exact(v, kappa, s)) != hipSuccess) return e;
-  hipLaunchKernelGGL(k_refine_combine, dim3((v.pc + 255) / 256), dim3(256), 0, s, v, v.xpart);
-  return hipGetLastError();
+  return launch_phase_wide(v, kappa, s);
 }
 
 }  // namespace
