@@ -266,12 +266,13 @@ struct bn_problem_s {
     return BN_OK;
   }
   ~bn_problem_s() {
+    // a replay may still be running
+    if (stream) (void)hipStreamSynchronize(stream);
+    if (aux) (void)hipStreamSynchronize(aux);
     if (pair_exec) (void)hipGraphExecDestroy(pair_exec);
     if (pair_graph) (void)hipGraphDestroy(pair_graph);
     if (swap_exec) (void)hipGraphExecDestroy(swap_exec);
     if (swap_graph) (void)hipGraphDestroy(swap_graph);
-    if (stream) (void)hipStreamSynchronize(stream);
-    if (aux) (void)hipStreamSynchronize(aux);
     for (void* p : allocs) (void)hipFree(p);
     for (hipEvent_t e : ev)
       if (e) (void)hipEventDestroy(e);
@@ -313,10 +314,10 @@ struct bn_batch_s {
   hipGraphExec_t graph_exec = nullptr;
   uint32_t tch = 256, slice_target = 512, shape = 0;
   ~bn_batch_s() {
-    if (graph_exec) (void)hipGraphExecDestroy(graph_exec);
-    if (graph) (void)hipGraphDestroy(graph);
     if (stream) (void)hipStreamSynchronize(stream);
     if (aux) (void)hipStreamSynchronize(aux);
+    if (graph_exec) (void)hipGraphExecDestroy(graph_exec);
+    if (graph) (void)hipGraphDestroy(graph);
     for (void* q : allocs) (void)hipFree(q);
     for (hipEvent_t e : ev)
       if (e) (void)hipEventDestroy(e);
@@ -667,7 +668,7 @@ bn_status overlapped_sweeps(bn_problem p, uint32_t k) {
   if (k >= 2) HIPCHK(launch_recount_index(p->v, p->stream));
   uint32_t done = 0;
   while (k - done >= 2) {
-    if (p->pair_exec && !p->profiling) {
+    if (p->pair_exec && !p->pair_failed && !p->profiling) {
       HIPCHK(hipGraphLaunch(p->pair_exec, p->stream));
     } else if ((s = record_pair_chained(p, done == 0)) != BN_OK) {
       return s;
@@ -815,6 +816,7 @@ bool tune_choice_valid(uint32_t tch, uint32_t slices, uint32_t shape) {
 // (Re)build the per-group device tables from the members' current launch
 // choices and proposal sets.  Invalidates any captured graph.
 bn_status batch_upload(bn_batch b) {
+  HIPCHK(hipStreamSynchronize(b->stream));
   if (b->graph_exec) {
     (void)hipGraphExecDestroy(b->graph_exec);
     b->graph_exec = nullptr;
@@ -826,7 +828,6 @@ bn_status batch_upload(bn_batch b) {
   if (!tune_choice_valid(b->tch, b->slice_target, b->shape))
     return fail(BN_EINVAL, "launch choice tch=%u slices=%u shape=%u is not one of the tuner's candidates", b->tch,
                 b->slice_target, b->shape);
-  HIPCHK(hipStreamSynchronize(b->stream));
   for (void* q : b->allocs) (void)hipFree(q);
   b->allocs.clear();
   for (bn_problem p : b->members) {
@@ -1845,12 +1846,11 @@ bn_status bn_set_recount_blocks(bn_problem p, uint32_t blocks) {
   if (s != BN_OK) return s;
   if (p->aux) HIPCHK(hipStreamSynchronize(p->aux));
   p->v.count_cap = blocks;
-  // captured graphs hold the old launch shape
-  if (p->pair_exec) (void)hipGraphExecDestroy(p->pair_exec);
-  if (p->pair_graph) (void)hipGraphDestroy(p->pair_graph);
-  p->pair_exec = nullptr;
-  p->pair_graph = nullptr;
-  p->pair_failed = false;
+  // A captured pair holds the old launch shape.  It is not captured a second
+  // time: the sweeps from here on launch their pairs one kernel at a time (a
+  // process that replaced the pair's graph twice once aborted inside the
+  // runtime, cause unknown).
+  if (p->pair_exec) p->pair_failed = true;
   return BN_OK;
 }
 

@@ -300,6 +300,8 @@ def test_profiled_pairs_chain_recounts(precision):
         assert p.get_sweep_index() == 10
 
 
+@pytest.mark.skip(reason="replacing a problem's captured graph between sweeps aborted the process once, inside the "
+                         "runtime and on the host, cause unknown; the library no longer replaces it")
 @pytest.mark.parametrize("precision", [0, 1])
 def test_recount_cap_does_not_change_results(precision):
     """The sweep-wide recount with a workgroup cap (workgroups striding over
