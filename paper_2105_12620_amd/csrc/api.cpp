@@ -1336,6 +1336,46 @@ bn_status bn_create_problem_ext(const bn_config* cfg, const bn_heaviside* heavis
       return fail(BN_EHIP, "uploading Gaussian tables: %s", hipGetErrorString(ge));
     }
   }
+  // Gaussian line form: from N = 16, where a line holds several samples, up to
+  // lines of 256 steps (a table of the steps' factors per Gaussian), and for
+  // launches over the tile that fill the chip (launch_gauss_est)
+  v.glines = 0;
+  std::vector<uint32_t> grow;
+  std::vector<int> gspans;
+  std::vector<double> gtab;
+  if (v.n >= 16 && gauss_lines_pay(v, (uint32_t)P)) {
+    GaussLines q = gauss_lines(v.n, v.gx, v.gy, g);
+    if (q.steps <= 256) {
+      v.glines = q.lines;
+      v.gwords = gauss_table_words(q);
+      gtab.assign((size_t)round_up(v.tg, 4) * v.gwords, 0.0);
+      for (uint32_t t = 0; t < v.tg; ++t)
+        gauss_table(v.n, g, q, gcoef[4 * t], gcoef[4 * t + 1], gcoef[4 * t + 2], gcoef[4 * t + 3], gauss[t].mx, gauss[t].my,
+                    &gtab[(size_t)(t & ~3u) * v.gwords + (t & 3)]);
+      grow.swap(q.rows);
+      for (uint32_t i = 0; i < q.lines; ++i)
+        gspans.insert(gspans.end(), {q.spans[i].steps, q.spans[i].full_lo, q.spans[i].full_hi,
+                                     i + 1 < q.lines ? (int)(q.j0[i + 1] - q.j0[i]) : 0});
+      uint32_t* grow_d;
+      int* gspans_d;
+      double* gtab_d;
+      if ((s = p->alloc(&grow_d, grow.size())) != BN_OK || (s = p->alloc(&gspans_d, gspans.size())) != BN_OK ||
+          (s = p->alloc(&gtab_d, gtab.size())) != BN_OK) {
+        delete p;
+        return s;
+      }
+      v.grow = grow_d;
+      v.gspans = gspans_d;
+      v.gtab = gtab_d;
+      hipError_t ge = hipMemcpyAsync(grow_d, grow.data(), grow.size() * 4, hipMemcpyHostToDevice, p->stream);
+      if (ge == hipSuccess) ge = hipMemcpyAsync(gspans_d, gspans.data(), gspans.size() * 4, hipMemcpyHostToDevice, p->stream);
+      if (ge == hipSuccess) ge = hipMemcpyAsync(gtab_d, gtab.data(), gtab.size() * 8, hipMemcpyHostToDevice, p->stream);
+      if (ge != hipSuccess) {
+        delete p;
+        return fail(BN_EHIP, "uploading Gaussian line tables: %s", hipGetErrorString(ge));
+      }
+    }
+  }
   v.pix_list = nullptr;
   const unsigned long long zero[4] = {0ull, 0ull, 0ull, 0ull};
   if (v.mfma && ((s = p->alloc(&v.bf, P * v.tb)) != BN_OK || (s = p->alloc(&v.delta_bf, v.pc)) != BN_OK)) {

@@ -74,6 +74,10 @@ struct DevView {
   // Gaussian integrands (tgp = 0 when there are none)
   uint32_t tg, tgp;          // count, padded to 64
   const double* gcoef;       // [tgp][4] exponent coefficients a, bx, by, c (base 2; 0 for padding)
+  uint32_t glines, gwords;   // Gaussian line form: lines (0: sample by sample), doubles per table
+  const uint32_t* grow;      // [n][1 + glines] lattice lines of each shift class (lattice_lines.h)
+  const int* gspans;         // [glines][4] steps, full_lo, full_hi, steps of b1 from O + b2 to the next origin
+  const double* gtab;        // [tg / 4 rounded up][gwords][4] tables (lattice_lines.h)
   const double* gint;        // [tgp] exact integrals
   float* gest;               // [P][tgp] estimates
   float* gerr;               // [P][tgp] errors g - I (refreshed on demand)
@@ -100,6 +104,8 @@ hipError_t launch_blur(const DevView& v, const float* field, uint32_t pitch, uin
                        uint32_t nkx, const int32_t* dx, const float* ky, uint32_t nky, const int32_t* dy,
                        float* tmp, double* partial, uint32_t* npartial, hipStream_t s);
 uint32_t blur_partials(const DevView& v, uint32_t pitch);
+bool gauss_lines_pay(const DevView& v, uint32_t m);
+hipError_t launch_gauss_lines(const DevView& v, bool all, uint32_t m, hipStream_t s);
 hipError_t launch_gauss_est(const DevView& v, int mode, uint32_t m, hipStream_t s);
 hipError_t launch_gauss_delta(const DevView& v, int mode, uint32_t kappa, uint32_t m, hipStream_t s);
 hipError_t launch_gauss_commit(const DevView& v, uint32_t kappa, hipStream_t s);

@@ -4,6 +4,7 @@
 #include <stdint.h>
 
 #include <algorithm>
+#include <cmath>
 #include <cstdlib>
 #include <utility>
 #include <vector>
@@ -72,6 +73,33 @@ inline LatticeLines lattice_lines(int64_t n, int64_t gx, int64_t gy) {
 
 inline int64_t floor_div(int64_t a, int64_t b) { return a / b - ((a % b != 0) && ((a < 0) != (b < 0))); }
 
+// Steps j in [lo, hi) with the points (x, y) + j (bx, by) inside [0, N)^2.
+inline void line_interval(int64_t n, int64_t x, int64_t y, int64_t bx, int64_t by, int64_t& lo, int64_t& hi) {
+  const int64_t top = n - 1;
+  int64_t a = -4 * n, b = 4 * n;
+  for (int axis = 0; axis < 2; ++axis) {
+    const int64_t c = axis ? y : x, s = axis ? by : bx;
+    if (s > 0) {
+      a = std::max(a, floor_div(-c + s - 1, s));
+      b = std::min(b, floor_div(top - c, s));
+    } else if (s < 0) {
+      a = std::max(a, floor_div(c - top - s - 1, -s));
+      b = std::min(b, floor_div(c, -s));
+    } else if (c < 0 || c > top) {
+      b = a - 1;
+    }
+  }
+  lo = a;
+  hi = std::max(a, b + 1);
+}
+
+// gx^-1 mod N (N a power of two, gx odd: Newton).
+inline int64_t generator_inverse(int64_t n, int64_t gx) {
+  int64_t inv = 1;
+  for (int i = 0; i < 6; ++i) inv = ((inv * (2 - gx * inv)) % n + n) % n;
+  return n == 1 ? 0 : inv;
+}
+
 // The lines of every shift class, rows of `stride` words: sample A of the
 // first line (x | y << 16, lattice units), sum of lo over the lines, then
 // lo | hi << 16 (int16) per line, j counted from A + l b2.  Class k holds the
@@ -79,9 +107,7 @@ inline int64_t floor_div(int64_t a, int64_t b) { return a / b - ((a % b != 0) &&
 inline bool lattice_rows(int64_t n, int64_t gx, int64_t gy, const LatticeLines& g, uint32_t max_lines, uint32_t stride,
                   std::vector<uint32_t>& rows) {
   rows.assign((size_t)n * stride, 0u);
-  int64_t inv = 1;   // gx^-1 mod N (N a power of two: Newton)
-  for (int i = 0; i < 6; ++i) inv = ((inv * (2 - gx * inv)) % n + n) % n;
-  if (n == 1) inv = 0;
+  const int64_t inv = generator_inverse(n, gx);
   const int64_t bx = g.b1[0], by = g.b1[1], top = n - 1;
   for (int64_t k = 0; k < n; ++k) {
     const int64_t py = k * inv % n;   // the class's sample with x = 0
@@ -98,27 +124,16 @@ inline bool lattice_rows(int64_t n, int64_t gx, int64_t gy, const LatticeLines& 
     int64_t base = 0, j0 = 0, sum = 0, total = 0;
     for (int64_t l = l0; l <= l1; ++l) {
       const int64_t x = l * g.b2[0], y = py + l * g.b2[1];
-      int64_t a = -4 * n, b = 4 * n;   // j range with the line's points in [0, N)^2
-      for (int axis = 0; axis < 2; ++axis) {
-        const int64_t c = axis ? y : x, s = axis ? by : bx;
-        if (s > 0) {
-          a = std::max(a, floor_div(-c + s - 1, s));
-          b = std::min(b, floor_div(top - c, s));
-        } else if (s < 0) {
-          a = std::max(a, floor_div(c - top - s - 1, -s));
-          b = std::min(b, floor_div(c, -s));
-        } else if (c < 0 || c > top) {
-          b = a - 1;
-        }
-      }
-      if (b < a) continue;
+      int64_t a, b;
+      line_interval(n, x, y, bx, by, a, b);
+      if (b <= a) continue;
       if (first) {
         first = false;
         base = l;
         j0 = a;
         row[0] = (uint32_t)(x + a * bx) | ((uint32_t)(y + a * by) << 16);
       }
-      const int64_t lo = a - j0, hi = b + 1 - j0;
+      const int64_t lo = a - j0, hi = b - j0;
       if (l - base >= max_lines || lo < -32768 || hi > 32767) return false;
       row[2 + (l - base)] = ((uint32_t)lo & 0xFFFFu) | ((uint32_t)hi << 16);
       sum += lo;
@@ -162,6 +177,135 @@ inline LineRec line_record(const LatticeLines& g, int64_t step, int64_t nx, int6
 inline uint32_t count_deviation(int64_t n, const LatticeLines& g) {
   const int64_t m = std::max(std::llabs(g.b1[0]), std::llabs(g.b1[1]));
   return g.lines && m ? (uint32_t)(g.lines + 1 + (n + m - 1) / m) : 0;
+}
+
+// The same lines for the Gaussian estimates (gauss_lines.hip): class rows
+// anchored at the lattice point A nearest the square's centre, line l at
+// A + l b2 for l = first .. first + lines - 1, steps counted from the line's
+// origin O_l = A + l b2 + j0_l b1, j0_l the smallest step any class has on it.
+struct GaussLines {
+  uint32_t lines = 0, stride = 0, steps = 0;   // steps: longest line
+  int64_t first = 0;
+  std::vector<int64_t> j0;                     // [lines]
+  // per line: steps to take, and the part [full_lo, full_hi) of them that
+  // every class has (without one: [steps, steps), so that a step above full_hi
+  // is above every class's first)
+  struct Span {
+    int32_t steps, full_lo, full_hi;
+  };
+  std::vector<Span> spans;
+  // [N][stride]: A (int16 x | y << 16), then lo | hi << 16 per line
+  std::vector<uint32_t> rows;
+};
+
+inline GaussLines gauss_lines(int64_t n, int64_t gx, int64_t gy, const LatticeLines& g) {
+  GaussLines out;
+  const int64_t inv = generator_inverse(n, gx), bx = g.b1[0], by = g.b1[1], cx = g.b2[0], cy = g.b2[1];
+  const int64_t reach = g.lines + 2;
+  // nearest integer to a / (2 n)
+  auto near = [&](int64_t a) { return floor_div(a + n, 2 * n); };
+  std::vector<std::pair<int64_t, int64_t>> anchor(n);
+  int64_t l0 = reach, l1 = -reach;
+  auto interval = [&](int64_t k, int64_t l, int64_t& lo, int64_t& hi) {
+    line_interval(n, anchor[k].first + l * cx, anchor[k].second + l * cy, bx, by, lo, hi);
+  };
+  for (int64_t k = 0; k < n; ++k) {
+    // twice the sample (0, py) less the centre, in units of b1 and b2
+    const int64_t x = -(n - 1), y = 2 * (k * inv % n) - (n - 1);
+    const int64_t al = near(x * cy - y * cx), be = near(bx * y - by * x);
+    anchor[k] = {-al * bx - be * cx, k * inv % n - al * by - be * cy};
+    for (int64_t l = -reach; l <= reach; ++l) {
+      int64_t lo, hi;
+      interval(k, l, lo, hi);
+      if (hi > lo) l0 = std::min(l0, l), l1 = std::max(l1, l);
+    }
+  }
+  out.first = l0;
+  out.lines = (uint32_t)(l1 - l0 + 1);
+  out.stride = 1 + out.lines;
+  out.rows.assign((size_t)n * out.stride, 0u);
+  out.j0.assign(out.lines, 0);
+  out.spans.assign(out.lines, GaussLines::Span{0, 0, 0});
+  for (uint32_t i = 0; i < out.lines; ++i) {
+    int64_t jmin = 0, jmax = 0, lo_max = 0, hi_min = 0;
+    bool any = false, all = true;
+    for (int64_t k = 0; k < n; ++k) {
+      int64_t lo, hi;
+      interval(k, l0 + i, lo, hi);
+      if (hi <= lo) {
+        all = false;
+        continue;
+      }
+      jmin = any ? std::min(jmin, lo) : lo;
+      jmax = any ? std::max(jmax, hi) : hi;
+      lo_max = any ? std::max(lo_max, lo) : lo;
+      hi_min = any ? std::min(hi_min, hi) : hi;
+      any = true;
+    }
+    if (!any) jmin = jmax = i ? out.j0[i - 1] : 0;
+    if (!all || hi_min < lo_max) lo_max = hi_min = jmax;
+    out.j0[i] = jmin;
+    out.spans[i] = GaussLines::Span{(int32_t)(jmax - jmin), (int32_t)(lo_max - jmin), (int32_t)(hi_min - jmin)};
+    out.steps = std::max(out.steps, (uint32_t)(jmax - jmin));
+    for (int64_t k = 0; k < n; ++k) {
+      int64_t lo, hi;
+      interval(k, l0 + i, lo, hi);
+      if (hi > lo)
+        out.rows[(size_t)k * out.stride + 1 + i] = (uint32_t)(lo - jmin) | ((uint32_t)(hi - jmin) << 16);
+    }
+  }
+  for (int64_t k = 0; k < n; ++k)
+    out.rows[(size_t)k * out.stride] =
+        ((uint32_t)anchor[k].first & 0xFFFFu) | ((uint32_t)anchor[k].second << 16);
+  return out;
+}
+
+// One Gaussian's table for the line form, doubles, interleaved with those of
+// the other three of its four (entry i at 4 i): with E(x) = a |x|^2 + bx x +
+// by y + c its base-2 exponent and lengths in the unit square,
+//   [0..3]   E at the first line's origin less a |O - A|^2, as a function of A:
+//            a, then the coefficients of x, y and 1
+//   [4..6]   exponent of the step b1 at A, less a |b1|^2: coefficients of x, y, 1
+//   [7..9]   the same for b2
+//   [11]     1 where the exponents leave FP64's range (counted sample by sample)
+//   [12 ..]  per line: ratio of its step factor to that at A, 2^(a |O - A|^2)
+//   then     2^(a |b1|^2 j^2) for j = 0 .. steps - 1
+constexpr uint32_t GAUSS_HEAD = 12;
+inline uint32_t gauss_table_words(const GaussLines& q) { return (GAUSS_HEAD + 2 * q.lines + q.steps + 3) / 4 * 4; }
+
+inline void gauss_table(int64_t n, const LatticeLines& g, const GaussLines& q, double a, double bx, double by, double c,
+                        double mx, double my, double* t) {
+  const double u = 1.0 / (double)n;
+  const double b1x = g.b1[0] * u, b1y = g.b1[1] * u, b2x = g.b2[0] * u, b2y = g.b2[1] * u;
+  const double d0x = q.first * b2x + q.j0[0] * b1x, d0y = q.first * b2y + q.j0[0] * b1y;
+  t[0] = a;
+  t[4] = bx + 2.0 * a * d0x;
+  t[8] = by + 2.0 * a * d0y;
+  t[12] = c + bx * d0x + by * d0y;
+  t[16] = 2.0 * a * b1x;
+  t[20] = 2.0 * a * b1y;
+  t[24] = bx * b1x + by * b1y;
+  t[28] = 2.0 * a * b2x;
+  t[32] = 2.0 * a * b2y;
+  t[36] = bx * b2x + by * b2y;
+  double far = 0.0;
+  for (uint32_t i = 0; i < q.lines; ++i) {
+    const double l = (double)(q.first + (int64_t)i), j = (double)q.j0[i];
+    const double dx = l * b2x + j * b1x, dy = l * b2y + j * b1y;
+    t[4 * (GAUSS_HEAD + 2 * i)] = std::exp2(2.0 * a * (dx * b1x + dy * b1y));
+    t[4 * (GAUSS_HEAD + 2 * i + 1)] = std::exp2(a * (dx * dx + dy * dy));
+    far = std::max(far, std::sqrt(dx * dx + dy * dy));
+  }
+  const double h = std::sqrt(b1x * b1x + b1y * b1y), k = std::sqrt(b2x * b2x + b2y * b2y);
+  for (uint32_t j = 0; j < q.steps; ++j) t[4 * (GAUSS_HEAD + 2 * q.lines + j)] = std::exp2(a * h * h * (double)j * (double)j);
+  // base-2 exponents met, over |a|: of a line's factor without and with its
+  // |O - A|^2, and of Horner's partial sums, 2^-E at the points of a line from
+  // its origin on (A is within half a cell of the centre)
+  const double rc = std::sqrt((mx - 0.5) * (mx - 0.5) + (my - 0.5) * (my - 0.5)), half = 0.5 * (h + k), ra = rc + half;
+  const double e1 = ra * ra + 2.0 * ra * far, e3 = rc + std::max(far + half, 0.7072);
+  const double most = std::max(std::max(e1, far * far), e3 * e3);
+  t[40] = 0.0;
+  t[44] = -a * most < 1000.0 ? 0.0 : 1.0;
 }
 
 // A padded integrand: a crossing far before every line, counted on the m < 0

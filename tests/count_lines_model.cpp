@@ -90,3 +90,62 @@ extern "C" int count_lines_padding(uint32_t n, uint32_t gx, uint32_t gy) {
 extern "C" uint32_t count_lines_deviation(uint32_t n, uint32_t gx, uint32_t gy) {
   return count_deviation(n, lattice_lines(n, gx, gy));
 }
+
+// Gaussian estimates along the lines (csrc/gauss_lines.hip) on the library's
+// tables, and the sum over the samples.  Returns the steps of the longest line;
+// flagged counts the rows whose exponents the table calls out of range (got is
+// then the direct sum).
+extern "C" int gauss_lines_model(uint32_t n, uint32_t gx, uint32_t gy, uint32_t k, const double* mx, const double* my,
+                                 const double* sd, const uint16_t* ux, const uint16_t* uy, double* got, double* want,
+                                 uint32_t* flagged) {
+  const LatticeLines g = lattice_lines(n, gx, gy);
+  const GaussLines q = gauss_lines(n, gx, gy, g);
+  const uint32_t step = 65536 / n;
+  uint32_t sh = 0;
+  while ((1u << sh) < step) ++sh;
+  std::vector<double> four(4 * gauss_table_words(q)), t(gauss_table_words(q));
+  *flagged = 0;
+  for (uint32_t i = 0; i < k; ++i) {
+    const double gm = 1.4426950408889634074 / (2.0 * sd[i] * sd[i]);
+    const double a = -gm, bx = 2.0 * gm * mx[i], by = 2.0 * gm * my[i], c = -gm * (mx[i] * mx[i] + my[i] * my[i]);
+    long double direct = 0;
+    for (uint32_t s = 0; s < n; ++s) {
+      const long double x = (((uint64_t)s * gx % n * step + ux[i]) & 0xFFFF) / 65536.0L - mx[i];
+      const long double y = (((uint64_t)s * gy % n * step + uy[i]) & 0xFFFF) / 65536.0L - my[i];
+      direct += std::exp2((long double)a * (x * x + y * y));
+    }
+    want[i] = (double)(direct / n);
+    gauss_table(n, g, q, a, bx, by, c, mx[i], my[i], four.data() + i % 4);
+    for (size_t e = 0; e < t.size(); ++e) t[e] = four[4 * e + i % 4];
+    if (t[11] != 0.0) {
+      ++*flagged;
+      got[i] = want[i];
+      continue;
+    }
+    const uint32_t cls = ((uint32_t)(uy[i] >> sh) * gx - (uint32_t)(ux[i] >> sh) * gy) & (n - 1), fm = (1u << sh) - 1;
+    const uint32_t* row = &q.rows[(size_t)cls * q.stride];
+    const double ax = ((int)(int16_t)(row[0] & 0xFFFF) * (int)(1u << sh) + (int)(ux[i] & fm)) / 65536.0;
+    const double ay = (((int)row[0] >> 16) * (int)(1u << sh) + (int)(uy[i] & fm)) / 65536.0;
+    double y = std::exp2(t[0] * (ax * ax + ay * ay) + t[1] * ax + t[2] * ay + t[3]);
+    const double za = std::exp2(t[4] * ax + t[5] * ay + t[6]), ys = std::exp2(t[7] * ax + t[8] * ay + t[9]);
+    const double* w = &t[GAUSS_HEAD + 2 * q.lines];
+    double total = 0.0;
+    for (uint32_t l = 0; l < q.lines; ++l) {
+      const GaussLines::Span& gr = q.spans[l];
+      const uint32_t r = row[1 + l];
+      const int lo = (int)(r & 0xFFFF), hi = (int)(r >> 16);
+      const double z = za * t[GAUSS_HEAD + 2 * l];
+      double p = 0.0;
+      for (int s = gr.steps - 1; s >= 0; --s) {
+        const bool in = s < hi && s >= lo;
+        if (s >= gr.full_lo && s < gr.full_hi && !in) return -1;   // the unmasked part
+        p = std::fma(p, z, in ? w[s] : 0.0);
+      }
+      if (hi > gr.steps) return -1;
+      total += y * t[GAUSS_HEAD + 2 * l + 1] * p;
+      if (l + 1 < q.lines) y *= ys * std::pow(za, (double)(q.j0[l + 1] - q.j0[l]));
+    }
+    got[i] = total / n;
+  }
+  return (int)q.steps;
+}

@@ -91,3 +91,29 @@ def test_counts_stay_within_the_lines_bound(model, n):
         assert np.abs(want.astype(int) - np.rint(n * areas).astype(int)).max() <= bound, g
     assert model.count_lines_deviation(256, 1, 79) <= 63
     assert model.count_lines_deviation(1024, 1, 381) <= 126
+
+
+@pytest.mark.parametrize("n", [16, 64, 256, 1024, 4096])
+def test_gauss_line_sums_equal_direct_sums(model, n):
+    """The Gaussian estimates along the lines against the sum over the samples,
+    both in 64 bits: the drawn range of centres and widths, centres outside the
+    square and narrow Gaussians up to where the table declines.  A term carries
+    at most some hundred roundings of 2^-53 relative each (steps of a line,
+    lines, four exponentials of exponents up to 1000: 2^-43 for those)."""
+    rng = np.random.default_rng(n + 7)
+    k = 300 if n <= 1024 else 60
+    for g in [(1, 1 + 2 * (n // 8)), (1, int(n * 0.618) | 1), (3, 2 * int(rng.integers(0, n // 2)) + 1)]:
+        mx, my = rng.uniform(0, 1, k), rng.uniform(0, 1, k)
+        mx[::7] += rng.choice([-0.5, 0.5])
+        s = rng.uniform(0.05, 0.3, k)
+        s[1::5] = rng.uniform(0.01, 0.06, len(s[1::5]))
+        s[2::11] = 3.0
+        u = rng.integers(0, 65536, (2, k), dtype=np.uint16)
+        got, want, few = np.zeros(k), np.zeros(k), C.c_uint32()
+        args = (mx, my, s, u[0].copy(), u[1].copy())
+        p = [x.ctypes.data_as(C.c_void_p) for x in args]
+        steps = model.gauss_lines_model(n, g[0], g[1], k, *p, got.ctypes.data_as(C.c_void_p),
+                                        want.ctypes.data_as(C.c_void_p), C.byref(few))
+        assert 0 < steps <= n
+        assert 0 < few.value < k / 3
+        np.testing.assert_allclose(got, want, rtol=2.0 ** -40)
