@@ -207,6 +207,9 @@ struct bn_problem_s {
   std::vector<double> cls_w;
   std::vector<void*> allocs;
   uint32_t list_cap = 0;
+  // rows on their way to the host (stage_rows)
+  void* stage = nullptr;
+  size_t stage_bytes = 0;
   uint16_t* list_cnt = nullptr;
   uint32_t* list_u = nullptr;
   uint32_t* list_pix = nullptr;
@@ -274,6 +277,7 @@ struct bn_problem_s {
     if (swap_exec) (void)hipGraphExecDestroy(swap_exec);
     if (swap_graph) (void)hipGraphDestroy(swap_graph);
     for (void* p : allocs) (void)hipFree(p);
+    if (stage) (void)hipFree(stage);
     for (hipEvent_t e : ev)
       if (e) (void)hipEventDestroy(e);
     for (auto* vec : {&prof_recount, &prof_eval, &prof_commit})
@@ -386,10 +390,40 @@ bn_status sync(bn_problem p) {
   return BN_OK;
 }
 
+// Rows of row_bytes bytes that the problem's staging buffer takes at a time, of
+// `rows`.  The buffer is kept with the problem, at most 64 MiB (larger results
+// cross in several rounds); 0 if there is no memory for it.
+uint32_t stage_rows(bn_problem p, uint32_t rows, size_t row_bytes) {
+  const size_t most = (size_t)64 << 20;
+  const size_t want = std::min(rows * row_bytes, std::max(most, row_bytes));
+  if (p->stage_bytes < want) {
+    if (sync(p) != BN_OK) return 0;
+    if (p->stage) (void)hipFree(p->stage);
+    p->stage = nullptr;
+    p->stage_bytes = 0;
+    if (hipMalloc(&p->stage, want) != hipSuccess) {
+      (void)hipGetLastError();
+      p->stage = nullptr;
+      return 0;
+    }
+    p->stage_bytes = want;
+  }
+  return (uint32_t)std::min<size_t>(rows, p->stage_bytes / row_bytes);
+}
+
 // Copy a tiled count buffer ([tp/8][rows][8] uint16 on the device) to host
-// rows [rows][t].  Synchronises.
+// rows [rows][t], laid out on the device (without memory for that, here).
+// Synchronises.
 bn_status untile_counts(bn_problem p, const uint16_t* dev, uint32_t rows, uint16_t* host) {
   const uint32_t t = p->v.t, tp = p->v.tp;
+  if (const uint32_t per = stage_rows(p, rows, (size_t)t * 2)) {
+    for (uint32_t r = 0; r < rows; r += per) {
+      const uint32_t n = std::min(per, rows - r);
+      HIPCHK(launch_untile_counts(dev, rows, r, n, t, (uint16_t*)p->stage, p->stream));
+      HIPCHK(hipMemcpyAsync(host + (size_t)r * t, p->stage, (size_t)n * t * 2, hipMemcpyDeviceToHost, p->stream));
+    }
+    return sync(p);
+  }
   std::vector<uint16_t> tmp((size_t)rows * tp);
   HIPCHK(hipMemcpyAsync(tmp.data(), dev, tmp.size() * 2, hipMemcpyDeviceToHost, p->stream));
   bn_status s = sync(p);
@@ -1688,6 +1722,15 @@ bn_status bn_get_errors(bn_problem p, float* host) {
   bn_status rs = refresh_errors(p);
   if (rs != BN_OK) return rs;
   const size_t P = (size_t)p->v.w * p->v.h, row = (size_t)(p->v.t + p->v.tg) * 4;
+  if (const uint32_t per = stage_rows(p, (uint32_t)P, row)) {
+    for (uint32_t r = 0; r < P; r += per) {
+      const uint32_t n = std::min(per, (uint32_t)P - r);
+      HIPCHK(launch_pack_errors(p->v, r, n, (float*)p->stage, p->stream));
+      HIPCHK(hipMemcpyAsync((char*)host + r * row, p->stage, n * row, hipMemcpyDeviceToHost, p->stream));
+    }
+    return sync(p);
+  }
+  // no memory to lay the rows out in
   HIPCHK(hipMemcpy2DAsync(host, row, p->v.err, p->v.tp * 4, p->v.t * 4, P, hipMemcpyDeviceToHost, p->stream));
   if (p->v.tg)
     HIPCHK(hipMemcpy2DAsync(host + p->v.t, row, p->v.gerr, p->v.tgp * 4, p->v.tg * 4, P, hipMemcpyDeviceToHost,
@@ -1776,7 +1819,7 @@ bn_status bn_delta_energy_noalloc(bn_problem p, const uint32_t* pixels, const ui
   HIPCHK(launch_delta(lv, MODE_LIST, 0, m, p->stream));
   HIPCHK(hipMemcpyAsync(out_de, lv.delta, (size_t)m * 8, hipMemcpyDeviceToHost, p->stream));
   if (out_counts) {
-    HIPCHK(launch_untile_counts(lv.c_new, m, p->v.t, rows, p->stream));
+    HIPCHK(launch_untile_counts(lv.c_new, m, 0, m, p->v.t, rows, p->stream));
     HIPCHK(hipMemcpyAsync(out_counts, rows, (size_t)m * p->v.t * 2, hipMemcpyDeviceToHost, p->stream));
   }
   return sync(p);

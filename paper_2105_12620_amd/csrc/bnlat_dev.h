@@ -95,6 +95,7 @@ hipError_t launch_phase(const DevView& v, uint32_t kappa, hipStream_t s);
 hipError_t launch_commit(const DevView& v, uint32_t kappa, hipStream_t s, bool advance = false);
 uint32_t commit_blocks(const DevView& v);
 hipError_t launch_errors(const DevView& v, hipStream_t s);
+hipError_t launch_pack_errors(const DevView& v, uint32_t first, uint32_t n, float* out, hipStream_t s);
 hipError_t launch_advance(const DevView& v, hipStream_t s);
 hipError_t launch_recount_index(const DevView& v, hipStream_t s);
 hipError_t launch_recount_advance_pair(const DevView& v, hipStream_t s);
@@ -170,6 +171,7 @@ hipError_t peak_launch(int kind, void* buf, void* buf2, uint64_t size, uint32_t 
 // allocation-free entry point: device address of the scratch array on
 // `device` (located once per device), and tiled counts -> host row layout
 hipError_t noalloc_scratch(int device, void** ptr);
-hipError_t launch_untile_counts(const uint16_t* tiled, uint32_t rows, uint32_t t, uint16_t* out, hipStream_t s);
+hipError_t launch_untile_counts(const uint16_t* tiled, uint32_t rows, uint32_t first, uint32_t n, uint32_t t,
+                                uint16_t* out, hipStream_t s);
 
 }  // namespace bnlat

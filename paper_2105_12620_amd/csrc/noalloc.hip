@@ -19,13 +19,15 @@ static __device__ __align__(256) unsigned char scratch[NOALLOC_SCRATCH_BYTES];
 
 constexpr int kMaxDevices = 64;
 
-// Tiled counts [tp/8][rows][8] -> rows [rows][t] (one thread per entry).
+// Rows first .. of tiled counts [tp/8][rows][8] -> [n][t], n rows (one thread
+// per entry).
 __global__ __launch_bounds__(256) void k_untile_counts(const uint16_t* __restrict__ tiled, uint32_t rows,
-                                                       uint32_t t, uint16_t* __restrict__ out) {
+                                                       uint32_t first, uint32_t n, uint32_t t,
+                                                       uint16_t* __restrict__ out) {
   const uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= (uint64_t)rows * t) return;
+  if (i >= (uint64_t)n * t) return;
   const uint32_t r = (uint32_t)(i / t), c = (uint32_t)(i - (uint64_t)r * t);
-  out[i] = tiled[((size_t)(c >> 3) * rows + r) * 8 + (c & 7)];
+  out[i] = tiled[((size_t)(c >> 3) * rows + first + r) * 8 + (c & 7)];
 }
 
 }  // namespace
@@ -53,10 +55,12 @@ hipError_t noalloc_scratch(int device, void** ptr) {
   return hipSuccess;
 }
 
-hipError_t launch_untile_counts(const uint16_t* tiled, uint32_t rows, uint32_t t, uint16_t* out, hipStream_t s) {
-  const uint64_t n = (uint64_t)rows * t;
-  if (n == 0) return hipSuccess;
-  hipLaunchKernelGGL(k_untile_counts, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, tiled, rows, t, out);
+hipError_t launch_untile_counts(const uint16_t* tiled, uint32_t rows, uint32_t first, uint32_t n, uint32_t t,
+                                uint16_t* out, hipStream_t s) {
+  const uint64_t items = (uint64_t)n * t;
+  if (items == 0) return hipSuccess;
+  hipLaunchKernelGGL(k_untile_counts, dim3((unsigned)((items + 255) / 256)), dim3(256), 0, s, tiled, rows, first, n, t,
+                     out);
   return hipGetLastError();
 }
 
