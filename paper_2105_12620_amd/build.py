@@ -14,7 +14,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 SOURCES = ["csrc/count.hip", "csrc/phase_wide.hip", "csrc/phase_narrow.hip", "csrc/phase_split.hip",
            "csrc/gauss_lines.hip", "csrc/kernels.hip", "csrc/swap.hip", "csrc/sampler.hip", "csrc/mfma.hip",
            "csrc/noalloc.hip", "csrc/peaks.hip",
-           "csrc/spectrum.hip", "csrc/api.cpp"]
+           "csrc/blur.hip", "csrc/spectrum.hip", "csrc/api.cpp"]
 LIB = os.path.join(HERE, "libbnlat.so")
 
 FLAGS = [

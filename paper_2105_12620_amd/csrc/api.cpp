@@ -165,8 +165,9 @@ void window_classes(uint32_t r, double sigma, std::vector<uint32_t>& d, std::vec
 }
 
 // Periodised, normalised Gaussian of standard deviation s on a ring of n
-// pixels; returns the taps above a negligible relative level.
-void blur_taps(uint32_t n, double s, std::vector<float>& k, std::vector<int32_t>& d) {
+// pixels; returns the taps above a negligible relative level and their runs of
+// consecutive distances.
+void blur_taps(uint32_t n, double s, std::vector<float>& k, std::vector<int2>& runs) {
   std::vector<double> kd(n, 0.0);
   const int reps = (int)std::ceil(6.0 * s / n) + 1;
   double total = 0.0, kmax = 0.0;
@@ -179,11 +180,12 @@ void blur_taps(uint32_t n, double s, std::vector<float>& k, std::vector<int32_t>
   }
   for (uint32_t i = 0; i < n; ++i) kmax = std::max(kmax, kd[i]);
   k.clear();
-  d.clear();
+  runs.clear();
   for (uint32_t i = 0; i < n; ++i)
     if (kd[i] > 1e-12 * kmax) {
       k.push_back((float)(kd[i] / total));
-      d.push_back((int32_t)i);
+      if (runs.empty() || runs.back().x + runs.back().y != (int)i) runs.push_back(make_int2((int)i, 0));
+      ++runs.back().y;
     }
 }
 
@@ -1328,7 +1330,8 @@ bn_status bn_create_problem_ext(const bn_config* cfg, const bn_heaviside* heavis
       (v.form != FIELD_WIDE && ((s = p->alloc(&v.d8, P * v.tp)) != BN_OK || (s = p->alloc(&v.n8, (size_t)v.pc * v.tp)) != BN_OK)) || (s = p->alloc(&v.delta, v.pc)) != BN_OK ||
       (s = p->alloc(&v.accept, v.pc)) != BN_OK || (s = p->alloc(&v.ctr, 4)) != BN_OK ||
       (s = p->alloc(&v.unsure, v.pc)) != BN_OK ||
-      (s = p->alloc(&p->ysum, v.ncls)) != BN_OK ||       (v.mfma && (s = p->alloc(&v.xpart, (size_t)v.ncls * v.pc)) != BN_OK)) {
+      (s = p->alloc(&p->ysum, ENERGY_ROWS * v.ncls)) != BN_OK ||
+      (v.mfma && (s = p->alloc(&v.xpart, (size_t)v.ncls * v.pc)) != BN_OK)) {
     delete p;
     return s;
   }
@@ -1509,12 +1512,13 @@ bn_status bn_sweep(bn_problem p, uint32_t k, bn_sweep_stats* stats) {
 bn_status bn_energy(bn_problem p, double* out) {
   if (!p || !out) return fail(BN_EINVAL, "NULL argument");
   if (!p->have_counts) return fail(BN_ESTATE, "bn_compute_errors must run first");
-  HIPCHK(hipMemsetAsync(p->ysum, 0, p->v.ncls * sizeof(unsigned long long), p->stream));
+  std::vector<unsigned long long> y(ENERGY_ROWS * p->v.ncls);
+  HIPCHK(hipMemsetAsync(p->ysum, 0, y.size() * 8, p->stream));
   HIPCHK(launch_energy(p->v, p->ysum, p->stream));
-  std::vector<unsigned long long> y(p->v.ncls);
   HIPCHK(hipMemcpyAsync(y.data(), p->ysum, y.size() * 8, hipMemcpyDeviceToHost, p->stream));
   bn_status s = sync(p);
   if (s != BN_OK) return s;
+  for (uint32_t i = p->v.ncls; i < y.size(); ++i) y[i % p->v.ncls] += y[i];
   // The kernel sums half of the window; the mirrored half has the same total.
   double acc = 0.0;
   for (uint32_t c = 0; c < p->v.ncls; ++c) acc = acc + p->cls_w[c] * (double)(long long)(2 * y[c]);
@@ -1582,18 +1586,18 @@ bn_status bn_quality_metric_family(bn_problem p, bn_rows rows, const double* sig
   const uint32_t pitch_max = std::max(p->v.tp, p->v.tgp);
   const uint32_t nparts = blur_partials(p->v, pitch_max);
   float *tmp = nullptr, *kx = nullptr, *ky = nullptr;
-  int32_t *dx = nullptr, *dy = nullptr;
+  int2 *rx = nullptr, *ry = nullptr;
   double* part = nullptr;
   // Scratch for the blur lives for the duration of the call only.
   auto release = [&]() {
-    for (void* q : {(void*)tmp, (void*)kx, (void*)ky, (void*)dx, (void*)dy, (void*)part})
+    for (void* q : {(void*)tmp, (void*)kx, (void*)ky, (void*)rx, (void*)ry, (void*)part})
       if (q) (void)hipFree(q);
   };
   hipError_t e = hipMalloc((void**)&tmp, P * pitch_max * sizeof(float));
-  if (e == hipSuccess) e = hipMalloc((void**)&kx, p->v.w * sizeof(float));
-  if (e == hipSuccess) e = hipMalloc((void**)&ky, p->v.h * sizeof(float));
-  if (e == hipSuccess) e = hipMalloc((void**)&dx, p->v.w * sizeof(int32_t));
-  if (e == hipSuccess) e = hipMalloc((void**)&dy, p->v.h * sizeof(int32_t));
+  if (e == hipSuccess) e = hipMalloc((void**)&kx, (p->v.w + BLUR_BLOCK) * sizeof(float));
+  if (e == hipSuccess) e = hipMalloc((void**)&ky, (p->v.h + BLUR_BLOCK) * sizeof(float));
+  if (e == hipSuccess) e = hipMalloc((void**)&rx, p->v.w * sizeof(int2));
+  if (e == hipSuccess) e = hipMalloc((void**)&ry, p->v.h * sizeof(int2));
   if (e == hipSuccess) e = hipMalloc((void**)&part, (size_t)nparts * sizeof(double));
   if (e != hipSuccess) {
     (void)hipGetLastError();
@@ -1603,21 +1607,21 @@ bn_status bn_quality_metric_family(bn_problem p, bn_rows rows, const double* sig
   std::vector<double> hp(nparts);
   for (uint32_t i = 0; i < n; ++i) {
     std::vector<float> hkx, hky;
-    std::vector<int32_t> hdx, hdy;
-    blur_taps(p->v.w, sigmas[i], hkx, hdx);
-    blur_taps(p->v.h, sigmas[i], hky, hdy);
+    std::vector<int2> hrx, hry;
+    blur_taps(p->v.w, sigmas[i], hkx, hrx);
+    blur_taps(p->v.h, sigmas[i], hky, hry);
     e = hipMemcpyAsync(kx, hkx.data(), hkx.size() * 4, hipMemcpyHostToDevice, p->stream);
-    if (e == hipSuccess) e = hipMemcpyAsync(dx, hdx.data(), hdx.size() * 4, hipMemcpyHostToDevice, p->stream);
+    if (e == hipSuccess) e = hipMemcpyAsync(rx, hrx.data(), hrx.size() * 8, hipMemcpyHostToDevice, p->stream);
     if (e == hipSuccess) e = hipMemcpyAsync(ky, hky.data(), hky.size() * 4, hipMemcpyHostToDevice, p->stream);
-    if (e == hipSuccess) e = hipMemcpyAsync(dy, hdy.data(), hdy.size() * 4, hipMemcpyHostToDevice, p->stream);
+    if (e == hipSuccess) e = hipMemcpyAsync(ry, hry.data(), hry.size() * 8, hipMemcpyHostToDevice, p->stream);
     double acc = 0.0;
     const float* fields[2] = {p->v.err, p->v.gerr};
     const uint32_t pitches[2] = {p->v.tp, p->v.tgp}, valids[2] = {p->v.t, p->v.tg};
     for (int f = 0; f < 2 && e == hipSuccess; ++f) {
       if (!pitches[f] || (rows == BN_ROWS_HEAVISIDE && f == 1) || (rows == BN_ROWS_GAUSSIAN && f == 0)) continue;
       uint32_t np = 0;
-      e = launch_blur(p->v, fields[f], pitches[f], valids[f], kx, (uint32_t)hkx.size(), dx, ky,
-                      (uint32_t)hky.size(), dy, tmp, part, &np, p->stream);
+      e = launch_blur(p->v, fields[f], pitches[f], valids[f], {kx, rx, (uint32_t)hrx.size()},
+                      {ky, ry, (uint32_t)hry.size()}, tmp, part, &np, p->stream);
       if (e == hipSuccess) e = hipMemcpyAsync(hp.data(), part, (size_t)np * 8, hipMemcpyDeviceToHost, p->stream);
       if (e == hipSuccess) e = hipStreamSynchronize(p->stream);
       for (uint32_t b = 0; b < np && e == hipSuccess; ++b) acc += hp[b];
@@ -1648,33 +1652,49 @@ bn_status bn_error_spectrum(bn_problem p, bn_rows rows, uint32_t nbins, double* 
     twx[k] = make_float2((float)std::cos(2.0 * M_PI * k / W), (float)-std::sin(2.0 * M_PI * k / W));
   for (uint32_t k = 0; k < H; ++k)
     twy[k] = make_float2((float)std::cos(2.0 * M_PI * k / H), (float)-std::sin(2.0 * M_PI * k / H));
-  float2 *d_rows = nullptr, *d_twx = nullptr, *d_twy = nullptr;
-  double* d_pw = nullptr;
+  // scratch for the duration of the call only; one chunk a launch if there is
+  // no memory for more
+  float2 *d_rows = nullptr, *d_twx = nullptr, *d_twy = nullptr, *d_mx = nullptr, *d_my = nullptr;
+  double *d_part = nullptr, *d_pw = nullptr;
   auto release = [&]() {
-    for (void* q : {(void*)d_rows, (void*)d_twx, (void*)d_twy, (void*)d_pw})
+    for (void* q : {(void*)d_rows, (void*)d_twx, (void*)d_twy, (void*)d_mx, (void*)d_my, (void*)d_part, (void*)d_pw})
       if (q) (void)hipFree(q);
+    d_rows = d_twx = d_twy = d_mx = d_my = nullptr;
+    d_part = d_pw = nullptr;
   };
-  // scratch for the duration of the call only
-  hipError_t e = hipMalloc((void**)&d_rows, spectrum_scratch_floats2(p->v) * sizeof(float2));
-  if (e == hipSuccess) e = hipMalloc((void**)&d_twx, W * sizeof(float2));
-  if (e == hipSuccess) e = hipMalloc((void**)&d_twy, H * sizeof(float2));
-  if (e == hipSuccess) e = hipMalloc((void**)&d_pw, P * sizeof(double));
-  if (e != hipSuccess) {
+  uint32_t chunks = spectrum_chunks(p->v, std::max(p->v.t, p->v.tg));
+  hipError_t e = hipSuccess;
+  for (;;) {
+    const SpectrumScratch n = spectrum_scratch(p->v, chunks);
+    e = hipMalloc((void**)&d_rows, n.rows * sizeof(float2));
+    if (e == hipSuccess) e = hipMalloc((void**)&d_twx, W * sizeof(float2));
+    if (e == hipSuccess) e = hipMalloc((void**)&d_twy, H * sizeof(float2));
+    if (e == hipSuccess) e = hipMalloc((void**)&d_mx, n.matx * sizeof(float2));
+    if (e == hipSuccess) e = hipMalloc((void**)&d_my, n.maty * sizeof(float2));
+    if (e == hipSuccess) e = hipMalloc((void**)&d_part, n.power * sizeof(double));
+    if (e == hipSuccess) e = hipMalloc((void**)&d_pw, P * sizeof(double));
+    if (e == hipSuccess) break;
     (void)hipGetLastError();
     release();
-    return fail(BN_ENOMEM, "spectrum scratch: %s", hipGetErrorString(e));
+    if (chunks == 1) return fail(BN_ENOMEM, "spectrum scratch: %s", hipGetErrorString(e));
+    chunks = 1;
   }
   e = hipMemcpyAsync(d_twx, twx.data(), W * sizeof(float2), hipMemcpyHostToDevice, p->stream);
   if (e == hipSuccess) e = hipMemcpyAsync(d_twy, twy.data(), H * sizeof(float2), hipMemcpyHostToDevice, p->stream);
+  if (e == hipSuccess) e = launch_twiddles(d_twx, W, d_mx, p->stream);
+  if (e == hipSuccess) e = launch_twiddles(d_twy, H, d_my, p->stream);
   if (e == hipSuccess) e = hipMemsetAsync(d_pw, 0, P * sizeof(double), p->stream);
   const float* fields[2] = {p->v.err, p->v.gerr};
   const uint32_t pitches[2] = {p->v.tp, p->v.tgp}, valids[2] = {p->v.t, p->v.tg};
+  const uint32_t per = spectrum_chunk();
   uint32_t used = 0;
   for (int f = 0; f < 2 && e == hipSuccess; ++f) {
     if (!valids[f] || (rows == BN_ROWS_HEAVISIDE && f == 1) || (rows == BN_ROWS_GAUSSIAN && f == 0)) continue;
     used += valids[f];
-    for (uint32_t t0 = 0; t0 < valids[f] && e == hipSuccess; t0 += spectrum_chunk())
-      e = launch_spectrum_chunk(p->v, fields[f], pitches[f], valids[f], t0, d_twx, d_twy, d_rows, d_pw, p->stream);
+    const uint32_t all = (valids[f] + per - 1) / per;
+    for (uint32_t c = 0; c < all && e == hipSuccess; c += chunks)
+      e = launch_spectrum_chunks(p->v, fields[f], pitches[f], valids[f], c * per, std::min(chunks, all - c), d_mx, d_my,
+                                 d_rows, d_part, d_pw, p->stream);
   }
   std::vector<double> pw(P);
   if (e == hipSuccess) e = hipMemcpyAsync(pw.data(), d_pw, P * sizeof(double), hipMemcpyDeviceToHost, p->stream);

@@ -100,10 +100,18 @@ hipError_t launch_advance(const DevView& v, hipStream_t s);
 hipError_t launch_recount_index(const DevView& v, hipStream_t s);
 hipError_t launch_recount_advance_pair(const DevView& v, hipStream_t s);
 hipError_t launch_points(const DevView& v, uint32_t pixel, uint32_t* out, hipStream_t s);
+constexpr uint32_t ENERGY_ROWS = 64;   // rows of class sums that k_energy spreads its atomics over
 hipError_t launch_energy(const DevView& v, unsigned long long* y, hipStream_t s);
-hipError_t launch_blur(const DevView& v, const float* field, uint32_t pitch, uint32_t valid, const float* kx,
-                       uint32_t nkx, const int32_t* dx, const float* ky, uint32_t nky, const int32_t* dy,
-                       float* tmp, double* partial, uint32_t* npartial, hipStream_t s);
+// Taps of a blur on the device: BLUR_BLOCK - 1 readable floats past the last,
+// runs of consecutive distances (first, count).
+constexpr uint32_t BLUR_BLOCK = 16;
+struct BlurTaps {
+  const float* taps;
+  const int2* runs;
+  uint32_t nruns;
+};
+hipError_t launch_blur(const DevView& v, const float* field, uint32_t pitch, uint32_t valid, const BlurTaps& x,
+                       const BlurTaps& y, float* tmp, double* partial, uint32_t* npartial, hipStream_t s);
 uint32_t blur_partials(const DevView& v, uint32_t pitch);
 bool gauss_lines_pay(const DevView& v, uint32_t m);
 hipError_t launch_gauss_lines(const DevView& v, bool all, uint32_t m, hipStream_t s);
@@ -159,9 +167,17 @@ hipError_t launch_gauss_delta_exact(const DevView& v, uint32_t kappa, hipStream_
 // into rows [H][W][chunk] (complex), then along y with |.|^2 summed over the
 // chunk into power [H][W] (added to)
 uint32_t spectrum_chunk();
-size_t spectrum_scratch_floats2(const DevView& v);
-hipError_t launch_spectrum_chunk(const DevView& v, const float* field, uint32_t pitch, uint32_t valid, uint32_t t0,
-                                 const float2* twx, const float2* twy, float2* rows, double* power, hipStream_t s);
+// chunks of `rows` integrand rows that one launch takes
+uint32_t spectrum_chunks(const DevView& v, uint32_t rows);
+// entries of the scratch buffers of such a launch
+struct SpectrumScratch {
+  size_t rows, power, matx, maty;
+};
+SpectrumScratch spectrum_scratch(const DevView& v, uint32_t chunks);
+hipError_t launch_twiddles(const float2* tw, uint32_t n, float2* mat, hipStream_t s);
+hipError_t launch_spectrum_chunks(const DevView& v, const float* field, uint32_t pitch, uint32_t valid, uint32_t t0,
+                                  uint32_t chunks, const float2* matx, const float2* maty, float2* rows, double* power,
+                                  double* sum, hipStream_t s);
 
 // device peak loops: kind 0 copy (buf -> buf2, size bytes), 1 dot2 chains,
 // 2 BF16 MFMA accumulations (iters iterations each); blocks workgroups of 256

@@ -23,6 +23,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <algorithm>
+
 #include "bnlat_dev.h"
 #include "device_common.h"
 
@@ -270,7 +272,12 @@ __global__ void k_points(DevView v, uint32_t pixel, uint32_t* out) {
 // pixels of a row, so every 16-byte tile load of a wave (8 integrands of 64
 // neighbouring pixels) is one contiguous 1 KiB run; per tile a lane's int32
 // partial sums (at most 12 offsets x 8 integrands x N^2 < 2^31) are widened
-// to 64 bits; atomics on integers only.
+// to 64 bits.  A workgroup takes 256 pixels and a share of the tiles (64-bit
+// atomics to one address follow one another, so each share has a row of sums
+// of its own modulo ENERGY_ROWS).  Bound by the L1s' reads of the neighbours'
+// tiles.  128^2, T = 1024, r = 3: 67 us; 498 with all tiles in one
+// workgroup per 256 pixels (64 of them), differences formed from unpacked
+// halves.
 template <int R>
 __global__ __launch_bounds__(256) void k_energy(DevView v, unsigned long long* ysum) {
   constexpr Window<R> W = WinConst<R>::w;
@@ -287,24 +294,21 @@ __global__ __launch_bounds__(256) void k_energy(DevView v, unsigned long long* y
 #pragma unroll
     for (int mm = 0; mm < W.M; ++mm)
       q[mm] = ((y + v.h + W.oy[mm]) % v.h) * v.w + (x + v.w + W.ox[mm]) % v.w;
-    for (uint32_t tt = 0; tt < (v.tp >> 3); ++tt) {
-      const uint4 cp = *(const uint4*)(v.cnt + ((size_t)tt * P + p) * 8);
-      const uint32_t pw[4] = {cp.x, cp.y, cp.z, cp.w};
+    for (uint32_t tt = blockIdx.y; tt < (v.tp >> 3); tt += gridDim.y) {
+      const u32x4 cp = *(const u32x4*)(v.cnt + ((size_t)tt * P + p) * 8);
       int part[NCLS];
 #pragma unroll
       for (int c = 0; c < NCLS; ++c) part[c] = 0;
 #pragma unroll
       for (int mm = 0; mm < W.M; ++mm) {
         if (!(W.oy[mm] > 0 || (W.oy[mm] == 0 && W.ox[mm] > 0))) continue;
-        const uint4 cq = *(const uint4*)(v.cnt + ((size_t)tt * P + q[mm]) * 8);
-        const uint32_t qw[4] = {cq.x, cq.y, cq.z, cq.w};
+        const u32x4 cq = *(const u32x4*)(v.cnt + ((size_t)tt * P + q[mm]) * 8);
         int a = part[W.cls[mm]];
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
-          const int d0 = (int)(pw[k] & 0xFFFFu) - (int)(qw[k] & 0xFFFFu);
-          const int d1 = (int)(pw[k] >> 16) - (int)(qw[k] >> 16);
-          const uint32_t dp = ((uint32_t)d0 & 0xFFFFu) | ((uint32_t)d1 << 16);
-          a = dot2(dp, dp, a);
+          uint32_t d;   // |halves| <= N (the compiler would take the halves apart)
+          asm("v_pk_sub_i16 %0, %1, %2" : "=v"(d) : "v"(cp[k]), "v"(cq[k]));
+          a = dot2(d, d, a);
         }
         part[W.cls[mm]] = a;
       }
@@ -317,63 +321,8 @@ __global__ __launch_bounds__(256) void k_energy(DevView v, unsigned long long* y
     long long s = yd[c];
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off);
-    if (lane == 0 && s) atomicAdd(&ysum[c], (unsigned long long)s);
+    if (lane == 0 && s) atomicAdd(&ysum[(blockIdx.y + 7 * blockIdx.x) % ENERGY_ROWS * NCLS + c], (unsigned long long)s);
   }
-}
-
-// ------------------------------------------------------------ blur criterion
-// Separable periodised Gaussian blur of an error tile (Sec. 3.3): taps
-// (d_i, k_i) with d_i in [0, W); b(x) = sum_i k_i e((x - d_i) mod W).  The
-// field is float [P][pitch] with `valid` meaningful columns.
-__global__ __launch_bounds__(256) void k_blur_x(DevView v, const float* __restrict__ field, uint32_t pitch,
-                                                const float* __restrict__ kx, const int32_t* __restrict__ dx,
-                                                uint32_t nk, float* __restrict__ out) {
-  const uint32_t lane = threadIdx.x & 63;
-  const uint32_t wave = wave_id();
-  const uint32_t nch = pitch >> 6;
-  const uint32_t p = wave / nch, ch = wave - p * nch;
-  if (p >= v.w * v.h) return;
-  const uint32_t y = p / v.w, x = p - y * v.w;
-  const uint32_t t = ch * 64 + lane;
-  const float* rowbase = field + (size_t)y * v.w * pitch + t;
-  float acc = 0.0f;
-  for (uint32_t i = 0; i < nk; ++i) {
-    uint32_t xs = x + v.w - (uint32_t)dx[i];
-    if (xs >= v.w) xs -= v.w;
-    acc = fmaf(kx[i], rowbase[(size_t)xs * pitch], acc);
-  }
-  out[(size_t)p * pitch + t] = acc;
-}
-
-__global__ __launch_bounds__(256) void k_blur_y_sq(DevView v, uint32_t pitch, uint32_t valid,
-                                                   const float* __restrict__ ky,
-                                                   const int32_t* __restrict__ dy, uint32_t nk,
-                                                   const float* __restrict__ in,
-                                                   double* __restrict__ partial) {
-  __shared__ double red[4];
-  const uint32_t lane = threadIdx.x & 63;
-  const uint32_t wave = wave_id();
-  const uint32_t nch = pitch >> 6;
-  // waves walk down one column (and 64-integrand chunk) at a time, so the
-  // waves in flight share the column's taps in L2
-  const uint32_t y = wave % v.h, rest = wave / v.h;
-  const uint32_t x = rest / nch, ch = rest - x * nch;
-  double sq = 0.0;
-  if (x < v.w) {
-    const uint32_t t = ch * 64 + lane;
-    float acc = 0.0f;
-    for (uint32_t i = 0; i < nk; ++i) {
-      uint32_t ys = y + v.h - (uint32_t)dy[i];
-      if (ys >= v.h) ys -= v.h;
-      acc = fmaf(ky[i], in[((size_t)ys * v.w + x) * pitch + t], acc);
-    }
-    if (t < valid) sq = (double)acc * (double)acc;
-  }
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) sq += __shfl_xor(sq, off);
-  if (lane == 0) red[threadIdx.x >> 6] = sq;
-  __syncthreads();
-  if (threadIdx.x == 0) partial[blockIdx.x] = (red[0] + red[1]) + (red[2] + red[3]);
 }
 
 // ----------------------------------------------------- Gaussian integrands
@@ -747,7 +696,9 @@ hipError_t launch_points(const DevView& v, uint32_t pixel, uint32_t* out, hipStr
 
 hipError_t launch_energy(const DevView& v, unsigned long long* y, hipStream_t s) {
   const uint32_t P = v.w * v.h;
-  const dim3 grid((P + 255) / 256), block(256);
+  // about eight workgroups per CU
+  const uint32_t gx = (P + 255) / 256, gy = std::max(1u, std::min(v.tp >> 3, 2048 / gx));
+  const dim3 grid(gx, gy), block(256);
   switch (v.radius) {
     case 1: hipLaunchKernelGGL(k_energy<1>, grid, block, 0, s, v, y); break;
     case 2: hipLaunchKernelGGL(k_energy<2>, grid, block, 0, s, v, y); break;
@@ -757,24 +708,6 @@ hipError_t launch_energy(const DevView& v, unsigned long long* y, hipStream_t s)
     case 6: hipLaunchKernelGGL(k_energy<6>, grid, block, 0, s, v, y); break;
     default: return hipErrorInvalidValue;
   }
-  return hipGetLastError();
-}
-
-uint32_t blur_partials(const DevView& v, uint32_t pitch) {
-  const uint64_t waves = (uint64_t)v.w * v.h * (pitch >> 6);
-  return (uint32_t)((waves + 3) / 4);
-}
-
-hipError_t launch_blur(const DevView& v, const float* field, uint32_t pitch, uint32_t valid, const float* kx,
-                       uint32_t nkx, const int32_t* dx, const float* ky, uint32_t nky, const int32_t* dy,
-                       float* tmp, double* partial, uint32_t* npartial, hipStream_t s) {
-  const uint32_t blocks = blur_partials(v, pitch);
-  hipLaunchKernelGGL(k_blur_x, dim3(blocks), dim3(256), 0, s, v, field, pitch, kx, dx, nkx, tmp);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_blur_y_sq, dim3(blocks), dim3(256), 0, s, v, pitch, valid, ky, dy, nky,
-                     (const float*)tmp, partial);
-  *npartial = blocks;
   return hipGetLastError();
 }
 
