@@ -244,6 +244,7 @@ struct bn_problem_s {
   // Swap mutation: permutation tables, pixel-major counts and pass scratch;
   // one captured sweep of K^2 passes.
   SwapView sv{};
+  bool counts_in_int7 = false;   // every |count - base| (bias8) is at most 63
   hipGraph_t swap_graph = nullptr;
   hipGraphExec_t swap_exec = nullptr;
   bool swap_failed = false;
@@ -752,18 +753,22 @@ bn_status setup_swap(bn_problem p) {
   int32_t* dcls_d;
   bn_status s;
   if ((s = p->alloc(&perm_d, P)) != BN_OK || (s = p->alloc(&pinv_d, P)) != BN_OK ||
-      (s = p->alloc(&dcls_d, dmax + 1)) != BN_OK || (s = p->alloc(&sv.xs, (size_t)p->v.ncls * M)) != BN_OK ||
-      (s = p->alloc(&sv.d2, M / 2)) != BN_OK || (s = p->alloc(&sv.row, (size_t)P * p->v.tp)) != BN_OK)
+      (s = p->alloc(&dcls_d, dmax + 1)) != BN_OK ||
+      (p->counts_in_int7 ? (s = p->alloc(&sv.field8, (size_t)P * p->v.tp)) != BN_OK ||
+                               (s = p->alloc(&sv.row8, (size_t)P * p->v.tp)) != BN_OK
+                         : (s = p->alloc(&sv.row, (size_t)P * p->v.tp)) != BN_OK))
     return s;
   sv.perm = perm_d;
   sv.pinv = pinv_d;
   sv.dcls = dcls_d;
   sv.m = M;
+  sv.slices = swap_slices(p->v, sv);
+  if ((s = p->alloc(&sv.xs, (size_t)sv.slices * p->v.ncls * M)) != BN_OK ||
+      (s = p->alloc(&sv.d2, (size_t)sv.slices * (M / 2))) != BN_OK)
+    return s;
   HIPCHK(hipMemcpyAsync(perm_d, perm.data(), (size_t)P * 4, hipMemcpyHostToDevice, p->stream));
   HIPCHK(hipMemcpyAsync(pinv_d, pinv.data(), (size_t)P * 4, hipMemcpyHostToDevice, p->stream));
   HIPCHK(hipMemcpyAsync(dcls_d, dcls.data(), dcls.size() * 4, hipMemcpyHostToDevice, p->stream));
-  HIPCHK(hipMemsetAsync(sv.xs, 0, (size_t)p->v.ncls * M * 8, p->stream));
-  HIPCHK(hipMemsetAsync(sv.d2, 0, (size_t)(M / 2) * 8, p->stream));
   HIPCHK(hipStreamSynchronize(p->stream));
   return BN_OK;
 }
@@ -1301,6 +1306,7 @@ bn_status bn_create_problem_ext(const bn_config* cfg, const bn_heaviside* heavis
   const uint32_t by_lines = count_deviation(v.n, g);
   const bool centred = v.n > 64 && by_lines && by_lines < dev;
   if (centred) dev = by_lines;
+  p->counts_in_int7 = dev <= 63;
   v.form = FIELD_WIDE;
   if (v.mfma == 0 && cfg->move == BN_REDRAW && (v.k == 1 || v.k == 2 || v.k == 4))
     v.form = dev <= 63 ? FIELD_NARROW : dev <= 126 && v.t <= 32768 ? FIELD_SPLIT : FIELD_WIDE;

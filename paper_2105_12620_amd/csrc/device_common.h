@@ -53,6 +53,31 @@ __device__ inline uint32_t wrap_add(uint32_t a, uint32_t b) {
 // S - 2^15 per component, as two int16.
 __device__ inline uint32_t centre(uint32_t s) { return s ^ 0x80008000u; }
 
+// 16 int8 deviations (bias: the bias8 words of their integrands) back as 16-bit
+// counts.
+__device__ __forceinline__ void widen8(const u32x4 d, const uint32_t* __restrict__ bias, uint4& lo, uint4& hi) {
+  uint32_t o[8];
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    const uint32_t x = d[k] ^ 0x80808080u;   // byte = count - base + 128
+    o[2 * k] = __builtin_amdgcn_perm(0u, x, 0x0C010C00u) - bias[2 * k];
+    o[2 * k + 1] = __builtin_amdgcn_perm(0u, x, 0x0C030C02u) - bias[2 * k + 1];
+  }
+  lo = make_uint4(o[0], o[1], o[2], o[3]);
+  hi = make_uint4(o[4], o[5], o[6], o[7]);
+}
+
+// 16 counts of two tiles as int8 deviations: per half count - base + 128 (no
+// borrow between the halves), then the low bytes, less 128.
+__device__ __forceinline__ u32x4 narrow8(const uint4 lo, const uint4 hi, const uint32_t* __restrict__ bias) {
+  const uint32_t c[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
+  u32x4 o;
+#pragma unroll
+  for (int k = 0; k < 4; ++k)
+    o[k] = __builtin_amdgcn_perm(c[2 * k + 1] + bias[2 * k + 1], c[2 * k] + bias[2 * k], 0x06040200u) ^ 0x80808080u;
+  return o;
+}
+
 // Element (row, t) of a tiled count buffer with `rows` rows.
 __device__ inline size_t tix(uint32_t row, uint32_t t, uint32_t rows) {
   return ((size_t)(t >> 3) * rows + row) * 8 + (t & 7);

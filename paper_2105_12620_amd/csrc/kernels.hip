@@ -134,19 +134,6 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 // 275 us per two sweeps).
 constexpr uint32_t COMMIT_WAVES = 16;
 
-// 16 proposal counts (narrow forms) back as 16-bit counts.
-__device__ __forceinline__ void widen8(const u32x4 d, const uint32_t* __restrict__ bias, uint4& lo, uint4& hi) {
-  uint32_t o[8];
-#pragma unroll
-  for (int k = 0; k < 4; ++k) {
-    const uint32_t x = d[k] ^ 0x80808080u;   // byte = count - base + 128
-    o[2 * k] = __builtin_amdgcn_perm(0u, x, 0x0C010C00u) - bias[2 * k];
-    o[2 * k + 1] = __builtin_amdgcn_perm(0u, x, 0x0C030C02u) - bias[2 * k + 1];
-  }
-  lo = make_uint4(o[0], o[1], o[2], o[3]);
-  hi = make_uint4(o[4], o[5], o[6], o[7]);
-}
-
 __device__ __forceinline__ void commit_body(const DevView& v, uint32_t kappa, uint32_t blk, bool advance) {
   const uint32_t lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const uint32_t j = blk * 64 + lane;

@@ -31,8 +31,9 @@ __device__ inline uint32_t swap_mask(const DevView& v, uint32_t kappa) {
 
 // LDS-staged member evaluation.  A workgroup owns a BW x BH block of tile
 // pixels; its pass members (pixels whose scrambled list position falls in the
-// pass) are listed in LDS.  For 16 integrands at a time (two 8-integrand count
-// planes, one stage) the counts of the block plus its window halo (region
+// pass) are listed in LDS.  For one stage at a time, two planes of 16-byte words
+// (8 integrands' counts, or 16 int8 deviations where every |count - base| is at
+// most 63: half the words, and v_dot4 in place of v_dot2), the counts of the block plus its window halo (region
 // RH x RW, row pitch RWP = RW + 1) and the two partner words of every member
 // are staged in LDS, and every member is served by a group of 16 lanes: lane
 // (i, p) forms dc = c_partner - c_own of plane p and, per step, reads one
@@ -55,17 +56,28 @@ __device__ inline uint32_t swap_mask(const DevView& v, uint32_t kappa) {
 // follows the last reads of it.
 //
 // A lane accumulates its product of each step separately (int32 per step);
-// when the member's integrand slice is done, the steps' sums are gathered
-// into distance classes (the lane's offset of a step fixes the class),
-// reduced over the group and added to HBM with exact int64 atomics, member
-// by member in a contiguous row of classes.  The workgroups are renumbered
+// when the member's integrand slice is done, the steps' sums are added into
+// distance classes (the lane's offset of a step fixes the class) by 64-bit
+// atomics in LDS and stored, a row of classes per member and slice; the
+// decision adds the slices.  (Gathering the classes in registers took 2200
+// instructions a round, more than half of the narrow form's stages, and 64-bit
+// atomics of the slices into one row go to memory on this part.)  The workgroups are renumbered
 // per XCD (xcd_block), so that the blocks one L2 serves at a time are whole
 // rows of blocks of one integrand slice and their halos are read from HBM
 // once.
 //
 // Integrand slices of the tile run in separate workgroups; per-lane int32
 // step sums stay below 2^31 because the host bounds a slice to S stages with
-// S * 8 N^2 < 2^31 (eight products of at most N^2 per lane and stage).
+// S * 8 N^2 < 2^31 (eight products of at most N^2 per lane and stage; sixteen of
+// at most 126^2 in the int8 form).
+//
+// 256^2, N = 256, T = 1024, r = 4, K = 2: 47 us per pass (86 on counts with the
+// classes gathered in registers), bound by the region's reads through the L2s
+// (2.5 times the tile); blocks of 32 x 16 pixels leave one workgroup per CU and
+// took 1.15 (1024 threads) to 1.7 times as long per sweep.
+
+// integrands of a stage
+constexpr uint32_t SWAP_STAGE(bool narrow) { return narrow ? 32 : 16; }
 
 template <int R>
 struct SwapGeom {
@@ -118,7 +130,7 @@ __device__ inline bool swap_step_offset(int st, int i, int& ox, int& oy) {
   return oy <= R;
 }
 
-template <int R>
+template <int R, bool NARROW>
 __global__ __launch_bounds__(SwapGeom<R>::NT, (R <= 4) ? 4 : 2) void k_swap_stage(DevView v, SwapView sv, uint32_t kappa,
                                                                     uint32_t slen, uint32_t gx, uint32_t gy) {
   using G = SwapGeom<R>;
@@ -195,19 +207,23 @@ __global__ __launch_bounds__(SwapGeom<R>::NT, (R <= 4) ? 4 : 2) void k_swap_stag
       lsrc[k] = 0;
     }
   }
-  const uint32_t tp8 = v.tp >> 3;
-  auto issue = [&](uint32_t t0, uint32_t buf) {
-    const u32x4* cs = (const u32x4*)(v.cnt + (size_t)(t0 >> 3) * P * 8);
-    const u32x4* rs = (const u32x4*)sv.row + (t0 >> 3);
+  // words of a pixel's row; a stage is two planes of words in either form
+  const uint32_t rowq = v.tp >> (NARROW ? 4 : 3);
+  const u32x4* field = NARROW ? (const u32x4*)sv.field8 : (const u32x4*)v.cnt;
+  const u32x4* rowsq = NARROW ? (const u32x4*)sv.row8 : (const u32x4*)sv.row;
+  auto issue = [&](uint32_t st, uint32_t buf) {
+    const u32x4* cs = field + (size_t)(2 * st) * P;
+    const u32x4* rs = rowsq + 2 * st;
 #pragma unroll
     for (int k = 0; k < G::D; ++k) {
-      const u32x4* src = ldst[k] < 2u * G::PLANE ? cs + lsrc[k] : rs + (size_t)(lsrc[k] >> 1) * tp8 + (lsrc[k] & 1);
+      const u32x4* src = ldst[k] < 2u * G::PLANE ? cs + lsrc[k] : rs + (size_t)(lsrc[k] >> 1) * rowq + (lsrc[k] & 1);
       __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)src,
                                        (__attribute__((address_space(3))) void*)(lds4 + buf * G::SBUF + ldst[k]),
                                        16, 0, 0);
     }
   };
 
+  auto dot = [](uint32_t a, uint32_t b, int c) { return NARROW ? dot4(a, b, c) : dot2(a, b, c); };
   const uint32_t grp = tid / G::GL, li = tid & 7, lp = (tid >> 3) & 1;
   // word of the lane's slot relative to the member's own word of plane lp:
   // row steps, column steps, a column's last step (lanes past the window
@@ -218,8 +234,8 @@ __global__ __launch_bounds__(SwapGeom<R>::NT, (R <= 4) ? 4 : 2) void k_swap_stag
   // offset, and the partner word of the group's first slot
   const uint32_t rof = lr - (R * G::RWP + R), cof = lc - (R * G::RWP + R - G::RC),
                  clof = lcl - (R * G::RWP + R - G::RC), pe0 = 2 * G::PLANE + 2 * grp + lp;
-  const uint32_t t_begin = bz * slen, t_end = min(t_begin + slen, v.tp);
-  const uint32_t nst = t_end > t_begin ? (t_end - t_begin) / 16 : 0;
+  const uint32_t st0 = bz * slen, st1 = min(st0 + slen, v.tp / SWAP_STAGE(NARROW));
+  const uint32_t nst = st1 > st0 ? st1 - st0 : 0;
   __syncthreads();
   for (uint32_t base = 0; base < nm; base += G::CAP) {
     // this round's partner pixels
@@ -254,7 +270,7 @@ __global__ __launch_bounds__(SwapGeom<R>::NT, (R <= 4) ? 4 : 2) void k_swap_stag
     barrier_vm<0>();
 #pragma unroll
     for (int k = 0; k < G::PD; ++k)
-      if ((uint32_t)k < nst) issue(t_begin + 16 * k, k);
+      if ((uint32_t)k < nst) issue(st0 + k, k);
     for (uint32_t si = 0; si < nst; ++si) {
       // stage si has landed once at most the loads of the stages issued
       // after it (up to PD - 1 of them) are in flight
@@ -262,7 +278,7 @@ __global__ __launch_bounds__(SwapGeom<R>::NT, (R <= 4) ? 4 : 2) void k_swap_stag
       if (G::PD >= 3 && ahead == 2) barrier_vm<2 * G::D>();
       else if (G::PD >= 2 && ahead == 1) barrier_vm<G::D>();
       else barrier_vm<0>();
-      if (si + G::PD < nst) issue(t_begin + 16 * (si + G::PD), (si + G::PD) % G::NBUF);
+      if (si + G::PD < nst) issue(st0 + si + G::PD, (si + G::PD) % G::NBUF);
       const u32x4* bf = lds4 + (si % G::NBUF) * G::SBUF;
 #pragma unroll
       for (int s = 0; s < G::SLOTS; ++s) {
@@ -271,13 +287,14 @@ __global__ __launch_bounds__(SwapGeom<R>::NT, (R <= 4) ? 4 : 2) void k_swap_stag
           uint32_t dl[4];
 #pragma unroll
           for (int h = 0; h < 4; ++h) {
-            // per int16 half: partner minus own count (|dc| <= N, no wrap); the
-            // words go through scalars (a bit cast straight from the vector
-            // element read only the first word)
+            // partner minus own, per int16 half (|dc| <= N, no wrap) or per
+            // byte (|dc| <= 126); the words go through scalars (a bit cast
+            // straight from the vector element read only the first word)
             const uint32_t pw_h = pc[h], ow_h = own[h];
-            dl[h] = __builtin_bit_cast(uint32_t, (v2i16)(__builtin_bit_cast(v2i16, pw_h) -
-                                                         __builtin_bit_cast(v2i16, ow_h)));
-            dd[s] = dot2(dl[h], dl[h], dd[s]);
+            dl[h] = NARROW ? sub_bytes(pw_h, ow_h)
+                           : __builtin_bit_cast(uint32_t, (v2i16)(__builtin_bit_cast(v2i16, pw_h) -
+                                                                  __builtin_bit_cast(v2i16, ow_h)));
+            dd[s] = dot(dl[h], dl[h], dd[s]);
           }
           const u32x4* rp = bf + (sp[s] + rof);
           const u32x4* cp = bf + (sp[s] + cof);
@@ -292,75 +309,64 @@ __global__ __launch_bounds__(SwapGeom<R>::NT, (R <= 4) ? 4 : 2) void k_swap_stag
               c = (part < G::CH - 1 ? cp : clp)[col + 8 * part * G::RWP];
             }
             int a = acc[s][st];
-            a = dot2(dl[0], c[0], a);
-            a = dot2(dl[1], c[1], a);
-            a = dot2(dl[2], c[2], a);
-            acc[s][st] = dot2(dl[3], c[3], a);
+            a = dot(dl[0], c[0], a);
+            a = dot(dl[1], c[1], a);
+            a = dot(dl[2], c[2], a);
+            acc[s][st] = dot(dl[3], c[3], a);
           }
         }
       }
     }
-    // gather each member's step sums into classes, reduce over the group's
-    // 16 lanes and add them to HBM
+    // the members' step sums, by class, in the ring's LDS; d2 last
+    barrier_vm<0>();
+    unsigned long long* sums = (unsigned long long*)lds4;
+    constexpr uint32_t ROW = NCLS + 1;
+    static_assert(8 * G::CAP * ROW <= 16 * G::NBUF * G::SBUF, "class sums exceed the ring");
+    for (uint32_t e = tid; e < G::CAP * ROW; e += G::NT) sums[e] = 0;
+    __syncthreads();
 #pragma unroll
     for (int s = 0; s < G::SLOTS; ++s) {
       if (!ok[s]) continue;
-      long long cl[NCLS];
-#pragma unroll
-      for (int c = 0; c < NCLS; ++c) cl[c] = 0;
+      unsigned long long* to = sums + (grp + G::GROUPS * s) * ROW;
 #pragma unroll
       for (int st = 0; st < G::STEPS; ++st) {
         const int c = ctab[st * 8 + li];
-#pragma unroll
-        for (int cc = 0; cc < NCLS; ++cc) cl[cc] += (c == cc) ? (long long)acc[s][st] : 0ll;
-      }
-#pragma unroll
-      for (int c = 0; c < NCLS; ++c) {
-#pragma unroll
-        for (int off = 1; off < G::GL; off <<= 1) cl[c] += __shfl_xor(cl[c], off);
+        if (c >= 0) atomicAdd(&to[c], (unsigned long long)(long long)acc[s][st]);
       }
       // dc^2 of plane lp is the same in the group's eight slots
-      long long d = li == 0 ? (long long)dd[s] : 0ll;
-#pragma unroll
-      for (int off = 1; off < G::GL; off <<= 1) d += __shfl_xor(d, off);
-      const uint32_t js = mj[base + grp + G::GROUPS * s];
-      const uint32_t l16 = tid & 15;
-#pragma unroll
-      for (int c0 = 0; c0 < NCLS; c0 += G::GL) {
-        const uint32_t c = c0 + l16;
-        long long x = 0;
-#pragma unroll
-        for (int cc = c0; cc < c0 + G::GL && cc < NCLS; ++cc) x = (c == (uint32_t)cc) ? cl[cc] : x;
-        if (c < (uint32_t)NCLS && x)
-          atomicAdd((unsigned long long*)&sv.xs[(size_t)js * NCLS + c], (unsigned long long)(-2 * x));
-      }
-      if (l16 == 0 && !(js & 1u) && d) atomicAdd((unsigned long long*)&sv.d2[js >> 1], (unsigned long long)d);
+      if (li == 0) atomicAdd(&to[NCLS], (unsigned long long)(long long)dd[s]);
+    }
+    __syncthreads();
+    const uint32_t mr = min(nm - base, (uint32_t)G::CAP);
+    for (uint32_t e = tid; e < mr * ROW; e += G::NT) {
+      const uint32_t m = e / ROW, c = e - m * ROW, js = mj[base + m];
+      const long long x = (long long)sums[e];
+      if (c < (uint32_t)NCLS) sv.xs[((size_t)bz * sv.m + js) * NCLS + c] = -2 * x;
+      else if (!(js & 1u)) sv.d2[(size_t)bz * (sv.m >> 1) + (js >> 1)] = x;
     }
   }
 }
 
-// Decision of couple i: add the two members' class sums and the pair
-// correction, take the FP64 weighted sum in increasing d and decide; the sums
-// are cleared for the next pass (all of a couple's sums are loaded before any
-// is cleared, so the loads are in flight together).  Writes delta, accept and
-// the couple's pixels (u_new); returns the decision and the pixels.
+// Decision of couple i by one wave: add the slices' class sums of the two
+// members (lane c + 32 m: class c of member m) and the pair correction, take the
+// FP64 weighted sum in increasing d and decide.  Writes delta, accept and the
+// couple's pixels (u_new); returns the decision and the pixels.
 template <int R>
 __device__ __forceinline__ bool swap_decide(const DevView& v, const SwapView& sv, uint32_t kappa, uint32_t i,
-                                            uint32_t& a, uint32_t& b) {
+                                            uint32_t lane, uint32_t& a, uint32_t& b) {
   constexpr int NCLS = WinConst<R>::NCLS;
+  static_assert(NCLS <= 32, "a lane per class and member");
   const uint32_t mask = swap_mask(v, kappa);
   const uint32_t L = kappa * sv.m + 2 * i;
-  a = sv.perm[L] ^ mask;
-  b = sv.perm[L + 1] ^ mask;
-  long long* xp = sv.xs + (size_t)2 * i * NCLS;
-  long long x[NCLS];
-#pragma unroll
-  for (int c = 0; c < NCLS; ++c) x[c] = xp[c] + xp[NCLS + c];
-  const long long d2 = sv.d2[i];
-  // the rows of the two members: 2 NCLS int64, 16-byte aligned
-#pragma unroll
-  for (int c = 0; c < NCLS; ++c) ((uint4*)xp)[c] = make_uint4(0u, 0u, 0u, 0u);
-  sv.d2[i] = 0;
+  a = __builtin_amdgcn_readfirstlane(sv.perm[L] ^ mask);
+  b = __builtin_amdgcn_readfirstlane(sv.perm[L + 1] ^ mask);
+  const int c = (int)(lane & 31);
+  long long x = 0, d2 = 0;
+  for (uint32_t z = 0; z < sv.slices; ++z) {
+    if (c < NCLS) x += sv.xs[((size_t)z * sv.m + 2 * i + (lane >> 5)) * NCLS + c];
+    d2 += sv.d2[(size_t)z * (sv.m >> 1) + i];
+  }
+  x += __shfl_xor(x, 32);
   // offsets o with a + o = b on the torus: o = d or d - W per axis with
   // d = (b - a) mod W (two per axis at most because r < min(W, H)); W and H
   // are powers of two
@@ -373,21 +379,25 @@ __device__ __forceinline__ bool swap_decide(const DevView& v, const SwapView& sv
     for (int kx = 0; kx < 2; ++kx) {
       const int ox = cx[kx], oy = cy[ky];
       if (ox < -R || ox > R || oy < -R || oy > R || (ox == 0 && oy == 0)) continue;
-      const int cl = sv.dcls[ox * ox + oy * oy];
-#pragma unroll
-      for (int c = 0; c < NCLS; ++c) x[c] += (c == cl) ? 2 * d2 : 0ll;
+      if (c == sv.dcls[ox * ox + oy * oy]) x += 2 * d2;
     }
   }
+  const double term = c < NCLS ? __dmul_rn(v.wd[c], (double)x) : 0.0;
+  const uint2 t = __builtin_bit_cast(uint2, term);
   double acc = 0.0;
 #pragma unroll
-  for (int c = 0; c < NCLS; ++c) acc = __dadd_rn(acc, __dmul_rn(v.wd[c], (double)x[c]));
+  for (int k = 0; k < NCLS; ++k)
+    acc = __dadd_rn(acc, __builtin_bit_cast(double, make_uint2(__builtin_amdgcn_readlane(t.x, k),
+                                                              __builtin_amdgcn_readlane(t.y, k))));
   const double total = __dmul_rn(acc, 2.0 / ((double)v.n * (double)v.n));
   const bool ok = (v.objective > 0) ? (total < 0.0) : (total > 0.0);
-  v.delta[i] = total;
-  v.accept[i] = ok;
-  v.u_new[2 * i] = a;
-  v.u_new[2 * i + 1] = b;
-  return ok;
+  if (lane == 0) {
+    v.delta[i] = total;
+    v.accept[i] = ok;
+    v.u_new[2 * i] = a;
+    v.u_new[2 * i + 1] = b;
+  }
+  return __builtin_amdgcn_readfirstlane(ok ? 1u : 0u) != 0;
 }
 
 // Exchange of an accepted couple's offsets and count tiles by one wave: the
@@ -399,9 +409,27 @@ __device__ __forceinline__ void swap_exchange(const DevView& v, const SwapView& 
     const uint32_t ua = v.U[a], ub = v.U[b];
     v.U[a] = ub;
     v.U[b] = ua;
-    atomicAdd(&v.ctr[1], 1ull);
   }
   const uint32_t P = v.w * v.h;
+  if (sv.row8) {
+    u32x4* wa = (u32x4*)(sv.row8 + (size_t)a * v.tp);
+    u32x4* wb = (u32x4*)(sv.row8 + (size_t)b * v.tp);
+    for (uint32_t tt = lane; tt < (v.tp >> 4); tt += 64) {
+      const u32x4 qa = wa[tt], qb = wb[tt];
+      wa[tt] = qb;
+      wb[tt] = qa;
+      *(u32x4*)(sv.field8 + ((size_t)tt * P + a) * 16) = qb;
+      *(u32x4*)(sv.field8 + ((size_t)tt * P + b) * 16) = qa;
+      uint4 lo, hi;
+      widen8(qb, v.bias8 + 8 * tt, lo, hi);
+      *(uint4*)(v.cnt + ((size_t)(2 * tt) * P + a) * 8) = lo;
+      *(uint4*)(v.cnt + ((size_t)(2 * tt + 1) * P + a) * 8) = hi;
+      widen8(qa, v.bias8 + 8 * tt, lo, hi);
+      *(uint4*)(v.cnt + ((size_t)(2 * tt) * P + b) * 8) = lo;
+      *(uint4*)(v.cnt + ((size_t)(2 * tt + 1) * P + b) * 8) = hi;
+    }
+    return;
+  }
   uint4* wa = (uint4*)(sv.row + (size_t)a * v.tp);
   uint4* wb = (uint4*)(sv.row + (size_t)b * v.tp);
   for (uint32_t tt = lane; tt < (v.tp >> 3); tt += 64) {
@@ -413,38 +441,65 @@ __device__ __forceinline__ void swap_exchange(const DevView& v, const SwapView& 
   }
 }
 
-// One thread per couple: the decision alone (the phase-stepping calls).
+// One wave per couple: the decision alone (the phase-stepping calls).
 template <int R>
-__global__ __launch_bounds__(128) void k_swap_finish(DevView v, SwapView sv, uint32_t kappa) {
-  const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
+__global__ __launch_bounds__(256) void k_swap_finish(DevView v, SwapView sv, uint32_t kappa) {
+  const uint32_t i = wave_id();
   if (i >= (sv.m >> 1)) return;
   uint32_t a, b;
-  (void)swap_decide<R>(v, sv, kappa, i, a, b);
+  (void)swap_decide<R>(v, sv, kappa, i, threadIdx.x & 63, a, b);
 }
 
 // One wave per couple: decision and, if accepted, the exchange (the sweeps:
 // one launch less per pass, and no round trip of the decision through HBM).
-// Lane 0 decides; the wave then exchanges the couple.
+// The accepted couples are counted by workgroup: a 64-bit atomic goes to memory,
+// and one per couple took 4 of the launch's 17 us at 256^2 (13 now, bound by the
+// latency of its dependent loads).
+constexpr uint32_t EXCHANGE_WAVES = 16;
+
+__device__ __forceinline__ void count_accept(const DevView& v, uint32_t* n, bool ok, uint32_t lane) {
+  if (ok && lane == 0) atomicAdd(n, 1u);
+  __syncthreads();
+  if (threadIdx.x == 0 && *n) atomicAdd(&v.ctr[1], (unsigned long long)*n);
+}
+
 template <int R>
-__global__ __launch_bounds__(256) void k_swap_decide_exchange(DevView v, SwapView sv, uint32_t kappa) {
+__global__ __launch_bounds__(64 * EXCHANGE_WAVES) void k_swap_decide_exchange(DevView v, SwapView sv, uint32_t kappa) {
+  __shared__ uint32_t n;
   const uint32_t lane = threadIdx.x & 63;
   const uint32_t i = wave_id();
-  if (i >= (sv.m >> 1)) return;
-  uint32_t a = 0, b = 0, ok = 0;
-  if (lane == 0) ok = swap_decide<R>(v, sv, kappa, i, a, b) ? 1u : 0u;
-  ok = __builtin_amdgcn_readfirstlane(ok);
-  if (!ok) return;
-  a = __builtin_amdgcn_readfirstlane(a);
-  b = __builtin_amdgcn_readfirstlane(b);
-  swap_exchange(v, sv, a, b, lane);
+  if (threadIdx.x == 0) n = 0;
+  __syncthreads();
+  uint32_t a = 0, b = 0;
+  const bool ok = i < (sv.m >> 1) && swap_decide<R>(v, sv, kappa, i, lane, a, b);
+  if (ok) swap_exchange(v, sv, a, b, lane);
+  count_accept(v, &n, ok, lane);
 }
 
 // One wave per accepted couple: exchange offsets and count tiles.
-__global__ __launch_bounds__(256) void k_swap_commit(DevView v, SwapView sv) {
+__global__ __launch_bounds__(64 * EXCHANGE_WAVES) void k_swap_commit(DevView v, SwapView sv) {
+  __shared__ uint32_t n;
   const uint32_t lane = threadIdx.x & 63;
   const uint32_t i = wave_id();
-  if (i >= (sv.m >> 1) || !v.accept[i]) return;
-  swap_exchange(v, sv, v.u_new[2 * i], v.u_new[2 * i + 1], lane);
+  if (threadIdx.x == 0) n = 0;
+  __syncthreads();
+  const bool ok = i < (sv.m >> 1) && v.accept[i];
+  if (ok) swap_exchange(v, sv, v.u_new[2 * i], v.u_new[2 * i + 1], lane);
+  count_accept(v, &n, ok, lane);
+}
+
+// int8 deviations from the tiled counts, tiled and pixel-major: thread per
+// (pixel, 16-integrand tile), pixels fastest, so that the tiled accesses are
+// coalesced.
+__global__ __launch_bounds__(256) void k_swap_rows8(DevView v, SwapView sv) {
+  const uint32_t P = v.w * v.h;
+  const uint64_t i = (uint64_t)blockIdx.x * 256 + threadIdx.x;
+  if (i >= (uint64_t)P * (v.tp >> 4)) return;
+  const uint32_t tt = (uint32_t)(i / P), p = (uint32_t)(i - (uint64_t)tt * P);
+  const u32x4 d = narrow8(*(const uint4*)(v.cnt + ((size_t)(2 * tt) * P + p) * 8),
+                          *(const uint4*)(v.cnt + ((size_t)(2 * tt + 1) * P + p) * 8), v.bias8 + 8 * tt);
+  *(u32x4*)(sv.field8 + ((size_t)tt * P + p) * 16) = d;
+  *((u32x4*)(sv.row8 + (size_t)p * v.tp) + tt) = d;
 }
 
 // Pixel-major copy of the tiled counts: thread per (pixel, 8-integrand tile),
@@ -466,7 +521,10 @@ hipError_t prepare_swap_kernels() {
     hipError_t e = hipSuccess;
 #define BN_SWAP_ATTR(RR)                                                                               \
   if (e == hipSuccess)                                                                                 \
-    e = hipFuncSetAttribute((const void*)k_swap_stage<RR>, hipFuncAttributeMaxDynamicSharedMemorySize, \
+    e = hipFuncSetAttribute((const void*)k_swap_stage<RR, false>, hipFuncAttributeMaxDynamicSharedMemorySize, \
+                            (int)SwapGeom<RR>::LDS_BYTES);                                             \
+  if (e == hipSuccess)                                                                                 \
+    e = hipFuncSetAttribute((const void*)k_swap_stage<RR, true>, hipFuncAttributeMaxDynamicSharedMemorySize, \
                             (int)SwapGeom<RR>::LDS_BYTES);
     BN_SWAP_ATTR(1)
     BN_SWAP_ATTR(2)
@@ -484,23 +542,47 @@ hipError_t prepare_swap_kernels() {
 // 256 CUs, and few enough stages per slice that every per-lane int32 step sum
 // stays below 2^31.
 template <int R>
+uint32_t stages_per_slice(const DevView& v, const SwapView& sv) {
+  using G = SwapGeom<R>;
+  const uint32_t blocks = ((v.w + G::BW - 1) / G::BW) * ((v.h + G::BH - 1) / G::BH);
+  const uint32_t stages = v.tp / SWAP_STAGE(sv.row8 != nullptr);
+  // products per lane and stage, and their bound
+  const double per_stage = sv.row8 ? 16.0 * 126.0 * 126.0 : 8.0 * (double)v.n * v.n;
+  const uint32_t smax = (uint32_t)std::max(1.0, std::floor(2147483647.0 / per_stage));
+  const uint32_t target = 262144 / G::NT;
+  const uint32_t nz = std::max<uint32_t>(1, std::min<uint32_t>(stages, (target + blocks - 1) / blocks));
+  return std::min((stages + nz - 1) / nz, smax);
+}
+
+template <int R>
+uint32_t slices(const DevView& v, const SwapView& sv) {
+  const uint32_t stages = v.tp / SWAP_STAGE(sv.row8 != nullptr), per = stages_per_slice<R>(v, sv);
+  return (stages + per - 1) / per;
+}
+
+uint32_t swap_slices(const DevView& v, const SwapView& sv) {
+  switch (v.radius) {
+    case 1: return slices<1>(v, sv);
+    case 2: return slices<2>(v, sv);
+    case 3: return slices<3>(v, sv);
+    case 4: return slices<4>(v, sv);
+    case 5: return slices<5>(v, sv);
+    default: return slices<6>(v, sv);
+  }
+}
+
+template <int R>
 hipError_t swap_stage_launch(const DevView& v, const SwapView& sv, uint32_t kappa, hipStream_t s, bool decide) {
   using G = SwapGeom<R>;
-  const uint32_t gx = (v.w + G::BW - 1) / G::BW, gy = (v.h + G::BH - 1) / G::BH, chunks = v.tp / 16;
-  const double n2 = (double)v.n * v.n;
-  const uint32_t smax = (uint32_t)std::max(1.0, std::floor(2147483647.0 / (8.0 * n2)));
-  // about 1024 threads per CU of 256 CUs
-  const uint32_t target = 262144 / G::NT;
-  uint32_t nz = std::max<uint32_t>(1, std::min<uint32_t>(chunks, (target + gx * gy - 1) / (gx * gy)));
-  uint32_t per = (chunks + nz - 1) / nz;
-  if (per > smax) per = smax;
-  nz = (chunks + per - 1) / per;
-  hipLaunchKernelGGL(k_swap_stage<R>, dim3(gx * gy * nz), dim3(G::NT), (size_t)G::LDS_BYTES, s, v, sv, kappa,
-                     per * 16, gx, gy);
+  const uint32_t gx = (v.w + G::BW - 1) / G::BW, gy = (v.h + G::BH - 1) / G::BH, per = stages_per_slice<R>(v, sv);
+  const dim3 grid(gx * gy * sv.slices), block(G::NT);
+  if (sv.row8)
+    hipLaunchKernelGGL((k_swap_stage<R, true>), grid, block, (size_t)G::LDS_BYTES, s, v, sv, kappa, per, gx, gy);
+  else
+    hipLaunchKernelGGL((k_swap_stage<R, false>), grid, block, (size_t)G::LDS_BYTES, s, v, sv, kappa, per, gx, gy);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || !decide) return e;
-  const uint32_t half = sv.m >> 1;
-  hipLaunchKernelGGL(k_swap_finish<R>, dim3((half + 127) / 128), dim3(128), 0, s, v, sv, kappa);
+  hipLaunchKernelGGL(k_swap_finish<R>, dim3(((sv.m >> 1) + 3) / 4), dim3(256), 0, s, v, sv, kappa);
   return hipGetLastError();
 }
 
@@ -517,7 +599,7 @@ hipError_t launch_swap_evaluate(const DevView& v, const SwapView& sv, uint32_t k
 }
 
 hipError_t launch_swap_decide_exchange(const DevView& v, const SwapView& sv, uint32_t kappa, hipStream_t s) {
-  const dim3 g(((sv.m >> 1) + 3) / 4), b(256);
+  const dim3 g(((sv.m >> 1) + EXCHANGE_WAVES - 1) / EXCHANGE_WAVES), b(64 * EXCHANGE_WAVES);
   switch (v.radius) {
     case 1: hipLaunchKernelGGL(k_swap_decide_exchange<1>, g, b, 0, s, v, sv, kappa); break;
     case 2: hipLaunchKernelGGL(k_swap_decide_exchange<2>, g, b, 0, s, v, sv, kappa); break;
@@ -531,14 +613,16 @@ hipError_t launch_swap_decide_exchange(const DevView& v, const SwapView& sv, uin
 }
 
 hipError_t launch_swap_rows(const DevView& v, const SwapView& sv, hipStream_t s) {
-  const uint64_t n = (uint64_t)v.w * v.h * (v.tp >> 3);
-  hipLaunchKernelGGL(k_swap_rows, dim3((uint32_t)((n + 255) / 256)), dim3(256), 0, s, v, sv);
+  const uint64_t n = (uint64_t)v.w * v.h * (v.tp >> (sv.row8 ? 4 : 3));
+  if (sv.row8) hipLaunchKernelGGL(k_swap_rows8, dim3((uint32_t)((n + 255) / 256)), dim3(256), 0, s, v, sv);
+  else hipLaunchKernelGGL(k_swap_rows, dim3((uint32_t)((n + 255) / 256)), dim3(256), 0, s, v, sv);
   return hipGetLastError();
 }
 
 hipError_t launch_swap_commit(const DevView& v, const SwapView& sv, hipStream_t s) {
   const uint32_t half = sv.m >> 1;
-  hipLaunchKernelGGL(k_swap_commit, dim3((half + 3) / 4), dim3(256), 0, s, v, sv);
+  hipLaunchKernelGGL(k_swap_commit, dim3((half + EXCHANGE_WAVES - 1) / EXCHANGE_WAVES), dim3(64 * EXCHANGE_WAVES), 0, s, v,
+                     sv);
   return hipGetLastError();
 }
 

@@ -18,12 +18,15 @@ constexpr uint32_t S_SWAP = 0xF;   // XOR masks of the passes
 struct SwapView {
   const uint32_t* perm;   // [P] pixel at list position L
   const uint32_t* pinv;   // [P] list position of pixel p
-  long long* xs;          // [ncls][M] integer class sums of each couple member's move (zero between passes)
-  long long* d2;          // [M/2] sum_t (c_a,t - c_b,t)^2 of each couple (zero between passes)
+  long long* xs;          // [slices][M][ncls] integer class sums of each couple member's move
+  long long* d2;          // [slices][M/2] sum_t (c_a,t - c_b,t)^2 of each couple
   const int32_t* dcls;    // [2 r^2 + 1] class index of a squared distance (-1: none)
   uint16_t* row;          // [P][Tp] pixel-major copy of the hit counts: a couple's partner counts
                           // are read whole lines at a time (kept in step by the exchanges)
+  int8_t* field8;         // [Tp/16][P][16] and [P][Tp]: the same as int8 deviations from the
+  int8_t* row8;           // integrands' bases (bias8), in place of row where |c - base| <= 63
   uint32_t m;             // list positions per pass
+  uint32_t slices;        // integrand slices of a pass's workgroups (swap_slices)
 };
 
 // Pass kappa of the sweep in the device counter: evaluate every couple
@@ -31,6 +34,8 @@ struct SwapView {
 // exchange the accepted couples' offsets and count tiles.
 // Once per process, before the first swap launch (not under stream capture).
 hipError_t prepare_swap_kernels();
+// the slices of v's passes, from row8 (set or null)
+uint32_t swap_slices(const DevView& v, const SwapView& sv);
 // class sums of the pass's couples (and, with decide, their decisions)
 hipError_t launch_swap_evaluate(const DevView& v, const SwapView& sv, uint32_t kappa, hipStream_t s,
                                 bool decide = true);
