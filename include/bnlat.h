@@ -67,9 +67,11 @@ typedef enum {
  *          from a BF16 copy of the error field kept in device memory; the
  *          self term W sum_t d_t (e'_t + e_t) stays in full precision.
  *          - N <= 256 with Heaviside rows only: the operands are the hit
- *            counts and their changes, exact in BF16, and a slice whose
- *            partial sums stay below 2^24 is exact; decisions equal BN_FP32's
- *            (uncertified accepted moves are re-checked exactly).
+ *            counts and their changes, as int8 deviations where those are
+ *            known to fit (BN_FP32's phases: exact), else exact in BF16, and
+ *            a slice whose partial sums stay below 2^24 is exact; decisions
+ *            equal BN_FP32's (uncertified accepted moves are re-checked
+ *            exactly).
  *          - otherwise: the operands are e = c/N - A (g - I for Gaussians)
  *            formed in FP32 and rounded to BF16, and d rounded to BF16: an
  *            approximate energy change.  Every move it accepts is
