@@ -231,6 +231,7 @@ struct bn_problem_s {
     uint32_t* un = nullptr;
     float* gn = nullptr;
   } sets[2];
+  uint8_t* accepts = nullptr;   // the sweep's decisions where its moves wait (moves_wait)
   bool sets_ready = false;
   uint64_t prefetched = ~0ull;
   hipStream_t aux = nullptr;
@@ -311,7 +312,8 @@ struct bn_batch_s {
   hipStream_t stream = nullptr;
   uint32_t colour_k = 0;
   std::vector<BatchGroup> count_groups, stage_groups;
-  BatchGroup commit_all;
+  BatchGroup commit_all;                   // every grouped member; of them, by when their
+  BatchGroup commit_phase, commit_sweep;   // moves are committed (moves_wait)
   // members outside the grouped FP32 redraw launches (BF16, Gaussian rows or
   // swap moves): their own overlapped sweeps are recorded into the same graph
   std::vector<uint32_t> solo;
@@ -517,6 +519,11 @@ DevView phase_view(bn_problem p, int b, uint32_t kappa) {
   v.n8 = p->sets[b].n8 ? p->sets[b].n8 + first : nullptr;
   v.u_new = p->sets[b].un + (size_t)kappa * v.pc;
   if (v.tgp) v.g_new = p->sets[b].gn + (size_t)kappa * v.pc * v.tgp;
+  if (moves_wait(v)) {
+    v.decided = kappa;
+    v.accepts = p->accepts;
+    v.n8_sweep = p->sets[b].n8;
+  }
   return v;
 }
 
@@ -525,6 +532,7 @@ DevView sweep_view(bn_problem p, int b) {
   v.c_new = p->sets[b].cn;
   v.n8 = p->sets[b].n8;
   v.u_new = p->sets[b].un;
+  v.accepts = p->accepts;
   if (v.tgp) v.g_new = p->sets[b].gn;
   return v;
 }
@@ -550,6 +558,7 @@ bn_status ensure_sweep_sets(bn_problem p) {
     if ((s = p->alloc(&p->sets[b].un, P)) != BN_OK) return s;
     if (p->v.tgp && (s = p->alloc(&p->sets[b].gn, P * p->v.tgp)) != BN_OK) return s;
   }
+  if (moves_wait(p->v) && (s = p->alloc(&p->accepts, P)) != BN_OK) return s;
   HIPCHK(hipStreamCreateWithFlags(&p->aux, hipStreamNonBlocking));
   for (hipEvent_t& e : p->ev) HIPCHK(hipEventCreateWithFlags(&e, hipEventDisableTiming));
   p->sets_ready = true;
@@ -600,6 +609,7 @@ bn_status record_proposals(bn_problem p, int b, uint32_t ahead, hipStream_t st, 
 // counter (by the last phase's commit).
 bn_status record_phases(bn_problem p, int b, bool advance) {
   const uint32_t phases = p->cfg.colour_k * p->cfg.colour_k;
+  const bool wait = moves_wait(p->v);
   for (uint32_t kappa = 0; kappa < phases; ++kappa) {
     const DevView v = phase_view(p, b, kappa);
     ProfMark me(p, &p->prof_eval, p->stream);
@@ -607,9 +617,14 @@ bn_status record_phases(bn_problem p, int b, bool advance) {
     HIPCHK(launch_delta(v, MODE_CLASS, kappa, v.pc, p->stream));
     bn_status s = me.end();
     if (s != BN_OK) return s;
+    if (wait && kappa + 1 < phases) continue;
     ProfMark mc(p, &p->prof_commit, p->stream);
-    HIPCHK(launch_commit(v, kappa, p->stream, advance && kappa + 1 == phases));
-    HIPCHK(launch_gauss_commit(v, kappa, p->stream));
+    if (wait) {
+      HIPCHK(launch_commit_sweep(sweep_view(p, b), p->stream, advance));
+    } else {
+      HIPCHK(launch_commit(v, kappa, p->stream, advance && kappa + 1 == phases));
+      HIPCHK(launch_gauss_commit(v, kappa, p->stream));
+    }
     if ((s = mc.end()) != BN_OK) return s;
   }
   return BN_OK;
@@ -919,7 +934,9 @@ bn_status batch_upload(bn_batch b) {
     if ((s = upload(g, 0, count_blocks)) != BN_OK) return s;
   for (BatchGroup& g : b->stage_groups)
     if ((s = upload(g, 1, phase_blocks)) != BN_OK) return s;
-  if ((s = upload(b->commit_all, 1, commit_blocks)) != BN_OK) return s;
+  if ((s = upload(b->commit_all, 0, commit_blocks)) != BN_OK) return s;
+  if ((s = upload(b->commit_phase, 1, commit_blocks)) != BN_OK) return s;
+  if ((s = upload(b->commit_sweep, 0, commit_sweep_blocks)) != BN_OK) return s;
   return BN_OK;
 }
 
@@ -946,9 +963,13 @@ bn_status batch_phases(bn_batch b, int set) {
   for (uint32_t kappa = 0; kappa < b->colour_k * b->colour_k; ++kappa) {
     if ((s = batch_evaluate(b, set, kappa)) != BN_OK) return s;
     const uint32_t t = set * b->colour_k * b->colour_k + kappa;
-    HIPCHK(launch_commit_batch(b->commit_all.views[t], b->commit_all.d_pre, (uint32_t)b->commit_all.idx.size(),
-                               b->commit_all.blocks, kappa, b->stream));
+    const BatchGroup& g = b->commit_phase;
+    if (!g.idx.empty())
+      HIPCHK(launch_commit_batch(g.views[t], g.d_pre, (uint32_t)g.idx.size(), g.blocks, kappa, b->stream));
   }
+  const BatchGroup& g = b->commit_sweep;
+  if (!g.idx.empty())
+    HIPCHK(launch_commit_sweep_batch(g.views[set], g.d_pre, (uint32_t)g.idx.size(), g.blocks, b->stream));
   return BN_OK;
 }
 
@@ -2180,6 +2201,7 @@ bn_status bn_create_batch(const bn_problem* members, uint32_t m, const char* tun
     }
     sg->idx.push_back(i);
     b->commit_all.idx.push_back(i);
+    (moves_wait(v) ? b->commit_sweep : b->commit_phase).idx.push_back(i);
   }
   // The recount launches follow the members' order, except that the one of
   // the smallest N goes first: a long VALU-bound launch first meets the first

@@ -53,6 +53,11 @@ struct DevView {
   int8_t* d8;                // narrow forms: [tp/16][P][16] counts less their integrand's base, else null
   int8_t* n8;                // narrow forms: [tp/16][M][16] the same of the proposals (c_new is null)
   const uint32_t* bias8;     // [tp/2] 0x00800080 - (base of 2 i | base of 2 i + 1 << 16)
+  // sweeps on narrow forms (moves_wait): the accepted moves of the classes
+  // before this one are still proposals, committed together after the last class
+  uint32_t decided;          // classes whose moves wait (0 otherwise)
+  uint8_t* accepts;          // [K^2][pc] the sweep's decisions, else null
+  const int8_t* n8_sweep;    // n8 of class 0
   double* delta;             // [M] energy change
   uint8_t* accept;           // [M] decision
   const uint32_t* pix_list;  // [M] pixels (list mode)
@@ -94,6 +99,12 @@ hipError_t launch_phase(const DevView& v, uint32_t kappa, hipStream_t s);
 // advance: also the sweep counter
 hipError_t launch_commit(const DevView& v, uint32_t kappa, hipStream_t s, bool advance = false);
 uint32_t commit_blocks(const DevView& v);
+bool moves_wait(const DevView& v);
+// the waiting moves of all classes (v: a sweep's view) in one launch
+hipError_t launch_commit_sweep(const DevView& v, hipStream_t s, bool advance);
+uint32_t commit_sweep_blocks(const DevView& v);
+hipError_t launch_commit_sweep_batch(const DevView* views, const uint32_t* pre, uint32_t nmem, uint32_t blocks,
+                                     hipStream_t s);
 hipError_t launch_errors(const DevView& v, hipStream_t s);
 hipError_t launch_pack_errors(const DevView& v, uint32_t first, uint32_t n, float* out, hipStream_t s);
 hipError_t launch_advance(const DevView& v, hipStream_t s);

@@ -220,6 +220,28 @@ __global__ __launch_bounds__(64 * COMMIT_WAVES) void k_commit_batch(const DevVie
   commit_body(v, kappa, blockIdx.x - pre[i], false);
 }
 
+// All classes' moves of a sweep whose phases left them waiting.
+__device__ __forceinline__ void commit_sweep_body(DevView v, uint32_t blk, bool advance) {
+  const uint32_t per = (v.pc + 63) / 64, kappa = blk / per;
+  v.n8 += (size_t)kappa * v.pc * v.tp;
+  v.u_new += (size_t)kappa * v.pc;
+  v.accept = v.accepts + (size_t)kappa * v.pc;
+  commit_body(v, kappa, blk - kappa * per, advance && kappa == 0);
+}
+
+__global__ __launch_bounds__(64 * COMMIT_WAVES) void k_commit_sweep(DevView v, bool advance) {
+  __builtin_amdgcn_s_setprio(2);
+  commit_sweep_body(v, blockIdx.x, advance);
+}
+
+__global__ __launch_bounds__(64 * COMMIT_WAVES) void k_commit_sweep_batch(const DevView* __restrict__ views,
+                                                                          const uint32_t* __restrict__ pre,
+                                                                          uint32_t nmem) {
+  __builtin_amdgcn_s_setprio(2);
+  const uint32_t i = batch_member(pre, nmem, blockIdx.x);
+  commit_sweep_body(views[i], blockIdx.x - pre[i], false);
+}
+
 __global__ void k_advance(unsigned long long* ctr) {
   if (threadIdx.x == 0 && blockIdx.x == 0) atomicAdd(&ctr[0], 1ull);
 }
@@ -646,6 +668,27 @@ uint32_t commit_blocks(const DevView& v) { return (v.pc + 63) / 64; }
 
 hipError_t launch_commit(const DevView& v, uint32_t kappa, hipStream_t s, bool advance) {
   hipLaunchKernelGGL(k_commit, dim3(commit_blocks(v)), dim3(64 * COMMIT_WAVES), 0, s, v, kappa, advance);
+  return hipGetLastError();
+}
+
+// Phases on narrow forms read an accepted move of an earlier class from its
+// proposal, so that a sweep has one commit launch: three of the eight launches
+// of a sweep's chain at K = 2 less, and the rows of all classes in flight
+// together (two sweeps of 256^2, N = 256, T = 1024: 312 -> 248 us, of 32^2, N = 16,
+// T = 64: 113 -> 95).  (Gaussian rows are read
+// from the estimates, which their commit updates class by class.)
+bool moves_wait(const DevView& v) { return v.form != FIELD_WIDE && !v.tgp; }
+
+uint32_t commit_sweep_blocks(const DevView& v) { return v.k * v.k * commit_blocks(v); }
+
+hipError_t launch_commit_sweep(const DevView& v, hipStream_t s, bool advance) {
+  hipLaunchKernelGGL(k_commit_sweep, dim3(commit_sweep_blocks(v)), dim3(64 * COMMIT_WAVES), 0, s, v, advance);
+  return hipGetLastError();
+}
+
+hipError_t launch_commit_sweep_batch(const DevView* views, const uint32_t* pre, uint32_t nmem, uint32_t blocks,
+                                     hipStream_t s) {
+  hipLaunchKernelGGL(k_commit_sweep_batch, dim3(blocks), dim3(64 * COMMIT_WAVES), 0, s, views, pre, nmem);
   return hipGetLastError();
 }
 

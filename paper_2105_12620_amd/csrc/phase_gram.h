@@ -95,7 +95,10 @@ __device__ __forceinline__ void gram_body(const DevView& v, uint32_t kappa, uint
   // past the region read its last pixel
   const uint32_t ys = (ky + K * a0 + v.h * (R / v.h + 1) - R) % v.h;
   const uint32_t xs = (kx + K * b0 + v.w * (R / v.w + 1) - R) % v.w;
-  uint32_t src[G::D];
+  // (an accepted move of an earlier class waits among the sweep's proposals)
+  const char* src[G::D];
+  uint32_t step[G::D];
+  uint32_t pix[G::D], prop[G::D], moved[G::D];
 #pragma unroll
   for (int k = 0; k < G::D; ++k) {
     const uint32_t d = min(w + G::NW * k, (uint32_t)G::NLD - 1);
@@ -105,22 +108,31 @@ __device__ __forceinline__ void gram_body(const DevView& v, uint32_t kappa, uint
     uint32_t y = ys + rr, x = xs + cc;
     while (y >= v.h) y -= v.h;
     while (x >= v.w) x -= v.w;
-    src[k] = (pl * P + y * v.w + x) * 16;
+    pix[k] = pl * P + y * v.w + x;
+    const uint32_t cls = (y % K) * K + x % K, j = (y / K) * v.cw + x / K;
+    prop[k] = cls * v.pc * (v.tp >> 4) + pl * v.pc + j;
+    moved[k] = cls < v.decided ? v.accepts[cls * v.pc + j] : 0u;
+  }
+#pragma unroll
+  for (int k = 0; k < G::D; ++k) {
+    src[k] = moved[k] ? (const char*)v.n8_sweep + (size_t)prop[k] * 16 : (const char*)v.d8 + (size_t)pix[k] * 16;
+    step[k] = (moved[k] ? v.pc : P) * 64;
   }
   // the class pixels' recounted words: wave w loads words 64 w .. of row
   // w mod BY (class pixels past the tile read pixel 0; their products are not
   // read back)
   const bool in = a0 + w % G::BY < v.ch && b0 + c16 < v.cw;
   const uint32_t nsrc = (g * v.pc + (in ? (a0 + w % G::BY) * v.cw + b0 + c16 : 0)) * 16;
-  auto issue = [&](uint32_t st, uint32_t buf) {
-    const char* fb = (const char*)v.d8 + (size_t)st * 64 * P;
+  auto issue = [&](uint32_t st, uint32_t buf) {   // stages in order
     const char* nb = (const char*)v.n8 + (size_t)st * 64 * v.pc;
     u32x4* to = lds4 + buf * G::STAGE;
 #pragma unroll
     for (int k = 0; k < G::D; ++k)
       __builtin_amdgcn_global_load_lds(
-          (const __attribute__((address_space(1))) void*)(fb + src[k]),
+          (const __attribute__((address_space(1))) void*)src[k],
           (__attribute__((address_space(3))) void*)(to + 64 * min(w + G::NW * k, (uint32_t)G::NLD - 1)), 16, 0, 0);
+#pragma unroll
+    for (int k = 0; k < G::D; ++k) src[k] += step[k];
     __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(nb + nsrc),
                                      (__attribute__((address_space(3))) void*)(to + 4 * G::PLANE + 64 * (w % G::BY)),
                                      16, 0, 0);
@@ -219,8 +231,10 @@ __device__ __forceinline__ void gram_body(const DevView& v, uint32_t kappa, uint
   }
   double total = __dmul_rn(sum, 2.0 / ((double)v.n * (double)v.n));
   if (v.tgp) total = __dadd_rn(total, v.gdelta[j]);
+  const bool ok = (v.objective > 0) ? (total < 0.0) : (total > 0.0);
   v.delta[j] = total;
-  v.accept[j] = (v.objective > 0) ? (total < 0.0) : (total > 0.0);
+  v.accept[j] = ok;
+  if (v.accepts) v.accepts[(size_t)kappa * v.pc + j] = ok;
 }
 
 // One-dimensional grid of gx blocks a row, renumbered per XCD: an L2 then
