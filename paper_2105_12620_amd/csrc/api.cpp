@@ -1411,12 +1411,13 @@ bn_status bn_create_problem_ext(const bn_config* cfg, const bn_heaviside* heavis
   }
   // Gaussian line form: from N = 16, where a line holds several samples, up to
   // lines of 256 steps (a table of the steps' factors per Gaussian), and for
-  // launches over the tile that fill the chip (launch_gauss_est)
+  // launches over the tile that fill the chip (launch_gauss_est); moves too
+  // close for it are decided sample by sample (launch_gauss_again)
   v.glines = 0;
   std::vector<uint32_t> grow;
   std::vector<int> gspans;
   std::vector<double> gtab;
-  if (v.n >= 16 && gauss_lines_pay(v, (uint32_t)P)) {
+  if (v.n >= 16 && staged_phases(v) && gauss_lines_pay(v, (uint32_t)P)) {
     GaussLines q = gauss_lines(v.n, v.gx, v.gy, g);
     if (q.steps <= 256) {
       v.glines = q.lines;
@@ -1439,6 +1440,15 @@ bn_status bn_create_problem_ext(const bn_config* cfg, const bn_heaviside* heavis
       }
       v.grow = grow_d;
       v.gspans = gspans_d;
+      if ((s = p->alloc(&v.gmargin, v.pc)) != BN_OK || (s = p->alloc(&v.gunsure, (size_t)v.pc + 1)) != BN_OK ||
+          (s = p->alloc(&v.hpart, v.pc)) != BN_OK || (s = p->alloc(&v.gpart, (size_t)v.pc * (v.tgp / 16))) != BN_OK) {
+        delete p;
+        return s;
+      }
+      if (hipMemsetAsync(v.gunsure, 0, 4, p->stream) != hipSuccess) {
+        delete p;
+        return fail(BN_EHIP, "clearing the list of unsure moves");
+      }
       v.gtab = gtab_d;
       hipError_t ge = hipMemcpyAsync(grow_d, grow.data(), grow.size() * 4, hipMemcpyHostToDevice, p->stream);
       if (ge == hipSuccess) ge = hipMemcpyAsync(gspans_d, gspans.data(), gspans.size() * 4, hipMemcpyHostToDevice, p->stream);

@@ -88,6 +88,11 @@ struct DevView {
   float* gerr;               // [P][tgp] errors g - I (refreshed on demand)
   float* g_new;              // [M][tgp] estimates of the proposals
   double* gdelta;            // [M] Gaussian part of the energy change
+  // line form in sweeps: moves decided again from estimates sample by sample
+  double* gmargin;           // [M] how far gdelta can be from theirs, else null
+  uint32_t* gunsure;         // count, then the moves within it ([1 + M]; 0 between phases)
+  double* hpart;             // [M] their Heaviside part
+  double* gpart;             // [M][tgp/16] their Gaussian parts by 16
 };
 
 hipError_t launch_init_offsets(const DevView& v, hipStream_t s);
@@ -125,6 +130,7 @@ hipError_t launch_blur(const DevView& v, const float* field, uint32_t pitch, uin
                        const BlurTaps& y, float* tmp, double* partial, uint32_t* npartial, hipStream_t s);
 uint32_t blur_partials(const DevView& v, uint32_t pitch);
 bool gauss_lines_pay(const DevView& v, uint32_t m);
+hipError_t launch_gauss_again(const DevView& v, uint32_t kappa, hipStream_t s);
 hipError_t launch_gauss_lines(const DevView& v, bool all, uint32_t m, hipStream_t s);
 hipError_t launch_gauss_est(const DevView& v, int mode, uint32_t m, hipStream_t s);
 hipError_t launch_gauss_delta(const DevView& v, int mode, uint32_t kappa, uint32_t m, hipStream_t s);

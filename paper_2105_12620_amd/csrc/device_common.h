@@ -139,6 +139,18 @@ __device__ inline uint32_t proposal(const DevView& v, uint32_t p, uint32_t sweep
   return q16_pair(philox_w01(p, sweep, v.problem, S_PROP, v.seed_lo, v.seed_hi));
 }
 
+// Energy change of class pixel j from its Heaviside part; a move too close to be
+// decided from the line form's estimates is listed (launch_gauss_again).
+__device__ __forceinline__ double with_gaussian_part(const DevView& v, uint32_t j, double heaviside) {
+  if (!v.tgp) return heaviside;
+  const double total = __dadd_rn(heaviside, v.gdelta[j]);
+  if (v.gmargin && fabs(total) <= v.gmargin[j]) {
+    v.gunsure[1 + atomicAdd(v.gunsure, 1u)] = j;
+    v.hpart[j] = heaviside;
+  }
+  return total;
+}
+
 // ------------------------------------------------- BF16 error field values
 
 // Round to the nearest BF16 (ties to even); bits of two values packed.

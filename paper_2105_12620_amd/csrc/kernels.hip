@@ -384,24 +384,11 @@ __device__ __forceinline__ void gauss_chunk(const DevView& v, uint32_t u, uint32
   }
 }
 
-template <int MODE>
-__global__ __launch_bounds__(256) void k_gauss_est(DevView v, uint32_t kappa, uint32_t m) {
-  constexpr uint32_t GB = 16, CH = 512;         // Gaussians per wave, samples per chunk
-  __shared__ double red[4][GB / 2][65];
-  const uint32_t lane = threadIdx.x & 63, wl = threadIdx.x >> 6;
-  const uint32_t wave = wave_id();
-  const uint32_t ngb = v.tgp / GB;
-  const uint32_t j = wave / ngb, gb = wave - j * ngb;
-  if (j >= m) return;
-  uint32_t u;
-  float* out;
-  if (MODE == MODE_ALL) {
-    u = v.U[j];
-    out = v.gest + (size_t)j * v.tgp;
-  } else {
-    u = v.u_new[j];
-    out = v.g_new + (size_t)j * v.tgp;
-  }
+// Estimates of Gaussians 16 gb .. of the pixel with offset u, by one wave (red:
+// its part of LDS).
+__device__ __forceinline__ void gauss_estimates(const DevView& v, uint32_t u, uint32_t gb, uint32_t lane,
+                                                double (*red)[65], float* out) {
+  constexpr uint32_t GB = 16, CH = 512;
   const double* gc = v.gcoef + (size_t)gb * GB * 4;
   double acc[GB];
 #pragma unroll
@@ -415,20 +402,105 @@ __global__ __launch_bounds__(256) void k_gauss_est(DevView v, uint32_t kappa, ui
 #pragma unroll
   for (uint32_t h = 0; h < 2; ++h) {
 #pragma unroll
-    for (uint32_t g = 0; g < GB / 2; ++g) red[wl][g][lane] = acc[8 * h + g];
+    for (uint32_t g = 0; g < GB / 2; ++g) red[g][lane] = acc[8 * h + g];
     __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
     __builtin_amdgcn_wave_barrier();
     const uint32_t g = lane & 7, q = lane >> 3;
     double t = 0.0;
 #pragma unroll
-    for (uint32_t k = 0; k < 8; ++k) t = __dadd_rn(t, red[wl][g][8 * q + k]);
+    for (uint32_t k = 0; k < 8; ++k) t = __dadd_rn(t, red[g][8 * q + k]);
     t = __dadd_rn(t, __shfl_xor(t, 8));
     t = __dadd_rn(t, __shfl_xor(t, 16));
     t = __dadd_rn(t, __shfl_xor(t, 32));
-    if (lane < GB / 2) out[gb * GB + 8 * h + g] = (float)(t / (double)v.n);
+    if (lane < GB / 2) out[8 * h + g] = (float)(t / (double)v.n);
     __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
     __builtin_amdgcn_wave_barrier();
   }
+}
+
+template <int MODE>
+__global__ __launch_bounds__(256) void k_gauss_est(DevView v, uint32_t kappa, uint32_t m) {
+  __shared__ double red[4][8][65];
+  const uint32_t lane = threadIdx.x & 63, wl = threadIdx.x >> 6;
+  const uint32_t wave = wave_id();
+  const uint32_t ngb = v.tgp / 16;
+  const uint32_t j = wave / ngb, gb = wave - j * ngb;
+  if (j >= m) return;
+  uint32_t u;
+  float* out;
+  if (MODE == MODE_ALL) {
+    u = v.U[j];
+    out = v.gest + (size_t)j * v.tgp;
+  } else {
+    u = v.u_new[j];
+    out = v.g_new + (size_t)j * v.tgp;
+  }
+  gauss_estimates(v, u, gb, lane, red[wl], out + gb * 16);
+}
+
+// Sweeps whose estimates come from the lattice lines (gauss_lines.hip) decide as
+// the sample by sample estimates would.  Those are off the exact mean by at most
+// 2^-24 (0.37 + 10 g): the exponent's rounding to FP32 (2^-24 max y 2^-y ln 2),
+// v_exp_f32 and seven FP32 additions per lane, and the result's rounding, as is the
+// lines' (exact but for that); with g <= 1 the two differ by less than
+// eta = 2^-24 11.4, and a Gaussian's part of the energy change,
+//   2 sum_m w_m d x_m,  d = g' - g,  x_m = g' + g - 2 g_m,
+// by less than 8 eta sum_m w_m (|x_m| + |d|).  A move whose energy change is
+// within that bound of 0 is listed and its Gaussian part evaluated again from
+// estimates sample by sample (of its window: k_gauss_again), then decided.
+// 512^2, N = 1024, 1024 Gaussians: about a move in a thousand, 0.3 to 1.4 ms a
+// phase (its cost is the exponentials of 122 pixels a move), where estimating
+// every proposal so would take 14.
+constexpr double GAUSS_MARGIN = 8 * 11.4 * 0x1p-24 * 1.01;
+
+// One workgroup per listed move and 16 Gaussians (striding over them).
+template <int R>
+__global__ __launch_bounds__(256) void k_gauss_again(DevView v, uint32_t kappa) {
+  constexpr int S = 2 * R + 1, SQ = S * S;
+  __shared__ double red[4][8][65];
+  __shared__ float est[SQ + 1][16];   // the window's estimates, raster order, then the move's
+  __shared__ double sums[4];
+  const uint32_t tid = threadIdx.x, lane = tid & 63, wl = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const uint32_t ngb = v.tgp / 16, items = v.gunsure[0] * ngb;
+  for (uint32_t it = blockIdx.x; it < items; it += gridDim.x) {
+    const uint32_t e = it / ngb, gb = it - e * ngb;
+    const uint32_t j = __builtin_amdgcn_readfirstlane(v.gunsure[1 + e]);
+    const uint32_t p = class_pixel(v, kappa, j), y = p / v.w, x = p - y * v.w;
+    for (uint32_t i = wl; i <= (uint32_t)SQ; i += 4) {
+      const uint32_t oy = i / S, ox = i - oy * S;
+      const uint32_t q = (y + oy + v.h * (R / v.h + 1) - R) % v.h * v.w + (x + ox + v.w * (R / v.w + 1) - R) % v.w;
+      gauss_estimates(v, i == (uint32_t)SQ ? v.u_new[j] : v.U[q], gb, lane, red[wl], est[i]);
+    }
+    __syncthreads();
+    const uint32_t t = tid & 15;
+    const double gn = est[SQ][t], go = est[SQ / 2][t], d = gn - go, sm = gn + go;
+    double acc = 0.0;
+    for (uint32_t i = tid >> 4; i < (uint32_t)SQ; i += 16) {
+      const int oy = (int)(i / S) - R, ox = (int)(i % S) - R;
+      if (oy || ox) acc += v.wd[v.dcls[ox * ox + oy * oy]] * (d * (sm - 2.0 * (double)est[i][t]));
+    }
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off);
+    if (lane == 0) sums[wl] = acc;
+    __syncthreads();
+    if (tid == 0) v.gpart[it] = (sums[0] + sums[1]) + (sums[2] + sums[3]);
+  }
+}
+
+// The listed moves' decisions (one workgroup); empties the list.
+__global__ __launch_bounds__(256) void k_gauss_decide_again(DevView v) {
+  const uint32_t n = v.gunsure[0], ngb = v.tgp / 16;
+  for (uint32_t e = threadIdx.x; e < n; e += 256) {
+    const uint32_t j = v.gunsure[1 + e];
+    double acc = 0.0;
+    for (uint32_t gb = 0; gb < ngb; ++gb) acc += v.gpart[(size_t)e * ngb + gb];
+    const double total = __dadd_rn(v.hpart[j], 2.0 * acc);
+    v.gdelta[j] = 2.0 * acc;
+    v.delta[j] = total;
+    v.accept[j] = (v.objective > 0) ? (total < 0.0) : (total > 0.0);
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) v.gunsure[0] = 0;
 }
 
 // Gaussian rows' part of a move's energy change (plain form of Eq. (1) over
@@ -448,6 +520,7 @@ __global__ __launch_bounds__(256) void k_delta_gauss(DevView v, uint32_t kappa, 
   double cs[NCLS];
 #pragma unroll
   for (int c = 0; c < NCLS; ++c) cs[c] = 0.0;
+  double margin = 0.0;
   for (uint32_t base = 0; base < v.tgp; base += 64) {
     const uint32_t t = base + lane;
     const double gn = v.g_new[(size_t)j * v.tgp + t], go = v.gest[(size_t)p * v.tgp + t];
@@ -455,8 +528,15 @@ __global__ __launch_bounds__(256) void k_delta_gauss(DevView v, uint32_t kappa, 
 #pragma unroll
     for (int mm = 0; mm < W.M; ++mm) {
       const uint32_t q = ((y + v.h + W.oy[mm]) % v.h) * v.w + (x + v.w + W.ox[mm]) % v.w;
-      cs[W.cls[mm]] += d * (sm - 2.0 * (double)v.gest[(size_t)q * v.tgp + t]);
+      const double e = sm - 2.0 * (double)v.gest[(size_t)q * v.tgp + t];
+      cs[W.cls[mm]] += d * e;
+      if (MODE == MODE_CLASS) margin += v.wd[W.cls[mm]] * (fabs(e) + fabs(d));
     }
+  }
+  if (MODE == MODE_CLASS && v.gmargin) {
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) margin += __shfl_xor(margin, off);
+    if (lane == 0) v.gmargin[j] = GAUSS_MARGIN * margin;
   }
   double acc = 0.0;
 #pragma unroll
@@ -514,9 +594,13 @@ __global__ __launch_bounds__(512) void k_delta_gauss_stage(DevView v, uint32_t k
     goff[it] = gy * v.w + gx;
   }
   const int own = (K * cy + R) * G::RW + K * cx + R;
-  double cs[NCLS];
+  double wd[NCLS], wsum = 0.0;
 #pragma unroll
-  for (int c = 0; c < NCLS; ++c) cs[c] = 0.0;
+  for (int c = 0; c < NCLS; ++c) {
+    wd[c] = v.wd[c];
+    wsum += (double)W.csize[c] * wd[c];
+  }
+  double acc = 0.0, margin = 0.0;
   for (uint32_t base = 0; base < v.tgp; base += 64) {
     f32x4 q[ITER];
 #pragma unroll
@@ -532,23 +616,27 @@ __global__ __launch_bounds__(512) void k_delta_gauss_stage(DevView v, uint32_t k
     if (act) {
       const double gn = v.g_new[(size_t)j * v.tgp + base + lane], go = gl[own * 64 + lane];
       const double d = gn - go, sm = gn + go;
+      double s = 0.0, a = 0.0;   // sums of w x and w |x| over the window
 #pragma unroll
       for (int mm = 0; mm < W.M; ++mm) {
         const int q = own + W.oy[mm] * G::RW + W.ox[mm];
-        cs[W.cls[mm]] += d * (sm - 2.0 * (double)gl[q * 64 + lane]);
+        const double x = __fma_rn(-2.0, (double)gl[q * 64 + lane], sm);
+        s = __fma_rn(wd[W.cls[mm]], x, s);
+        a = __fma_rn(wd[W.cls[mm]], fabs(x), a);
       }
+      acc = __fma_rn(d, s, acc);
+      margin += __fma_rn(wsum, fabs(d), a);
     }
   }
   if (!act) return;
-  double acc = 0.0;
 #pragma unroll
-  for (int c = 0; c < NCLS; ++c) {
-    double xv = cs[c];
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) xv += __shfl_xor(xv, off);
-    acc += v.wd[c] * xv;
+  for (int off = 32; off > 0; off >>= 1) {
+    acc += __shfl_xor(acc, off);
+    margin += __shfl_xor(margin, off);
   }
-  if (lane == 0) v.gdelta[j] = 2.0 * acc;
+  if (lane != 0) return;
+  v.gdelta[j] = 2.0 * acc;
+  if (v.gmargin) v.gmargin[j] = GAUSS_MARGIN * margin;
 }
 
 // Gaussian rows' part of the energy: per distance class, sum over the half
@@ -656,7 +744,9 @@ hipError_t launch_delta(const DevView& v, int mode, uint32_t kappa, uint32_t m, 
   if (mode != MODE_CLASS) return delta_dispatch<MODE_LIST>(v, kappa, m, s);
   // BF16 precision form: matrix-core Gram pass, decision, exact re-evaluation
   if (v.mfma) return launch_delta_bf16(v, kappa, s);
-  return staged_phases(v) ? launch_phase(v, kappa, s) : delta_dispatch<MODE_CLASS>(v, kappa, m, s);
+  if (!staged_phases(v)) return delta_dispatch<MODE_CLASS>(v, kappa, m, s);
+  hipError_t e = launch_phase(v, kappa, s);
+  return e != hipSuccess || !v.gmargin ? e : launch_gauss_again(v, kappa, s);
 }
 
 hipError_t launch_finish(const DevView& v, hipStream_t s) {
@@ -738,6 +828,23 @@ hipError_t launch_energy(const DevView& v, unsigned long long* y, hipStream_t s)
     case 6: hipLaunchKernelGGL(k_energy<6>, grid, block, 0, s, v, y); break;
     default: return hipErrorInvalidValue;
   }
+  return hipGetLastError();
+}
+
+hipError_t launch_gauss_again(const DevView& v, uint32_t kappa, hipStream_t s) {
+  const dim3 grid(2048), block(256);
+  switch (v.radius) {
+    case 1: hipLaunchKernelGGL(k_gauss_again<1>, grid, block, 0, s, v, kappa); break;
+    case 2: hipLaunchKernelGGL(k_gauss_again<2>, grid, block, 0, s, v, kappa); break;
+    case 3: hipLaunchKernelGGL(k_gauss_again<3>, grid, block, 0, s, v, kappa); break;
+    case 4: hipLaunchKernelGGL(k_gauss_again<4>, grid, block, 0, s, v, kappa); break;
+    case 5: hipLaunchKernelGGL(k_gauss_again<5>, grid, block, 0, s, v, kappa); break;
+    case 6: hipLaunchKernelGGL(k_gauss_again<6>, grid, block, 0, s, v, kappa); break;
+    default: return hipErrorInvalidValue;
+  }
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(k_gauss_decide_again, dim3(1), dim3(256), 0, s, v);
   return hipGetLastError();
 }
 
