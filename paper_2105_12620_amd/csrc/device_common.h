@@ -151,6 +151,30 @@ __device__ __forceinline__ double with_gaussian_part(const DevView& v, uint32_t 
   return total;
 }
 
+// The window's offsets in steps of up to eight: row steps of consecutive offsets
+// of a window row, then column steps of eight rows of the columns they leave
+// over.  offset: slot i of step st, and whether the slot holds one.
+template <int R>
+struct WindowSteps {
+  static constexpr int WS = 2 * R + 1;
+  static constexpr int RC = WS < 8 ? WS : 8;             // offsets of a row step
+  static constexpr int LC = WS - RC;                     // columns left to column steps
+  static constexpr int CH = (WS + 7) / 8;                // column steps per such column
+  static constexpr int LASTROWS = WS - 8 * (CH - 1);     // rows of a column's last step
+  static constexpr int STEPS = WS + LC * CH;
+  __device__ static inline bool offset(int st, int i, int& ox, int& oy) {
+    if (st < WS) {
+      oy = st - R;
+      ox = -R + i;
+      return i < RC;
+    }
+    const int t = st - WS, col = t / CH, part = t % CH;
+    ox = -R + RC + col;
+    oy = -R + 8 * part + i;
+    return oy <= R;
+  }
+};
+
 // ------------------------------------------------- BF16 error field values
 
 // Round to the nearest BF16 (ties to even); bits of two values packed.

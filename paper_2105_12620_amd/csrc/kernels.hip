@@ -37,58 +37,79 @@ namespace {
 // orderings):  dE = (2/N^2) sum_d w(d) X_d,
 //   X_d = |class d| * Z0 - 2 Z_d,  Z0 = sum_t dc_t (c'_t + c_t),
 //   Z_d = sum_{o in class d} sum_t dc_t c_{p+o,t},  dc = c' - c,
-// all in exact integers.  One wave per moved pixel; a lane handles two
-// adjacent integrands and each (neighbour, integrand pair) costs one v_dot2 of
-// packed int16 pairs.  Used for explicit pixel lists; colour phases use the
-// LDS-staged kernel below.
+// all in exact integers.  One wave per moved pixel: lane (i, q) takes the i-th
+// offset of each step (WindowSteps: eight consecutive offsets of a window row,
+// or of a column that those leave over) and plane q of 64 integrands, so that a
+// load reads whole lines of eight planes; a word is 8 integrands, four v_dot2.
+// The steps' sums meet by class in LDS.  Used for explicit pixel lists and
+// colourings without a phase kernel.  Bound by the latency of a moved pixel's
+// serial planes and the L2s' reads.  2000 moves at T = 1024, r = 4: 71 us; 195
+// with a lane per integrand pair (a load touched 16 lines for 256 bytes), 213 to
+// 265 with a lane per word (64 lines for 1 KiB).
 template <int R, int MODE>
 __global__ __launch_bounds__(256) void k_delta(DevView v, uint32_t kappa, uint32_t m) {
+  using S = WindowSteps<R>;
   constexpr Window<R> W = WinConst<R>::w;
   constexpr int NCLS = WinConst<R>::NCLS;
-  const uint32_t lane = threadIdx.x & 63;
+  static_assert(NCLS < 64, "a lane per class");
+  __shared__ unsigned long long sums[4][NCLS + 1];
+  const uint32_t lane = threadIdx.x & 63, wl = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const uint32_t j = wave_id();
   if (j >= m) return;
   const uint32_t p = (MODE == MODE_CLASS) ? class_pixel(v, kappa, j) : v.pix_list[j];
-  const uint32_t y = p / v.w, x = p - y * v.w;
-  uint32_t rowq[2 * R + 1], colq[2 * R + 1];
+  const uint32_t y = p / v.w, x = p - y * v.w, i = lane & 7, P = v.w * v.h;
+  uint32_t q[S::STEPS];
+  int cl[S::STEPS];
 #pragma unroll
-  for (int i = 0; i < 2 * R + 1; ++i) {
-    rowq[i] = ((y + v.h + i - R) % v.h) * v.w;
-    colq[i] = (x + v.w + i - R) % v.w;
+  for (int st = 0; st < S::STEPS; ++st) {
+    int ox, oy;
+    const bool in = S::offset(st, (int)i, ox, oy) && (ox || oy);
+    cl[st] = in ? v.dcls[ox * ox + oy * oy] : -1;
+    q[st] = in ? (y + v.h * (R / v.h + 1) + oy) % v.h * v.w + (x + v.w * (R / v.w + 1) + ox) % v.w : p;
   }
-  const uint32_t P = v.w * v.h;
-  long long z0 = 0;
-  long long zd[NCLS];
+  if (lane <= (uint32_t)NCLS) sums[wl][lane] = 0;
+  long long z0 = 0, zd[S::STEPS];
 #pragma unroll
-  for (int c = 0; c < NCLS; ++c) zd[c] = 0;
-
-  for (uint32_t base = 0; base < v.tp; base += 128) {
-    const uint32_t t = base + 2 * lane;
-    const uint32_t cn = *(const uint32_t*)(v.c_new + tix(j, t, m));
-    const uint32_t co = *(const uint32_t*)(v.cnt + tix(p, t, P));
-    const int n0 = (int)(cn & 0xFFFFu), n1 = (int)(cn >> 16);
-    const int o0 = (int)(co & 0xFFFFu), o1 = (int)(co >> 16);
-    const int dc0 = n0 - o0, dc1 = n1 - o1;
-    const uint32_t dcp = ((uint32_t)dc0 & 0xFFFFu) | ((uint32_t)dc1 << 16);
-    z0 += (long long)(dc0 * (n0 + o0) + dc1 * (n1 + o1));
-    int part = 0;
+  for (int st = 0; st < S::STEPS; ++st) zd[st] = 0;
+  const u32x4* nw = (const u32x4*)v.c_new + (size_t)(lane >> 3) * m + j;
+  const u32x4* plane = (const u32x4*)v.cnt + (size_t)(lane >> 3) * P;
+  for (uint32_t t = 0; t < v.tp; t += 64, nw += (size_t)8 * m, plane += (size_t)8 * P) {
+    const u32x4 cn = *nw, co = plane[p];
+    u32x4 c[S::STEPS];
 #pragma unroll
-    for (int mm = 0; mm < W.M; ++mm) {
-      const uint32_t q = rowq[W.oy[mm] + R] + colq[W.ox[mm] + R];
-      const uint32_t cq = *(const uint32_t*)(v.cnt + tix(q, t, P));
-      part = dot2(dcp, cq, part);
-      if (mm == W.M - 1 || W.cls[mm + 1] != W.cls[mm]) {
-        zd[W.cls[mm]] += part;
-        part = 0;
-      }
+    for (int st = 0; st < S::STEPS; ++st) c[st] = plane[q[st]];
+    uint32_t dc[4];
+    int z = 0;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const int n0 = (int)(cn[k] & 0xFFFFu), n1 = (int)(cn[k] >> 16);
+      const int o0 = (int)(co[k] & 0xFFFFu), o1 = (int)(co[k] >> 16);
+      const int dc0 = n0 - o0, dc1 = n1 - o1;
+      dc[k] = ((uint32_t)dc0 & 0xFFFFu) | ((uint32_t)dc1 << 16);
+      z += dc0 * (n0 + o0) + dc1 * (n1 + o1);
+    }
+    z0 += z;
+#pragma unroll
+    for (int st = 0; st < S::STEPS; ++st) {
+      int part = 0;   // |part| <= 8 N^2
+#pragma unroll
+      for (int k = 0; k < 4; ++k) part = dot2(dc[k], c[st][k], part);
+      zd[st] += part;
     }
   }
+  __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+#pragma unroll
+  for (int st = 0; st < S::STEPS; ++st)
+    if (cl[st] >= 0) atomicAdd(&sums[wl][cl[st]], (unsigned long long)zd[st]);
+  if (i == 0) atomicAdd(&sums[wl][NCLS], (unsigned long long)z0);
+  __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  const long long z = (long long)sums[wl][NCLS];
   double acc = 0.0;
 #pragma unroll
   for (int c = 0; c < NCLS; ++c) {
-    long long xv = (long long)W.csize[c] * z0 - 2 * zd[c];
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) xv += __shfl_xor(xv, off);
+    const long long xv = (long long)W.csize[c] * z - 2 * (long long)sums[wl][c];
     acc = __dadd_rn(acc, __dmul_rn(v.wd[c], (double)xv));
   }
   if (lane == 0) {

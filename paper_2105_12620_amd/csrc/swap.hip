@@ -101,11 +101,8 @@ struct SwapGeom {
   static constexpr int NRL = 2 * RA_PAD / 64;            // region loads per stage
   static constexpr int NLD = NRL + PART / 64;            // loads per stage
   static constexpr int D = (NLD + NWAVE - 1) / NWAVE;    // loads per wave and stage
-  static constexpr int RC = WS < 8 ? WS : 8;             // offsets of a row step
-  static constexpr int LC = WS - RC;                     // columns left to column steps
-  static constexpr int CH = (WS + 7) / 8;                // column steps per such column
-  static constexpr int LASTROWS = WS - 8 * (CH - 1);     // rows of a column's last step
-  static constexpr int STEPS = WS + LC * CH;
+  static constexpr int RC = WindowSteps<R>::RC, CH = WindowSteps<R>::CH, STEPS = WindowSteps<R>::STEPS;
+  static constexpr int LASTROWS = WindowSteps<R>::LASTROWS;
   static constexpr int NPIX = BW * BH;
   static constexpr int NWV = NPIX / 64;                  // waves that test membership
   static constexpr int LDS_BYTES = NBUF * SBUF * 16 + (3 * NPIX + NWV + 8 * STEPS) * 4;
@@ -113,22 +110,6 @@ struct SwapGeom {
   static_assert(D * NWAVE < 2 * NLD, "repeated load slots");
   static_assert(PD >= 1 && PD <= 3 && (PD - 1) * D < 64, "ring depth and vmcnt");
 };
-
-// Window offset of lane slot i at step st (row steps first, then column
-// steps), and whether the slot holds one.
-template <int R>
-__device__ inline bool swap_step_offset(int st, int i, int& ox, int& oy) {
-  using G = SwapGeom<R>;
-  if (st < G::WS) {
-    oy = st - R;
-    ox = -R + i;
-    return i < G::RC;
-  }
-  const int t = st - G::WS, col = t / G::CH, part = t % G::CH;
-  ox = -R + G::RC + col;
-  oy = -R + 8 * part + i;
-  return oy <= R;
-}
 
 template <int R, bool NARROW>
 __global__ __launch_bounds__(SwapGeom<R>::NT, (R <= 4) ? 4 : 2) void k_swap_stage(DevView v, SwapView sv, uint32_t kappa,
@@ -165,7 +146,7 @@ __global__ __launch_bounds__(SwapGeom<R>::NT, (R <= 4) ? 4 : 2) void k_swap_stag
   if (lane == 0 && wv < (uint32_t)G::NWV) wcnt[wv] = (uint32_t)__popcll(bal);
   if (tid < 8u * G::STEPS) {
     int ox, oy;
-    ctab[tid] = swap_step_offset<R>((int)tid / 8, (int)tid % 8, ox, oy) ? sv.dcls[ox * ox + oy * oy] : -1;
+    ctab[tid] = WindowSteps<R>::offset((int)tid / 8, (int)tid % 8, ox, oy) ? sv.dcls[ox * ox + oy * oy] : -1;
   }
   __syncthreads();
   uint32_t before = 0, nm = 0;
