@@ -65,8 +65,8 @@ struct GramGeom {
   static constexpr int RH = rows(BY), PLANE = plane(BY), STAGE = stage(BY);
   static constexpr int PX = 16 * BY;                               // class pixels per workgroup
   static constexpr int NO = (R + S) / S;                           // |oy| values of a wave
-  static constexpr int NLD = 4 * PLANE / 64;                       // region loads per stage
-  static constexpr int D = (NLD + NW - 1) / NW;                    // of a wave (the last repeated)
+  static constexpr int CHUNKS = PLANE / 64;                        // 64-word loads of a plane
+  static constexpr int NC = (CHUNKS + NW - 1) / NW;                // of a wave (of all four planes)
   static constexpr int PITCH = 16 * CT + 4;                        // words of a row of products in LDS
   static constexpr int ENTRIES = (R + 1) * (2 * R + 1);            // window offsets with oy >= 0
   // after the stages, in their place: products [BY][R + 1][16][PITCH], then class sums
@@ -90,33 +90,29 @@ __device__ __forceinline__ void gram_body(const DevView& v, uint32_t kappa, uint
   const uint32_t ky = kappa / K, kx = kappa - ky * K;
   const uint32_t P = v.w * v.h;
 
-  // region load d = w + NW k of a stage (slots past the last repeat it):
-  // plane d / (PLANE / 64), region words 64 (d mod PLANE / 64) + lane; words
-  // past the region read its last pixel
+  // chunk w + NW k of the four planes' region words: word u = 64 chunk + lane
+  // (words past the region read its last pixel) of planes ps bytes apart; an
+  // accepted move of an earlier class waits among the sweep's proposals
   const uint32_t ys = (ky + K * a0 + v.h * (R / v.h + 1) - R) % v.h;
   const uint32_t xs = (kx + K * b0 + v.w * (R / v.w + 1) - R) % v.w;
-  // (an accepted move of an earlier class waits among the sweep's proposals)
-  const char* src[G::D];
-  uint32_t step[G::D];
-  uint32_t pix[G::D], prop[G::D], moved[G::D];
+  const char* src[G::NC];
+  uint32_t ps[G::NC], prop[G::NC], moved[G::NC];
 #pragma unroll
-  for (int k = 0; k < G::D; ++k) {
-    const uint32_t d = min(w + G::NW * k, (uint32_t)G::NLD - 1);
-    const uint32_t pl = d / (G::PLANE / 64);
-    const uint32_t u = min((d % (G::PLANE / 64)) * 64 + lane, (uint32_t)(G::RH * G::RW) - 1);
+  for (int k = 0; k < G::NC; ++k) {
+    const uint32_t u = min((w + G::NW * k) * 64 + lane, (uint32_t)(G::RH * G::RW) - 1);
     const uint32_t rr = u / G::RW, cc = u - rr * G::RW;
     uint32_t y = ys + rr, x = xs + cc;
     while (y >= v.h) y -= v.h;
     while (x >= v.w) x -= v.w;
-    pix[k] = pl * P + y * v.w + x;
+    src[k] = (const char*)v.d8 + (size_t)(y * v.w + x) * 16;
     const uint32_t cls = (y % K) * K + x % K, j = (y / K) * v.cw + x / K;
-    prop[k] = cls * v.pc * (v.tp >> 4) + pl * v.pc + j;
+    prop[k] = cls * v.pc * (v.tp >> 4) + j;
     moved[k] = cls < v.decided ? v.accepts[cls * v.pc + j] : 0u;
   }
 #pragma unroll
-  for (int k = 0; k < G::D; ++k) {
-    src[k] = moved[k] ? (const char*)v.n8_sweep + (size_t)prop[k] * 16 : (const char*)v.d8 + (size_t)pix[k] * 16;
-    step[k] = (moved[k] ? v.pc : P) * 64;
+  for (int k = 0; k < G::NC; ++k) {
+    if (moved[k]) src[k] = (const char*)v.n8_sweep + (size_t)prop[k] * 16;
+    ps[k] = (moved[k] ? v.pc : P) * 16;
   }
   // the class pixels' recounted words: wave w loads words 64 w .. of row
   // w mod BY (class pixels past the tile read pixel 0; their products are not
@@ -127,12 +123,16 @@ __device__ __forceinline__ void gram_body(const DevView& v, uint32_t kappa, uint
     const char* nb = (const char*)v.n8 + (size_t)st * 64 * v.pc;
     u32x4* to = lds4 + buf * G::STAGE;
 #pragma unroll
-    for (int k = 0; k < G::D; ++k)
-      __builtin_amdgcn_global_load_lds(
-          (const __attribute__((address_space(1))) void*)src[k],
-          (__attribute__((address_space(3))) void*)(to + 64 * min(w + G::NW * k, (uint32_t)G::NLD - 1)), 16, 0, 0);
+    for (int k = 0; k < G::NC; ++k) {
+      if (w + G::NW * k >= (uint32_t)G::CHUNKS) break;   // wave-uniform
 #pragma unroll
-    for (int k = 0; k < G::D; ++k) src[k] += step[k];
+      for (int pl = 0; pl < 4; ++pl) {
+        __builtin_amdgcn_global_load_lds(
+            (const __attribute__((address_space(1))) void*)src[k],
+            (__attribute__((address_space(3))) void*)(to + pl * G::PLANE + 64 * (w + G::NW * k)), 16, 0, 0);
+        src[k] += ps[k];
+      }
+    }
     __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(nb + nsrc),
                                      (__attribute__((address_space(3))) void*)(to + 4 * G::PLANE + 64 * (w % G::BY)),
                                      16, 0, 0);
