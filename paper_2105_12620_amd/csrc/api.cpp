@@ -9,6 +9,7 @@
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
+#include <mutex>
 #include <string>
 #include <vector>
 
@@ -209,7 +210,8 @@ struct bn_problem_s {
   std::vector<double> cls_w;
   std::vector<void*> allocs;
   uint32_t list_cap = 0;
-  // rows on their way to the host (stage_rows)
+  // rows and sampler queries on their way (stage_rows)
+  std::mutex stage_mutex;
   void* stage = nullptr;
   size_t stage_bytes = 0;
   uint16_t* list_cnt = nullptr;
@@ -401,10 +403,12 @@ bn_status sync(bn_problem p) {
 
 // Rows of row_bytes bytes that the problem's staging buffer takes at a time, of
 // `rows`.  The buffer is kept with the problem, at most 64 MiB (larger results
-// cross in several rounds); 0 if there is no memory for it.
+// cross in several rounds); 0 if there is no memory for it.  Called, and the
+// buffer used, with stage_mutex held.
+constexpr size_t STAGE_MAX = (size_t)64 << 20;
+
 uint32_t stage_rows(bn_problem p, uint32_t rows, size_t row_bytes) {
-  const size_t most = (size_t)64 << 20;
-  const size_t want = std::min(rows * row_bytes, std::max(most, row_bytes));
+  const size_t want = std::min(rows * row_bytes, std::max(STAGE_MAX, row_bytes));
   if (p->stage_bytes < want) {
     if (sync(p) != BN_OK) return 0;
     if (p->stage) (void)hipFree(p->stage);
@@ -425,6 +429,7 @@ uint32_t stage_rows(bn_problem p, uint32_t rows, size_t row_bytes) {
 // Synchronises.
 bn_status untile_counts(bn_problem p, const uint16_t* dev, uint32_t rows, uint16_t* host) {
   const uint32_t t = p->v.t, tp = p->v.tp;
+  std::lock_guard<std::mutex> lock(p->stage_mutex);
   if (const uint32_t per = stage_rows(p, rows, (size_t)t * 2)) {
     for (uint32_t r = 0; r < rows; r += per) {
       const uint32_t n = std::min(per, rows - r);
@@ -455,6 +460,34 @@ bn_status untile_narrow(bn_problem p, const int8_t* dev, uint32_t rows, uint16_t
     const int base = (int)(((0x00800080u - bias[i / 2]) >> (16 * (i & 1))) & 0xFFFFu);
     for (uint32_t r = 0; r < rows; ++r)
       host[(size_t)r * t + i] = (uint16_t)(tmp[((size_t)(i >> 4) * rows + r) * 16 + (i & 15)] + base);
+  }
+  return BN_OK;
+}
+
+// The dimension pairs' tables, once each pair's own work is done.
+bn_status sampler_pairs(const bn_problem* pairs, uint32_t npairs, std::vector<SamplerPair>& tab) {
+  tab.resize(npairs);
+  for (uint32_t d = 0; d < npairs; ++d) {
+    const bn_problem p = pairs[d];
+    if (!p) return fail(BN_EINVAL, "pair %u is NULL", d);
+    if (!p->have_offsets) return fail(BN_ESTATE, "pair %u has no offsets", d);
+    tab[d] = SamplerPair{p->v.lat, p->v.U, p->v.w, p->v.h, p->v.n, p->v.log2n};
+    // the pair's own work (sweeps) must be finished before its tile is read
+    bn_status s = sync(p);
+    if (s != BN_OK) return s;
+    if (p->aux) HIPCHK(hipStreamSynchronize(p->aux));
+  }
+  return BN_OK;
+}
+
+// The query's launches on st, SAMPLER_PAIRS pairs at a time.
+bn_status sampler_query(const std::vector<SamplerPair>& tab, const uint32_t* x, const uint32_t* y, const uint32_t* k,
+                        uint32_t m, float* out, hipStream_t st) {
+  for (uint32_t d = 0; d < tab.size(); d += SAMPLER_PAIRS) {
+    SamplerPairs some{};
+    const uint32_t n = std::min<uint32_t>(SAMPLER_PAIRS, (uint32_t)tab.size() - d);
+    std::copy(tab.begin() + d, tab.begin() + d + n, some.pair);
+    HIPCHK(launch_sample(some, d, n, (uint32_t)tab.size(), x, y, k, m, out, st));
   }
   return BN_OK;
 }
@@ -1797,6 +1830,7 @@ bn_status bn_get_errors(bn_problem p, float* host) {
   bn_status rs = refresh_errors(p);
   if (rs != BN_OK) return rs;
   const size_t P = (size_t)p->v.w * p->v.h, row = (size_t)(p->v.t + p->v.tg) * 4;
+  std::lock_guard<std::mutex> lock(p->stage_mutex);
   if (const uint32_t per = stage_rows(p, (uint32_t)P, row)) {
     for (uint32_t r = 0; r < P; r += per) {
       const uint32_t n = std::min(per, (uint32_t)P - r);
@@ -2016,26 +2050,12 @@ bn_status bn_sample_device(const bn_problem* pairs, uint32_t npairs, const uint3
                            const uint32_t* k, uint32_t m, float* out, void* stream) {
   if (!pairs || !npairs) return fail(BN_EINVAL, "no dimension pairs");
   if (m && (!x || !y || !k || !out)) return fail(BN_EINVAL, "NULL query or output buffer");
-  std::vector<SamplerPair> tab(npairs);
-  for (uint32_t d = 0; d < npairs; ++d) {
-    const bn_problem p = pairs[d];
-    if (!p) return fail(BN_EINVAL, "pair %u is NULL", d);
-    if (!p->have_offsets) return fail(BN_ESTATE, "pair %u has no offsets", d);
-    tab[d] = SamplerPair{p->v.lat, p->v.U, p->v.w, p->v.h, p->v.n, p->v.log2n};
-    // the pair's own work (sweeps) must be finished before its tile is read
-    bn_status s = sync(p);
-    if (s != BN_OK) return s;
-    if (p->aux) HIPCHK(hipStreamSynchronize(p->aux));
-  }
-  if (!m) return BN_OK;
+  std::vector<SamplerPair> tab;
+  bn_status s = sampler_pairs(pairs, npairs, tab);
+  if (s != BN_OK || !m) return s;
   hipStream_t st = stream ? (hipStream_t)stream : pairs[0]->stream;
-  SamplerPair* dtab = nullptr;
-  HIPCHK(hipMalloc((void**)&dtab, npairs * sizeof(SamplerPair)));
-  hipError_t e = hipMemcpyAsync(dtab, tab.data(), npairs * sizeof(SamplerPair), hipMemcpyHostToDevice, st);
-  if (e == hipSuccess) e = launch_sample(dtab, npairs, x, y, k, m, out, st);
-  if (e == hipSuccess) e = hipStreamSynchronize(st);
-  (void)hipFree(dtab);
-  if (e != hipSuccess) return fail(BN_EHIP, "sampler query: %s", hipGetErrorString(e));
+  if ((s = sampler_query(tab, x, y, k, m, out, st)) != BN_OK) return s;
+  HIPCHK(hipStreamSynchronize(st));
   return BN_OK;
 }
 
@@ -2043,30 +2063,38 @@ bn_status bn_sample(const bn_problem* pairs, uint32_t npairs, const uint32_t* x,
                     const uint32_t* k, uint32_t m, float* out) {
   if (!pairs || !npairs) return fail(BN_EINVAL, "no dimension pairs");
   if (m && (!x || !y || !k || !out)) return fail(BN_EINVAL, "NULL query or output buffer");
-  if (!m) return bn_sample_device(pairs, npairs, nullptr, nullptr, nullptr, 0, nullptr, nullptr);
-  uint32_t* dq = nullptr;
-  float* dout = nullptr;
-  const size_t nout = (size_t)m * 2 * npairs;
-  hipError_t e = hipMalloc((void**)&dq, (size_t)3 * m * 4);
-  if (e == hipSuccess) e = hipMalloc((void**)&dout, nout * 4);
-  if (e != hipSuccess) {
-    (void)hipGetLastError();
-    if (dq) (void)hipFree(dq);
-    return fail(BN_ENOMEM, "sampler query buffers: %s", hipGetErrorString(e));
+  std::vector<SamplerPair> tab;
+  bn_status s = sampler_pairs(pairs, npairs, tab);
+  if (s != BN_OK || !m) return s;
+  // queries and results in the first pair's staging buffer where they fit it
+  const bn_problem p = pairs[0];
+  const size_t qbytes = ((size_t)3 * m * 4 + 255) & ~(size_t)255, nout = (size_t)m * 2 * npairs * 4;
+  std::lock_guard<std::mutex> lock(p->stage_mutex);
+  void* own = nullptr;
+  if (qbytes + nout > STAGE_MAX || !stage_rows(p, 1, qbytes + nout)) {
+    const hipError_t e = hipMalloc(&own, qbytes + nout);
+    if (e != hipSuccess) {
+      (void)hipGetLastError();
+      return fail(BN_ENOMEM, "sampler query buffers: %s", hipGetErrorString(e));
+    }
   }
-  hipStream_t st = pairs[0] ? pairs[0]->stream : nullptr;
-  e = hipMemcpyAsync(dq, x, (size_t)m * 4, hipMemcpyHostToDevice, st);
+  uint32_t* dq = (uint32_t*)(own ? own : p->stage);
+  float* dout = (float*)((char*)dq + qbytes);
+  hipStream_t st = p->stream;
+  hipError_t e = hipMemcpyAsync(dq, x, (size_t)m * 4, hipMemcpyHostToDevice, st);
   if (e == hipSuccess) e = hipMemcpyAsync(dq + m, y, (size_t)m * 4, hipMemcpyHostToDevice, st);
   if (e == hipSuccess) e = hipMemcpyAsync(dq + 2 * (size_t)m, k, (size_t)m * 4, hipMemcpyHostToDevice, st);
-  bn_status s = BN_OK;
   if (e != hipSuccess) s = fail(BN_EHIP, "sampler query upload: %s", hipGetErrorString(e));
-  if (s == BN_OK) s = bn_sample_device(pairs, npairs, dq, dq + m, dq + 2 * (size_t)m, m, dout, st);
+  if (s == BN_OK) s = sampler_query(tab, dq, dq + m, dq + 2 * (size_t)m, m, dout, st);
   if (s == BN_OK) {
-    e = hipMemcpy(out, dout, nout * 4, hipMemcpyDeviceToHost);
+    e = hipMemcpyAsync(out, dout, nout, hipMemcpyDeviceToHost, st);
+    if (e == hipSuccess) e = hipStreamSynchronize(st);
     if (e != hipSuccess) s = fail(BN_EHIP, "sampler query download: %s", hipGetErrorString(e));
   }
-  (void)hipFree(dq);
-  (void)hipFree(dout);
+  if (own) {
+    (void)hipStreamSynchronize(st);
+    (void)hipFree(own);
+  }
   return s;
 }
 
