@@ -41,6 +41,32 @@ TRAFFIC_FILE = os.path.join(ROOT, "profiles", "traffic_tile256_n256_t1024_fp32.m
 COUNT_KERNEL_SOURCES = ("lattice_lines.h", "bnlat_dev.h", "device_common.h", "count.hip")
 
 
+def shortest(n: int, g) -> tuple:
+    """The lattice's L1-shortest vector in units of 1 / N, and N if there is none."""
+    half = n // 2
+    vec = [((i * g[0] + half) % n - half, (i * g[1] + half) % n - half) for i in range(1, n)] or [(n, 0)]
+    return min(vec, key=lambda v: abs(v[0]) + abs(v[1]))
+
+
+def count_ops_per_pair(n: int, g) -> float:
+    """Vector lane-operations that counting one integrand's hits at one pixel
+    needs: per lattice line a 64-bit addition, a clamp and half a three-operand
+    addition (|x| + |y| lines for the shortest vector (x, y)); up to N = 8 a dot
+    product, half a sign gather and a quarter of a three-operand addition per
+    sample."""
+    x, y = shortest(n, g)
+    return 2.5 * (abs(x) + abs(y)) if n >= 16 else 1.75 * n
+
+
+def operand_bytes(n: int, g) -> int:
+    """Bytes of a count in the colour phases: int8 deviations from a base where
+    the bound on them allows, else uint16."""
+    x, y = shortest(n, g)
+    lines, longest = abs(x) + abs(y), max(abs(x), abs(y))
+    dev = min(max(1, n // 2), lines + 1 + -(-n // longest) if n > 64 else n)
+    return 1 if dev <= 126 else 2
+
+
 def kernel_digest() -> str:
     """sha256 over the sources the counting kernel is compiled from."""
     import hashlib
@@ -324,7 +350,7 @@ def main() -> int:
         torch.cuda.synchronize()
         ms = e0.elapsed_time(e1)
         pix = sum(mw["width"] * mw["height"] for mw in members)
-        ops = sum(2.0 * mw["width"] * mw["height"] * mw["n"] * mw["t_heaviside"] for mw in members)
+        ops = sum(count_ops_per_pair(mw["n"], mw["g"]) * mw["width"] * mw["height"] * mw["t_heaviside"] for mw in members)
         out = {"value": pix * steps / (ms * 1e-3), "unit": "pixel-updates/s", "members": len(members),
                "count_lane_ops_per_sweep": ops,
                "pixels": pix, "sweeps": steps, "ms_per_sweep": ms / steps, "tuning": b.tuning(),
@@ -420,21 +446,20 @@ def main() -> int:
     prec_large = precision_large() if "precision_large" in forms else None
 
     # Algorithmic work per launch of the counting kernel (one sweep-wide
-    # recount): N*T predicates per proposal at two vector lane-operations each
-    # (int16 dot product + sign test).  The kernel's own instruction count is
-    # 1.75 per predicate (one v_dot2, half a v_perm_b32, a quarter of a
-    # v_add3_u32), reported beside it.
-    count_ops = 2.0 * P * N * T
+    # recount): the lattice's lines per proposal and integrand.
+    pair_ops = count_ops_per_pair(N, w["g"])
+    count_ops = pair_ops * P * T
     count_tops = count_ops / (avg["recount_per_sweep"] * 1e-3) / 1e12
     win = (2 * w["radius"] + 1) ** 2 - 1
-    # evaluation of a phase: the tile's counts once (2 B each) plus the moved
-    # pixels' proposal rows, and the decisions
-    delta_bytes = 2.0 * T * (P + M) + 9.0 * M
-    # a swap pass reads the tile's counts once and every member's partner row
-    swap_bytes = 2.0 * T * (P + M)
-    # the stencils' arithmetic: one product per (moved pixel, window offset,
-    # integrand), two per v_dot2 lane-instruction
-    stencil_lane_ops = M * win * T / 2.0
+    # evaluation of a phase: the tile's field once (1 byte an integrand as int8
+    # deviations, else 2) plus the moved pixels' proposal rows, and the decisions
+    ob = operand_bytes(N, w["g"])
+    delta_bytes = ob * T * (P + M) + 9.0 * M
+    # a swap pass reads the tile's field once and every member's partner row
+    swap_bytes = ob * T * (P + M)
+    # the neighbour products: one per (moved pixel, window offset, integrand);
+    # the swap stencil forms four (int8) or two per lane-instruction
+    products = M * win * T
 
     def roof(bound, achieved, unit, kernel, work):
         vendor = {"hbm": HBM_PEAK_GBS, "alu": VALU_PEAK_TOPS, "mfma": MFMA_BF16_PEAK_TFLOPS}[bound]
@@ -452,10 +477,9 @@ def main() -> int:
         "config": {"workload": args.workload, "tile": f"{w['width']}x{w['height']}", "n": N, "t": T,
                    "window": f"{2 * w['radius'] + 1}x{2 * w['radius'] + 1}", "colour_classes": K2,
                    "precision": "fp32", "mutation": "redraw"},
-        "roofline": dict(roof("alu", count_tops, "TOP/s", "k_count<64, 4, 3> (sweep-wide proposal recount)",
-                              f"{P} pixels x {N} samples x {T} integrands x 2 lane-ops"),
-                         traffic=measured_traffic(),
-                         frac_at_instruction_count=0.875 * count_tops / VALU_PEAK_TOPS),
+        "roofline": dict(roof("alu", count_tops, "TOP/s", "k_count (sweep-wide proposal recount)",
+                              f"{P} pixels x {T} integrands x {pair_ops:g} lane-ops"),
+                         traffic=measured_traffic()),
         "measured_peaks": peaks,
         "kernels_ms": avg,
         "evaluate_hbm_gbs": delta_bytes / (avg["evaluate_per_phase"] * 1e-3) / 1e9,
@@ -464,11 +488,9 @@ def main() -> int:
                            "hbm_gbs": delta_bytes / (fp32["evaluate_alone_ms"] * 1e-3) / 1e9,
                            "frac": delta_bytes / (fp32["evaluate_alone_ms"] * 1e-3) / 1e9 / HBM_PEAK_GBS,
                            "roofline": roof("hbm", delta_bytes / (fp32["evaluate_alone_ms"] * 1e-3) / 1e9,
-                                            "GB/s", "k_delta_stage + k_delta_finish (one colour phase, alone)",
-                                            f"tile counts once + {M} proposal rows, 2 B per integrand"),
-                           "roofline_alu": roof("alu", stencil_lane_ops / (fp32["evaluate_alone_ms"] * 1e-3) / 1e12,
-                                                "TOP/s", "k_delta_stage + k_delta_finish (one colour phase, alone)",
-                                                f"{M} pixels x {win} offsets x {T} integrands / 2 per v_dot2")},
+                                            "GB/s", "energy change and decision of one colour phase, alone",
+                                            f"tile's field once + {M} proposal rows, {ob} B per integrand"),
+                           "useful_product_tops": 2.0 * products / (fp32["evaluate_alone_ms"] * 1e-3) / 1e12},
         "graph_value": P * args.steps / (fp32["graph_ms"] * 1e-3),
         "bf16": None if bf16 is None else {
             "value": P * args.steps / (bf16["total_ms"] * 1e-3),
@@ -477,9 +499,9 @@ def main() -> int:
             "evaluate_hbm_gbs": delta_bytes / (bf16["kernels_ms"]["evaluate_per_phase"] * 1e-3) / 1e9,
             "evaluate_alone_ms_per_phase": bf16["evaluate_alone_ms"],
             "roofline": roof("hbm", delta_bytes / (bf16["evaluate_alone_ms"] * 1e-3) / 1e9, "GB/s",
-                             "BF16 matrix-core energy change of one colour phase, run alone",
-                             f"tile counts once + {M} proposal rows, 2 B per integrand"),
-            "mfma_useful_tflops": 2.0 * win * T * M / (bf16["evaluate_alone_ms"] * 1e-3) / 1e12,
+                             "BF16 form's energy change of one colour phase, run alone",
+                             f"tile's field once + {M} proposal rows, {ob} B per integrand"),
+            "mfma_useful_tflops": 2.0 * products / (bf16["evaluate_alone_ms"] * 1e-3) / 1e12,
             "energy_rel_diff_vs_fp32": abs(bf16["energy"] - fp32["energy"]) / abs(fp32["energy"]),
             "quality_rel_diff_vs_fp32": max(abs(a - b) / b for a, b in zip(bf16["quality_sigma_1_4_16"],
                                                                             fp32["quality_sigma_1_4_16"]))},
@@ -493,14 +515,14 @@ def main() -> int:
             "evaluate_hbm_gbs": swap_bytes / (swap["kernels_ms"]["evaluate_per_phase"] * 1e-3) / 1e9,
             "roofline": roof("hbm", swap_bytes / (swap["kernels_ms"]["evaluate_per_phase"] * 1e-3) / 1e9, "GB/s",
                              "k_swap_stage (class sums of one swap pass)",
-                             f"tile counts once + {M} partner rows ({T} integrands x 2 B)"),
-            "roofline_alu": roof("alu", stencil_lane_ops / (swap["kernels_ms"]["evaluate_per_phase"] * 1e-3) / 1e12,
+                             f"tile's field once + {M} partner rows ({T} integrands x {ob} B)"),
+            "roofline_alu": roof("alu", products * ob / 4 / (swap["kernels_ms"]["evaluate_per_phase"] * 1e-3) / 1e12,
                                  "TOP/s", "k_swap_stage (class sums of one swap pass)",
-                                 f"{M} members x {win} offsets x {T} integrands / 2 per v_dot2")},
+                                 f"{M} members x {win} offsets x {T} integrands, {4 // ob} per lane-instruction")},
         "batched": None if batch is None else dict(batch, roofline=roof(
             "alu", batch["count_lane_ops_per_sweep"] / (batch["ms_per_sweep"] * 1e-3) / 1e12, "TOP/s",
             "whole batched sweep (recounts of every member's proposals over the sweep time)",
-            "sum over members of P N T x 2 lane-ops")),
+            "sum over members of P T x the lattice lines' lane-ops")),
         "batched_large": big,
         "precision_large": prec_large,
         "window_offsets": win,
