@@ -10,6 +10,7 @@
 #include <cstdlib>
 #include <cstring>
 #include <mutex>
+#include <optional>
 #include <string>
 #include <vector>
 
@@ -402,10 +403,10 @@ bn_status sync(bn_problem p) {
 }
 
 // Rows of row_bytes bytes that the problem's staging buffer takes at a time, of
-// `rows`.  The buffer is kept with the problem, at most 64 MiB (larger results
-// cross in several rounds); 0 if there is no memory for it.  Called, and the
+// `rows`.  The buffer is kept with the problem, at most STAGE_MAX bytes (larger
+// results cross in several rounds); 0 if there is no memory for it.  Called, and the
 // buffer used, with stage_mutex held.
-constexpr size_t STAGE_MAX = (size_t)64 << 20;
+constexpr size_t STAGE_MAX = (size_t)128 << 20;
 
 uint32_t stage_rows(bn_problem p, uint32_t rows, size_t row_bytes) {
   const size_t want = std::min(rows * row_bytes, std::max(STAGE_MAX, row_bytes));
@@ -423,6 +424,27 @@ uint32_t stage_rows(bn_problem p, uint32_t rows, size_t row_bytes) {
   }
   return (uint32_t)std::min<size_t>(rows, p->stage_bytes / row_bytes);
 }
+
+// Scratch of one call: the staging buffer where it fits, else an allocation of
+// its own (base is null without memory for either).  Freed with the call.
+struct CallScratch {
+  std::lock_guard<std::mutex> lock;
+  void* own = nullptr;
+  char* base = nullptr;
+  CallScratch(bn_problem p, size_t bytes) : lock(p->stage_mutex) {
+    if (bytes <= STAGE_MAX && stage_rows(p, 1, bytes)) {
+      base = (char*)p->stage;
+    } else if (hipMalloc(&own, bytes) == hipSuccess) {
+      base = (char*)own;
+    } else {
+      (void)hipGetLastError();
+      own = nullptr;
+    }
+  }
+  ~CallScratch() {
+    if (own) (void)hipFree(own);   // waits for the device
+  }
+};
 
 // Copy a tiled count buffer ([tp/8][rows][8] uint16 on the device) to host
 // rows [rows][t], laid out on the device (without memory for that, here).
@@ -1673,25 +1695,24 @@ bn_status bn_quality_metric_family(bn_problem p, bn_rows rows, const double* sig
   const size_t P = (size_t)p->v.w * p->v.h;
   const uint32_t pitch_max = std::max(p->v.tp, p->v.tgp);
   const uint32_t nparts = blur_partials(p->v, pitch_max);
-  float *tmp = nullptr, *kx = nullptr, *ky = nullptr;
-  int2 *rx = nullptr, *ry = nullptr;
-  double* part = nullptr;
-  // Scratch for the blur lives for the duration of the call only.
-  auto release = [&]() {
-    for (void* q : {(void*)tmp, (void*)kx, (void*)ky, (void*)rx, (void*)ry, (void*)part})
-      if (q) (void)hipFree(q);
+  float *tmp, *kx, *ky;
+  int2 *rx, *ry;
+  double* part;
+  auto lay = [&](Carve& c) {
+    tmp = c.take<float>(P * pitch_max);
+    kx = c.take<float>(p->v.w + BLUR_BLOCK);
+    ky = c.take<float>(p->v.h + BLUR_BLOCK);
+    rx = c.take<int2>(p->v.w);
+    ry = c.take<int2>(p->v.h);
+    part = c.take<double>(nparts);
   };
-  hipError_t e = hipMalloc((void**)&tmp, P * pitch_max * sizeof(float));
-  if (e == hipSuccess) e = hipMalloc((void**)&kx, (p->v.w + BLUR_BLOCK) * sizeof(float));
-  if (e == hipSuccess) e = hipMalloc((void**)&ky, (p->v.h + BLUR_BLOCK) * sizeof(float));
-  if (e == hipSuccess) e = hipMalloc((void**)&rx, p->v.w * sizeof(int2));
-  if (e == hipSuccess) e = hipMalloc((void**)&ry, p->v.h * sizeof(int2));
-  if (e == hipSuccess) e = hipMalloc((void**)&part, (size_t)nparts * sizeof(double));
-  if (e != hipSuccess) {
-    (void)hipGetLastError();
-    release();
-    return fail(BN_ENOMEM, "quality metric scratch: %s", hipGetErrorString(e));
-  }
+  Carve measure, c;
+  lay(measure);
+  CallScratch scratch(p, measure.off);
+  if (!scratch.base) return fail(BN_ENOMEM, "quality metric scratch of %zu bytes", measure.off);
+  c.base = scratch.base;
+  lay(c);
+  hipError_t e = hipSuccess;
   std::vector<double> hp(nparts);
   for (uint32_t i = 0; i < n; ++i) {
     std::vector<float> hkx, hky;
@@ -1715,13 +1736,12 @@ bn_status bn_quality_metric_family(bn_problem p, bn_rows rows, const double* sig
       for (uint32_t b = 0; b < np && e == hipSuccess; ++b) acc += hp[b];
     }
     if (e != hipSuccess) {
-      release();
+      (void)hipStreamSynchronize(p->stream);
       return fail(BN_EHIP, "quality metric: %s", hipGetErrorString(e));
     }
     const uint32_t count = rows == BN_ROWS_HEAVISIDE ? p->v.t : rows == BN_ROWS_GAUSSIAN ? p->v.tg : p->v.t + p->v.tg;
     out[i] = std::sqrt(acc / ((double)P * count));
   }
-  release();
   return BN_OK;
 }
 
@@ -1740,33 +1760,34 @@ bn_status bn_error_spectrum(bn_problem p, bn_rows rows, uint32_t nbins, double* 
     twx[k] = make_float2((float)std::cos(2.0 * M_PI * k / W), (float)-std::sin(2.0 * M_PI * k / W));
   for (uint32_t k = 0; k < H; ++k)
     twy[k] = make_float2((float)std::cos(2.0 * M_PI * k / H), (float)-std::sin(2.0 * M_PI * k / H));
-  // scratch for the duration of the call only; one chunk a launch if there is
-  // no memory for more
-  float2 *d_rows = nullptr, *d_twx = nullptr, *d_twy = nullptr, *d_mx = nullptr, *d_my = nullptr;
-  double *d_part = nullptr, *d_pw = nullptr;
-  auto release = [&]() {
-    for (void* q : {(void*)d_rows, (void*)d_twx, (void*)d_twy, (void*)d_mx, (void*)d_my, (void*)d_part, (void*)d_pw})
-      if (q) (void)hipFree(q);
-    d_rows = d_twx = d_twy = d_mx = d_my = nullptr;
-    d_part = d_pw = nullptr;
-  };
+  // one chunk a launch if there is no memory for more
+  float2 *d_rows, *d_twx, *d_twy, *d_mx, *d_my;
+  double *d_part, *d_pw;
   uint32_t chunks = spectrum_chunks(p->v, std::max(p->v.t, p->v.tg));
-  hipError_t e = hipSuccess;
-  for (;;) {
+  auto lay = [&](Carve& c) {
     const SpectrumScratch n = spectrum_scratch(p->v, chunks);
-    e = hipMalloc((void**)&d_rows, n.rows * sizeof(float2));
-    if (e == hipSuccess) e = hipMalloc((void**)&d_twx, W * sizeof(float2));
-    if (e == hipSuccess) e = hipMalloc((void**)&d_twy, H * sizeof(float2));
-    if (e == hipSuccess) e = hipMalloc((void**)&d_mx, n.matx * sizeof(float2));
-    if (e == hipSuccess) e = hipMalloc((void**)&d_my, n.maty * sizeof(float2));
-    if (e == hipSuccess) e = hipMalloc((void**)&d_part, n.power * sizeof(double));
-    if (e == hipSuccess) e = hipMalloc((void**)&d_pw, P * sizeof(double));
-    if (e == hipSuccess) break;
-    (void)hipGetLastError();
-    release();
-    if (chunks == 1) return fail(BN_ENOMEM, "spectrum scratch: %s", hipGetErrorString(e));
+    d_rows = c.take<float2>(n.rows);
+    d_twx = c.take<float2>(W);
+    d_twy = c.take<float2>(H);
+    d_mx = c.take<float2>(n.matx);
+    d_my = c.take<float2>(n.maty);
+    d_part = c.take<double>(n.power);
+    d_pw = c.take<double>(P);
+  };
+  std::optional<CallScratch> scratch;
+  for (;;) {
+    Carve measure;
+    lay(measure);
+    scratch.emplace(p, measure.off);
+    if (scratch->base) break;
+    if (chunks == 1) return fail(BN_ENOMEM, "spectrum scratch of %zu bytes", measure.off);
+    scratch.reset();
     chunks = 1;
   }
+  Carve c;
+  c.base = scratch->base;
+  lay(c);
+  hipError_t e = hipSuccess;
   e = hipMemcpyAsync(d_twx, twx.data(), W * sizeof(float2), hipMemcpyHostToDevice, p->stream);
   if (e == hipSuccess) e = hipMemcpyAsync(d_twy, twy.data(), H * sizeof(float2), hipMemcpyHostToDevice, p->stream);
   if (e == hipSuccess) e = launch_twiddles(d_twx, W, d_mx, p->stream);
@@ -1787,7 +1808,7 @@ bn_status bn_error_spectrum(bn_problem p, bn_rows rows, uint32_t nbins, double* 
   std::vector<double> pw(P);
   if (e == hipSuccess) e = hipMemcpyAsync(pw.data(), d_pw, P * sizeof(double), hipMemcpyDeviceToHost, p->stream);
   if (e == hipSuccess) e = hipStreamSynchronize(p->stream);
-  release();
+  scratch.reset();
   if (e != hipSuccess) return fail(BN_EHIP, "error spectrum: %s", hipGetErrorString(e));
   // radial bins: the frequency in cycles per pixel, folded to [-1/2, 1/2),
   // in units of 1 / min(W, H), rounded
@@ -2069,16 +2090,9 @@ bn_status bn_sample(const bn_problem* pairs, uint32_t npairs, const uint32_t* x,
   // queries and results in the first pair's staging buffer where they fit it
   const bn_problem p = pairs[0];
   const size_t qbytes = ((size_t)3 * m * 4 + 255) & ~(size_t)255, nout = (size_t)m * 2 * npairs * 4;
-  std::lock_guard<std::mutex> lock(p->stage_mutex);
-  void* own = nullptr;
-  if (qbytes + nout > STAGE_MAX || !stage_rows(p, 1, qbytes + nout)) {
-    const hipError_t e = hipMalloc(&own, qbytes + nout);
-    if (e != hipSuccess) {
-      (void)hipGetLastError();
-      return fail(BN_ENOMEM, "sampler query buffers: %s", hipGetErrorString(e));
-    }
-  }
-  uint32_t* dq = (uint32_t*)(own ? own : p->stage);
+  CallScratch scratch(p, qbytes + nout);
+  if (!scratch.base) return fail(BN_ENOMEM, "sampler query buffers of %zu bytes", qbytes + nout);
+  uint32_t* dq = (uint32_t*)scratch.base;
   float* dout = (float*)((char*)dq + qbytes);
   hipStream_t st = p->stream;
   hipError_t e = hipMemcpyAsync(dq, x, (size_t)m * 4, hipMemcpyHostToDevice, st);
@@ -2091,10 +2105,7 @@ bn_status bn_sample(const bn_problem* pairs, uint32_t npairs, const uint32_t* x,
     if (e == hipSuccess) e = hipStreamSynchronize(st);
     if (e != hipSuccess) s = fail(BN_EHIP, "sampler query download: %s", hipGetErrorString(e));
   }
-  if (own) {
-    (void)hipStreamSynchronize(st);
-    (void)hipFree(own);
-  }
+  if (s != BN_OK) (void)hipStreamSynchronize(st);
   return s;
 }
 

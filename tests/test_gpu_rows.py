@@ -1,5 +1,5 @@
 """Counts and error rows that cross to the host in more than one round of the
-staging buffer (64 MiB): every row against the other call's, and sampled rows
+staging buffer (128 MiB): every row against the other call's, and sampled rows
 about the rounds' boundaries against the oracle."""
 import numpy as np
 import pytest
@@ -12,7 +12,7 @@ from cases import gpu_problem, say, workload
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("t,tg", [(531, 0), (520, 3)])
+@pytest.mark.parametrize("t,tg", [(1061, 0), (1040, 3)])
 def test_rows_in_several_rounds(t, tg):
     w = workload(n=4, g=(1, 3), width=256, height=256, t_heaviside=t, t_gauss=tg, radius=1)
     say("case rows", t, tg)
@@ -20,11 +20,11 @@ def test_rows_in_several_rounds(t, tg):
     with gpu_problem(w, inp) as p:
         c, e = p.get_counts(), p.get_errors()
         _, area = p.get_integrands()
-    P, mib64 = 256 * 256, 64 << 20
-    assert c.nbytes > mib64 and e.nbytes > mib64
+    P, most = 256 * 256, 128 << 20
+    assert c.nbytes > most and e.nbytes > most
     edge = {0, P - 1}
     for row in (2 * t, 4 * (t + tg)):
-        per = mib64 // row
+        per = most // row
         edge |= {r + d for r in range(per, P, per) for d in (-1, 0, 1)}
     px = np.array(sorted(edge))
     want = estimator.hit_counts(w["n"], w["g"], inp["offsets"].reshape(-1, 2)[px], inp["heaviside"])
