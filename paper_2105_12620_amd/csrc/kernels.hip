@@ -460,19 +460,26 @@ __global__ __launch_bounds__(256) void k_gauss_est(DevView v, uint32_t kappa, ui
 }
 
 // Sweeps whose estimates come from the lattice lines (gauss_lines.hip) decide as
-// the sample by sample estimates would.  Those are off the exact mean by at most
+// the sample by sample estimates would.  Those are off the exact mean g by at most
 // 2^-24 (0.37 + 10 g): the exponent's rounding to FP32 (2^-24 max y 2^-y ln 2),
-// v_exp_f32 and seven FP32 additions per lane, and the result's rounding, as is the
-// lines' (exact but for that); with g <= 1 the two differ by less than
-// eta = 2^-24 11.4, and a Gaussian's part of the energy change,
+// v_exp_f32 and seven FP32 additions per lane, and the result's rounding; the
+// lines' are exact but for that.  The two differ by less than
+// eta(g) = 2^-24 (0.37 + 11 g), and a Gaussian's part of the energy change,
 //   2 sum_m w_m d x_m,  d = g' - g,  x_m = g' + g - 2 g_m,
-// by less than 8 eta sum_m w_m (|x_m| + |d|).  A move whose energy change is
-// within that bound of 0 is listed and its Gaussian part evaluated again from
-// estimates sample by sample (of its window: k_gauss_again), then decided.
-// 512^2, N = 1024, 1024 Gaussians: about a move in a thousand, 0.3 to 1.4 ms a
-// phase (its cost is the exponentials of 122 pixels a move), where estimating
-// every proposal so would take 14.
-constexpr double GAUSS_MARGIN = 8 * 11.4 * 0x1p-24 * 1.01;
+// by less than 2 sum_m w_m (|x_m| + |d|) (eta(g') + eta(g) + 2 eta(g_m)), where
+// g_m <= (g' + g + |x_m|) / 2.  A move whose energy change is within that bound of
+// 0 is listed and its Gaussian part evaluated again from estimates sample by
+// sample (of its window: k_gauss_again), then decided.
+// 512^2, N = 1024, 1024 Gaussians: about one move in 5000, 0.36 ms a phase (its cost
+// is the exponentials of 122 pixels a move), where estimating every proposal so
+// would take 14.  With eta(1) for every g
+// four times as many (1.39 ms).
+//
+// The bound from W = sum w, b = sum w x^2 (sum w |x| <= sqrt(W b)), s = g' + g.
+__device__ __forceinline__ double gauss_margin(double W, double b, double s, double d) {
+  const double r = sqrt(W * b) * (1.0 + 1e-12);
+  return 2.0 * 0x1p-24 * 1.01 * ((W * d + r) * (1.48 + 22.0 * s) + 11.0 * (b + d * r));
+}
 
 // One workgroup per listed move and 16 Gaussians (striding over them).
 template <int R>
@@ -546,18 +553,23 @@ __global__ __launch_bounds__(256) void k_delta_gauss(DevView v, uint32_t kappa, 
     const uint32_t t = base + lane;
     const double gn = v.g_new[(size_t)j * v.tgp + t], go = v.gest[(size_t)p * v.tgp + t];
     const double d = gn - go, sm = gn + go;
+    double b = 0.0, wsum = 0.0;
 #pragma unroll
     for (int mm = 0; mm < W.M; ++mm) {
       const uint32_t q = ((y + v.h + W.oy[mm]) % v.h) * v.w + (x + v.w + W.ox[mm]) % v.w;
       const double e = sm - 2.0 * (double)v.gest[(size_t)q * v.tgp + t];
       cs[W.cls[mm]] += d * e;
-      if (MODE == MODE_CLASS) margin += v.wd[W.cls[mm]] * (fabs(e) + fabs(d));
+      if (MODE == MODE_CLASS) {
+        b += v.wd[W.cls[mm]] * e * e;
+        wsum += v.wd[W.cls[mm]];
+      }
     }
+    if (MODE == MODE_CLASS) margin += gauss_margin(wsum, b, sm, fabs(d));
   }
   if (MODE == MODE_CLASS && v.gmargin) {
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) margin += __shfl_xor(margin, off);
-    if (lane == 0) v.gmargin[j] = GAUSS_MARGIN * margin;
+    if (lane == 0) v.gmargin[j] = margin;
   }
   double acc = 0.0;
 #pragma unroll
@@ -637,16 +649,18 @@ __global__ __launch_bounds__(512) void k_delta_gauss_stage(DevView v, uint32_t k
     if (act) {
       const double gn = v.g_new[(size_t)j * v.tgp + base + lane], go = gl[own * 64 + lane];
       const double d = gn - go, sm = gn + go;
-      double s = 0.0, a = 0.0;   // sums of w x and w |x| over the window
+      double s1 = 0.0, s2 = 0.0;   // sums of w g_m and w g_m^2 over the window
 #pragma unroll
       for (int mm = 0; mm < W.M; ++mm) {
         const int q = own + W.oy[mm] * G::RW + W.ox[mm];
-        const double x = __fma_rn(-2.0, (double)gl[q * 64 + lane], sm);
-        s = __fma_rn(wd[W.cls[mm]], x, s);
-        a = __fma_rn(wd[W.cls[mm]], fabs(x), a);
+        const double g = (double)gl[q * 64 + lane];
+        s1 = __fma_rn(wd[W.cls[mm]], g, s1);
+        s2 = __fma_rn(wd[W.cls[mm]], g * g, s2);
       }
-      acc = __fma_rn(d, s, acc);
-      margin += __fma_rn(wsum, fabs(d), a);
+      acc = __fma_rn(d, __fma_rn(wsum, sm, -2.0 * s1), acc);
+      // sum w x^2, with room for its rounding
+      const double b = __fma_rn(wsum * sm, sm, 4.0 * __fma_rn(-sm, s1, s2));
+      margin += gauss_margin(wsum, fmax(b, 0.0) + 1e-13 * wsum, sm, fabs(d));
     }
   }
   if (!act) return;
@@ -657,7 +671,7 @@ __global__ __launch_bounds__(512) void k_delta_gauss_stage(DevView v, uint32_t k
   }
   if (lane != 0) return;
   v.gdelta[j] = 2.0 * acc;
-  if (v.gmargin) v.gmargin[j] = GAUSS_MARGIN * margin;
+  if (v.gmargin) v.gmargin[j] = margin;
 }
 
 // Gaussian rows' part of the energy: per distance class, sum over the half
