@@ -674,6 +674,117 @@ __global__ __launch_bounds__(512) void k_delta_gauss_stage(DevView v, uint32_t k
   if (v.gmargin) v.gmargin[j] = margin;
 }
 
+// The same for launches with many blocks: a workgroup owns 8 x BCY class pixels
+// and 16 Gaussians at a time, a thread four neighbouring pixels of a row and one
+// Gaussian, so that a window row's values are read from LDS, and converted and
+// squared, once for four pixels (12 against 30 a pixel at r = 5, K = 2), and the
+// region from memory once for 64 (10 pixels of it a pixel against 28).  Bound by
+// the FP64 FMAs.  512^2, N = 1024, 1024 Gaussians, r = 5: 0.91 ms a phase, 1.52 with
+// k_delta_gauss_stage.
+template <int R, int K>
+struct GaussTile {
+  static constexpr int BCX = 8, BCY = K == 4 ? 4 : 8, PX = 4, NT = BCX / PX * BCY * 16;
+  static constexpr int RH = K * (BCY - 1) + 2 * R + 1, RW = K * (BCX - 1) + 2 * R + 1, RA = RH * RW;
+  static constexpr int LDS_BYTES = RA * 16 * 4;
+};
+
+template <int R, int K>
+__global__ __launch_bounds__((GaussTile<R, K>::NT)) void k_delta_gauss_tile(DevView v, uint32_t kappa, uint32_t gx) {
+  using G = GaussTile<R, K>;
+  constexpr Window<R> W = WinConst<R>::w;
+  constexpr int NCLS = WinConst<R>::NCLS, S = 2 * R + 1, COLS = K * (G::PX - 1) + S;
+  constexpr int ITER = (G::RA * 4 + G::NT - 1) / G::NT;
+  extern __shared__ float gl[];                  // [RA][16] estimates of the region
+  const uint32_t tid = threadIdx.x, t = tid & 15, grp = tid >> 4;
+  // (four consecutive rows a wave: their words meet different banks)
+  const uint32_t cy = grp % G::BCY, half = grp / G::BCY;
+  const uint32_t wk = xcd_block(blockIdx.x, gridDim.x), a0 = wk / gx * G::BCY, b0 = wk % gx * G::BCX;
+  const uint32_t ky = kappa / K, kx = kappa - ky * K;
+  const uint32_t ys = (ky + K * a0 + v.h * (R / v.h + 1) - R) % v.h;
+  const uint32_t xs = (kx + K * b0 + v.w * (R / v.w + 1) - R) % v.w;
+  uint32_t goff[ITER];
+#pragma unroll
+  for (int it = 0; it < ITER; ++it) {
+    const uint32_t r = min((tid + it * G::NT) >> 2, (uint32_t)G::RA - 1);
+    const uint32_t rr = r / G::RW, cc = r - rr * G::RW;
+    uint32_t y = ys + rr, x = xs + cc;
+    while (y >= v.h) y -= v.h;
+    while (x >= v.w) x -= v.w;
+    goff[it] = y * v.w + x;
+  }
+  bool act[G::PX];
+  uint32_t j[G::PX];
+#pragma unroll
+  for (int i = 0; i < G::PX; ++i) {
+    const uint32_t a = a0 + cy, b = b0 + G::PX * half + i;
+    act[i] = a < v.ch && b < v.cw;
+    j[i] = act[i] ? a * v.cw + b : 0;
+  }
+  double wd[NCLS], wsum = 0.0;
+#pragma unroll
+  for (int c = 0; c < NCLS; ++c) {
+    wd[c] = v.wd[c];
+    wsum += (double)W.csize[c] * wd[c];
+  }
+  const float* col0 = gl + (K * cy * G::RW + K * G::PX * half) * 16 + t;   // window corner of the first pixel
+  double acc[G::PX], margin[G::PX];
+#pragma unroll
+  for (int i = 0; i < G::PX; ++i) acc[i] = margin[i] = 0.0;
+  for (uint32_t base = 0; base < v.tgp; base += 16) {
+    f32x4 q[ITER];
+#pragma unroll
+    for (int it = 0; it < ITER; ++it)
+      q[it] = *(const f32x4*)(v.gest + (size_t)goff[it] * v.tgp + base + 4 * ((tid + it * G::NT) & 3));
+    float gn[G::PX];
+#pragma unroll
+    for (int i = 0; i < G::PX; ++i) gn[i] = v.g_new[(size_t)j[i] * v.tgp + base + t];
+    __syncthreads();
+#pragma unroll
+    for (int it = 0; it < ITER; ++it) {
+      const uint32_t idx = tid + it * G::NT;
+      if (idx < (uint32_t)G::RA * 4) *(f32x4*)&gl[idx * 4] = q[it];
+    }
+    __syncthreads();
+    double s1[G::PX], s2[G::PX];   // sums of w g_m and w g_m^2 over the window
+#pragma unroll
+    for (int i = 0; i < G::PX; ++i) s1[i] = s2[i] = 0.0;
+#pragma unroll
+    for (int oy = 0; oy < S; ++oy) {
+#pragma unroll
+      for (int x = 0; x < COLS; ++x) {
+        const double g = (double)col0[(oy * G::RW + x) * 16], gg = g * g;
+#pragma unroll
+        for (int i = 0; i < G::PX; ++i) {
+          const int ox = x - K * i;
+          if (ox < 0 || ox >= S || (ox == R && oy == R)) continue;
+          const double w = wd[W.cmap[oy * S + ox]];
+          s1[i] = __fma_rn(w, g, s1[i]);
+          s2[i] = __fma_rn(w, gg, s2[i]);
+        }
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < G::PX; ++i) {
+      const double go = (double)col0[(R * G::RW + K * i + R) * 16], d = (double)gn[i] - go, sm = (double)gn[i] + go;
+      acc[i] = __fma_rn(d, __fma_rn(wsum, sm, -2.0 * s1[i]), acc[i]);
+      const double b = __fma_rn(wsum * sm, sm, 4.0 * __fma_rn(-sm, s1[i], s2[i]));
+      margin[i] += gauss_margin(wsum, fmax(b, 0.0) + 1e-13 * wsum, sm, fabs(d));
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < G::PX; ++i) {
+#pragma unroll
+    for (int off = 8; off > 0; off >>= 1) {
+      acc[i] += __shfl_xor(acc[i], off);
+      margin[i] += __shfl_xor(margin[i], off);
+    }
+    if (t == 0 && act[i]) {
+      v.gdelta[j[i]] = 2.0 * acc[i];
+      if (v.gmargin) v.gmargin[j[i]] = margin[i];
+    }
+  }
+}
+
 // Gaussian rows' part of the energy: per distance class, sum over the half
 // window of |g_p - g_q|^2 (FP64 atomics; doubled by the host).
 template <int R>
@@ -919,6 +1030,15 @@ hipError_t gauss_delta_dispatch(const DevView& v, uint32_t kappa, uint32_t m, hi
 
 template <int R, int K>
 hipError_t gauss_stage_launch(const DevView& v, uint32_t kappa, hipStream_t s) {
+  using T = GaussTile<R, K>;
+  if constexpr (T::LDS_BYTES <= 65536) {
+    // tiles from 256 blocks on, a workgroup per CU; smaller blocks below
+    const uint32_t gx = (v.cw + T::BCX - 1) / T::BCX, blocks = gx * ((v.ch + T::BCY - 1) / T::BCY);
+    if (blocks >= 256) {
+      hipLaunchKernelGGL((k_delta_gauss_tile<R, K>), dim3(blocks), dim3(T::NT), (size_t)T::LDS_BYTES, s, v, kappa, gx);
+      return hipGetLastError();
+    }
+  }
   using G = GaussStage<R, K>;
   if constexpr (G::LDS_BYTES > 65536) {
     return gauss_delta_dispatch<MODE_CLASS>(v, kappa, v.pc, s);
