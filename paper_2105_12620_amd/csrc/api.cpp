@@ -237,6 +237,7 @@ struct bn_problem_s {
   uint8_t* accepts = nullptr;   // the sweep's decisions where its moves wait (moves_wait)
   bool sets_ready = false;
   uint64_t prefetched = ~0ull;
+  uint64_t recount_from = ~0ull;   // the recount index (counter word 3) is one past this sweep
   hipStream_t aux = nullptr;
   hipEvent_t ev[5] = {nullptr, nullptr, nullptr, nullptr, nullptr};
   hipGraph_t pair_graph = nullptr;
@@ -775,8 +776,10 @@ bn_status overlapped_sweeps(bn_problem p, uint32_t k) {
   }
   if (k >= 2 && !p->profiling && (s = build_pair_graph(p)) != BN_OK) return s;
   // the recount index one past the sweep counter, which other calls may have
-  // moved
-  if (k >= 2) HIPCHK(launch_recount_index(p->v, p->stream));
+  // moved (a pair moves both by two: a launch ahead of every pair cost a call of
+  // two sweeps of 32^2, N = 16, T = 64 20 of 110 us)
+  if (k >= 2 && p->recount_from != p->sweep) HIPCHK(launch_recount_index(p->v, p->stream));
+  if (k >= 2) p->recount_from = ~0ull;   // until the pairs are launched
   uint32_t done = 0;
   while (k - done >= 2) {
     if (p->pair_exec && !p->pair_failed && !p->profiling) {
@@ -786,6 +789,7 @@ bn_status overlapped_sweeps(bn_problem p, uint32_t k) {
     }
     done += 2;
   }
+  if (done) p->recount_from = p->sweep + done;
   if (done < k) {
     // one more sweep, then the next sweep's proposals into set 0
     if ((s = record_phases(p, 0, true)) != BN_OK) return s;
