@@ -150,7 +150,8 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 // word per lane, pixels fastest, so that the proposal rows are read coalesced.
 // Few moves are accepted after the first sweeps: bound by the latency of the
 // decision's and then the rows' loads, hence many waves with few words each
-// (10 us at 256^2, N = 256, T = 1024 beside the recount; committing the class
+// (10 us a class at 256^2, N = 256, T = 1024 beside the recount, 19 for all four
+// of a sweep in one launch; committing the class
 // before inside the next phase kernel kept the recount off the CUs: 351 against
 // 275 us per two sweeps).
 constexpr uint32_t COMMIT_WAVES = 16;
