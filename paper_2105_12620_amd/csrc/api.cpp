@@ -1759,22 +1759,23 @@ bn_status bn_error_spectrum(bn_problem p, bn_rows rows, uint32_t nbins, double* 
   if (rs != BN_OK) return rs;
   const uint32_t W = p->v.w, H = p->v.h;
   const size_t P = (size_t)W * H;
-  std::vector<float2> twx(W), twy(H);
+  std::vector<float2> tw((size_t)W + H);   // along x, then along y
   for (uint32_t k = 0; k < W; ++k)
-    twx[k] = make_float2((float)std::cos(2.0 * M_PI * k / W), (float)-std::sin(2.0 * M_PI * k / W));
+    tw[k] = make_float2((float)std::cos(2.0 * M_PI * k / W), (float)-std::sin(2.0 * M_PI * k / W));
   for (uint32_t k = 0; k < H; ++k)
-    twy[k] = make_float2((float)std::cos(2.0 * M_PI * k / H), (float)-std::sin(2.0 * M_PI * k / H));
+    tw[W + k] = make_float2((float)std::cos(2.0 * M_PI * k / H), (float)-std::sin(2.0 * M_PI * k / H));
   // one chunk a launch if there is no memory for more
-  float2 *d_rows, *d_twx, *d_twy, *d_mx, *d_my;
+  float2 *d_rows, *d_tw, *d_mx = nullptr, *d_my = nullptr;
   double *d_part, *d_pw;
   uint32_t chunks = spectrum_chunks(p->v, std::max(p->v.t, p->v.tg));
+  const uint32_t all_rows = (rows == BN_ROWS_GAUSSIAN ? 0 : p->v.t) + (rows == BN_ROWS_HEAVISIDE ? 0 : p->v.tg);
+  const bool mat_x = spectrum_matrix(p->v, W, all_rows), mat_y = spectrum_matrix(p->v, H, all_rows);
   auto lay = [&](Carve& c) {
     const SpectrumScratch n = spectrum_scratch(p->v, chunks);
     d_rows = c.take<float2>(n.rows);
-    d_twx = c.take<float2>(W);
-    d_twy = c.take<float2>(H);
-    d_mx = c.take<float2>(n.matx);
-    d_my = c.take<float2>(n.maty);
+    d_tw = c.take<float2>(tw.size());
+    if (mat_x) d_mx = c.take<float2>(spectrum_matrix_size(W));
+    if (mat_y) d_my = mat_x && H == W ? d_mx : c.take<float2>(spectrum_matrix_size(H));
     d_part = c.take<double>(n.power);
     d_pw = c.take<double>(P);
   };
@@ -1792,22 +1793,22 @@ bn_status bn_error_spectrum(bn_problem p, bn_rows rows, uint32_t nbins, double* 
   c.base = scratch->base;
   lay(c);
   hipError_t e = hipSuccess;
-  e = hipMemcpyAsync(d_twx, twx.data(), W * sizeof(float2), hipMemcpyHostToDevice, p->stream);
-  if (e == hipSuccess) e = hipMemcpyAsync(d_twy, twy.data(), H * sizeof(float2), hipMemcpyHostToDevice, p->stream);
-  if (e == hipSuccess) e = launch_twiddles(d_twx, W, d_mx, p->stream);
-  if (e == hipSuccess) e = launch_twiddles(d_twy, H, d_my, p->stream);
-  if (e == hipSuccess) e = hipMemsetAsync(d_pw, 0, P * sizeof(double), p->stream);
+  e = hipMemcpyAsync(d_tw, tw.data(), tw.size() * sizeof(float2), hipMemcpyHostToDevice, p->stream);
+  if (e == hipSuccess && mat_x) e = launch_twiddles(d_tw, W, d_mx, p->stream);
+  if (e == hipSuccess && mat_y && d_my != d_mx) e = launch_twiddles(d_tw + W, H, d_my, p->stream);
+  const SpectrumTwiddles x{mat_x ? d_mx : d_tw, mat_x}, y{mat_y ? d_my : d_tw + W, mat_y};
   const float* fields[2] = {p->v.err, p->v.gerr};
   const uint32_t pitches[2] = {p->v.tp, p->v.tgp}, valids[2] = {p->v.t, p->v.tg};
   const uint32_t per = spectrum_chunk();
   uint32_t used = 0;
   for (int f = 0; f < 2 && e == hipSuccess; ++f) {
     if (!valids[f] || (rows == BN_ROWS_HEAVISIDE && f == 1) || (rows == BN_ROWS_GAUSSIAN && f == 0)) continue;
+    const bool none = used == 0;   // summed so far
     used += valids[f];
     const uint32_t all = (valids[f] + per - 1) / per;
     for (uint32_t c = 0; c < all && e == hipSuccess; c += chunks)
-      e = launch_spectrum_chunks(p->v, fields[f], pitches[f], valids[f], c * per, std::min(chunks, all - c), d_mx, d_my,
-                                 d_rows, d_part, d_pw, p->stream);
+      e = launch_spectrum_chunks(p->v, fields[f], pitches[f], valids[f], c * per, std::min(chunks, all - c),
+                                 none && c == 0, x, y, d_rows, d_part, d_pw, p->stream);
   }
   std::vector<double> pw(P);
   if (e == hipSuccess) e = hipMemcpyAsync(pw.data(), d_pw, P * sizeof(double), hipMemcpyDeviceToHost, p->stream);

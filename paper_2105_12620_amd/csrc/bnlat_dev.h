@@ -188,13 +188,21 @@ uint32_t spectrum_chunk();
 uint32_t spectrum_chunks(const DevView& v, uint32_t rows);
 // entries of the scratch buffers of such a launch
 struct SpectrumScratch {
-  size_t rows, power, matx, maty;
+  size_t rows, power;
 };
 SpectrumScratch spectrum_scratch(const DevView& v, uint32_t chunks);
+// the twiddles along a side of n: the n values, or their matrix
+bool spectrum_matrix(const DevView& v, uint32_t n, uint32_t rows);
+size_t spectrum_matrix_size(uint32_t n);
 hipError_t launch_twiddles(const float2* tw, uint32_t n, float2* mat, hipStream_t s);
+struct SpectrumTwiddles {
+  const float2* tw;
+  bool matrix;
+};
+// integrands t0 ..; first: of a spectrum (sum starts with theirs)
 hipError_t launch_spectrum_chunks(const DevView& v, const float* field, uint32_t pitch, uint32_t valid, uint32_t t0,
-                                  uint32_t chunks, const float2* matx, const float2* maty, float2* rows, double* power,
-                                  double* sum, hipStream_t s);
+                                  uint32_t chunks, bool first, const SpectrumTwiddles& x, const SpectrumTwiddles& y,
+                                  float2* rows, double* power, double* sum, hipStream_t s);
 
 // device peak loops: kind 0 copy (buf -> buf2, size bytes), 1 dot2 chains,
 // 2 BF16 MFMA accumulations (iters iterations each); blocks workgroups of 256
