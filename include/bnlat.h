@@ -167,7 +167,12 @@ bn_status bn_create_problem(const bn_config* cfg, const bn_heaviside* heavisides
  * Each must be device memory of at least that size, 256-byte aligned (else
  * BN_EINVAL), alive and unmoved until bn_destroy_problem; the library never
  * frees them and the caller must not write them while the problem's stream
- * has work pending.  Otherwise identical to bn_create_problem (the
+ * has work pending, except in that stream's order.  A caller may so put another
+ * state of the problem, read from them earlier, back into offsets and counts
+ * (both): redraw sweeps of Heaviside rows in the FP32 form, alone or in a batch,
+ * go on from it at the present sweep index, and errors follow with them; the
+ * BF16 form, Gaussian rows and swap moves keep data of their own and need
+ * bn_compute_errors first.  Otherwise identical to bn_create_problem (the
  * ownership convention of the C ABI's boundary). */
 typedef struct {
   void* offsets;

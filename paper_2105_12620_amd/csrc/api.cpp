@@ -567,6 +567,15 @@ bn_status refresh_errors(bn_problem p) {
   return BN_OK;
 }
 
+// The int8 field follows a state that the caller has put into offsets and counts
+// of its own: ahead of the phases of a call, and of the recount beside them, whose
+// workgroups it would wait for.  (A node of the captured pairs: launched before a
+// replay it cost 25 us of a call of two sweeps of 32^2, N = 16, T = 64.)
+bn_status follow_caller(bn_problem p) {
+  if (p->v.seen) HIPCHK(launch_follow(p->v, p->stream));
+  return BN_OK;
+}
+
 // The view of colour phase kappa reading proposals from sweep buffer set b.
 DevView phase_view(bn_problem p, int b, uint32_t kappa) {
   DevView v = p->v;
@@ -696,6 +705,7 @@ bn_status record_pair(bn_problem p) {
   bn_status s;
   for (int half = 0; half < 2; ++half) {
     const int cur = half, nxt = 1 - half;
+    if (half == 0 && (s = follow_caller(p)) != BN_OK) return s;
     HIPCHK(hipEventRecord(p->ev[2 * half], p->stream));
     HIPCHK(hipStreamWaitEvent(p->aux, p->ev[2 * half], 0));
     if ((s = record_proposals(p, nxt, 1, p->aux)) != BN_OK) return s;
@@ -724,6 +734,7 @@ bn_status record_pair_chained(bn_problem p, bool fork) {
     if (half == 1) {
       HIPCHK(hipStreamWaitEvent(p->aux, p->ev[2], 0));
     } else if (fork) {
+      if ((s = follow_caller(p)) != BN_OK) return s;
       HIPCHK(hipEventRecord(p->ev[0], p->stream));
       HIPCHK(hipStreamWaitEvent(p->aux, p->ev[0], 0));
     } else {
@@ -792,6 +803,7 @@ bn_status overlapped_sweeps(bn_problem p, uint32_t k) {
   if (done) p->recount_from = p->sweep + done;
   if (done < k) {
     // one more sweep, then the next sweep's proposals into set 0
+    if (!done && (s = follow_caller(p)) != BN_OK) return s;
     if ((s = record_phases(p, 0, true)) != BN_OK) return s;
     if ((s = record_proposals(p, 0, 0, p->stream)) != BN_OK) return s;
     done += 1;
@@ -1051,6 +1063,15 @@ bn_status batch_prefetch(bn_batch b) {
   return BN_OK;
 }
 
+// follow_caller for the grouped members.
+bn_status batch_follow(bn_batch b) {
+  const BatchGroup& g = b->commit_all;
+  bool any = false;
+  for (uint32_t i : g.idx) any = any || b->members[i]->v.seen;
+  if (any) HIPCHK(launch_follow_batch(g.views[0], g.d_pre, (uint32_t)g.idx.size(), g.blocks, b->stream));
+  return BN_OK;
+}
+
 // Two sweeps of every member: the grouped members' overlapped halves
 // [recount(s+1) -> set 1 || phases(s) from set 0], join, advance, then the
 // same with the sets exchanged; each solo member's own overlapped pair (or two
@@ -1061,6 +1082,7 @@ bn_status batch_record_pair(bn_batch b) {
   if (batch_has_groups(b)) {
     for (int half = 0; half < 2; ++half) {
       const int cur = half, nxt = 1 - half;
+      if (half == 0 && (s = batch_follow(b)) != BN_OK) return s;
       HIPCHK(hipEventRecord(b->ev[2 * half], b->stream));
       HIPCHK(hipStreamWaitEvent(b->aux, b->ev[2 * half], 0));
       if ((s = batch_recount(b, nxt, 1, b->aux)) != BN_OK) return s;
@@ -1086,7 +1108,7 @@ bn_status batch_record_pair(bn_batch b) {
 bn_status batch_single_sweep(bn_batch b) {
   bn_status s;
   if (batch_has_groups(b)) {
-    if ((s = batch_phases(b, 0)) != BN_OK) return s;
+    if ((s = batch_follow(b)) != BN_OK || (s = batch_phases(b, 0)) != BN_OK) return s;
     HIPCHK(launch_advance_batch(b->commit_all.views[0], (uint32_t)b->commit_all.idx.size(), b->stream));
     if ((s = batch_recount(b, 0, 0, b->stream)) != BN_OK) return s;
   }
@@ -1095,7 +1117,7 @@ bn_status batch_single_sweep(bn_batch b) {
     if (p->cfg.move == BN_SWAP) {
       if ((s = record_swap_sweep(p)) != BN_OK) return s;
     } else {
-      if ((s = record_phases(p, 0, true)) != BN_OK) return s;
+      if ((s = follow_caller(p)) != BN_OK || (s = record_phases(p, 0, true)) != BN_OK) return s;
       if ((s = record_proposals(p, 0, 0, p->stream)) != BN_OK) return s;
     }
   }
@@ -1426,7 +1448,9 @@ bn_status bn_create_problem_ext(const bn_config* cfg, const bn_heaviside* heavis
       (s = p->alloc(&v.accept, v.pc)) != BN_OK || (s = p->alloc(&v.ctr, 4)) != BN_OK ||
       (s = p->alloc(&v.unsure, v.pc)) != BN_OK ||
       (s = p->alloc(&p->ysum, ENERGY_ROWS * v.ncls)) != BN_OK ||
-      (v.mfma && (s = p->alloc(&v.xpart, (size_t)v.ncls * v.pc)) != BN_OK)) {
+      (v.mfma && (s = p->alloc(&v.xpart, (size_t)v.ncls * v.pc)) != BN_OK) ||
+      (bufs && bufs->offsets && bufs->counts && v.form != FIELD_WIDE && !p->bf_in_int8 &&
+       (s = p->alloc(&v.seen, P)) != BN_OK)) {
     delete p;
     return s;
   }
@@ -2150,6 +2174,8 @@ bn_status bn_phase_evaluate(bn_problem p, uint32_t kappa) {
   if (!p->have_counts) return fail(BN_ESTATE, "bn_compute_errors must run first");
   if (kappa >= p->v.k * p->v.k) return fail(BN_EINVAL, "class %u out of range", kappa);
   if (p->cfg.move == BN_SWAP) return swap_evaluate(p, kappa);
+  bn_status s = follow_caller(p);
+  if (s != BN_OK) return s;
   HIPCHK(launch_gauss_delta(p->v, MODE_CLASS, kappa, p->v.pc, p->stream));
   HIPCHK(launch_delta(p->v, MODE_CLASS, kappa, p->v.pc, p->stream));
   return BN_OK;

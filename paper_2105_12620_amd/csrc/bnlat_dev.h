@@ -45,6 +45,8 @@ struct DevView {
   const int32_t* dcls;       // [2 radius^2 + 1] class of a squared distance
   const double* wd;          // [ncls] class weights exp(-d / sigma^2)
   uint32_t* U;               // [P] offsets, x | y << 16
+  uint32_t* seen;            // [P] offsets whose counts d8 holds, where the caller owns offsets and counts,
+                             // else null
   uint16_t* cnt;             // [tp/8][P][8] hit counts (16-byte integrand tiles)
   float* err;                // [P][tp] error vectors
   uint32_t* u_new;           // [M] proposals of the current phase / list
@@ -105,6 +107,9 @@ hipError_t launch_phase(const DevView& v, uint32_t kappa, hipStream_t s);
 hipError_t launch_commit(const DevView& v, uint32_t kappa, hipStream_t s, bool advance = false);
 uint32_t commit_blocks(const DevView& v);
 bool moves_wait(const DevView& v);
+// d8 of the pixels whose offset the caller has replaced, from their counts
+hipError_t launch_follow(const DevView& v, hipStream_t s);
+hipError_t launch_follow_batch(const DevView* views, const uint32_t* pre, uint32_t nmem, uint32_t blocks, hipStream_t s);
 // the waiting moves of all classes (v: a sweep's view) in one launch
 hipError_t launch_commit_sweep(const DevView& v, hipStream_t s, bool advance);
 uint32_t commit_sweep_blocks(const DevView& v);

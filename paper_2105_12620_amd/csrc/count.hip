@@ -291,6 +291,7 @@ __device__ __forceinline__ void count_body(const DevView& v, uint32_t kappa, uin
   const bool to_wide = MODE == MODE_ALL || MODE == MODE_LIST || v.form == FIELD_WIDE;
   const bool to_narrow = MODE != MODE_LIST && v.form != FIELD_WIDE;
   if ((MODE == MODE_CLASS || MODE == MODE_SWEEP) && ch == 0 && live) v.u_new[j] = u;
+  if (MODE == MODE_ALL && v.seen && ch == 0 && live) v.seen[p] = u;
   const Counter counter(v, u);
   const float inv_n = 1.0f / (float)v.n;
   const uint32_t t0 = ch * tch, t1 = min(t0 + tch, v.tp), tz = min(t1, (v.t + 7) & ~7u);

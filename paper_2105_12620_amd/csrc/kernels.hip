@@ -166,6 +166,7 @@ __device__ __forceinline__ void commit_body(const DevView& v, uint32_t kappa, ui
     if (lane == 0 && m) atomicAdd(&v.ctr[1], (unsigned long long)__popcll(m));
     if (lane == 0 && advance && blk == 0) atomicAdd(&v.ctr[0], 1ull);
     if (acc) v.U[p] = v.u_new[j];
+    if (acc && v.seen) v.seen[p] = v.u_new[j];
   }
   if (!acc) return;
   const size_t P = (size_t)v.w * v.h;
@@ -262,6 +263,50 @@ __global__ __launch_bounds__(64 * COMMIT_WAVES) void k_commit_sweep_batch(const 
   __builtin_amdgcn_s_setprio(2);
   const uint32_t i = batch_member(pre, nmem, blockIdx.x);
   commit_sweep_body(views[i], blockIdx.x - pre[i], false);
+}
+
+// A caller that owns offsets and counts may have put another state of the problem
+// there: the words of d8 of the pixels whose offset is not the one they were
+// written for, from the counts.  A pixel's counts follow from its offset, so
+// comparing those (8 bytes a pixel) finds the ones to read: 4 us a call of two
+// sweeps where nothing was replaced (10 in a batch of 32 tiles of 64^2 and 128^2);
+// reading every count would take 45 at 256^2, T = 1024.
+constexpr uint32_t FOLLOW_PIXELS = 256;   // of a workgroup at a time
+
+__device__ __forceinline__ void follow_body(const DevView& v, uint32_t blk, uint32_t nblk) {
+  const uint32_t lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), P = v.w * v.h;
+  constexpr int N = FOLLOW_PIXELS / 64;
+  for (uint32_t p0 = blk * FOLLOW_PIXELS; p0 < P; p0 += nblk * FOLLOW_PIXELS) {
+    uint32_t u[N];
+    bool changed[N], any = false;
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+      const uint32_t p = p0 + 64 * i + lane;
+      u[i] = p < P ? v.U[p] : 0;
+      changed[i] = p < P && u[i] != v.seen[p];
+      any = any || changed[i];
+    }
+    if (!__syncthreads_or(any)) continue;   // (every wave has read seen)
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+      const uint32_t p = p0 + 64 * i + lane;
+      if (!changed[i]) continue;
+      for (uint32_t tt = w; tt < v.tp >> 4; tt += 4)
+        *(u32x4*)(v.d8 + ((size_t)tt * P + p) * 16) =
+            narrow8(*(const uint4*)(v.cnt + ((size_t)(2 * tt) * P + p) * 8),
+                    *(const uint4*)(v.cnt + ((size_t)(2 * tt + 1) * P + p) * 8), v.bias8 + 8 * tt);
+      if (w == 0) v.seen[p] = u[i];
+    }
+  }
+}
+
+__global__ __launch_bounds__(256) void k_follow(DevView v) { follow_body(v, blockIdx.x, gridDim.x); }
+
+__global__ __launch_bounds__(256) void k_follow_batch(const DevView* __restrict__ views, const uint32_t* __restrict__ pre,
+                                                      uint32_t nmem) {
+  const uint32_t i = batch_member(pre, nmem, blockIdx.x);
+  const DevView v = views[i];
+  if (v.seen) follow_body(v, blockIdx.x - pre[i], pre[i + 1] - pre[i]);
 }
 
 __global__ void k_advance(unsigned long long* ctr) {
@@ -926,6 +971,16 @@ hipError_t launch_commit_sweep(const DevView& v, hipStream_t s, bool advance) {
 hipError_t launch_commit_sweep_batch(const DevView* views, const uint32_t* pre, uint32_t nmem, uint32_t blocks,
                                      hipStream_t s) {
   hipLaunchKernelGGL(k_commit_sweep_batch, dim3(blocks), dim3(64 * COMMIT_WAVES), 0, s, views, pre, nmem);
+  return hipGetLastError();
+}
+
+hipError_t launch_follow(const DevView& v, hipStream_t s) {
+  hipLaunchKernelGGL(k_follow, dim3((v.w * v.h + FOLLOW_PIXELS - 1) / FOLLOW_PIXELS), dim3(256), 0, s, v);
+  return hipGetLastError();
+}
+
+hipError_t launch_follow_batch(const DevView* views, const uint32_t* pre, uint32_t nmem, uint32_t blocks, hipStream_t s) {
+  hipLaunchKernelGGL(k_follow_batch, dim3(blocks), dim3(256), 0, s, views, pre, nmem);
   return hipGetLastError();
 }
 
