@@ -502,6 +502,15 @@ __global__ __launch_bounds__(256) void k_gauss_est(DevView v, uint32_t kappa, ui
     u = v.u_new[j];
     out = v.g_new + (size_t)j * v.tgp;
   }
+  if (MODE == MODE_LIST) {
+    // a move to the offset that its pixel has changes nothing, whichever form the
+    // tile's estimates took
+    const uint32_t p = v.pix_list[j];
+    if (u == v.U[p]) {
+      if (lane < 16) out[gb * 16 + lane] = v.gest[(size_t)p * v.tgp + gb * 16 + lane];
+      return;
+    }
+  }
   gauss_estimates(v, u, gb, lane, red[wl], out + gb * 16);
 }
 
@@ -1064,6 +1073,7 @@ hipError_t launch_gauss_est(const DevView& v, int mode, uint32_t m, hipStream_t 
   const uint64_t waves = (uint64_t)m * (v.tgp >> 4);
   const dim3 grid((unsigned)((waves + 3) / 4)), block(256);
   if (mode == MODE_ALL) hipLaunchKernelGGL(k_gauss_est<MODE_ALL>, grid, block, 0, s, v, 0u, m);
+  else if (mode == MODE_LIST) hipLaunchKernelGGL(k_gauss_est<MODE_LIST>, grid, block, 0, s, v, 0u, m);
   else hipLaunchKernelGGL(k_gauss_est<MODE_CLASS>, grid, block, 0, s, v, 0u, m);
   return hipGetLastError();
 }
