@@ -14,18 +14,20 @@
 // (the relative error of a term, about j^2 2^-52, is far below the FP32
 // result's), where the exponentials were FP32 before.
 //
-// A lane owns one pixel; a wave walks 16 Gaussians, four at a time (four
-// independent chains), their interleaved tables in scalar registers, and the
-// four waves of a workgroup share the pixels.  Which steps of a line a pixel
+// A lane owns one pixel and a wave four Gaussians (four independent chains),
+// their interleaved tables in scalar registers; the four waves of a workgroup
+// share the pixels.  Which steps of a line a pixel
 // has depends on the class of its shift: the few steps at either end that not
 // every class has run under the execution mask (one comparison for the four
 // Gaussians), those in between without.  The classes' rows are kept in LDS, and
 // the results change hands there so that whole runs of a pixel's row are
 // written.  Bound by the vector ALUs (1.7 slots per sample at N = 1024, 12 ms of
 // issue) and the latency of the scalar loads (five waves a SIMD).
-// Measured at 512^2, N = 1024, 1024 Gaussians: 15.6 ms per estimate of all
-// pixels against 57.4 sample by sample; four lines at a time in place of four
-// Gaussians, whose common steps are fewer, took 41.
+// Measured at 512^2, N = 1024, 1024 Gaussians: 13.9 ms per estimate of all
+// pixels against 57.4 sample by sample; 15.6 with 16 Gaussians a wave, one four
+// after the other, and a launch over few pixels took four times as long (256
+// listed moves: 283 us the call against 141); four lines at a time in place of
+// four Gaussians, whose common steps are fewer, took 41.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -41,7 +43,7 @@ __device__ inline const BN_UNIFORM T* uniform(const T* p) {
   return (const BN_UNIFORM T*)p;
 }
 
-constexpr uint32_t GC = 16;          // Gaussians per wave
+constexpr uint32_t GC = 4;           // Gaussians per wave
 constexpr uint32_t OUT_PITCH = GC + 1;
 
 typedef double Two __attribute__((ext_vector_type(8), aligned(8)));   // two steps' entries of four tables
@@ -74,8 +76,8 @@ template <bool ALL>
 __global__ __launch_bounds__(256, 5) void k_gauss_lines(DevView v, uint32_t m) {
   extern __shared__ uint32_t rows[];
   const uint32_t lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const uint32_t ng = v.tgp / 64;                  // workgroups per 64 pixels
-  const uint32_t jg = blockIdx.x / ng, t0 = (blockIdx.x - jg * ng) * 64 + w * GC;
+  const uint32_t ng = v.tgp / (4 * GC);            // workgroups per 64 pixels
+  const uint32_t jg = blockIdx.x / ng, t0 = ((blockIdx.x - jg * ng) * 4 + w) * GC;
   float* outs = (float*)(rows + v.glines * 64) + w * 64 * OUT_PITCH;
   const uint32_t j = min(jg * 64 + lane, m - 1);
   const uint32_t u = ALL ? v.U[j] : v.u_new[j];
@@ -92,126 +94,123 @@ __global__ __launch_bounds__(256, 5) void k_gauss_lines(DevView v, uint32_t m) {
   const double a2 = __fma_rn(ax, ax, ay * ay);
   const double inv_n = 1.0 / (double)v.n;
 
+  double total[4] = {0.0, 0.0, 0.0, 0.0};
+  if (t0 < v.tg) {
+    const BN_UNIFORM double* tab = uniform(v.gtab) + (size_t)t0 * v.gwords;
+    double y[4], za[4], zi[4], ys[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      y[e] = exp2(__fma_rn(tab[e], a2, __fma_rn(tab[4 + e], ax, __fma_rn(tab[8 + e], ay, tab[12 + e]))));
+      const double le = __fma_rn(tab[16 + e], ax, __fma_rn(tab[20 + e], ay, tab[24 + e]));
+      za[e] = exp2(le);
+      zi[e] = exp2(-le);
+      ys[e] = exp2(__fma_rn(tab[28 + e], ax, __fma_rn(tab[32 + e], ay, tab[36 + e])));
+    }
+    const BN_UNIFORM double* wt = tab + 4 * (GAUSS_HEAD + 2 * v.glines);
 #pragma unroll 1
-  for (uint32_t t = t0; t < t0 + GC; t += 4) {
-    double total[4] = {0.0, 0.0, 0.0, 0.0};
-    if (t < v.tg) {
-      const BN_UNIFORM double* tab = uniform(v.gtab) + (size_t)t * v.gwords;
-      double y[4], za[4], zi[4], ys[4];
+    for (uint32_t l = 0; l < v.glines; ++l) {
+      const uint32_t r = rows[l * 64 + lane];
+      const int lo = (int)(r & 0xFFFFu), hi = (int)(r >> 16);
+      const BN_UNIFORM int* span = uniform(v.gspans) + 4 * l;
+      const BN_UNIFORM double* kc = tab + 4 * (GAUSS_HEAD + 2 * l);
+      double z[4], f[4], p[4];
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        y[e] = exp2(__fma_rn(tab[e], a2, __fma_rn(tab[4 + e], ax, __fma_rn(tab[8 + e], ay, tab[12 + e]))));
-        const double le = __fma_rn(tab[16 + e], ax, __fma_rn(tab[20 + e], ay, tab[24 + e]));
-        za[e] = exp2(le);
-        zi[e] = exp2(-le);
-        ys[e] = exp2(__fma_rn(tab[28 + e], ax, __fma_rn(tab[32 + e], ay, tab[36 + e])));
+        z[e] = za[e] * kc[e];
+        f[e] = y[e] * kc[4 + e];
+        p[e] = 0.0;
       }
-      const BN_UNIFORM double* wt = tab + 4 * (GAUSS_HEAD + 2 * v.glines);
+      const int flo = span[1], fhi = span[2], d = span[3];
+      int s = span[0] - 1;
+      const BN_UNIFORM double* wp = wt + 4 * (s - 1);
+      // (the empty asm keeps the steps under the execution mask; as selects
+      // they would cost two instructions each)
 #pragma unroll 1
-      for (uint32_t l = 0; l < v.glines; ++l) {
-        const uint32_t r = rows[l * 64 + lane];
-        const int lo = (int)(r & 0xFFFFu), hi = (int)(r >> 16);
-        const BN_UNIFORM int* span = uniform(v.gspans) + 4 * l;
-        const BN_UNIFORM double* kc = tab + 4 * (GAUSS_HEAD + 2 * l);
-        double z[4], f[4], p[4];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          z[e] = za[e] * kc[e];
-          f[e] = y[e] * kc[4 + e];
-          p[e] = 0.0;
-        }
-        const int flo = span[1], fhi = span[2], d = span[3];
-        int s = span[0] - 1;
-        const BN_UNIFORM double* wp = wt + 4 * (s - 1);
-        // (the empty asm keeps the steps under the execution mask; as selects
-        // they would cost two instructions each)
-#pragma unroll 1
-        for (; s >= fhi; s -= 2, wp -= 8) {
-          const Two w = *(const BN_UNIFORM Two*)wp;
-          if (s < hi) {
-#pragma unroll
-            for (int e = 0; e < 4; ++e) horner(p[e], z[e], w[4 + e]);
-            asm volatile("" : "+v"(p[0]), "+v"(p[1]), "+v"(p[2]), "+v"(p[3]));
-          }
-          if (s == fhi) {
-            --s;
-            wp -= 4;
-            break;
-          }
-          if (s <= hi) {
-#pragma unroll
-            for (int e = 0; e < 4; ++e) horner(p[e], z[e], w[e]);
-            asm volatile("" : "+v"(p[0]), "+v"(p[1]), "+v"(p[2]), "+v"(p[3]));
-          }
-        }
-#pragma unroll 1
-        for (; s >= flo + 3; s -= 4, wp -= 16) {
-          const Two w0 = *(const BN_UNIFORM Two*)wp, w1 = *(const BN_UNIFORM Two*)(wp - 8);
-          __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-          for (int e = 0; e < 4; ++e) horner(p[e], z[e], w0[4 + e]);
-#pragma unroll
-          for (int e = 0; e < 4; ++e) horner(p[e], z[e], w0[e]);
-#pragma unroll
-          for (int e = 0; e < 4; ++e) horner(p[e], z[e], w1[4 + e]);
-#pragma unroll
-          for (int e = 0; e < 4; ++e) horner(p[e], z[e], w1[e]);
-        }
-        if (s > flo) {
-          const Two w = *(const BN_UNIFORM Two*)wp;
+      for (; s >= fhi; s -= 2, wp -= 8) {
+        const Two w = *(const BN_UNIFORM Two*)wp;
+        if (s < hi) {
 #pragma unroll
           for (int e = 0; e < 4; ++e) horner(p[e], z[e], w[4 + e]);
-#pragma unroll
-          for (int e = 0; e < 4; ++e) horner(p[e], z[e], w[e]);
-          s -= 2;
-          wp -= 8;
+          asm volatile("" : "+v"(p[0]), "+v"(p[1]), "+v"(p[2]), "+v"(p[3]));
         }
-        if (s >= flo) {   // one common step left
-          const Two w = *(const BN_UNIFORM Two*)wp;
-#pragma unroll
-          for (int e = 0; e < 4; ++e) horner(p[e], z[e], w[4 + e]);
+        if (s == fhi) {
           --s;
           wp -= 4;
+          break;
         }
+        if (s <= hi) {
+#pragma unroll
+          for (int e = 0; e < 4; ++e) horner(p[e], z[e], w[e]);
+          asm volatile("" : "+v"(p[0]), "+v"(p[1]), "+v"(p[2]), "+v"(p[3]));
+        }
+      }
 #pragma unroll 1
-        for (; s >= 0; s -= 2, wp -= 8) {
-          const Two w = *(const BN_UNIFORM Two*)wp;
+      for (; s >= flo + 3; s -= 4, wp -= 16) {
+        const Two w0 = *(const BN_UNIFORM Two*)wp, w1 = *(const BN_UNIFORM Two*)(wp - 8);
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-          for (int k = 0; k < 2; ++k) {
-            if (s >= k) {
+        for (int e = 0; e < 4; ++e) horner(p[e], z[e], w0[4 + e]);
 #pragma unroll
-              for (int e = 0; e < 4; ++e) p[e] *= z[e];
-              if (s - k >= lo && s - k < hi) {
+        for (int e = 0; e < 4; ++e) horner(p[e], z[e], w0[e]);
 #pragma unroll
-                for (int e = 0; e < 4; ++e) p[e] = __dadd_rn(p[e], w[4 - 4 * k + e]);
-                asm volatile("" : "+v"(p[0]), "+v"(p[1]), "+v"(p[2]), "+v"(p[3]));
-              }
+        for (int e = 0; e < 4; ++e) horner(p[e], z[e], w1[4 + e]);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) horner(p[e], z[e], w1[e]);
+      }
+      if (s > flo) {
+        const Two w = *(const BN_UNIFORM Two*)wp;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) horner(p[e], z[e], w[4 + e]);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) horner(p[e], z[e], w[e]);
+        s -= 2;
+        wp -= 8;
+      }
+      if (s >= flo) {   // one common step left
+        const Two w = *(const BN_UNIFORM Two*)wp;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) horner(p[e], z[e], w[4 + e]);
+        --s;
+        wp -= 4;
+      }
+#pragma unroll 1
+      for (; s >= 0; s -= 2, wp -= 8) {
+        const Two w = *(const BN_UNIFORM Two*)wp;
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+          if (s >= k) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) p[e] *= z[e];
+            if (s - k >= lo && s - k < hi) {
+#pragma unroll
+              for (int e = 0; e < 4; ++e) p[e] = __dadd_rn(p[e], w[4 - 4 * k + e]);
+              asm volatile("" : "+v"(p[0]), "+v"(p[1]), "+v"(p[2]), "+v"(p[3]));
             }
           }
         }
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          total[e] = __fma_rn(f[e], p[e], total[e]);
-          y[e] *= ys[e];   // origin of the next line: b2 and d steps of b1 further
-        }
-#pragma unroll 1
-        for (int k = 0; k < d; ++k)
-#pragma unroll
-          for (int e = 0; e < 4; ++e) y[e] *= za[e];
-#pragma unroll 1
-        for (int k = 0; k > d; --k)
-#pragma unroll
-          for (int e = 0; e < 4; ++e) y[e] *= zi[e];
       }
 #pragma unroll
-      for (int e = 0; e < 4; ++e)
-        if (tab[44 + e] != 0.0) total[e] = gauss_by_sample(v, u, t + e);
+      for (int e = 0; e < 4; ++e) {
+        total[e] = __fma_rn(f[e], p[e], total[e]);
+        y[e] *= ys[e];   // origin of the next line: b2 and d steps of b1 further
+      }
+#pragma unroll 1
+      for (int k = 0; k < d; ++k)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) y[e] *= za[e];
+#pragma unroll 1
+      for (int k = 0; k > d; --k)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) y[e] *= zi[e];
     }
 #pragma unroll
-    for (uint32_t e = 0; e < 4; ++e) {
-      if (t + e >= v.tg) total[e] = (double)v.n;   // padding: estimate 1
-      outs[lane * OUT_PITCH + (t - t0) + e] = (float)(total[e] * inv_n);
-    }
+    for (int e = 0; e < 4; ++e)
+      if (tab[44 + e] != 0.0) total[e] = gauss_by_sample(v, u, t0 + e);
+  }
+#pragma unroll
+  for (uint32_t e = 0; e < 4; ++e) {
+    if (t0 + e >= v.tg) total[e] = (double)v.n;   // padding: estimate 1
+    outs[lane * OUT_PITCH + e] = (float)(total[e] * inv_n);
   }
   __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
   __builtin_amdgcn_wave_barrier();
@@ -227,7 +226,7 @@ __global__ __launch_bounds__(256, 5) void k_gauss_lines(DevView v, uint32_t m) {
 
 hipError_t launch_gauss_lines(const DevView& v, bool all, uint32_t m, hipStream_t s) {
   const size_t lds = 4 * lds_words(v.glines);
-  const dim3 grid((m + 63) / 64 * (v.tgp / 64)), block(256);
+  const dim3 grid((m + 63) / 64 * (v.tgp / (4 * GC))), block(256);
   if (all) hipLaunchKernelGGL(k_gauss_lines<true>, grid, block, lds, s, v, m);
   else hipLaunchKernelGGL(k_gauss_lines<false>, grid, block, lds, s, v, m);
   return hipGetLastError();

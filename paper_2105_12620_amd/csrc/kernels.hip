@@ -1059,18 +1059,22 @@ hipError_t launch_gauss_again(const DevView& v, uint32_t kappa, hipStream_t s) {
   return hipGetLastError();
 }
 
-// The line form gives a wave 64 pixels and 16 Gaussians, the sample form one
-// pixel and 16 Gaussians: below about 256 waves the former leaves most of the
-// chip idle (at N = 1024 a wave takes about 50 us, where the sample form is
-// done in 5 us for 144 pixels and 128 Gaussians).
+// Tiles whose estimates come from the lines: the line form gives a wave 64 pixels
+// and 4 Gaussians, the sample form one pixel and 16 Gaussians: below about 1024
+// waves, one a SIMD, the former leaves most of the chip idle (at N = 1024 a wave
+// takes about 50 us, where the sample form is done in 5 us for 144 pixels and 128
+// Gaussians).
 bool gauss_lines_pay(const DevView& v, uint32_t m) { return (uint64_t)((m + 63) / 64) * (v.tgp / 16) >= 256; }
 
 hipError_t launch_gauss_est(const DevView& v, int mode, uint32_t m, hipStream_t s) {
   if (!v.tgp || m == 0) return hipSuccess;
   // a problem's sweeps, phases and whole tile use one form; pixel lists the one
   // that is faster at their size
-  if (v.glines && (mode != MODE_LIST || gauss_lines_pay(v, m))) return launch_gauss_lines(v, mode == MODE_ALL, m, s);
+  // (from 16384 of its waves on the sample form fills the chip several times over;
+  // N = 1024, 1024 Gaussians: 85 us the call against 133 at 64 moves, 131 against 141 at
+  // 256, 188 against 144 at 512; N = 256: 89 against 91 at 128, 107 against 93 at 256)
   const uint64_t waves = (uint64_t)m * (v.tgp >> 4);
+  if (v.glines && (mode != MODE_LIST || waves >= 16384)) return launch_gauss_lines(v, mode == MODE_ALL, m, s);
   const dim3 grid((unsigned)((waves + 3) / 4)), block(256);
   if (mode == MODE_ALL) hipLaunchKernelGGL(k_gauss_est<MODE_ALL>, grid, block, 0, s, v, 0u, m);
   else if (mode == MODE_LIST) hipLaunchKernelGGL(k_gauss_est<MODE_LIST>, grid, block, 0, s, v, 0u, m);
