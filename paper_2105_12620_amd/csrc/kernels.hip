@@ -637,11 +637,88 @@ __global__ __launch_bounds__(256) void k_delta_gauss(DevView v, uint32_t kappa, 
   if (lane == 0) v.gdelta[j] = 2.0 * acc;
 }
 
+// hi + lo += x, with the rounding of hi kept in lo.
+__device__ __forceinline__ void add_exact(double& hi, double& lo, double x) {
+  const double s = __dadd_rn(hi, x), b = __dsub_rn(s, hi);
+  lo = __dadd_rn(lo, __dadd_rn(__dsub_rn(hi, __dsub_rn(s, b)), __dsub_rn(x, b)));
+  hi = s;
+}
+
+// One Gaussian's window sums of PX class pixels K apart in a row,
+//   t = sum_m w_m x_m (rounding of its rows' sums in tl),  s2 = sum_m w_m g_m^2,
+// x_m = sm - 2 g_m, from estimates in LDS (corner: the first pixel's window corner;
+// column and row strides CS, RS).  The two or four offsets (+-ox, +-oy) share
+// their weight: their estimates are added first, without rounding (FP32 values),
+// the rows +-oy for all pixels at once.
+template <int R, int K, int PX, int CS, int RS, bool MARGIN>
+__device__ __forceinline__ void gauss_window(const float* corner, const double* wd, const double (&sm)[PX],
+                                             double (&t)[PX], double (&tl)[PX], double (&s2)[PX]) {
+  constexpr Window<R> W = WinConst<R>::w;
+  constexpr int S = 2 * R + 1, COLS = K * (PX - 1) + S;
+#pragma unroll
+  for (int i = 0; i < PX; ++i) t[i] = tl[i] = s2[i] = 0.0;
+#pragma unroll
+  for (int oy = R; oy >= 0; --oy) {
+    double h[COLS], q[COLS];
+#pragma unroll
+    for (int x = 0; x < COLS; ++x) {
+      const double a = (double)corner[(R + oy) * RS + x * CS];
+      h[x] = a;
+      q[x] = a * a;
+      if (oy) {
+        const double b = (double)corner[(R - oy) * RS + x * CS];
+        h[x] += b;
+        q[x] = __fma_rn(b, b, q[x]);
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < PX; ++i) {
+      double row = 0.0;
+#pragma unroll
+      for (int ox = R; ox >= 0; --ox) {
+        if (!ox && !oy) continue;
+        const int c = K * i + R;
+        const double u = ox ? h[c + ox] + h[c - ox] : h[c], uu = ox ? q[c + ox] + q[c - ox] : q[c];
+        const double w = wd[W.cmap[(R + oy) * S + R + ox]];
+        const double x = __fma_rn(-2.0, u, (double)((oy ? 2 : 1) * (ox ? 2 : 1)) * sm[i]);
+        if (MARGIN) s2[i] = __fma_rn(w, uu, s2[i]);
+        row = ox == R ? __dmul_rn(w, x) : __fma_rn(w, x, row);
+      }
+      add_exact(t[i], tl[i], row);
+    }
+    // (rows apart: their values for several pixels in flight together would halve
+    // the waves)
+    if (PX > 1) __builtin_amdgcn_sched_barrier(0);
+  }
+}
+
+// A Gaussian's part d sum w x of a move into acc + lo, and (MARGIN) its share of the
+// margin.
+// sum w x^2 = 4 s2 + sm (2 t - W sm), with room for its rounding.
+template <bool MARGIN>
+__device__ __forceinline__ void gauss_part(double W, double d, double sm, double t, double tl, double s2, double& acc,
+                                           double& lo, double& margin) {
+  const double p = __dmul_rn(d, t);
+  add_exact(acc, lo, p);
+  lo += __fma_rn(d, tl, __fma_rn(d, t, -p));
+  if (!MARGIN) return;
+  const double b = __fma_rn(4.0, s2, sm * __fma_rn(-W, sm, 2.0 * t));
+  margin += gauss_margin(W, fmax(b, 0.0) + 1e-13 * W, sm, fabs(d));
+}
+
 // Colour-phase form of the same sum: a workgroup owns 4 x 2 class pixels (one
 // wave each) and, for 64 Gaussians at a time, stages the estimate rows of
 // their window region ((K + 2r + 1) x (3K + 2r + 1) pixels) in LDS, so that
 // each row is read from memory once per workgroup rather than once per moved
-// pixel.  Same arithmetic and summation order as k_delta_gauss.
+// pixel.
+//
+// Rounding: k_delta_gauss adds d x_m per class.  Here a Gaussian's weighted sum of
+// x_m is formed first: at most R + 1 roundings in a row of the window, those of
+// everything after it kept.  Against 80-bit sums (radii 1 to 5, 64 to 1024
+// Gaussians, estimates spread by 0.1 and by 0.01) its mean error is 0.3 to 0.95 of
+// k_delta_gauss's; W sm - 2 sum w g, which cancels after the sums, had 5 to 90
+// times that.  It also takes fewer FP64 operations (at r = 5 28 a pixel and pair of
+// rows with the margin's, 44 before).
 template <int R, int K>
 struct GaussStage {
   static constexpr int BCX = 4, BCY = 2, NW = BCX * BCY;
@@ -651,7 +728,7 @@ struct GaussStage {
   static constexpr int LDS_BYTES = RA * 64 * 4;
 };
 
-template <int R, int K>
+template <int R, int K, bool MARGIN>
 __global__ __launch_bounds__(512) void k_delta_gauss_stage(DevView v, uint32_t kappa) {
   using G = GaussStage<R, K>;
   constexpr Window<R> W = WinConst<R>::w;
@@ -682,13 +759,14 @@ __global__ __launch_bounds__(512) void k_delta_gauss_stage(DevView v, uint32_t k
     goff[it] = gy * v.w + gx;
   }
   const int own = (K * cy + R) * G::RW + K * cx + R;
+  const float* corner = gl + ((K * cy) * G::RW + K * cx) * 64 + lane;
   double wd[NCLS], wsum = 0.0;
 #pragma unroll
   for (int c = 0; c < NCLS; ++c) {
     wd[c] = v.wd[c];
     wsum += (double)W.csize[c] * wd[c];
   }
-  double acc = 0.0, margin = 0.0;
+  double acc = 0.0, lo = 0.0, margin = 0.0;
   for (uint32_t base = 0; base < v.tgp; base += 64) {
     f32x4 q[ITER];
 #pragma unroll
@@ -703,39 +781,33 @@ __global__ __launch_bounds__(512) void k_delta_gauss_stage(DevView v, uint32_t k
     __syncthreads();
     if (act) {
       const double gn = v.g_new[(size_t)j * v.tgp + base + lane], go = gl[own * 64 + lane];
-      const double d = gn - go, sm = gn + go;
-      double s1 = 0.0, s2 = 0.0;   // sums of w g_m and w g_m^2 over the window
-#pragma unroll
-      for (int mm = 0; mm < W.M; ++mm) {
-        const int q = own + W.oy[mm] * G::RW + W.ox[mm];
-        const double g = (double)gl[q * 64 + lane];
-        s1 = __fma_rn(wd[W.cls[mm]], g, s1);
-        s2 = __fma_rn(wd[W.cls[mm]], g * g, s2);
-      }
-      acc = __fma_rn(d, __fma_rn(wsum, sm, -2.0 * s1), acc);
-      // sum w x^2, with room for its rounding
-      const double b = __fma_rn(wsum * sm, sm, 4.0 * __fma_rn(-sm, s1, s2));
-      margin += gauss_margin(wsum, fmax(b, 0.0) + 1e-13 * wsum, sm, fabs(d));
+      const double sm[1] = {gn + go};
+      double t[1], tl[1], s2[1];
+      gauss_window<R, K, 1, 64, 64 * G::RW, MARGIN>(corner, wd, sm, t, tl, s2);
+      gauss_part<MARGIN>(wsum, gn - go, sm[0], t[0], tl[0], s2[0], acc, lo, margin);
     }
   }
   if (!act) return;
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) {
-    acc += __shfl_xor(acc, off);
-    margin += __shfl_xor(margin, off);
+    const double a = __shfl_xor(acc, off);
+    lo += __shfl_xor(lo, off);
+    add_exact(acc, lo, a);
+    if (MARGIN) margin += __shfl_xor(margin, off);
   }
   if (lane != 0) return;
-  v.gdelta[j] = 2.0 * acc;
-  if (v.gmargin) v.gmargin[j] = margin;
+  v.gdelta[j] = 2.0 * (acc + lo);
+  if (MARGIN) v.gmargin[j] = margin;
 }
 
 // The same for launches with many blocks: a workgroup owns 8 x BCY class pixels
 // and 16 Gaussians at a time, a thread four neighbouring pixels of a row and one
-// Gaussian, so that a window row's values are read from LDS, and converted and
-// squared, once for four pixels (12 against 30 a pixel at r = 5, K = 2), and the
+// Gaussian, so that a window row's values are read from LDS, converted and
+// paired once for four pixels (12 against 30 a pixel at r = 5, K = 2), and the
 // region from memory once for 64 (10 pixels of it a pixel against 28).  Bound by
-// the FP64 FMAs.  512^2, N = 1024, 1024 Gaussians, r = 5: 0.91 ms a phase, 1.52 with
-// k_delta_gauss_stage.
+// the FP64 operations.  512^2, 1024 Gaussians, r = 5: 0.75 ms a phase without the
+// margin, 0.97 with it; 1.8 and, with it, 1.5 with k_delta_gauss_stage's layout and
+// one sum per window offset.
 template <int R, int K>
 struct GaussTile {
   static constexpr int BCX = 8, BCY = K == 4 ? 4 : 8, PX = 4, NT = BCX / PX * BCY * 16;
@@ -743,11 +815,11 @@ struct GaussTile {
   static constexpr int LDS_BYTES = RA * 16 * 4;
 };
 
-template <int R, int K>
+template <int R, int K, bool MARGIN>
 __global__ __launch_bounds__((GaussTile<R, K>::NT)) void k_delta_gauss_tile(DevView v, uint32_t kappa, uint32_t gx) {
   using G = GaussTile<R, K>;
   constexpr Window<R> W = WinConst<R>::w;
-  constexpr int NCLS = WinConst<R>::NCLS, S = 2 * R + 1, COLS = K * (G::PX - 1) + S;
+  constexpr int NCLS = WinConst<R>::NCLS;
   constexpr int ITER = (G::RA * 4 + G::NT - 1) / G::NT;
   extern __shared__ float gl[];                  // [RA][16] estimates of the region
   const uint32_t tid = threadIdx.x, t = tid & 15, grp = tid >> 4;
@@ -782,9 +854,9 @@ __global__ __launch_bounds__((GaussTile<R, K>::NT)) void k_delta_gauss_tile(DevV
     wsum += (double)W.csize[c] * wd[c];
   }
   const float* col0 = gl + (K * cy * G::RW + K * G::PX * half) * 16 + t;   // window corner of the first pixel
-  double acc[G::PX], margin[G::PX];
+  double acc[G::PX], lo[G::PX], margin[G::PX];
 #pragma unroll
-  for (int i = 0; i < G::PX; ++i) acc[i] = margin[i] = 0.0;
+  for (int i = 0; i < G::PX; ++i) acc[i] = lo[i] = margin[i] = 0.0;
   for (uint32_t base = 0; base < v.tgp; base += 16) {
     f32x4 q[ITER];
 #pragma unroll
@@ -800,42 +872,29 @@ __global__ __launch_bounds__((GaussTile<R, K>::NT)) void k_delta_gauss_tile(DevV
       if (idx < (uint32_t)G::RA * 4) *(f32x4*)&gl[idx * 4] = q[it];
     }
     __syncthreads();
-    double s1[G::PX], s2[G::PX];   // sums of w g_m and w g_m^2 over the window
-#pragma unroll
-    for (int i = 0; i < G::PX; ++i) s1[i] = s2[i] = 0.0;
-#pragma unroll
-    for (int oy = 0; oy < S; ++oy) {
-#pragma unroll
-      for (int x = 0; x < COLS; ++x) {
-        const double g = (double)col0[(oy * G::RW + x) * 16], gg = g * g;
-#pragma unroll
-        for (int i = 0; i < G::PX; ++i) {
-          const int ox = x - K * i;
-          if (ox < 0 || ox >= S || (ox == R && oy == R)) continue;
-          const double w = wd[W.cmap[oy * S + ox]];
-          s1[i] = __fma_rn(w, g, s1[i]);
-          s2[i] = __fma_rn(w, gg, s2[i]);
-        }
-      }
-    }
+    double d[G::PX], sm[G::PX], ts[G::PX], tl[G::PX], s2[G::PX];
 #pragma unroll
     for (int i = 0; i < G::PX; ++i) {
-      const double go = (double)col0[(R * G::RW + K * i + R) * 16], d = (double)gn[i] - go, sm = (double)gn[i] + go;
-      acc[i] = __fma_rn(d, __fma_rn(wsum, sm, -2.0 * s1[i]), acc[i]);
-      const double b = __fma_rn(wsum * sm, sm, 4.0 * __fma_rn(-sm, s1[i], s2[i]));
-      margin[i] += gauss_margin(wsum, fmax(b, 0.0) + 1e-13 * wsum, sm, fabs(d));
+      const double go = (double)col0[(R * G::RW + K * i + R) * 16];
+      d[i] = (double)gn[i] - go;
+      sm[i] = (double)gn[i] + go;
     }
+    gauss_window<R, K, G::PX, 16, 16 * G::RW, MARGIN>(col0, wd, sm, ts, tl, s2);
+#pragma unroll
+    for (int i = 0; i < G::PX; ++i) gauss_part<MARGIN>(wsum, d[i], sm[i], ts[i], tl[i], s2[i], acc[i], lo[i], margin[i]);
   }
 #pragma unroll
   for (int i = 0; i < G::PX; ++i) {
 #pragma unroll
     for (int off = 8; off > 0; off >>= 1) {
-      acc[i] += __shfl_xor(acc[i], off);
-      margin[i] += __shfl_xor(margin[i], off);
+      const double a = __shfl_xor(acc[i], off);
+      lo[i] += __shfl_xor(lo[i], off);
+      add_exact(acc[i], lo[i], a);
+      if (MARGIN) margin[i] += __shfl_xor(margin[i], off);
     }
     if (t == 0 && act[i]) {
-      v.gdelta[j[i]] = 2.0 * acc[i];
-      if (v.gmargin) v.gmargin[j[i]] = margin[i];
+      v.gdelta[j[i]] = 2.0 * (acc[i] + lo[i]);
+      if (MARGIN) v.gmargin[j[i]] = margin[i];
     }
   }
 }
@@ -1105,7 +1164,7 @@ hipError_t gauss_stage_launch(const DevView& v, uint32_t kappa, hipStream_t s) {
     // tiles from 256 blocks on, a workgroup per CU; smaller blocks below
     const uint32_t gx = (v.cw + T::BCX - 1) / T::BCX, blocks = gx * ((v.ch + T::BCY - 1) / T::BCY);
     if (blocks >= 256) {
-      hipLaunchKernelGGL((k_delta_gauss_tile<R, K>), dim3(blocks), dim3(T::NT), (size_t)T::LDS_BYTES, s, v, kappa, gx);
+      hipLaunchKernelGGL((v.gmargin ? k_delta_gauss_tile<R, K, true> : k_delta_gauss_tile<R, K, false>), dim3(blocks), dim3(T::NT), (size_t)T::LDS_BYTES, s, v, kappa, gx);
       return hipGetLastError();
     }
   }
@@ -1114,7 +1173,7 @@ hipError_t gauss_stage_launch(const DevView& v, uint32_t kappa, hipStream_t s) {
     return gauss_delta_dispatch<MODE_CLASS>(v, kappa, v.pc, s);
   } else {
     const dim3 grid((v.cw + G::BCX - 1) / G::BCX, (v.ch + G::BCY - 1) / G::BCY);
-    hipLaunchKernelGGL((k_delta_gauss_stage<R, K>), grid, dim3(64 * G::NW), (size_t)G::LDS_BYTES, s, v, kappa);
+    hipLaunchKernelGGL((v.gmargin ? k_delta_gauss_stage<R, K, true> : k_delta_gauss_stage<R, K, false>), grid, dim3(64 * G::NW), (size_t)G::LDS_BYTES, s, v, kappa);
     return hipGetLastError();
   }
 }
