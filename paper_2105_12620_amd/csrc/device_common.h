@@ -139,12 +139,13 @@ __device__ inline uint32_t proposal(const DevView& v, uint32_t p, uint32_t sweep
   return q16_pair(philox_w01(p, sweep, v.problem, S_PROP, v.seed_lo, v.seed_hi));
 }
 
-// Energy change of class pixel j from its Heaviside part; a move too close to be
-// decided from the line form's estimates is listed (launch_gauss_again).
-__device__ __forceinline__ double with_gaussian_part(const DevView& v, uint32_t j, double heaviside) {
+// Energy change of class pixel j (pixel p) from its Heaviside part; a move too close
+// to be decided from the line form's estimates is listed (launch_gauss_again), but
+// for one to the offset that the pixel has: it changes nothing in either form.
+__device__ __forceinline__ double with_gaussian_part(const DevView& v, uint32_t j, uint32_t p, double heaviside) {
   if (!v.tgp) return heaviside;
   const double total = __dadd_rn(heaviside, v.gdelta[j]);
-  if (v.gmargin && fabs(total) <= v.gmargin[j]) {
+  if (v.gmargin && fabs(total) <= v.gmargin[j] && v.u_new[j] != v.U[p]) {
     v.gunsure[1 + atomicAdd(v.gunsure, 1u)] = j;
     v.hpart[j] = heaviside;
   }

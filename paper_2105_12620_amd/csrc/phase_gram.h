@@ -230,7 +230,7 @@ __device__ __forceinline__ void gram_body(const DevView& v, uint32_t kappa, uint
     sum = __dadd_rn(sum, __dmul_rn(v.wd[c], (double)x));
   }
   double total = __dmul_rn(sum, 2.0 / ((double)v.n * (double)v.n));
-  total = with_gaussian_part(v, j, total);
+  total = with_gaussian_part(v, j, (ky + K * a) * v.w + kx + K * b, total);
   const bool ok = (v.objective > 0) ? (total < 0.0) : (total > 0.0);
   v.delta[j] = total;
   v.accept[j] = ok;

@@ -232,7 +232,7 @@ __device__ __forceinline__ void phase_body(const DevView& v, uint32_t kappa, uin
     acc = __dadd_rn(acc, __dmul_rn(v.wd[c], (double)x));
   }
   double total = __dmul_rn(acc, 2.0 / ((double)v.n * (double)v.n));
-  total = with_gaussian_part(v, j, total);
+  total = with_gaussian_part(v, j, (ky + K * a) * v.w + kx + K * b, total);
   const bool ok = (v.objective > 0) ? (total < 0.0) : (total > 0.0);
   v.delta[j] = total;
   v.accept[j] = ok;
