@@ -12,6 +12,7 @@ from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 SOURCES = ["csrc/count.hip", "csrc/phase_wide.hip", "csrc/phase_narrow.hip", "csrc/phase_split.hip",
+           "csrc/phase_decide.hip",
            "csrc/gauss_lines.hip", "csrc/kernels.hip", "csrc/swap.hip", "csrc/sampler.hip", "csrc/mfma.hip",
            "csrc/noalloc.hip", "csrc/peaks.hip",
            "csrc/blur.hip", "csrc/spectrum.hip", "csrc/api.cpp"]

@@ -309,6 +309,15 @@ struct BatchGroup {
   std::vector<DevView*> views;
   uint32_t* d_pre = nullptr;  // block prefix sums, idx.size() + 1 entries
   uint32_t blocks = 0;
+  // phase groups: the members' integrand slices, and the blocks of the decisions
+  // of those that have several
+  std::vector<uint32_t> slices;
+  uint32_t* d_decide = nullptr;
+  uint32_t decide = 0;
+  DevView sliced(DevView v, size_t n) const {
+    if (n < slices.size()) v.slices = slices[n];
+    return v;
+  }
 };
 
 struct bn_batch_s {
@@ -978,21 +987,24 @@ bn_status batch_upload(bn_batch b) {
     return BN_OK;
   };
   // kind 0: whole-sweep counting views per set; kind 1: phase views per (set, class)
+  auto prefix = [&](const BatchGroup& g, auto blocks_of, uint32_t** dev, uint32_t* total) -> bn_status {
+    std::vector<uint32_t> pre(1, 0);
+    for (size_t n = 0; n < g.idx.size(); ++n) pre.push_back(pre.back() + blocks_of(g.sliced(b->members[g.idx[n]]->v, n)));
+    *total = pre.back();
+    return dev_copy(pre.data(), pre.size() * 4, (void**)dev);
+  };
   auto upload = [&](BatchGroup& g, int kind, auto blocks_of) -> bn_status {
     g.blocks = 0;
     g.views.clear();
     if (g.idx.empty()) return BN_OK;
-    std::vector<uint32_t> pre(1, 0);
-    for (uint32_t i : g.idx) pre.push_back(pre.back() + blocks_of(b->members[i]->v));
-    g.blocks = pre.back();
     bn_status st;
-    if ((st = dev_copy(pre.data(), pre.size() * 4, (void**)&g.d_pre)) != BN_OK) return st;
+    if ((st = prefix(g, blocks_of, &g.d_pre, &g.blocks)) != BN_OK) return st;
     const uint32_t ntab = kind == 0 ? 2 : 2 * K2;
     for (uint32_t tab = 0; tab < ntab; ++tab) {
       std::vector<DevView> views;
-      for (uint32_t i : g.idx) {
-        bn_problem p = b->members[i];
-        views.push_back(kind == 0 ? sweep_view(p, (int)tab) : phase_view(p, (int)(tab / K2), tab % K2));
+      for (size_t n = 0; n < g.idx.size(); ++n) {
+        bn_problem p = b->members[g.idx[n]];
+        views.push_back(g.sliced(kind == 0 ? sweep_view(p, (int)tab) : phase_view(p, (int)(tab / K2), tab % K2), n));
       }
       DevView* d = nullptr;
       if ((st = dev_copy(views.data(), views.size() * sizeof(DevView), (void**)&d)) != BN_OK) return st;
@@ -1003,8 +1015,15 @@ bn_status batch_upload(bn_batch b) {
   bn_status s;
   for (BatchGroup& g : b->count_groups)
     if ((s = upload(g, 0, count_blocks)) != BN_OK) return s;
-  for (BatchGroup& g : b->stage_groups)
-    if ((s = upload(g, 1, phase_blocks)) != BN_OK) return s;
+  for (BatchGroup& g : b->stage_groups) {
+    // slices that the group's launch needs to fill the chip
+    g.slices.assign(g.idx.size(), 1);
+    uint32_t blocks = 0;
+    for (size_t n = 0; n < g.idx.size(); ++n) blocks += phase_blocks(g.sliced(b->members[g.idx[n]]->v, n));
+    for (size_t n = 0; n < g.idx.size(); ++n) g.slices[n] = phase_slices(b->members[g.idx[n]]->v, blocks);
+    if ((s = upload(g, 1, phase_blocks)) != BN_OK || (s = prefix(g, decide_blocks, &g.d_decide, &g.decide)) != BN_OK)
+      return s;
+  }
   if ((s = upload(b->commit_all, 0, commit_blocks)) != BN_OK) return s;
   if ((s = upload(b->commit_phase, 1, commit_blocks)) != BN_OK) return s;
   if ((s = upload(b->commit_sweep, 0, commit_sweep_blocks)) != BN_OK) return s;
@@ -1023,9 +1042,13 @@ bn_status batch_recount(bn_batch b, int set, uint32_t ahead, hipStream_t st) {
 // proposals from set `set` (no state change).
 bn_status batch_evaluate(bn_batch b, int set, uint32_t kappa) {
   const uint32_t t = set * b->colour_k * b->colour_k + kappa;
-  for (BatchGroup& g : b->stage_groups)
+  for (BatchGroup& g : b->stage_groups) {
     HIPCHK(launch_phase_batch(g.form, g.radius, g.k, g.views[t], g.d_pre, (uint32_t)g.idx.size(), g.blocks, kappa,
                               b->stream));
+    if (g.decide)
+      HIPCHK(launch_phase_decide_batch(g.radius, g.views[t], g.d_decide, (uint32_t)g.idx.size(), g.decide, kappa,
+                                       b->stream));
+  }
   return BN_OK;
 }
 
@@ -1432,6 +1455,8 @@ bn_status bn_create_problem_ext(const bn_config* cfg, const bn_heaviside* heavis
   std::vector<int32_t> dcls(2 * v.radius * v.radius + 1, -1);
   for (uint32_t c = 0; c < v.ncls; ++c) dcls[p->cls_d[c]] = (int32_t)c;
   v.span = phase_span_wide(v.n);
+  v.slices = 1;
+  if (cfg->move == BN_REDRAW && (staged_phases(v) || v.mfma == 2)) v.slices = phase_slices(v, phase_blocks(v));
   LineRec* lrec_d;
   int2* ihp_d;
   float* area_d;
@@ -1449,6 +1474,7 @@ bn_status bn_create_problem_ext(const bn_config* cfg, const bn_heaviside* heavis
       (s = p->alloc(&v.unsure, v.pc)) != BN_OK ||
       (s = p->alloc(&p->ysum, ENERGY_ROWS * v.ncls)) != BN_OK ||
       (v.mfma && (s = p->alloc(&v.xpart, (size_t)v.ncls * v.pc)) != BN_OK) ||
+      (v.slices > 1 && (s = p->alloc(&v.xsum, (size_t)v.slices * v.pc * (v.ncls + 1))) != BN_OK) ||
       (bufs && bufs->offsets && bufs->counts && v.form != FIELD_WIDE && !p->bf_in_int8 &&
        (s = p->alloc(&v.seen, P)) != BN_OK)) {
     delete p;

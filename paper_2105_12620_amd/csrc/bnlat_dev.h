@@ -66,6 +66,8 @@ struct DevView {
   unsigned long long* ctr;   // [0] sweep index, [1] accepted total, [2] BF16 vetoes,
                              // [3] the overlapped schedule's recount index
   uint32_t span;             // words of 8 counts whose class sums fit int32 (wide form)
+  uint32_t slices;           // integrand slices of a colour phase (phase_slices)
+  long long* xsum;           // [slices][pc][ncls + 1] their class sums and self terms (null: one slice)
   long long* xpart;          // [ncls][pc] integer class sums of the BF16 pass (kept zero between phases), else null
   uint32_t* unsure;          // [pc] matrix-core results not certified exact (kept zero between phases)
   uint32_t mfma;             // colour phases' evaluation: 0 FP32 form (exact integer stencil), 1 BF16 matrix
@@ -156,7 +158,15 @@ hipError_t launch_phase_split(const DevView& v, uint32_t kappa, hipStream_t s);
 hipError_t launch_phase_batch_split(uint32_t radius, uint32_t k, const DevView* views, const uint32_t* pre,
                                uint32_t nmem, uint32_t blocks, uint32_t kappa, hipStream_t s);
 uint32_t phase_blocks_split(const DevView& v);
+// workgroups of a phase launch: those of its class pixels, for each slice
 uint32_t phase_blocks(const DevView& v);
+// the integrand slices of v's phases where `blocks` workgroups have one slice
+uint32_t phase_slices(const DevView& v, uint32_t blocks);
+// decisions from the slices' class sums
+hipError_t launch_phase_decide(const DevView& v, uint32_t kappa, hipStream_t s);
+uint32_t decide_blocks(const DevView& v);
+hipError_t launch_phase_decide_batch(uint32_t radius, const DevView* views, const uint32_t* pre, uint32_t nmem,
+                                     uint32_t blocks, uint32_t kappa, hipStream_t s);
 // words of 8 counts whose class sums fit int32 (wide form)
 uint32_t phase_span_wide(uint32_t n);
 

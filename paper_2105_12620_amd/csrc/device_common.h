@@ -152,6 +152,45 @@ __device__ __forceinline__ double with_gaussian_part(const DevView& v, uint32_t 
   return total;
 }
 
+// Decision of class pixel j (pixel p) from its weighted class sums; in the BF16
+// form's re-evaluation of a move that its own value accepted, a move that the exact
+// value rejects is a veto.
+__device__ __forceinline__ void decide_move(const DevView& v, uint32_t kappa, uint32_t j, uint32_t p, double sum) {
+  const double total = with_gaussian_part(v, j, p, __dmul_rn(sum, 2.0 / ((double)v.n * (double)v.n)));
+  const bool ok = (v.objective > 0) ? (total < 0.0) : (total > 0.0);
+  v.delta[j] = total;
+  v.accept[j] = ok;
+  if (v.accepts) v.accepts[(size_t)kappa * v.pc + j] = ok;
+  if (v.mfma && !ok) atomicAdd(&v.ctr[2], 1ull);
+}
+
+// A phase launch's blocks, slice after slice: b of the launch's (or member's) n is
+// block b of slice z, with stages (64 integrands) [first, last).
+struct SliceBlock {
+  uint32_t b, z, first, last;
+  __device__ __forceinline__ SliceBlock(const DevView& v, uint32_t b_, uint32_t n)
+      : b(b_), z(0), first(0), last((v.t + 63) / 64) {
+    if (v.slices == 1) return;
+    const uint32_t blocks = n / v.slices, per = (last + v.slices - 1) / v.slices;
+    z = b / blocks;
+    b -= z * blocks;
+    first = z * per;
+    last = min(first + per, last);
+  }
+};
+
+// A workgroup's class sums of one slice (LDS, [NCLS + 1][PX], the self terms last)
+// into xsum; pixel(px) is the class pixel's index, or v.pc past the tile.
+template <int NCLS, uint32_t PX, class F>
+__device__ __forceinline__ void store_slice(const DevView& v, uint32_t z, const unsigned long long* sums, uint32_t threads,
+                                            F pixel) {
+  constexpr uint32_t ROW = NCLS + 1;
+  for (uint32_t e = threadIdx.x; e < PX * ROW; e += threads) {
+    const uint32_t px = e / ROW, c = e - px * ROW, j = pixel(px);
+    if (j < v.pc) v.xsum[((size_t)z * v.pc + j) * ROW + c] = (long long)sums[c * PX + px];
+  }
+}
+
 // The window's offsets in steps of up to eight: row steps of consecutive offsets
 // of a window row, then column steps of eight rows of the columns they leave
 // over.  offset: slot i of step st, and whether the slot holds one.

@@ -78,7 +78,7 @@ struct GramGeom {
 };
 
 template <int FORM, int R, int K>
-__device__ __forceinline__ void gram_body(const DevView& v, uint32_t kappa, uint32_t bkx, uint32_t bky) {
+__device__ __forceinline__ void gram_body(const DevView& v, uint32_t kappa, const SliceBlock sb, uint32_t gx) {
   using G = GramGeom<R, K>;
   constexpr Window<R> WN = WinConst<R>::w;
   constexpr int NCLS = G::NCLS, CT = G::CT, WS = 2 * R + 1, S = G::S;
@@ -86,7 +86,7 @@ __device__ __forceinline__ void gram_body(const DevView& v, uint32_t kappa, uint
   const uint32_t tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const uint32_t c16 = lane & 15, g = lane >> 4;
   const uint32_t m = w / S, part = w % S;      // class row of the wave, its offsets
-  const uint32_t a0 = bky * G::BY, b0 = bkx * 16;
+  const uint32_t a0 = sb.b / gx * G::BY, b0 = sb.b % gx * 16;
   const uint32_t ky = kappa / K, kx = kappa - ky * K;
   const uint32_t P = v.w * v.h;
 
@@ -119,6 +119,9 @@ __device__ __forceinline__ void gram_body(const DevView& v, uint32_t kappa, uint
   // read back)
   const bool in = a0 + w % G::BY < v.ch && b0 + c16 < v.cw;
   const uint32_t nsrc = (g * v.pc + (in ? (a0 + w % G::BY) * v.cw + b0 + c16 : 0)) * 16;
+  const uint32_t first = sb.first, last = sb.last;   // Tp is a multiple of 128, padded integrands are 0
+#pragma unroll
+  for (int k = 0; k < G::NC; ++k) src[k] += (size_t)first * 4 * ps[k];
   auto issue = [&](uint32_t st, uint32_t buf) {   // stages in order
     const char* nb = (const char*)v.n8 + (size_t)st * 64 * v.pc;
     u32x4* to = lds4 + buf * G::STAGE;
@@ -145,17 +148,16 @@ __device__ __forceinline__ void gram_body(const DevView& v, uint32_t kappa, uint
     for (int ct = 0; ct < CT; ++ct) acc[o][ct] = (i32x4){0, 0, 0, 0};
   int zn = 0, zo = 0;
 
-  const uint32_t stages = (v.t + 63) / 64;   // Tp is a multiple of 128, padded integrands are 0
-  issue(0, 0);
+  issue(first, 0);
   // words of the lane in a stage: its class pixel's, and column c16 of the
   // wave's first region row, in plane g
   const uint32_t nword = 4 * G::PLANE + 64 * m + lane, fword = g * G::PLANE + K * m * G::RW + c16;
   const uint32_t own = g * G::PLANE + (K * m + R) * G::RW + K * c16 + R;
-  for (uint32_t st = 0; st < stages; ++st) {
+  for (uint32_t st = first; st < last; ++st) {
     // stage st has landed in every wave, and the other half is read
     barrier_vm<0>();
-    if (st + 1 < stages) issue(st + 1, (st + 1) & 1);
-    const u32x4* bf = lds4 + (st & 1) * G::STAGE;
+    if (st + 1 < last) issue(st + 1, (st + 1 - first) & 1);
+    const u32x4* bf = lds4 + ((st - first) & 1) * G::STAGE;
     const u32x4 cn = bf[nword], cp = bf[own];
     i32x4 an, am;   // A operands: dc, or f' and -f
 #pragma unroll
@@ -218,10 +220,17 @@ __device__ __forceinline__ void gram_body(const DevView& v, uint32_t kappa, uint
     }
   }
   __syncthreads();
+  auto pixel = [&](uint32_t px) {
+    const uint32_t a = a0 + (px >> 4), b = b0 + (px & 15);
+    return a < v.ch && b < v.cw ? a * v.cw + b : v.pc;
+  };
+  if (v.slices > 1) {
+    store_slice<NCLS, G::PX>(v, sb.z, sums, 64 * G::NW, pixel);
+    return;
+  }
   if (tid >= (uint32_t)G::PX) return;
-  const uint32_t a = a0 + (tid >> 4), b = b0 + (tid & 15);
-  if (a >= v.ch || b >= v.cw) return;
-  const uint32_t j = a * v.cw + b;
+  const uint32_t j = pixel(tid);
+  if (j == v.pc) return;
   const long long z = (long long)sums[NCLS * G::PX + tid];
   double sum = 0.0;
 #pragma unroll
@@ -229,24 +238,18 @@ __device__ __forceinline__ void gram_body(const DevView& v, uint32_t kappa, uint
     const long long x = (long long)WN.csize[c] * z - 2 * (long long)sums[c * G::PX + tid];
     sum = __dadd_rn(sum, __dmul_rn(v.wd[c], (double)x));
   }
-  double total = __dmul_rn(sum, 2.0 / ((double)v.n * (double)v.n));
-  total = with_gaussian_part(v, j, (ky + K * a) * v.w + kx + K * b, total);
-  const bool ok = (v.objective > 0) ? (total < 0.0) : (total > 0.0);
-  v.delta[j] = total;
-  v.accept[j] = ok;
-  if (v.accepts) v.accepts[(size_t)kappa * v.pc + j] = ok;
+  decide_move(v, kappa, j, (ky + K * (a0 + (tid >> 4))) * v.w + kx + K * (b0 + (tid & 15)), sum);
 }
 
-// One-dimensional grid of gx blocks a row, renumbered per XCD: an L2 then
-// serves whole rows of blocks and their halos are read from memory once.
+// One-dimensional grid of gx blocks a row, slice after slice, renumbered per XCD:
+// an L2 then serves whole rows of blocks and their halos are read from memory once.
 template <int FORM, int R, int K>
 __global__ __launch_bounds__(64 * (GramGeom<R, K>::NW)) void k_gram(DevView v, uint32_t kappa, uint32_t gx) {
   // the colour phases' waves issue ahead of the sweep-wide recount running
   // beside them (k_commit and the BF16 form's kernels likewise), which fills
   // the remaining issue slots
   __builtin_amdgcn_s_setprio(2);
-  const uint32_t wk = xcd_block(blockIdx.x, gridDim.x);
-  gram_body<FORM, R, K>(v, kappa, wk % gx, wk / gx);
+  gram_body<FORM, R, K>(v, kappa, SliceBlock(v, xcd_block(blockIdx.x, gridDim.x), gridDim.x), gx);
 }
 
 // Batched form: member i owns blocks pre[i] .. pre[i+1]-1, laid out as its own
@@ -259,8 +262,7 @@ __global__ __launch_bounds__(64 * (GramGeom<R, K>::NW)) void k_gram_batch(const 
   const uint32_t wk = xcd_block(blockIdx.x, gridDim.x);
   const uint32_t i = batch_member(pre, nmem, wk);
   const DevView v = views[i];
-  const uint32_t lb = wk - pre[i], gx = (v.cw + 15) / 16;
-  gram_body<FORM, R, K>(v, kappa, lb % gx, lb / gx);
+  gram_body<FORM, R, K>(v, kappa, SliceBlock(v, wk - pre[i], pre[i + 1] - pre[i]), (v.cw + 15) / 16);
 }
 
 // Raises the LDS launch limit (gfx950 has 160 KiB per CU), once per kernel.
@@ -274,15 +276,16 @@ hipError_t gram_lds(F kernel, int bytes) {
 
 // The entry points of one form (one source each).
 #define BN_GRAM_FORM(FORM, NAME)                                                                                       \
-  hipError_t launch_phase_##NAME(const DevView& v, uint32_t kappa, hipStream_t s) {                                 \
-    return by_radius_k(v.radius, v.k, [&](auto r, auto k) {                                                            \
+  hipError_t launch_phase_##NAME(const DevView& v, uint32_t kappa, hipStream_t s) {                                    \
+    const hipError_t e = by_radius_k(v.radius, v.k, [&](auto r, auto k) {                                              \
       using G = GramGeom<r(), k()>;                                                                                    \
       static const hipError_t ready = gram_lds(k_gram<FORM, r(), k()>, G::LDS_BYTES);                                  \
       if (ready != hipSuccess) return ready;                                                                           \
       hipLaunchKernelGGL((k_gram<FORM, r(), k()>), dim3(phase_blocks_##NAME(v)), dim3(64 * G::NW),                          \
-                         (size_t)G::LDS_BYTES, s, v, kappa, (v.cw + 15) / 16);                                \
+                         (size_t)G::LDS_BYTES, s, v, kappa, (v.cw + 15) / 16);                                         \
       return hipGetLastError();                                                                                        \
     });                                                                                                                \
+    return e != hipSuccess || v.slices == 1 ? e : launch_phase_decide(v, kappa, s);                                    \
   }                                                                                                                    \
   hipError_t launch_phase_batch_##NAME(uint32_t radius, uint32_t k, const DevView* views, const uint32_t* pre,         \
                                        uint32_t nmem, uint32_t blocks, uint32_t kappa, hipStream_t s) {  \
@@ -301,7 +304,7 @@ hipError_t gram_lds(F kernel, int bytes) {
       rows = (uint32_t)GramGeom<r(), k()>::BY;                                                                         \
       return hipSuccess;                                                                                               \
     });                                                                                                                \
-    return ((v.cw + 15) / 16) * ((v.ch + rows - 1) / rows);                                                            \
+    return ((v.cw + 15) / 16) * ((v.ch + rows - 1) / rows) * v.slices;                                                 \
   }
 
 }  // namespace bnlat

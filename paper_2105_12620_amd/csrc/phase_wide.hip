@@ -86,7 +86,8 @@ __device__ __forceinline__ int stage_dc(const u32x4 cn, const u32x4 co, uint32_t
 }
 
 template <int R, int K>
-__device__ __forceinline__ void phase_body(const DevView& v, uint32_t kappa, uint32_t span, uint32_t bkx, uint32_t bky) {
+__device__ __forceinline__ void phase_body(const DevView& v, uint32_t kappa, uint32_t span, const SliceBlock sb,
+                                           uint32_t bgx) {
   using G = PhaseGeom<R, K>;
   constexpr Window<R> WN = WinConst<R>::w;
   constexpr int NCLS = G::NCLS, V = G::V, WS = 2 * R + 1;
@@ -96,7 +97,7 @@ __device__ __forceinline__ void phase_body(const DevView& v, uint32_t kappa, uin
   const uint32_t tid = threadIdx.x, lane = tid % G::TPW, slot = tid / G::TPW;
   u32x4* reg = lds4 + G::SUMS / 2 + slot * G::PLANE;
   const uint32_t tx = lane & 7, ty = lane >> 3;
-  const uint32_t a0 = bky * 8, b0 = bkx * 8;
+  const uint32_t a0 = sb.b / bgx * 8, b0 = sb.b % bgx * 8;
   const uint32_t ky = kappa / K, kx = kappa - ky * K;
   // top-left region pixel, made non-negative modulo the tile
   const uint32_t ys = (ky + K * a0 + v.h * (R / v.h + 1) - R) % v.h;
@@ -148,7 +149,8 @@ __device__ __forceinline__ void phase_body(const DevView& v, uint32_t kappa, uin
 
   const char* fld = (const char*)v.cnt;
   const char* nfl = (const char*)v.c_new;
-  const uint32_t words = (v.t + IPW - 1) / IPW;
+  // words of the slice: up to `words`
+  const uint32_t from = sb.first * (64 / IPW), words = min(sb.last * (64 / IPW), (v.t + IPW - 1) / IPW);
   u32x4 q[G::ITER], qc[V];
   // words past the last repeat it (and count nothing)
   auto issue = [&](uint32_t word) {
@@ -162,10 +164,10 @@ __device__ __forceinline__ void phase_body(const DevView& v, uint32_t kappa, uin
   };
   // first word of the wave: uniform, so the loop is
   const uint32_t first = __builtin_amdgcn_readfirstlane(slot);
-  if (G::AHEAD) issue(slot);
+  if (G::AHEAD) issue(from + slot);
   __syncthreads();   // the sums are cleared
   uint32_t since = 0;
-  for (uint32_t wd = first; wd < words; wd += G::W) {
+  for (uint32_t wd = from + first; wd < words; wd += G::W) {
     const uint32_t word = wd + (slot - first);
     if (!G::AHEAD) issue(word);
 #pragma unroll
@@ -217,12 +219,19 @@ __device__ __forceinline__ void phase_body(const DevView& v, uint32_t kappa, uin
   flush();
   __syncthreads();
 
+  auto pixel = [&](uint32_t px) {
+    const uint32_t a = a0 + (px >> 3), b = b0 + (px & 7);
+    return a < v.ch && b < v.cw ? a * v.cw + b : v.pc;
+  };
+  if (v.slices > 1) {
+    store_slice<NCLS, 64>(v, sb.z, sums, G::NT, pixel);
+    return;
+  }
   // decision, a lane of the first wave per class pixel: one FP64 weighted sum
   // of the exact class sums in increasing distance
   if (tid >= 64) return;
-  const uint32_t a = a0 + (tid >> 3), b = b0 + (tid & 7);
-  if (a >= v.ch || b >= v.cw) return;
-  const uint32_t j = a * v.cw + b;
+  const uint32_t j = pixel(tid);
+  if (j == v.pc) return;
   if (v.mfma && !v.accept[j]) return;
   const long long z = (long long)sums[NCLS * 64 + tid];
   double acc = 0.0;
@@ -231,26 +240,18 @@ __device__ __forceinline__ void phase_body(const DevView& v, uint32_t kappa, uin
     const long long x = (long long)WN.csize[c] * z - 2 * (long long)sums[c * 64 + tid];
     acc = __dadd_rn(acc, __dmul_rn(v.wd[c], (double)x));
   }
-  double total = __dmul_rn(acc, 2.0 / ((double)v.n * (double)v.n));
-  total = with_gaussian_part(v, j, (ky + K * a) * v.w + kx + K * b, total);
-  const bool ok = (v.objective > 0) ? (total < 0.0) : (total > 0.0);
-  v.delta[j] = total;
-  v.accept[j] = ok;
-  // the BF16 form's re-evaluation of a move that its own value accepted: a
-  // move the exact value rejects is a veto
-  if (v.mfma && !ok) atomicAdd(&v.ctr[2], 1ull);
+  decide_move(v, kappa, j, (ky + K * (a0 + (tid >> 3))) * v.w + kx + K * (b0 + (tid & 7)), acc);
 }
 
-// One-dimensional grid of gx blocks a row, renumbered per XCD: an L2 then
-// serves whole rows of blocks and their halos are read from memory once.
+// One-dimensional grid of gx blocks a row, slice after slice, renumbered per XCD:
+// an L2 then serves whole rows of blocks and their halos are read from memory once.
 template <int R, int K>
 __global__ __launch_bounds__((PhaseGeom<R, K>::NT)) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_phase(DevView v, uint32_t kappa, uint32_t span, uint32_t gx) {
   // the colour phases' waves issue ahead of the sweep-wide recount running
   // beside them (k_commit and the BF16 form's kernels likewise), which fills
   // the remaining issue slots
   __builtin_amdgcn_s_setprio(2);
-  const uint32_t wk = xcd_block(blockIdx.x, gridDim.x);
-  phase_body<R, K>(v, kappa, span, wk % gx, wk / gx);
+  phase_body<R, K>(v, kappa, span, SliceBlock(v, xcd_block(blockIdx.x, gridDim.x), gridDim.x), gx);
 }
 
 // Batched form: member i owns blocks pre[i] .. pre[i+1]-1, laid out as its own
@@ -263,8 +264,7 @@ __global__ __launch_bounds__((PhaseGeom<R, K>::NT)) __attribute__((amdgpu_waves_
   const uint32_t wk = xcd_block(blockIdx.x, gridDim.x);
   const uint32_t i = batch_member(pre, nmem, wk);
   const DevView v = views[i];
-  const uint32_t lb = wk - pre[i], gx = (v.cw + 7) / 8;
-  phase_body<R, K>(v, kappa, v.span, lb % gx, lb / gx);
+  phase_body<R, K>(v, kappa, v.span, SliceBlock(v, wk - pre[i], pre[i + 1] - pre[i]), (v.cw + 7) / 8);
 }
 
 // Raises the LDS launch limit (gfx950 has 160 KiB per CU), once per kernel.
@@ -299,7 +299,8 @@ hipError_t phase_batch_rk(const DevView* views, const uint32_t* pre, uint32_t nm
 }  // namespace
 
 hipError_t launch_phase_wide(const DevView& v, uint32_t kappa, hipStream_t s) {
-  return by_radius_k(v.radius, v.k, [&](auto r, auto k) { return phase_rk<r(), k()>(v, kappa, s); });
+  const hipError_t e = by_radius_k(v.radius, v.k, [&](auto r, auto k) { return phase_rk<r(), k()>(v, kappa, s); });
+  return e != hipSuccess || v.slices == 1 ? e : launch_phase_decide(v, kappa, s);
 }
 
 hipError_t launch_phase_batch_wide(uint32_t radius, uint32_t k, const DevView* views, const uint32_t* pre,
@@ -309,7 +310,7 @@ hipError_t launch_phase_batch_wide(uint32_t radius, uint32_t k, const DevView* v
   });
 }
 
-uint32_t phase_blocks_wide(const DevView& v) { return ((v.cw + 7) / 8) * ((v.ch + 7) / 8); }
+uint32_t phase_blocks_wide(const DevView& v) { return ((v.cw + 7) / 8) * ((v.ch + 7) / 8) * v.slices; }
 
 // Words of 8 integrands whose class sums fit int32: every product dc_t c_q,t is
 // at most N^2 and a class has at most 12 offsets for radii up to 6.
