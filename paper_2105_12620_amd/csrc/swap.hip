@@ -15,6 +15,7 @@
 #include <stdint.h>
 
 #include <algorithm>
+#include <cmath>
 
 #include "bnlat_dev.h"
 #include "device_common.h"
@@ -336,17 +337,22 @@ template <int R>
 __device__ __forceinline__ bool swap_decide(const DevView& v, const SwapView& sv, uint32_t kappa, uint32_t i,
                                             uint32_t lane, uint32_t& a, uint32_t& b) {
   constexpr int NCLS = WinConst<R>::NCLS;
-  static_assert(NCLS <= 32, "a lane per class and member");
+  static_assert(NCLS < 32, "a lane per class and member, and one for d2");
   const uint32_t mask = swap_mask(v, kappa);
   const uint32_t L = kappa * sv.m + 2 * i;
   a = __builtin_amdgcn_readfirstlane(sv.perm[L] ^ mask);
   b = __builtin_amdgcn_readfirstlane(sv.perm[L + 1] ^ mask);
   const int c = (int)(lane & 31);
-  long long x = 0, d2 = 0;
-  for (uint32_t z = 0; z < sv.slices; ++z) {
-    if (c < NCLS) x += sv.xs[((size_t)z * sv.m + 2 * i + (lane >> 5)) * NCLS + c];
-    d2 += sv.d2[(size_t)z * (sv.m >> 1) + i];
+  // lane NCLS: the slices' d2
+  long long x = 0;
+  const bool sq = lane == (uint32_t)NCLS;
+  const long long* q = sq ? sv.d2 + i : sv.xs + ((size_t)2 * i + (lane >> 5)) * NCLS + c;
+  const size_t step = sq ? sv.m >> 1 : (size_t)sv.m * NCLS;
+  if (sq || c < NCLS) {
+#pragma unroll 8
+    for (uint32_t z = 0; z < sv.slices; ++z) x += q[z * step];
   }
+  const long long d2 = __shfl(x, NCLS);
   x += __shfl_xor(x, 32);
   // offsets o with a + o = b on the torus: o = d or d - W per axis with
   // d = (b - a) mod W (two per axis at most because r < min(W, H)); W and H
@@ -520,8 +526,11 @@ hipError_t prepare_swap_kernels() {
 }
 
 // Integrand slices: enough workgroups for about 1024 threads on each of the
-// 256 CUs, and few enough stages per slice that every per-lane int32 step sum
-// stays below 2^31.
+// 256 CUs; at least sqrt(stages / 8) stages a slice, for the decision reads every
+// slice's sums; and few enough that every per-lane int32 step sum stays below 2^31.
+// Sweeps on int8 at r = 4 by least stages a slice: 32^2 (four blocks) T = 256
+// 1: 65 us, 2: 72; T = 1024 1: 77, 2: 74, 4: 81; T = 4096 1: 149, 2: 108, 4: 102,
+// 8: 115; 8^2 T = 16384 1: 170, 4: 85, 8: 80.
 template <int R>
 uint32_t stages_per_slice(const DevView& v, const SwapView& sv) {
   using G = SwapGeom<R>;
@@ -531,7 +540,8 @@ uint32_t stages_per_slice(const DevView& v, const SwapView& sv) {
   const double per_stage = sv.row8 ? 16.0 * 126.0 * 126.0 : 8.0 * (double)v.n * v.n;
   const uint32_t smax = (uint32_t)std::max(1.0, std::floor(2147483647.0 / per_stage));
   const uint32_t target = 262144 / G::NT;
-  const uint32_t nz = std::max<uint32_t>(1, std::min<uint32_t>(stages, (target + blocks - 1) / blocks));
+  const uint32_t least = std::max(1u, (uint32_t)std::sqrt(stages / 8.0));
+  const uint32_t nz = std::max<uint32_t>(1, std::min<uint32_t>(stages / least, (target + blocks - 1) / blocks));
   return std::min((stages + nz - 1) / nz, smax);
 }
 
