@@ -1043,7 +1043,7 @@ bn_status batch_recount(bn_batch b, int set, uint32_t ahead, hipStream_t st) {
 bn_status batch_evaluate(bn_batch b, int set, uint32_t kappa) {
   const uint32_t t = set * b->colour_k * b->colour_k + kappa;
   for (BatchGroup& g : b->stage_groups) {
-    HIPCHK(launch_phase_batch(g.form, g.radius, g.k, g.views[t], g.d_pre, (uint32_t)g.idx.size(), g.blocks, kappa,
+    HIPCHK(launch_phase_batch(g.form, g.radius, g.k, g.decide > 0, g.views[t], g.d_pre, (uint32_t)g.idx.size(), g.blocks, kappa,
                               b->stream));
     if (g.decide)
       HIPCHK(launch_phase_decide_batch(g.radius, g.views[t], g.d_decide, (uint32_t)g.idx.size(), g.decide, kappa,

@@ -147,15 +147,15 @@ hipError_t launch_gauss_energy(const DevView& v, double* gsum, hipStream_t s);
 
 // energy change and decision of a colour phase, one source per form
 hipError_t launch_phase_wide(const DevView& v, uint32_t kappa, hipStream_t s);
-hipError_t launch_phase_batch_wide(uint32_t radius, uint32_t k, const DevView* views, const uint32_t* pre,
+hipError_t launch_phase_batch_wide(uint32_t radius, uint32_t k, bool sliced, const DevView* views, const uint32_t* pre,
                                uint32_t nmem, uint32_t blocks, uint32_t kappa, hipStream_t s);
 uint32_t phase_blocks_wide(const DevView& v);
 hipError_t launch_phase_narrow(const DevView& v, uint32_t kappa, hipStream_t s);
-hipError_t launch_phase_batch_narrow(uint32_t radius, uint32_t k, const DevView* views, const uint32_t* pre,
+hipError_t launch_phase_batch_narrow(uint32_t radius, uint32_t k, bool sliced, const DevView* views, const uint32_t* pre,
                                uint32_t nmem, uint32_t blocks, uint32_t kappa, hipStream_t s);
 uint32_t phase_blocks_narrow(const DevView& v);
 hipError_t launch_phase_split(const DevView& v, uint32_t kappa, hipStream_t s);
-hipError_t launch_phase_batch_split(uint32_t radius, uint32_t k, const DevView* views, const uint32_t* pre,
+hipError_t launch_phase_batch_split(uint32_t radius, uint32_t k, bool sliced, const DevView* views, const uint32_t* pre,
                                uint32_t nmem, uint32_t blocks, uint32_t kappa, hipStream_t s);
 uint32_t phase_blocks_split(const DevView& v);
 // workgroups of a phase launch: those of its class pixels, for each slice
@@ -175,7 +175,8 @@ int count_kind(const DevView& v);
 uint32_t count_blocks(const DevView& v);
 hipError_t launch_count_batch(int kind, const DevView* views, const uint32_t* pre, uint32_t nmem,
                               uint32_t blocks, uint32_t kappa, hipStream_t s);
-hipError_t launch_phase_batch(uint32_t form, uint32_t radius, uint32_t k, const DevView* views, const uint32_t* pre,
+// sliced: a member has several integrand slices
+hipError_t launch_phase_batch(uint32_t form, uint32_t radius, uint32_t k, bool sliced, const DevView* views, const uint32_t* pre,
                               uint32_t nmem, uint32_t blocks, uint32_t kappa, hipStream_t s);
 hipError_t launch_commit_batch(const DevView* views, const uint32_t* pre, uint32_t nmem, uint32_t blocks,
                                uint32_t kappa, hipStream_t s);

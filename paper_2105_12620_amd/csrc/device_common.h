@@ -165,12 +165,15 @@ __device__ __forceinline__ void decide_move(const DevView& v, uint32_t kappa, ui
 }
 
 // A phase launch's blocks, slice after slice: b of the launch's (or member's) n is
-// block b of slice z, with stages (64 integrands) [first, last).
+// block b of slice z, with stages (64 integrands) [first, last).  SLICED: launches
+// of problems with several slices (the others' kernels are compiled without; their
+// prologue was 1 to 2 us longer with).
+template <bool SLICED>
 struct SliceBlock {
   uint32_t b, z, first, last;
   __device__ __forceinline__ SliceBlock(const DevView& v, uint32_t b_, uint32_t n)
       : b(b_), z(0), first(0), last((v.t + 63) / 64) {
-    if (v.slices == 1) return;
+    if (!SLICED) return;
     const uint32_t blocks = n / v.slices, per = (last + v.slices - 1) / v.slices;
     z = b / blocks;
     b -= z * blocks;

@@ -1254,12 +1254,12 @@ hipError_t launch_gauss_energy(const DevView& v, double* gsum, hipStream_t s) {
 
 // ------------------------------------------------------------------ batches
 
-hipError_t launch_phase_batch(uint32_t form, uint32_t radius, uint32_t k, const DevView* views, const uint32_t* pre,
+hipError_t launch_phase_batch(uint32_t form, uint32_t radius, uint32_t k, bool sliced, const DevView* views, const uint32_t* pre,
                               uint32_t nmem, uint32_t blocks, uint32_t kappa, hipStream_t s) {
   switch (form) {
-    case FIELD_NARROW: return launch_phase_batch_narrow(radius, k, views, pre, nmem, blocks, kappa, s);
-    case FIELD_SPLIT: return launch_phase_batch_split(radius, k, views, pre, nmem, blocks, kappa, s);
-    default: return launch_phase_batch_wide(radius, k, views, pre, nmem, blocks, kappa, s);
+    case FIELD_NARROW: return launch_phase_batch_narrow(radius, k, sliced, views, pre, nmem, blocks, kappa, s);
+    case FIELD_SPLIT: return launch_phase_batch_split(radius, k, sliced, views, pre, nmem, blocks, kappa, s);
+    default: return launch_phase_batch_wide(radius, k, sliced, views, pre, nmem, blocks, kappa, s);
   }
 }
 

@@ -77,8 +77,8 @@ struct GramGeom {
   static_assert(LDS_BYTES <= 163840, "phase block exceeds the LDS");
 };
 
-template <int FORM, int R, int K>
-__device__ __forceinline__ void gram_body(const DevView& v, uint32_t kappa, const SliceBlock sb, uint32_t gx) {
+template <int FORM, int R, int K, bool SLICED>
+__device__ __forceinline__ void gram_body(const DevView& v, uint32_t kappa, const SliceBlock<SLICED> sb, uint32_t gx) {
   using G = GramGeom<R, K>;
   constexpr Window<R> WN = WinConst<R>::w;
   constexpr int NCLS = G::NCLS, CT = G::CT, WS = 2 * R + 1, S = G::S;
@@ -120,8 +120,10 @@ __device__ __forceinline__ void gram_body(const DevView& v, uint32_t kappa, cons
   const bool in = a0 + w % G::BY < v.ch && b0 + c16 < v.cw;
   const uint32_t nsrc = (g * v.pc + (in ? (a0 + w % G::BY) * v.cw + b0 + c16 : 0)) * 16;
   const uint32_t first = sb.first, last = sb.last;   // Tp is a multiple of 128, padded integrands are 0
+  if (SLICED) {
 #pragma unroll
-  for (int k = 0; k < G::NC; ++k) src[k] += (size_t)first * 4 * ps[k];
+    for (int k = 0; k < G::NC; ++k) src[k] += (size_t)first * 4 * ps[k];
+  }
   auto issue = [&](uint32_t st, uint32_t buf) {   // stages in order
     const char* nb = (const char*)v.n8 + (size_t)st * 64 * v.pc;
     u32x4* to = lds4 + buf * G::STAGE;
@@ -224,7 +226,7 @@ __device__ __forceinline__ void gram_body(const DevView& v, uint32_t kappa, cons
     const uint32_t a = a0 + (px >> 4), b = b0 + (px & 15);
     return a < v.ch && b < v.cw ? a * v.cw + b : v.pc;
   };
-  if (v.slices > 1) {
+  if (SLICED && v.slices > 1) {
     store_slice<NCLS, G::PX>(v, sb.z, sums, 64 * G::NW, pixel);
     return;
   }
@@ -243,18 +245,18 @@ __device__ __forceinline__ void gram_body(const DevView& v, uint32_t kappa, cons
 
 // One-dimensional grid of gx blocks a row, slice after slice, renumbered per XCD:
 // an L2 then serves whole rows of blocks and their halos are read from memory once.
-template <int FORM, int R, int K>
+template <int FORM, int R, int K, bool SLICED>
 __global__ __launch_bounds__(64 * (GramGeom<R, K>::NW)) void k_gram(DevView v, uint32_t kappa, uint32_t gx) {
   // the colour phases' waves issue ahead of the sweep-wide recount running
   // beside them (k_commit and the BF16 form's kernels likewise), which fills
   // the remaining issue slots
   __builtin_amdgcn_s_setprio(2);
-  gram_body<FORM, R, K>(v, kappa, SliceBlock(v, xcd_block(blockIdx.x, gridDim.x), gridDim.x), gx);
+  gram_body<FORM, R, K, SLICED>(v, kappa, SliceBlock<SLICED>(v, xcd_block(blockIdx.x, gridDim.x), gridDim.x), gx);
 }
 
 // Batched form: member i owns blocks pre[i] .. pre[i+1]-1, laid out as its own
 // grid.
-template <int FORM, int R, int K>
+template <int FORM, int R, int K, bool SLICED>
 __global__ __launch_bounds__(64 * (GramGeom<R, K>::NW)) void k_gram_batch(const DevView* __restrict__ views,
                                                                           const uint32_t* __restrict__ pre,
                                                                           uint32_t nmem, uint32_t kappa) {
@@ -262,7 +264,8 @@ __global__ __launch_bounds__(64 * (GramGeom<R, K>::NW)) void k_gram_batch(const 
   const uint32_t wk = xcd_block(blockIdx.x, gridDim.x);
   const uint32_t i = batch_member(pre, nmem, wk);
   const DevView v = views[i];
-  gram_body<FORM, R, K>(v, kappa, SliceBlock(v, wk - pre[i], pre[i + 1] - pre[i]), (v.cw + 15) / 16);
+  gram_body<FORM, R, K, SLICED>(v, kappa, SliceBlock<SLICED>(v, wk - pre[i], SLICED ? pre[i + 1] - pre[i] : 0),
+                                (v.cw + 15) / 16);
 }
 
 // Raises the LDS launch limit (gfx950 has 160 KiB per CU), once per kernel.
@@ -279,23 +282,30 @@ hipError_t gram_lds(F kernel, int bytes) {
   hipError_t launch_phase_##NAME(const DevView& v, uint32_t kappa, hipStream_t s) {                                    \
     const hipError_t e = by_radius_k(v.radius, v.k, [&](auto r, auto k) {                                              \
       using G = GramGeom<r(), k()>;                                                                                    \
-      static const hipError_t ready = gram_lds(k_gram<FORM, r(), k()>, G::LDS_BYTES);                                  \
-      if (ready != hipSuccess) return ready;                                                                           \
-      hipLaunchKernelGGL((k_gram<FORM, r(), k()>), dim3(phase_blocks_##NAME(v)), dim3(64 * G::NW),                          \
-                         (size_t)G::LDS_BYTES, s, v, kappa, (v.cw + 15) / 16);                                         \
-      return hipGetLastError();                                                                                        \
+      auto launch = [&](auto sliced) {                                                                                 \
+        static const hipError_t ready = gram_lds(k_gram<FORM, r(), k(), sliced()>, G::LDS_BYTES);                      \
+        if (ready != hipSuccess) return ready;                                                                         \
+        hipLaunchKernelGGL((k_gram<FORM, r(), k(), sliced()>), dim3(phase_blocks_##NAME(v)), dim3(64 * G::NW),         \
+                           (size_t)G::LDS_BYTES, s, v, kappa, (v.cw + 15) / 16);                                       \
+        return hipGetLastError();                                                                                      \
+      };                                                                                                               \
+      return v.slices > 1 ? launch(std::true_type()) : launch(std::false_type());                                      \
     });                                                                                                                \
     return e != hipSuccess || v.slices == 1 ? e : launch_phase_decide(v, kappa, s);                                    \
   }                                                                                                                    \
-  hipError_t launch_phase_batch_##NAME(uint32_t radius, uint32_t k, const DevView* views, const uint32_t* pre,         \
-                                       uint32_t nmem, uint32_t blocks, uint32_t kappa, hipStream_t s) {  \
+  hipError_t launch_phase_batch_##NAME(uint32_t radius, uint32_t k, bool sliced, const DevView* views,                 \
+                                       const uint32_t* pre, uint32_t nmem, uint32_t blocks, uint32_t kappa,            \
+                                       hipStream_t s) {                                                                \
     return by_radius_k(radius, k, [&](auto r, auto kk) {                                                               \
       using G = GramGeom<r(), kk()>;                                                                                   \
-      static const hipError_t ready = gram_lds(k_gram_batch<FORM, r(), kk()>, G::LDS_BYTES);                           \
-      if (ready != hipSuccess) return ready;                                                                           \
-      hipLaunchKernelGGL((k_gram_batch<FORM, r(), kk()>), dim3(blocks), dim3(64 * G::NW), (size_t)G::LDS_BYTES, s,          \
-                         views, pre, nmem, kappa);                                                            \
-      return hipGetLastError();                                                                                        \
+      auto launch = [&](auto sl) {                                                                                     \
+        static const hipError_t ready = gram_lds(k_gram_batch<FORM, r(), kk(), sl()>, G::LDS_BYTES);                   \
+        if (ready != hipSuccess) return ready;                                                                         \
+        hipLaunchKernelGGL((k_gram_batch<FORM, r(), kk(), sl()>), dim3(blocks), dim3(64 * G::NW),                      \
+                           (size_t)G::LDS_BYTES, s, views, pre, nmem, kappa);                                          \
+        return hipGetLastError();                                                                                      \
+      };                                                                                                               \
+      return sliced ? launch(std::true_type()) : launch(std::false_type());                                            \
     });                                                                                                                \
   }                                                                                                                    \
   uint32_t phase_blocks_##NAME(const DevView& v) {                                                                     \

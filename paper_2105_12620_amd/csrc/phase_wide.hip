@@ -85,8 +85,8 @@ __device__ __forceinline__ int stage_dc(const u32x4 cn, const u32x4 co, uint32_t
   return z;
 }
 
-template <int R, int K>
-__device__ __forceinline__ void phase_body(const DevView& v, uint32_t kappa, uint32_t span, const SliceBlock sb,
+template <int R, int K, bool SLICED>
+__device__ __forceinline__ void phase_body(const DevView& v, uint32_t kappa, uint32_t span, const SliceBlock<SLICED> sb,
                                            uint32_t bgx) {
   using G = PhaseGeom<R, K>;
   constexpr Window<R> WN = WinConst<R>::w;
@@ -223,7 +223,7 @@ __device__ __forceinline__ void phase_body(const DevView& v, uint32_t kappa, uin
     const uint32_t a = a0 + (px >> 3), b = b0 + (px & 7);
     return a < v.ch && b < v.cw ? a * v.cw + b : v.pc;
   };
-  if (v.slices > 1) {
+  if (SLICED && v.slices > 1) {
     store_slice<NCLS, 64>(v, sb.z, sums, G::NT, pixel);
     return;
   }
@@ -245,18 +245,18 @@ __device__ __forceinline__ void phase_body(const DevView& v, uint32_t kappa, uin
 
 // One-dimensional grid of gx blocks a row, slice after slice, renumbered per XCD:
 // an L2 then serves whole rows of blocks and their halos are read from memory once.
-template <int R, int K>
+template <int R, int K, bool SLICED>
 __global__ __launch_bounds__((PhaseGeom<R, K>::NT)) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_phase(DevView v, uint32_t kappa, uint32_t span, uint32_t gx) {
   // the colour phases' waves issue ahead of the sweep-wide recount running
   // beside them (k_commit and the BF16 form's kernels likewise), which fills
   // the remaining issue slots
   __builtin_amdgcn_s_setprio(2);
-  phase_body<R, K>(v, kappa, span, SliceBlock(v, xcd_block(blockIdx.x, gridDim.x), gridDim.x), gx);
+  phase_body<R, K, SLICED>(v, kappa, span, SliceBlock<SLICED>(v, xcd_block(blockIdx.x, gridDim.x), gridDim.x), gx);
 }
 
 // Batched form: member i owns blocks pre[i] .. pre[i+1]-1, laid out as its own
 // grid.
-template <int R, int K>
+template <int R, int K, bool SLICED>
 __global__ __launch_bounds__((PhaseGeom<R, K>::NT)) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_phase_batch(const DevView* __restrict__ views,
                                                                      const uint32_t* __restrict__ pre, uint32_t nmem,
                                                                      uint32_t kappa) {
@@ -264,7 +264,8 @@ __global__ __launch_bounds__((PhaseGeom<R, K>::NT)) __attribute__((amdgpu_waves_
   const uint32_t wk = xcd_block(blockIdx.x, gridDim.x);
   const uint32_t i = batch_member(pre, nmem, wk);
   const DevView v = views[i];
-  phase_body<R, K>(v, kappa, v.span, SliceBlock(v, wk - pre[i], pre[i + 1] - pre[i]), (v.cw + 7) / 8);
+  phase_body<R, K, SLICED>(v, kappa, v.span, SliceBlock<SLICED>(v, wk - pre[i], SLICED ? pre[i + 1] - pre[i] : 0),
+                           (v.cw + 7) / 8);
 }
 
 // Raises the LDS launch limit (gfx950 has 160 KiB per CU), once per kernel.
@@ -274,24 +275,24 @@ hipError_t phase_lds(F kernel, int bytes) {
                        : hipSuccess;
 }
 
-template <int R, int K>
+template <int R, int K, bool SLICED>
 hipError_t phase_rk(const DevView& v, uint32_t kappa, hipStream_t s) {
   using G = PhaseGeom<R, K>;
-  static const hipError_t ready = phase_lds(k_phase<R, K>, G::LDS_BYTES);
+  static const hipError_t ready = phase_lds(k_phase<R, K, SLICED>, G::LDS_BYTES);
   if (ready != hipSuccess) return ready;
   const uint32_t gx = (v.cw + 7) / 8;
-  hipLaunchKernelGGL((k_phase<R, K>), dim3(phase_blocks_wide(v)), dim3(G::NT), (size_t)G::LDS_BYTES, s, v, kappa,
+  hipLaunchKernelGGL((k_phase<R, K, SLICED>), dim3(phase_blocks_wide(v)), dim3(G::NT), (size_t)G::LDS_BYTES, s, v, kappa,
                      v.span, gx);
   return hipGetLastError();
 }
 
-template <int R, int K>
+template <int R, int K, bool SLICED>
 hipError_t phase_batch_rk(const DevView* views, const uint32_t* pre, uint32_t nmem, uint32_t blocks, uint32_t kappa,
                           hipStream_t s) {
   using G = PhaseGeom<R, K>;
-  static const hipError_t ready = phase_lds(k_phase_batch<R, K>, G::LDS_BYTES);
+  static const hipError_t ready = phase_lds(k_phase_batch<R, K, SLICED>, G::LDS_BYTES);
   if (ready != hipSuccess) return ready;
-  hipLaunchKernelGGL((k_phase_batch<R, K>), dim3(blocks), dim3(G::NT), (size_t)G::LDS_BYTES, s, views, pre, nmem,
+  hipLaunchKernelGGL((k_phase_batch<R, K, SLICED>), dim3(blocks), dim3(G::NT), (size_t)G::LDS_BYTES, s, views, pre, nmem,
                      kappa);
   return hipGetLastError();
 }
@@ -299,14 +300,17 @@ hipError_t phase_batch_rk(const DevView* views, const uint32_t* pre, uint32_t nm
 }  // namespace
 
 hipError_t launch_phase_wide(const DevView& v, uint32_t kappa, hipStream_t s) {
-  const hipError_t e = by_radius_k(v.radius, v.k, [&](auto r, auto k) { return phase_rk<r(), k()>(v, kappa, s); });
+  const hipError_t e = by_radius_k(v.radius, v.k, [&](auto r, auto k) {
+    return v.slices > 1 ? phase_rk<r(), k(), true>(v, kappa, s) : phase_rk<r(), k(), false>(v, kappa, s);
+  });
   return e != hipSuccess || v.slices == 1 ? e : launch_phase_decide(v, kappa, s);
 }
 
-hipError_t launch_phase_batch_wide(uint32_t radius, uint32_t k, const DevView* views, const uint32_t* pre,
+hipError_t launch_phase_batch_wide(uint32_t radius, uint32_t k, bool sliced, const DevView* views, const uint32_t* pre,
                                    uint32_t nmem, uint32_t blocks, uint32_t kappa, hipStream_t s) {
   return by_radius_k(radius, k, [&](auto r, auto kk) {
-    return phase_batch_rk<r(), kk()>(views, pre, nmem, blocks, kappa, s);
+    return sliced ? phase_batch_rk<r(), kk(), true>(views, pre, nmem, blocks, kappa, s)
+                  : phase_batch_rk<r(), kk(), false>(views, pre, nmem, blocks, kappa, s);
   });
 }
 
