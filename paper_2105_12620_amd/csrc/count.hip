@@ -87,8 +87,11 @@ __device__ inline void count_target(const DevView& v, uint32_t kappa, uint32_t j
 // (one FP64 fma onto 1.5 2^20, whose last bit is 2^-32), the uniform offset
 // and the slope of each further line, (R + 1) 2^-33 in all for R lines;
 // |m| <= 2^30 R / N and R^2 <= 2 N keep that below 1 / (2 |m|).  Integrands
-// with |m| < LINE_MIN_M (edges nearly along the lines, about one in 10^4) are
-// counted sample by sample, so that the crossings stay inside the fma's range.
+// with |m| < LINE_MIN_M (edges nearly along the lines: about one drawn in 10^4, and
+// short normals that a caller gives), whose crossings leave the fma's range, take
+// FP64 throughout, six operations a line (128^2, N = 4096, 256 normals (0, 1): 35 us
+// per bn_compute_errors; sample by sample, in a loop of dependent loads, 6.3 ms, and one
+// such integrand among ordinary ones made 512 of them take 272 us in place of 33).
 //
 // SampleCounter (N <= 8, where it costs less: 14 lane-operations at N = 8
 // against 17): per (sample, integrand) one v_dot2 with the threshold folded in
@@ -211,21 +214,30 @@ struct LineCounter {
       hi[l] = ((int)w[2 + l] >> 16) + BIAS;
     }
   }
-  __device__ __forceinline__ uint32_t by_sample(const DevView& v, uint32_t n, int d) const {
-    uint32_t c = 0;
-#pragma unroll 1
-    for (uint32_t k = 0; k < v.n; ++k) c += dot2(n, centre(wrap_add(uniform(v.lat)[k], u)), -d - 1) >= 0 ? 1u : 0u;
-    return c;
+  // Hits of an integrand whose edge is nearly along the lines.
+  __device__ __forceinline__ uint32_t flat(const DevView& v, const BN_UNIFORM int* w) const {
+    const double inv = *(const BN_UNIFORM double*)(w + 4), m2 = *(const BN_UNIFORM double*)(w + 6);
+    double x = (double)w[1] + 0.5 - (double)dot2((uint32_t)w[0], a, 0);
+    uint32_t s = (uint32_t)start;
+#pragma unroll
+    for (int l = 0; l < R; ++l) {
+      int k;
+      asm("v_cvt_i32_f64 %0, %1" : "=v"(k) : "v"(floor(x * inv)));   // saturates, as the addition does
+      s += (uint32_t)med3(__builtin_elementwise_add_sat(k, BIAS + 1), lo[l], hi[l]);
+      x -= m2;
+    }
+    return inv > 0.0 ? v.n - s : s;
   }
   __device__ __forceinline__ void count8(const DevView& v, uint32_t t, uint32_t c[4]) const {
     const BN_UNIFORM i32x16* rec = uniform((const i32x16*)(v.lrec + t));
-    i32x16 next = rec[0];
+    // all pairs' terms load while the first is counted
+    i32x16 pair[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) pair[i] = rec[i];
     uint32_t plain = 1;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      // the next pair's terms load while this pair is counted
-      const LineTerms q0(next, 0), q1(next, 8);
-      if (i < 3) next = rec[i + 1];
+      const LineTerms q0(pair[i], 0), q1(pair[i], 8);
       unsigned long long x0 = __builtin_bit_cast(unsigned long long,
                                                  __fma_rn((double)dot2(q0.n, a, 0), q0.inv, MAGIC));
       unsigned long long x1 = __builtin_bit_cast(unsigned long long,
@@ -256,11 +268,13 @@ struct LineCounter {
       plain = min(plain, min((uint32_t)q0.inv_hi, (uint32_t)q1.inv_hi));
     }
     if (plain == 0) {
+#pragma unroll 1
+      for (int i = 0; i < 8; ++i) {
+        const BN_UNIFORM int* w = (const BN_UNIFORM int*)rec + 8 * i;
+        if (w[3] != 0) continue;
+        const uint32_t h = flat(v, w) << (16 * (i & 1)), keep = i & 1 ? 0xFFFFu : 0xFFFF0000u;
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const LineTerms q0(rec[i], 0), q1(rec[i], 8);
-        if (q0.inv_hi == 0) c[i] = (c[i] & 0xFFFF0000u) | by_sample(v, q0.n, q0.d);
-        if (q1.inv_hi == 0) c[i] = (c[i] & 0xFFFFu) | (by_sample(v, q1.n, q1.d) << 16);
+        for (int k = 0; k < 4; ++k) c[k] = k == i >> 1 ? (c[k] & keep) | h : c[k];
       }
     }
   }

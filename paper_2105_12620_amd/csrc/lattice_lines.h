@@ -6,6 +6,7 @@
 #include <algorithm>
 #include <cmath>
 #include <cstdlib>
+#include <cstring>
 #include <utility>
 #include <vector>
 
@@ -15,10 +16,15 @@ namespace bnlat {
 // line vectors b1 (along a line) and b2 (to the next one) in Q0.16 units,
 // m = n . b1 and m2 = n . b2: the crossing of line l is
 // -dot * inv + off + l * slope in units of b1, as int64 with 32 fraction bits.
+// Edges nearly along the lines (|m| < LINE_MIN_M), whose crossings leave that
+// format, have inv = 0 and, in off and slope, the doubles 1 / m (2^40 for m = 0)
+// and m2: the crossing of line l is floor((D' + 1/2 - dot - l m2) / m) + 1, exactly
+// (the numerator is a half integer under 2^34, so 1 / (2 |m|) away from the next
+// crossing, and the quotient's rounding is below 2^-18).
 struct LineRec {
   uint32_t n;        // nx | ny << 16
   int32_t d;         // D' = n . (C - 2^15)
-  double inv;        // -1 / m; 0: counted sample by sample (|m| < LINE_MIN_M)
+  double inv;        // -1 / m, or 0
   long long off;     // ((D' + 1/2) / m + 1) 2^32, rounded
   long long slope;   // -(m2 / m) 2^32, rounded
 };
@@ -160,7 +166,12 @@ inline LineRec line_record(const LatticeLines& g, int64_t step, int64_t nx, int6
   r.inv = 0.0;
   r.off = r.slope = 0;
   const int64_t m = (nx * g.b1[0] + ny * g.b1[1]) * step, m2 = (nx * g.b2[0] + ny * g.b2[1]) * step;
-  if (std::llabs(m) < LINE_MIN_M) return r;
+  if (std::llabs(m) < LINE_MIN_M) {
+    const double flat[2] = {m ? 1.0 / (double)m : 0x1p40, (double)m2};
+    std::memcpy(&r.off, &flat[0], 8);
+    std::memcpy(&r.slope, &flat[1], 8);
+    return r;
+  }
   r.inv = -1.0 / (double)m;
   r.off = (long long)round_div((__int128)(2 * (int64_t)r.d + 1) << 31, m) + (1ll << 32);
   r.slope = (long long)round_div((__int128)(-m2) << 32, m);
