@@ -456,38 +456,54 @@ struct CallScratch {
   }
 };
 
+// Rows [rows][t] of counts to the host, `lay(first, n, out)` laying n of them out
+// on the device, in the staging buffer; false without memory for it.  Synchronises.
+template <class F>
+bn_status staged_counts(bn_problem p, uint32_t rows, uint16_t* host, F lay, bool* done) {
+  const uint32_t t = p->v.t;
+  std::lock_guard<std::mutex> lock(p->stage_mutex);
+  const uint32_t per = stage_rows(p, rows, (size_t)t * 2);
+  *done = per > 0;
+  if (!per) return BN_OK;
+  for (uint32_t r = 0; r < rows; r += per) {
+    const uint32_t n = std::min(per, rows - r);
+    HIPCHK(lay(r, n, (uint16_t*)p->stage));
+    HIPCHK(hipMemcpyAsync(host + (size_t)r * t, p->stage, (size_t)n * t * 2, hipMemcpyDeviceToHost, p->stream));
+  }
+  return sync(p);
+}
+
 // Copy a tiled count buffer ([tp/8][rows][8] uint16 on the device) to host
 // rows [rows][t], laid out on the device (without memory for that, here).
-// Synchronises.
 bn_status untile_counts(bn_problem p, const uint16_t* dev, uint32_t rows, uint16_t* host) {
   const uint32_t t = p->v.t, tp = p->v.tp;
-  std::lock_guard<std::mutex> lock(p->stage_mutex);
-  if (const uint32_t per = stage_rows(p, rows, (size_t)t * 2)) {
-    for (uint32_t r = 0; r < rows; r += per) {
-      const uint32_t n = std::min(per, rows - r);
-      HIPCHK(launch_untile_counts(dev, rows, r, n, t, (uint16_t*)p->stage, p->stream));
-      HIPCHK(hipMemcpyAsync(host + (size_t)r * t, p->stage, (size_t)n * t * 2, hipMemcpyDeviceToHost, p->stream));
-    }
-    return sync(p);
-  }
+  bool done;
+  bn_status s = staged_counts(p, rows, host, [&](uint32_t r, uint32_t n, uint16_t* out) {
+    return launch_untile_counts(dev, rows, r, n, t, out, p->stream);
+  }, &done);
+  if (s != BN_OK || done) return s;
   std::vector<uint16_t> tmp((size_t)rows * tp);
   HIPCHK(hipMemcpyAsync(tmp.data(), dev, tmp.size() * 2, hipMemcpyDeviceToHost, p->stream));
-  bn_status s = sync(p);
-  if (s != BN_OK) return s;
+  if ((s = sync(p)) != BN_OK) return s;
   for (uint32_t r = 0; r < rows; ++r)
     for (uint32_t i = 0; i < t; ++i) host[(size_t)r * t + i] = tmp[((size_t)(i >> 3) * rows + r) * 8 + (i & 7)];
   return BN_OK;
 }
 
-// The same from a tiled buffer of int8 deviations ([tp/16][rows][16]).
+// The same from a tiled buffer of int8 deviations ([tp/16][rows][16]): laid out here,
+// integrand by integrand, it took 1.8 ms for 4096 rows of 256 counts, 0.14 so.
 bn_status untile_narrow(bn_problem p, const int8_t* dev, uint32_t rows, uint16_t* host) {
   const uint32_t t = p->v.t, tp = p->v.tp;
+  bool done;
+  bn_status s = staged_counts(p, rows, host, [&](uint32_t r, uint32_t n, uint16_t* out) {
+    return launch_untile_narrow(dev, p->v.bias8, rows, r, n, t, out, p->stream);
+  }, &done);
+  if (s != BN_OK || done) return s;
   std::vector<int8_t> tmp((size_t)rows * tp);
   std::vector<uint32_t> bias(tp / 2);
   HIPCHK(hipMemcpyAsync(tmp.data(), dev, tmp.size(), hipMemcpyDeviceToHost, p->stream));
   HIPCHK(hipMemcpyAsync(bias.data(), p->v.bias8, bias.size() * 4, hipMemcpyDeviceToHost, p->stream));
-  bn_status s = sync(p);
-  if (s != BN_OK) return s;
+  if ((s = sync(p)) != BN_OK) return s;
   for (uint32_t i = 0; i < t; ++i) {
     const int base = (int)(((0x00800080u - bias[i / 2]) >> (16 * (i & 1))) & 0xFFFFu);
     for (uint32_t r = 0; r < rows; ++r)

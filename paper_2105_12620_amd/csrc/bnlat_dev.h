@@ -230,5 +230,7 @@ hipError_t peak_launch(int kind, void* buf, void* buf2, uint64_t size, uint32_t 
 hipError_t noalloc_scratch(int device, void** ptr);
 hipError_t launch_untile_counts(const uint16_t* tiled, uint32_t rows, uint32_t first, uint32_t n, uint32_t t,
                                 uint16_t* out, hipStream_t s);
+hipError_t launch_untile_narrow(const int8_t* tiled, const uint32_t* bias8, uint32_t rows, uint32_t first, uint32_t n,
+                                uint32_t t, uint16_t* out, hipStream_t s);
 
 }  // namespace bnlat
