@@ -307,8 +307,8 @@ bn_status bn_set_profiling(bn_problem p, int enable);
  * beside it (rounded down to the workgroup count that gives every workgroup
  * the same number of blocks); 0 removes the cap.  Default: four workgroups per
  * CU.  Results do not depend on it.  Set it before the first sweeps: a pair of
- * sweeps captured by then is not captured again, later ones are launched kernel
- * by kernel.
+ * sweeps captured with another cap is not captured again, later ones are
+ * launched kernel by kernel.
  * Synchronises. */
 bn_status bn_set_recount_blocks(bn_problem p, uint32_t blocks);
 bn_status bn_get_profile(bn_problem p, bn_profile_stats* out);

@@ -2129,6 +2129,7 @@ bn_status bn_set_recount_blocks(bn_problem p, uint32_t blocks) {
   bn_status s = sync(p);
   if (s != BN_OK) return s;
   if (p->aux) HIPCHK(hipStreamSynchronize(p->aux));
+  if (blocks == p->v.count_cap) return BN_OK;   // a captured pair has this launch shape
   p->v.count_cap = blocks;
   // A captured pair holds the old launch shape.  It is not captured a second
   // time: the sweeps from here on launch their pairs one kernel at a time (a
