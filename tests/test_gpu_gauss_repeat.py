@@ -11,7 +11,7 @@ from cases import gpu_problem, say, workload
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("n,g,t,k", [(16, (1, 7), 20, 2), (4096, (1, 1365), 8, 1)])   # int8 and uint16 operands
+@pytest.mark.parametrize("n,g,t,k", [(16, (1, 7), 20, 2), (2048, (1, 717), 8, 1)])   # int8 and uint16 operands
 def test_taken_moves_change_nothing(n, g, t, k):
     w = workload(n=n, g=g, width=48, height=46, t_heaviside=t, t_gauss=130, colour_k=k)
     say("case repeat", n)
