@@ -76,7 +76,7 @@ template <bool ALL>
 __global__ __launch_bounds__(256, 5) void k_gauss_lines(DevView v, uint32_t m) {
   extern __shared__ uint32_t rows[];
   const uint32_t lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const uint32_t ng = v.tgp / (4 * GC);            // workgroups per 64 pixels
+  const uint32_t ng = (v.tg + 4 * GC - 1) / (4 * GC);   // workgroups per 64 pixels
   const uint32_t jg = blockIdx.x / ng, t0 = ((blockIdx.x - jg * ng) * 4 + w) * GC;
   float* outs = (float*)(rows + v.glines * 64) + w * 64 * OUT_PITCH;
   const uint32_t j = min(jg * 64 + lane, m - 1);
@@ -220,13 +220,20 @@ __global__ __launch_bounds__(256, 5) void k_gauss_lines(DevView v, uint32_t m) {
     const uint32_t px = r + lane / GC, jp = jg * 64 + px;
     if (jp < m) out[(size_t)jp * v.tgp + lane % GC] = outs[px * OUT_PITCH + lane % GC];
   }
+  // the padding past the last workgroup's Gaussians
+  const uint32_t pad = v.tgp - ng * 4 * GC;
+  if (pad && (blockIdx.x + 1) % ng == 0)
+    for (uint32_t i = threadIdx.x; i < 64 * pad; i += 256) {
+      const uint32_t jp = jg * 64 + i / pad;
+      if (jp < m) (ALL ? v.gest : v.g_new)[(size_t)jp * v.tgp + (v.tgp - pad) + i % pad] = 1.0f;
+    }
 }
 
 }  // namespace
 
 hipError_t launch_gauss_lines(const DevView& v, bool all, uint32_t m, hipStream_t s) {
   const size_t lds = 4 * lds_words(v.glines);
-  const dim3 grid((m + 63) / 64 * (v.tgp / (4 * GC))), block(256);
+  const dim3 grid((m + 63) / 64 * ((v.tg + 4 * GC - 1) / (4 * GC))), block(256);
   if (all) hipLaunchKernelGGL(k_gauss_lines<true>, grid, block, lds, s, v, m);
   else hipLaunchKernelGGL(k_gauss_lines<false>, grid, block, lds, s, v, m);
   return hipGetLastError();
