@@ -58,13 +58,13 @@ def count_ops_per_pair(n: int, g) -> float:
     return 2.5 * (abs(x) + abs(y)) if n >= 16 else 1.75 * n
 
 
-def operand_bytes(n: int, g) -> int:
+def operand_bytes(n: int, g, limit: int = 126) -> int:
     """Bytes of a count in the colour phases: int8 deviations from a base where
-    the bound on them allows, else uint16."""
+    the bound on them allows (limit: 126, of swap passes 63), else uint16."""
     x, y = shortest(n, g)
     lines, longest = abs(x) + abs(y), max(abs(x), abs(y))
     dev = min(max(1, n // 2), lines + 1 + -(-n // longest) if n > 64 else n)
-    return 1 if dev <= 126 else 2
+    return 1 if dev <= limit else 2
 
 
 def kernel_digest() -> str:
@@ -456,7 +456,8 @@ def main() -> int:
     ob = operand_bytes(N, w["g"])
     delta_bytes = ob * T * (P + M) + 9.0 * M
     # a swap pass reads the tile's field once and every member's partner row
-    swap_bytes = ob * T * (P + M)
+    sb = operand_bytes(N, w["g"], 63)
+    swap_bytes = sb * T * (P + M)
     # the neighbour products: one per (moved pixel, window offset, integrand);
     # the swap stencil forms four (int8) or two per lane-instruction
     products = M * win * T
@@ -515,10 +516,10 @@ def main() -> int:
             "evaluate_hbm_gbs": swap_bytes / (swap["kernels_ms"]["evaluate_per_phase"] * 1e-3) / 1e9,
             "roofline": roof("hbm", swap_bytes / (swap["kernels_ms"]["evaluate_per_phase"] * 1e-3) / 1e9, "GB/s",
                              "k_swap_stage (class sums of one swap pass)",
-                             f"tile's field once + {M} partner rows ({T} integrands x {ob} B)"),
-            "roofline_alu": roof("alu", products * ob / 4 / (swap["kernels_ms"]["evaluate_per_phase"] * 1e-3) / 1e12,
+                             f"tile's field once + {M} partner rows ({T} integrands x {sb} B)"),
+            "roofline_alu": roof("alu", products * sb / 4 / (swap["kernels_ms"]["evaluate_per_phase"] * 1e-3) / 1e12,
                                  "TOP/s", "k_swap_stage (class sums of one swap pass)",
-                                 f"{M} members x {win} offsets x {T} integrands, {4 // ob} per lane-instruction")},
+                                 f"{M} members x {win} offsets x {T} integrands, {4 // sb} per lane-instruction")},
         "batched": None if batch is None else dict(batch, roofline=roof(
             "alu", batch["count_lane_ops_per_sweep"] / (batch["ms_per_sweep"] * 1e-3) / 1e12, "TOP/s",
             "whole batched sweep (recounts of every member's proposals over the sweep time)",
