@@ -23,7 +23,12 @@
  *     divide 65536.
  *   - Memory: the library allocates and owns every device buffer of a
  *     problem (created in bn_create_problem, freed in bn_destroy_problem),
- *     except those a caller hands to bn_create_problem_ext.
+ *     except those a caller hands to bn_create_problem_ext.  The calls that
+ *     return rows of counts or errors, bn_sample, the blur criterion and the
+ *     error spectrum lay their data out in a buffer that the problem allocates
+ *     at the first of them and keeps, of the size that they need up to 128 MiB;
+ *     the criterion's and the spectrum's scratch, and a sampler query, of more
+ *     than that is allocated for the call.
  *     Every pointer argument named host_* or out is caller-owned host
  *     memory of the size stated; the library never keeps it.
  *   - Streams: all device work of a problem is ordered on its HIP stream
@@ -240,7 +245,7 @@ bn_status bn_quality_metric_family(bn_problem p, bn_rows rows, const double* sig
  * nbins on are dropped.  out double [nbins] (0 for an empty bin), counts
  * uint32 [nbins] frequencies per bin (nullable).  White noise of variance s^2
  * gives s^2 in every bin.  Direct DFT on the device (FP32 within a row or
- * column, FP64 across rows); allocates scratch for the call.  Synchronises. */
+ * column, FP64 across rows).  Synchronises. */
 bn_status bn_error_spectrum(bn_problem p, bn_rows rows, uint32_t nbins, double* out, uint32_t* counts);
 
 /* Copy the offset tile to host_u: uint16 [H][W][2].  Synchronises. */
@@ -374,9 +379,9 @@ bn_status bn_measure_peak(bn_peak kind, uint64_t bytes, uint32_t reps, double* o
  * of pair d's sample, a float in [0, 1) (exact: the Q0.16 value / 65536).
  * Every pair must have offsets (bn_init_offsets); the pairs' pending work is
  * waited for.  bn_sample takes host arrays x, y, k uint32 [m] and host out
- * float [m][2 npairs]; bn_sample_device takes device arrays and a stream
- * (NULL: pairs[0]'s stream) and synchronises it.  Both allocate a small
- * device table per call. */
+ * float [m][2 npairs], which cross in pairs[0]'s buffer; bn_sample_device takes
+ * device arrays and a stream (NULL: pairs[0]'s stream), synchronises it and
+ * allocates nothing. */
 bn_status bn_sample(const bn_problem* pairs, uint32_t npairs, const uint32_t* x, const uint32_t* y,
                     const uint32_t* k, uint32_t m, float* out);
 bn_status bn_sample_device(const bn_problem* pairs, uint32_t npairs, const uint32_t* x, const uint32_t* y,
@@ -389,8 +394,10 @@ bn_status bn_sample_device(const bn_problem* pairs, uint32_t npairs, const uint3
  * in the FP32 form with Heaviside rows only and redraw moves share grouped
  * launches: one sweep-wide recount launch per samples-per-pixel class (on an
  * auxiliary stream, for the next sweep) beside, per colour class, one launch
- * per window radius for the energy change and one decision and one commit
- * launch over all of them.  Members in the BF16 form, with Gaussian rows or
+ * per operand form and window radius for the energy changes and their
+ * decisions (two where integrands are split over workgroups), and one commit
+ * launch over all of them per sweep (per class for uint16 operands).  Members
+ * in the BF16 form, with Gaussian rows or
  * with swap moves have their own overlapped sweeps recorded into the same
  * graph as independent branches.  Each member's trajectory equals the one
  * bn_sweep gives it alone.  Requirements: members distinct, created on one
@@ -404,10 +411,10 @@ bn_status bn_sample_device(const bn_problem* pairs, uint32_t npairs, const uint3
 bn_status bn_create_batch(const bn_problem* members, uint32_t m, const char* tune_cache,
                           bn_batch* out);
 bn_status bn_batch_sweep(bn_batch b, uint32_t k);
-/* Launch choices the tuner picked (integrands per counting wave, workgroup
- * target of the staged energy-change launch, its block shape: 0 the
- * single-problem shape, 1 the alternative with half the waves per workgroup
- * for K = 1, 2 and twice for K = 4); every pointer nullable; no device work. */
+/* Launch choices: the integrands per counting wave that the tuner picked, and the
+ * workgroup target and block shape of a tuning file's line (512 and 0 by default;
+ * the grouped launches have no use for them); every pointer nullable; no device
+ * work. */
 bn_status bn_batch_tuning(bn_batch b, uint32_t* tch, uint32_t* slice_target, uint32_t* stage_shape);
 bn_status bn_destroy_batch(bn_batch b);
 

@@ -957,8 +957,9 @@ bn_status swap_sweeps(bn_problem p, uint32_t k) {
   return BN_OK;
 }
 
-// Candidates of the launch-shape tuner: integrands per counting wave and the
-// workgroup target of the staged energy-change launch.
+// Candidates of the launch-shape tuner: integrands per counting wave; and what a
+// line of its file may hold beside them (a workgroup target and a block shape, of
+// an energy-change kernel that is no more).
 const uint32_t kTuneTch[] = {64, 128, 256, 512};
 const uint32_t kTuneSlices[] = {128, 256, 512, 1024, 2048};
 const uint32_t kTuneShapes[] = {0, 1};
@@ -1452,9 +1453,9 @@ bn_status bn_create_problem_ext(const bn_config* cfg, const bn_heaviside* heavis
   const bool centred = v.n > 64 && by_lines && by_lines < dev;
   if (centred) dev = by_lines;
   p->counts_in_int7 = dev <= 63;
-  // The BF16 form's exact mode (counts as BF16 operands) gives the same integers
-  // and moves half as many bytes as int8: 273 against 690 us per two sweeps of a
-  // 256^2 tile, N = 256, T = 1024.
+  // They serve the BF16 form's exact mode too: the same integers as from counts as
+  // BF16 operands, which are twice as many bytes (273 against 690 us per two sweeps
+  // of a 256^2 tile, N = 256, T = 1024).
   v.form = FIELD_WIDE;
   if (v.mfma != 2 && cfg->move == BN_REDRAW && (v.k == 1 || v.k == 2 || v.k == 4))
     v.form = dev <= 63 ? FIELD_NARROW : dev <= 126 && v.t <= 32768 ? FIELD_SPLIT : FIELD_WIDE;

@@ -79,8 +79,8 @@ __device__ inline void count_target(const DevView& v, uint32_t kappa, uint32_t j
 // pixel's shift falls in (shifts that differ by a lattice vector give the
 // same lines) and come from a table; A is a sample of the pixel.  Bound by
 // the vector ALU; measured at 256^2, N = 256, T = 1000 with the error vectors
-// written: 102 us per bn_compute_errors against 877 us sample by sample
-// (393 MB written, 3.8 TB/s).
+// written: 105 us per bn_compute_errors against 877 us sample by sample
+// (470 MB written, padded rows and the int8 field among them: 4.5 TB/s).
 //   Exactness: with D' + 1/2 in place of D', the crossings are odd multiples
 // of 1 / (2 |m|), m = n . b1, hence at least that far from an integer.  The
 // fixed-point value is off by at most 2^-33 per rounding: the first crossing

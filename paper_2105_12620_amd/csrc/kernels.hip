@@ -527,8 +527,10 @@ __global__ __launch_bounds__(256) void k_gauss_est(DevView v, uint32_t kappa, ui
 // sample (of its window: k_gauss_again), then decided.
 // 512^2, N = 1024, 1024 Gaussians: about one move in 5000, 0.36 ms a phase (its cost
 // is the exponentials of 122 pixels a move), where estimating every proposal so
-// would take 14.  With eta(1) for every g
-// four times as many (1.39 ms).
+// would take 14.  With eta(1) for every g four times as many (1.39 ms).  (Where
+// nearly all moves are close it costs more than it spares: one Heaviside beside 64
+// Gaussians of s = 5, 128^2, N = 1024, 2.3 ms a sweep against 0.5 sample by sample;
+// with eight Heavisides or s up to 1 it is faster.)
 //
 // The bound from W = sum w, b = sum w x^2 (sum w |x| <= sqrt(W b)), s = g' + g.
 __device__ __forceinline__ double gauss_margin(double W, double b, double s, double d) {
@@ -1205,8 +1207,7 @@ hipError_t launch_gauss_delta(const DevView& v, int mode, uint32_t kappa, uint32
       default: return hipErrorInvalidValue;
     }
   }
-  return mode == MODE_CLASS ? gauss_delta_dispatch<MODE_CLASS>(v, kappa, m, s)
-                            : gauss_delta_dispatch<MODE_LIST>(v, kappa, m, s);
+  return gauss_delta_dispatch<MODE_LIST>(v, kappa, m, s);
 }
 
 hipError_t launch_gauss_delta_exact(const DevView& v, uint32_t kappa, hipStream_t s) {
