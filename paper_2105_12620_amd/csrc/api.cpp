@@ -568,6 +568,19 @@ struct Carve {
   }
 };
 
+// A problem's tables on their way to the device, in one allocation and one copy
+// (each takes the host 5 to 10 us, and there are up to fourteen tables).
+struct Tables {
+  std::vector<char> bytes;
+  template <class T>
+  size_t add(const std::vector<T>& v) {
+    const size_t at = (bytes.size() + 255) & ~(size_t)255;
+    bytes.resize(at + v.size() * sizeof(T));
+    if (!v.empty()) std::memcpy(&bytes[at], v.data(), v.size() * sizeof(T));
+    return at;
+  }
+};
+
 // The list buffers of a delta-energy call over m pixels (and, when untiled
 // counts are returned, their row layout) in scratch area c.
 DevView list_view_in(bn_problem p, Carve& c, uint32_t m, bool counts, uint16_t** rows) {
@@ -1465,46 +1478,11 @@ bn_status bn_create_problem_ext(const bn_config* cfg, const bn_heaviside* heavis
   for (uint32_t t = 0; t < v.t; ++t)
     bias8[t / 2] -= (centred ? (uint32_t)std::lround(v.n * area[t]) : v.n / 2) << (16 * (t & 1));
 
-  uint32_t* lat_d;
-  uint32_t* lrow_d;
-  uint32_t* bias_d;
-  int32_t* dcls_d;
   std::vector<int32_t> dcls(2 * v.radius * v.radius + 1, -1);
   for (uint32_t c = 0; c < v.ncls; ++c) dcls[p->cls_d[c]] = (int32_t)c;
   v.span = phase_span_wide(v.n);
   v.slices = 1;
   if (cfg->move == BN_REDRAW && (staged_phases(v) || v.mfma == 2)) v.slices = phase_slices(v, phase_blocks(v));
-  LineRec* lrec_d;
-  int2* ihp_d;
-  float* area_d;
-  double* wd_d;
-  if ((s = p->alloc(&lat_d, v.n)) != BN_OK || (s = p->alloc(&ihp_d, v.tp)) != BN_OK ||
-      (s = p->alloc(&lrow_d, lrow.size())) != BN_OK || (s = p->alloc(&lrec_d, lrec.size())) != BN_OK ||
-      (s = p->alloc(&area_d, v.tp)) != BN_OK || (s = p->alloc(&wd_d, v.ncls)) != BN_OK ||
-      (s = p->adopt(&v.U, bufs ? bufs->offsets : nullptr, P)) != BN_OK ||
-      (s = p->adopt(&v.cnt, bufs ? bufs->counts : nullptr, P * v.tp)) != BN_OK ||
-      (s = p->adopt(&v.err, bufs ? bufs->errors : nullptr, P * v.tp)) != BN_OK || (s = p->alloc(&v.u_new, v.pc)) != BN_OK ||
-      (s = p->alloc(&bias_d, bias8.size())) != BN_OK || (s = p->alloc(&dcls_d, dcls.size())) != BN_OK ||
-      (v.form == FIELD_WIDE && (s = p->alloc(&v.c_new, (size_t)v.pc * v.tp)) != BN_OK) ||
-      (v.form != FIELD_WIDE && ((s = p->alloc(&v.d8, P * v.tp)) != BN_OK || (s = p->alloc(&v.n8, (size_t)v.pc * v.tp)) != BN_OK)) || (s = p->alloc(&v.delta, v.pc)) != BN_OK ||
-      (s = p->alloc(&v.accept, v.pc)) != BN_OK || (s = p->alloc(&v.ctr, 4)) != BN_OK ||
-      (s = p->alloc(&v.unsure, v.pc)) != BN_OK ||
-      (s = p->alloc(&p->ysum, ENERGY_ROWS * v.ncls)) != BN_OK ||
-      (v.mfma && (s = p->alloc(&v.xpart, (size_t)v.ncls * v.pc)) != BN_OK) ||
-      (v.slices > 1 && (s = p->alloc(&v.xsum, (size_t)v.slices * v.pc * (v.ncls + 1))) != BN_OK) ||
-      (bufs && bufs->offsets && bufs->counts && v.form != FIELD_WIDE && !p->bf_in_int8 &&
-       (s = p->alloc(&v.seen, P)) != BN_OK)) {
-    delete p;
-    return s;
-  }
-  v.lat = lat_d;
-  v.bias8 = bias_d;
-  v.dcls = dcls_d;
-  v.lrow = lrow_d;
-  v.lrec = lrec_d;
-  v.ihp = ihp_d;
-  v.area = area_d;
-  v.wd = wd_d;
   // Gaussian t as exponent coefficients (base 2): with g = log2(e) / (2 s^2),
   // -g |x - mu|^2 = a |x|^2 + bx x + by y + c, a = -g, (bx, by) = 2 g mu,
   // c = -g |mu|^2.  Padding rows are all zero (estimate 1, integral 0).
@@ -1516,24 +1494,6 @@ bn_status bn_create_problem_ext(const bn_config* cfg, const bn_heaviside* heavis
     gcoef[4 * t + 2] = 2.0 * g * gauss[t].my;
     gcoef[4 * t + 3] = -g * (gauss[t].mx * gauss[t].mx + gauss[t].my * gauss[t].my);
     gintp[t] = gint[t];
-  }
-  if (v.tgp) {
-    double *gcoef_d, *gint_d;
-    if ((s = p->alloc(&gcoef_d, (size_t)v.tgp * 4)) != BN_OK || (s = p->alloc(&gint_d, v.tgp)) != BN_OK ||
-        (s = p->alloc(&v.gest, P * v.tgp)) != BN_OK || (s = p->alloc(&v.gerr, P * v.tgp)) != BN_OK ||
-        (s = p->alloc(&v.g_new, (size_t)v.pc * v.tgp)) != BN_OK || (s = p->alloc(&v.gdelta, v.pc)) != BN_OK ||
-        (s = p->alloc(&p->gsum, v.ncls)) != BN_OK) {
-      delete p;
-      return s;
-    }
-    v.gcoef = gcoef_d;
-    v.gint = gint_d;
-    hipError_t ge = hipMemcpyAsync(gcoef_d, gcoef.data(), (size_t)v.tgp * 32, hipMemcpyHostToDevice, p->stream);
-    if (ge == hipSuccess) ge = hipMemcpyAsync(gint_d, gintp.data(), v.tgp * 8, hipMemcpyHostToDevice, p->stream);
-    if (ge != hipSuccess) {
-      delete p;
-      return fail(BN_EHIP, "uploading Gaussian tables: %s", hipGetErrorString(ge));
-    }
   }
   // Gaussian line form: from N = 16, where a line holds several samples, up to
   // lines of 256 steps (a table of the steps' factors per Gaussian), and for
@@ -1556,52 +1516,69 @@ bn_status bn_create_problem_ext(const bn_config* cfg, const bn_heaviside* heavis
       for (uint32_t i = 0; i < q.lines; ++i)
         gspans.insert(gspans.end(), {q.spans[i].steps, q.spans[i].full_lo, q.spans[i].full_hi,
                                      i + 1 < q.lines ? (int)(q.j0[i + 1] - q.j0[i]) : 0});
-      uint32_t* grow_d;
-      int* gspans_d;
-      double* gtab_d;
-      if ((s = p->alloc(&grow_d, grow.size())) != BN_OK || (s = p->alloc(&gspans_d, gspans.size())) != BN_OK ||
-          (s = p->alloc(&gtab_d, gtab.size())) != BN_OK) {
-        delete p;
-        return s;
-      }
-      v.grow = grow_d;
-      v.gspans = gspans_d;
-      if ((s = p->alloc(&v.gmargin, v.pc)) != BN_OK || (s = p->alloc(&v.gunsure, (size_t)v.pc + 1)) != BN_OK ||
-          (s = p->alloc(&v.hpart, v.pc)) != BN_OK || (s = p->alloc(&v.gpart, (size_t)v.pc * (v.tgp / 16))) != BN_OK) {
-        delete p;
-        return s;
-      }
-      if (hipMemsetAsync(v.gunsure, 0, 4, p->stream) != hipSuccess) {
-        delete p;
-        return fail(BN_EHIP, "clearing the list of unsure moves");
-      }
-      v.gtab = gtab_d;
-      hipError_t ge = hipMemcpyAsync(grow_d, grow.data(), grow.size() * 4, hipMemcpyHostToDevice, p->stream);
-      if (ge == hipSuccess) ge = hipMemcpyAsync(gspans_d, gspans.data(), gspans.size() * 4, hipMemcpyHostToDevice, p->stream);
-      if (ge == hipSuccess) ge = hipMemcpyAsync(gtab_d, gtab.data(), gtab.size() * 8, hipMemcpyHostToDevice, p->stream);
-      if (ge != hipSuccess) {
-        delete p;
-        return fail(BN_EHIP, "uploading Gaussian line tables: %s", hipGetErrorString(ge));
-      }
+    }
+  }
+  Tables tab;
+  const size_t at_ctr = tab.add(std::vector<unsigned long long>(4, 0ull)), at_lat = tab.add(lat), at_ihp = tab.add(ihp),
+               at_lrow = tab.add(lrow), at_lrec = tab.add(lrec), at_area = tab.add(areaf), at_wd = tab.add(p->cls_w),
+               at_bias = tab.add(bias8), at_dcls = tab.add(dcls), at_gcoef = tab.add(gcoef), at_gint = tab.add(gintp),
+               at_grow = tab.add(grow), at_gspans = tab.add(gspans), at_gtab = tab.add(gtab);
+  char* tables;
+  if ((s = p->alloc(&tables, tab.bytes.size())) != BN_OK ||
+      (s = p->adopt(&v.U, bufs ? bufs->offsets : nullptr, P)) != BN_OK ||
+      (s = p->adopt(&v.cnt, bufs ? bufs->counts : nullptr, P * v.tp)) != BN_OK ||
+      (s = p->adopt(&v.err, bufs ? bufs->errors : nullptr, P * v.tp)) != BN_OK || (s = p->alloc(&v.u_new, v.pc)) != BN_OK ||
+      (v.form == FIELD_WIDE && (s = p->alloc(&v.c_new, (size_t)v.pc * v.tp)) != BN_OK) ||
+      (v.form != FIELD_WIDE &&
+       ((s = p->alloc(&v.d8, P * v.tp)) != BN_OK || (s = p->alloc(&v.n8, (size_t)v.pc * v.tp)) != BN_OK)) ||
+      (s = p->alloc(&v.delta, v.pc)) != BN_OK || (s = p->alloc(&v.accept, v.pc)) != BN_OK ||
+      (s = p->alloc(&v.unsure, v.pc)) != BN_OK ||
+      (s = p->alloc(&p->ysum, ENERGY_ROWS * v.ncls)) != BN_OK ||
+      (v.mfma && (s = p->alloc(&v.xpart, (size_t)v.ncls * v.pc)) != BN_OK) ||
+      (v.slices > 1 && (s = p->alloc(&v.xsum, (size_t)v.slices * v.pc * (v.ncls + 1))) != BN_OK) ||
+      (bufs && bufs->offsets && bufs->counts && v.form != FIELD_WIDE && !p->bf_in_int8 &&
+       (s = p->alloc(&v.seen, P)) != BN_OK)) {
+    delete p;
+    return s;
+  }
+  v.ctr = (unsigned long long*)(tables + at_ctr);
+  v.lat = (const uint32_t*)(tables + at_lat);
+  v.ihp = (const int2*)(tables + at_ihp);
+  v.lrow = (const uint32_t*)(tables + at_lrow);
+  v.lrec = (const LineRec*)(tables + at_lrec);
+  v.area = (const float*)(tables + at_area);
+  v.wd = (const double*)(tables + at_wd);
+  v.bias8 = (const uint32_t*)(tables + at_bias);
+  v.dcls = (const int32_t*)(tables + at_dcls);
+  if (v.tgp) {
+    v.gcoef = (const double*)(tables + at_gcoef);
+    v.gint = (const double*)(tables + at_gint);
+    if ((s = p->alloc(&v.gest, P * v.tgp)) != BN_OK || (s = p->alloc(&v.gerr, P * v.tgp)) != BN_OK ||
+        (s = p->alloc(&v.g_new, (size_t)v.pc * v.tgp)) != BN_OK || (s = p->alloc(&v.gdelta, v.pc)) != BN_OK ||
+        (s = p->alloc(&p->gsum, v.ncls)) != BN_OK) {
+      delete p;
+      return s;
+    }
+  }
+  if (v.glines) {
+    v.grow = (const uint32_t*)(tables + at_grow);
+    v.gspans = (const int*)(tables + at_gspans);
+    v.gtab = (const double*)(tables + at_gtab);
+    if ((s = p->alloc(&v.gmargin, v.pc)) != BN_OK || (s = p->alloc(&v.gunsure, (size_t)v.pc + 1)) != BN_OK ||
+        (s = p->alloc(&v.hpart, v.pc)) != BN_OK || (s = p->alloc(&v.gpart, (size_t)v.pc * (v.tgp / 16))) != BN_OK) {
+      delete p;
+      return s;
     }
   }
   v.pix_list = nullptr;
-  const unsigned long long zero[4] = {0ull, 0ull, 0ull, 0ull};
   if (v.mfma && ((s = p->alloc(&v.bf, P * v.tb)) != BN_OK || (s = p->alloc(&v.delta_bf, v.pc)) != BN_OK)) {
     delete p;
     return s;
   }
   hipError_t e = v.mfma ? prepare_bf_kernels(v.radius, v.k) : hipSuccess;
-  if (e == hipSuccess) e = hipMemcpyAsync(lat_d, lat.data(), v.n * 4, hipMemcpyHostToDevice, p->stream);
-  if (e == hipSuccess && v.lines) e = hipMemcpyAsync(lrow_d, lrow.data(), lrow.size() * 4, hipMemcpyHostToDevice, p->stream);
-  if (e == hipSuccess && v.lines)
-    e = hipMemcpyAsync(lrec_d, lrec.data(), lrec.size() * sizeof(LineRec), hipMemcpyHostToDevice, p->stream);
-  if (e == hipSuccess) e = hipMemcpyAsync(dcls_d, dcls.data(), dcls.size() * 4, hipMemcpyHostToDevice, p->stream);
-  if (e == hipSuccess) e = hipMemcpyAsync(bias_d, bias8.data(), bias8.size() * 4, hipMemcpyHostToDevice, p->stream);
-  if (e == hipSuccess) e = hipMemcpyAsync(ihp_d, ihp.data(), v.tp * 8, hipMemcpyHostToDevice, p->stream);
-  if (e == hipSuccess) e = hipMemcpyAsync(area_d, areaf.data(), v.tp * 4, hipMemcpyHostToDevice, p->stream);
-  if (e == hipSuccess) e = hipMemcpyAsync(wd_d, p->cls_w.data(), v.ncls * 8, hipMemcpyHostToDevice, p->stream);
-  if (e == hipSuccess) e = hipMemcpyAsync(v.ctr, zero, sizeof zero, hipMemcpyHostToDevice, p->stream);
+  if (e == hipSuccess)
+    e = hipMemcpyAsync(tables, tab.bytes.data(), tab.bytes.size(), hipMemcpyHostToDevice, p->stream);
+  if (e == hipSuccess && v.gunsure) e = hipMemsetAsync(v.gunsure, 0, 4, p->stream);
   if (e == hipSuccess && v.xpart) e = hipMemsetAsync(v.xpart, 0, (size_t)v.ncls * v.pc * 8, p->stream);
   if (e == hipSuccess) e = hipMemsetAsync(v.unsure, 0, (size_t)v.pc * 4, p->stream);
   if (e == hipSuccess) e = hipStreamSynchronize(p->stream);
