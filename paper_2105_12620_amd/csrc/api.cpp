@@ -1447,9 +1447,11 @@ bn_status bn_create_problem_ext(const bn_config* cfg, const bn_heaviside* heavis
   std::vector<uint32_t> lrow;
   std::vector<LineRec> lrec;
   const LatticeLines g = lattice_lines(v.n, v.gx, v.gy);
+  ClassLines classes;
   if (v.n >= 16) {
     v.lines = line_template(g.lines);
-    if (!g.lines || !v.lines || !lattice_rows(v.n, v.gx, v.gy, g, v.lines, line_row_words(v.lines), lrow)) {
+    classes = class_lines(v.n, v.gx, v.gy, g);
+    if (!g.lines || !v.lines || !lattice_rows(v.n, classes, g, v.lines, line_row_words(v.lines), lrow)) {
       delete p;
       return fail(BN_EINVAL, "the lattice (%u, %u) / %u has no line decomposition", cfg->g[0], cfg->g[1], v.n);
     }
@@ -1504,7 +1506,7 @@ bn_status bn_create_problem_ext(const bn_config* cfg, const bn_heaviside* heavis
   std::vector<int> gspans;
   std::vector<double> gtab;
   if (v.n >= 16 && staged_phases(v) && gauss_lines_pay(v, (uint32_t)P)) {
-    GaussLines q = gauss_lines(v.n, v.gx, v.gy, g);
+    GaussLines q = gauss_lines(v.n, classes, g);
     if (q.steps <= 256) {
       v.glines = q.lines;
       v.gwords = gauss_table_words(q);

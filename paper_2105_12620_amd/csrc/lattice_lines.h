@@ -50,54 +50,75 @@ struct LatticeLines {
 };
 
 inline LatticeLines lattice_lines(int64_t n, int64_t gx, int64_t gy) {
-  std::vector<std::pair<int64_t, int64_t>> vec;   // lattice vectors in (-N, N)^2, and N along each axis
-  for (int64_t k = 1; k < n; ++k) {
-    const int64_t x = k * gx % n, y = k * gy % n;
-    for (int64_t a : {x, x - n})
-      for (int64_t b : {y, y - n}) vec.emplace_back(a, b);
-  }
-  for (int64_t s : {n, -n}) {
-    vec.emplace_back(s, 0);
-    vec.emplace_back((int64_t)0, s);
-  }
-  auto size = [](const std::pair<int64_t, int64_t>& v) { return std::llabs(v.first) + std::llabs(v.second); };
-  const auto b1 = *std::min_element(vec.begin(), vec.end(), [&](const auto& a, const auto& b) { return size(a) < size(b); });
-  LatticeLines out{{b1.first, b1.second}, {0, 0}, (uint32_t)size(b1)};
+  // f(x, y) for the lattice vectors in (-N, N)^2, and N along each axis
+  auto each = [&](auto f) {
+    for (int64_t k = 1, x = gx % n, y = gy % n; k < n; ++k) {
+      f(x, y), f(x, y - n), f(x - n, y), f(x - n, y - n);
+      if ((x += gx) >= n) x %= n;
+      if ((y += gy) >= n) y %= n;
+    }
+    for (int64_t s : {n, -n}) f(s, (int64_t)0), f((int64_t)0, s);
+  };
+  LatticeLines out{{0, 0}, {0, 0}, 0};
   int64_t best = -1;
-  for (const auto& v : vec) {
-    const int64_t det = b1.first * v.second - b1.second * v.first;
-    if (det != n && det != -n) continue;
-    const int64_t s = det > 0 ? 1 : -1, x = s * v.first, y = s * v.second, len = x * x + y * y;
-    if (best >= 0 && len >= best) continue;
+  each([&](int64_t x, int64_t y) {
+    const int64_t size = std::llabs(x) + std::llabs(y);
+    if (best >= 0 && size >= best) return;
+    best = size;
+    out.b1[0] = x;
+    out.b1[1] = y;
+  });
+  out.lines = (uint32_t)best;
+  best = -1;
+  each([&](int64_t x, int64_t y) {
+    const int64_t det = out.b1[0] * y - out.b1[1] * x;
+    if (det != n && det != -n) return;
+    const int64_t s = det > 0 ? 1 : -1, len = x * x + y * y;
+    if (best >= 0 && len >= best) return;
     best = len;
-    out.b2[0] = x;
-    out.b2[1] = y;
-  }
+    out.b2[0] = s * x;
+    out.b2[1] = s * y;
+  });
   if (best < 0) out.lines = 0;
   return out;
 }
 
 inline int64_t floor_div(int64_t a, int64_t b) { return a / b - ((a % b != 0) && ((a < 0) != (b < 0))); }
 
+// floor(c / s) for |c| < 2^22 (s > 0), by the reciprocal: (c + 1/2) / s is 1 / (2 s)
+// away from the next integer.
+struct FloorDiv {
+  double inv;
+  int64_t up, whole;   // whole multiples of s that make the quotient positive
+  explicit FloorDiv(int64_t s) : inv(1.0 / (double)s), up(((int64_t)1 << 22) / s + 1), whole(up * s) {}
+  int64_t operator()(int64_t c) const { return (int64_t)(((double)(c + whole) + 0.5) * inv) - up; }
+};
+
 // Steps j in [lo, hi) with the points (x, y) + j (bx, by) inside [0, N)^2.
-inline void line_interval(int64_t n, int64_t x, int64_t y, int64_t bx, int64_t by, int64_t& lo, int64_t& hi) {
-  const int64_t top = n - 1;
-  int64_t a = -4 * n, b = 4 * n;
-  for (int axis = 0; axis < 2; ++axis) {
-    const int64_t c = axis ? y : x, s = axis ? by : bx;
-    if (s > 0) {
-      a = std::max(a, floor_div(-c + s - 1, s));
-      b = std::min(b, floor_div(top - c, s));
-    } else if (s < 0) {
-      a = std::max(a, floor_div(c - top - s - 1, -s));
-      b = std::min(b, floor_div(c, -s));
-    } else if (c < 0 || c > top) {
-      b = a - 1;
+struct LineInterval {
+  int64_t n, step[2];
+  FloorDiv div[2];
+  LineInterval(int64_t n_, int64_t bx, int64_t by)
+      : n(n_), step{bx, by}, div{FloorDiv(std::max<int64_t>(1, std::llabs(bx))), FloorDiv(std::max<int64_t>(1, std::llabs(by)))} {}
+  void operator()(int64_t x, int64_t y, int64_t& lo, int64_t& hi) const {
+    const int64_t top = n - 1;
+    int64_t a = -4 * n, b = 4 * n;
+    for (int axis = 0; axis < 2; ++axis) {
+      const int64_t c = axis ? y : x, s = step[axis];
+      if (s > 0) {
+        a = std::max(a, div[axis](-c + s - 1));
+        b = std::min(b, div[axis](top - c));
+      } else if (s < 0) {
+        a = std::max(a, div[axis](c - top - s - 1));
+        b = std::min(b, div[axis](c));
+      } else if (c < 0 || c > top) {
+        b = a - 1;
+      }
     }
+    lo = a;
+    hi = std::max(a, b + 1);
   }
-  lo = a;
-  hi = std::max(a, b + 1);
-}
+};
 
 // gx^-1 mod N (N a power of two, gx odd: Newton).
 inline int64_t generator_inverse(int64_t n, int64_t gx) {
@@ -106,42 +127,64 @@ inline int64_t generator_inverse(int64_t n, int64_t gx) {
   return n == 1 ? 0 : inv;
 }
 
-// The lines of every shift class, rows of `stride` words: sample A of the
-// first line (x | y << 16, lattice units), sum of lo over the lines, then
-// lo | hi << 16 (int16) per line, j counted from A + l b2.  Class k holds the
-// shifts (x, y) with y gx - x gy = k mod N.  False if a row does not fit.
-inline bool lattice_rows(int64_t n, int64_t gx, int64_t gy, const LatticeLines& g, uint32_t max_lines, uint32_t stride,
-                  std::vector<uint32_t>& rows) {
-  rows.assign((size_t)n * stride, 0u);
-  const int64_t inv = generator_inverse(n, gx);
-  const int64_t bx = g.b1[0], by = g.b1[1], top = n - 1;
+// The lines that meet the square in every shift class: class k holds the shifts
+// (x, y) with y gx - x gy = k mod N.  Line l of class k is that of the points
+// (0, py) + l b2 + j b1, (0, py) its sample with x = 0; the steps j in [lo, hi).
+struct ClassLines {
+  struct Span {
+    int32_t l, lo, hi;
+  };
+  std::vector<uint32_t> start;   // [N + 1] spans of each class, by l; none is empty
+  std::vector<Span> spans;
+  std::vector<int32_t> py;       // [N]
+};
+
+inline ClassLines class_lines(int64_t n, int64_t gx, int64_t gy, const LatticeLines& g) {
+  ClassLines out;
+  const int64_t inv = generator_inverse(n, gx), bx = g.b1[0], by = g.b1[1], top = n - 1;
+  const LineInterval interval(n, bx, by);
+  out.spans.reserve((size_t)n * (g.lines + 1));
   for (int64_t k = 0; k < n; ++k) {
-    const int64_t py = k * inv % n;   // the class's sample with x = 0
+    const int64_t py = k * inv % n;
+    out.py.push_back((int32_t)py);
+    out.start.push_back((uint32_t)out.spans.size());
     // line index of the square's corners relative to the sample's line
     int64_t l0 = 0, l1 = 0;
     for (int64_t cx : {(int64_t)0, top})
       for (int64_t cy : {(int64_t)0, top}) {
-        const int64_t d = bx * (cy - py) - by * cx;
-        l0 = std::min(l0, floor_div(d, n));
-        l1 = std::max(l1, floor_div(d, n) + 1);
+        const int64_t d = floor_div(bx * (cy - py) - by * cx, n);
+        l0 = std::min(l0, d);
+        l1 = std::max(l1, d + 1);
       }
-    uint32_t* row = &rows[(size_t)k * stride];
-    bool first = true;
-    int64_t base = 0, j0 = 0, sum = 0, total = 0;
     for (int64_t l = l0; l <= l1; ++l) {
-      const int64_t x = l * g.b2[0], y = py + l * g.b2[1];
       int64_t a, b;
-      line_interval(n, x, y, bx, by, a, b);
-      if (b <= a) continue;
-      if (first) {
-        first = false;
-        base = l;
-        j0 = a;
-        row[0] = (uint32_t)(x + a * bx) | ((uint32_t)(y + a * by) << 16);
-      }
-      const int64_t lo = a - j0, hi = b - j0;
-      if (l - base >= max_lines || lo < -32768 || hi > 32767) return false;
-      row[2 + (l - base)] = ((uint32_t)lo & 0xFFFFu) | ((uint32_t)hi << 16);
+      interval(l * g.b2[0], py + l * g.b2[1], a, b);
+      if (b > a) out.spans.push_back({(int32_t)l, (int32_t)a, (int32_t)b});
+    }
+  }
+  out.start.push_back((uint32_t)out.spans.size());
+  return out;
+}
+
+// The lines of every shift class, rows of `stride` words: sample A of the
+// first line (x | y << 16, lattice units), sum of lo over the lines, then
+// lo | hi << 16 (int16) per line, j counted from A + l b2.  False if a row does
+// not fit.
+inline bool lattice_rows(int64_t n, const ClassLines& c, const LatticeLines& g, uint32_t max_lines, uint32_t stride,
+                         std::vector<uint32_t>& rows) {
+  rows.assign((size_t)n * stride, 0u);
+  for (int64_t k = 0; k < n; ++k) {
+    uint32_t* row = &rows[(size_t)k * stride];
+    if (c.start[k] == c.start[k + 1]) return false;
+    const ClassLines::Span first = c.spans[c.start[k]];
+    const int64_t x = first.l * g.b2[0] + first.lo * g.b1[0], y = c.py[k] + first.l * g.b2[1] + first.lo * g.b1[1];
+    row[0] = (uint32_t)x | ((uint32_t)y << 16);
+    int64_t sum = 0, total = 0;
+    for (uint32_t i = c.start[k]; i < c.start[k + 1]; ++i) {
+      const ClassLines::Span q = c.spans[i];
+      const int64_t lo = q.lo - first.lo, hi = q.hi - first.lo;
+      if (q.l - first.l >= (int64_t)max_lines || lo < -32768 || hi > 32767) return false;
+      row[2 + (q.l - first.l)] = ((uint32_t)lo & 0xFFFFu) | ((uint32_t)hi << 16);
       sum += lo;
       total += hi - lo;
     }
@@ -149,6 +192,11 @@ inline bool lattice_rows(int64_t n, int64_t gx, int64_t gy, const LatticeLines& 
     row[1] = (uint32_t)(int32_t)sum;
   }
   return true;
+}
+
+inline bool lattice_rows(int64_t n, int64_t gx, int64_t gy, const LatticeLines& g, uint32_t max_lines, uint32_t stride,
+                         std::vector<uint32_t>& rows) {
+  return lattice_rows(n, class_lines(n, gx, gy, g), g, max_lines, stride, rows);
 }
 
 // a / b rounded to the nearest integer (b != 0).
@@ -209,66 +257,64 @@ struct GaussLines {
   std::vector<uint32_t> rows;
 };
 
-inline GaussLines gauss_lines(int64_t n, int64_t gx, int64_t gy, const LatticeLines& g) {
+inline GaussLines gauss_lines(int64_t n, const ClassLines& c, const LatticeLines& g) {
   GaussLines out;
-  const int64_t inv = generator_inverse(n, gx), bx = g.b1[0], by = g.b1[1], cx = g.b2[0], cy = g.b2[1];
-  const int64_t reach = g.lines + 2;
+  const int64_t bx = g.b1[0], by = g.b1[1], cx = g.b2[0], cy = g.b2[1];
   // nearest integer to a / (2 n)
   auto near = [&](int64_t a) { return floor_div(a + n, 2 * n); };
-  std::vector<std::pair<int64_t, int64_t>> anchor(n);
-  int64_t l0 = reach, l1 = -reach;
-  auto interval = [&](int64_t k, int64_t l, int64_t& lo, int64_t& hi) {
-    line_interval(n, anchor[k].first + l * cx, anchor[k].second + l * cy, bx, by, lo, hi);
-  };
+  // A = (0, py) - al b1 - be b2: step j of line l is step j + al of line l + be from A
+  std::vector<int32_t> al(n), be(n);
+  int64_t l0 = INT32_MAX, l1 = INT32_MIN;
   for (int64_t k = 0; k < n; ++k) {
     // twice the sample (0, py) less the centre, in units of b1 and b2
-    const int64_t x = -(n - 1), y = 2 * (k * inv % n) - (n - 1);
-    const int64_t al = near(x * cy - y * cx), be = near(bx * y - by * x);
-    anchor[k] = {-al * bx - be * cx, k * inv % n - al * by - be * cy};
-    for (int64_t l = -reach; l <= reach; ++l) {
-      int64_t lo, hi;
-      interval(k, l, lo, hi);
-      if (hi > lo) l0 = std::min(l0, l), l1 = std::max(l1, l);
-    }
+    const int64_t x = -(n - 1), y = 2 * (int64_t)c.py[k] - (n - 1);
+    al[k] = (int32_t)near(x * cy - y * cx);
+    be[k] = (int32_t)near(bx * y - by * x);
+    l0 = std::min<int64_t>(l0, c.spans[c.start[k]].l + be[k]);
+    l1 = std::max<int64_t>(l1, c.spans[c.start[k + 1] - 1].l + be[k]);
   }
   out.first = l0;
   out.lines = (uint32_t)(l1 - l0 + 1);
   out.stride = 1 + out.lines;
-  out.rows.assign((size_t)n * out.stride, 0u);
+  struct Range {
+    int64_t jmin = INT32_MAX, jmax = INT32_MIN, lo_max = INT32_MIN, hi_min = INT32_MAX, classes = 0;
+  };
+  std::vector<Range> range(out.lines);
+  for (int64_t k = 0; k < n; ++k)
+    for (uint32_t i = c.start[k]; i < c.start[k + 1]; ++i) {
+      Range& r = range[c.spans[i].l + be[k] - l0];
+      const int64_t lo = c.spans[i].lo + al[k], hi = c.spans[i].hi + al[k];
+      r.jmin = std::min(r.jmin, lo);
+      r.lo_max = std::max(r.lo_max, lo);
+      r.jmax = std::max(r.jmax, hi);
+      r.hi_min = std::min(r.hi_min, hi);
+      ++r.classes;
+    }
   out.j0.assign(out.lines, 0);
   out.spans.assign(out.lines, GaussLines::Span{0, 0, 0});
   for (uint32_t i = 0; i < out.lines; ++i) {
-    int64_t jmin = 0, jmax = 0, lo_max = 0, hi_min = 0;
-    bool any = false, all = true;
-    for (int64_t k = 0; k < n; ++k) {
-      int64_t lo, hi;
-      interval(k, l0 + i, lo, hi);
-      if (hi <= lo) {
-        all = false;
-        continue;
-      }
-      jmin = any ? std::min(jmin, lo) : lo;
-      jmax = any ? std::max(jmax, hi) : hi;
-      lo_max = any ? std::max(lo_max, lo) : lo;
-      hi_min = any ? std::min(hi_min, hi) : hi;
-      any = true;
-    }
-    if (!any) jmin = jmax = i ? out.j0[i - 1] : 0;
-    if (!all || hi_min < lo_max) lo_max = hi_min = jmax;
-    out.j0[i] = jmin;
-    out.spans[i] = GaussLines::Span{(int32_t)(jmax - jmin), (int32_t)(lo_max - jmin), (int32_t)(hi_min - jmin)};
-    out.steps = std::max(out.steps, (uint32_t)(jmax - jmin));
-    for (int64_t k = 0; k < n; ++k) {
-      int64_t lo, hi;
-      interval(k, l0 + i, lo, hi);
-      if (hi > lo)
-        out.rows[(size_t)k * out.stride + 1 + i] = (uint32_t)(lo - jmin) | ((uint32_t)(hi - jmin) << 16);
+    Range r = range[i];
+    if (!r.classes) r.jmin = r.jmax = i ? out.j0[i - 1] : 0;
+    if (r.classes < n || r.hi_min < r.lo_max) r.lo_max = r.hi_min = r.jmax;
+    out.j0[i] = r.jmin;
+    out.spans[i] = GaussLines::Span{(int32_t)(r.jmax - r.jmin), (int32_t)(r.lo_max - r.jmin), (int32_t)(r.hi_min - r.jmin)};
+    out.steps = std::max(out.steps, (uint32_t)(r.jmax - r.jmin));
+  }
+  out.rows.assign((size_t)n * out.stride, 0u);
+  for (int64_t k = 0; k < n; ++k) {
+    uint32_t* row = &out.rows[(size_t)k * out.stride];
+    const int64_t ax = -al[k] * bx - be[k] * cx, ay = c.py[k] - al[k] * by - be[k] * cy;
+    row[0] = ((uint32_t)ax & 0xFFFFu) | ((uint32_t)ay << 16);
+    for (uint32_t i = c.start[k]; i < c.start[k + 1]; ++i) {
+      const int64_t l = c.spans[i].l + be[k] - l0, shift = al[k] - out.j0[l];
+      row[1 + l] = (uint32_t)(c.spans[i].lo + shift) | ((uint32_t)(c.spans[i].hi + shift) << 16);
     }
   }
-  for (int64_t k = 0; k < n; ++k)
-    out.rows[(size_t)k * out.stride] =
-        ((uint32_t)anchor[k].first & 0xFFFFu) | ((uint32_t)anchor[k].second << 16);
   return out;
+}
+
+inline GaussLines gauss_lines(int64_t n, int64_t gx, int64_t gy, const LatticeLines& g) {
+  return gauss_lines(n, class_lines(n, gx, gy, g), g);
 }
 
 // One Gaussian's table for the line form, doubles, interleaved with those of
