@@ -23,7 +23,7 @@
 // the results change hands there so that whole runs of a pixel's row are
 // written.  Bound by the vector ALUs (1.7 slots per sample at N = 1024, 12 ms of
 // issue) and the latency of the scalar loads (five waves a SIMD).
-// Measured at 512^2, N = 1024, 1024 Gaussians: 13.9 ms per estimate of all
+// Measured at 512^2, N = 1024, 1024 Gaussians: 13.8 ms per estimate of all
 // pixels against 57.4 sample by sample; 15.6 with 16 Gaussians a wave, one four
 // after the other, and a launch over few pixels took four times as long (256
 // listed moves: 283 us the call against 141); four lines at a time in place of

@@ -525,7 +525,7 @@ __global__ __launch_bounds__(256) void k_gauss_est(DevView v, uint32_t kappa, ui
 // g_m <= (g' + g + |x_m|) / 2.  A move whose energy change is within that bound of
 // 0 is listed and its Gaussian part evaluated again from estimates sample by
 // sample (of its window: k_gauss_again), then decided.
-// 512^2, N = 1024, 1024 Gaussians: about one move in 5000, 0.36 ms a phase (its cost
+// 512^2, N = 1024, 1024 Gaussians: about one move in 5000, 0.33 ms a phase (its cost
 // is the exponentials of 122 pixels a move), where estimating every proposal so
 // would take 14.  With eta(1) for every g four times as many (1.39 ms).  (Where
 // nearly all moves are close it costs more than it spares: one Heaviside beside 64
@@ -807,8 +807,8 @@ __global__ __launch_bounds__(512) void k_delta_gauss_stage(DevView v, uint32_t k
 // Gaussian, so that a window row's values are read from LDS, converted and
 // paired once for four pixels (12 against 30 a pixel at r = 5, K = 2), and the
 // region from memory once for 64 (10 pixels of it a pixel against 28).  Bound by
-// the FP64 operations.  512^2, 1024 Gaussians, r = 5: 0.75 ms a phase without the
-// margin, 0.97 with it; 1.8 and, with it, 1.5 with k_delta_gauss_stage's layout and
+// the FP64 operations.  512^2, 1024 Gaussians, r = 5: 0.72 ms a phase without the
+// margin, 1.04 with it; 1.8 and, with it, 1.5 with k_delta_gauss_stage's layout and
 // one sum per window offset.
 template <int R, int K>
 struct GaussTile {
